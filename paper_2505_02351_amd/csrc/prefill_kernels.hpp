@@ -62,6 +62,10 @@ namespace optgqa {
 #define OPTGQA_PF_SKIP_LOG2 (-24.f)
 #endif
 constexpr float kPfSkipLog2 = OPTGQA_PF_SKIP_LOG2;
+#ifndef OPTGQA_PF_CHECK_TILES
+#define OPTGQA_PF_CHECK_TILES 4
+#endif
+constexpr int kPfCheckTiles = OPTGQA_PF_CHECK_TILES;
 
 struct PrefillParams {
     void* out;                  // [T][Hq][D] dtype
@@ -170,6 +174,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // two tile buffers, each a K tile [32][kPfKRow] followed by a V tile [32][kPfVRow]
     constexpr int kKTile = kPfKeys * kPfKRow, kBuf = kKTile + kPfKeys * kPfVRow;
     extern __shared__ __attribute__((aligned(16))) uint16_t tile_lds[];          // PfTile<D>::kLdsBytes
+    __shared__ float vote[2][kPfWaves];                          // rest_negligible
 
     // ---- which rows -----------------------------------------------------------------------
     // XCD-aware order: workgroups go to XCD (flat id % 8); all query tiles of one (sequence, KV
@@ -435,7 +440,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
             // below 2^kPfSkipLog2 of the row's sum (this lane's half of it, which is no more) for
             // every row of the wave, the tile changes no bit that the accumulators keep.
             const float room = __builtin_amdgcn_logf(lsum) + kPfSkipLog2;        // log2; -inf before the row's first key
-            if (__builtin_amdgcn_ballot_w64(mx > room) == 0) return;
+            if (__builtin_amdgcn_ballot_w64(mx > room) == 0) return true;
         }
         // Has the row seen a key yet?  Walking backwards from the diagonal, a row's first visible key
         // may lie in a later tile of the walk than another row's.
@@ -498,6 +503,101 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
                 if (PfSoftmax<DT>::kSplitWeights)
                     acc[db] = mfma32<DT>(va, make_uint4(pk_lo[m][0], pk_lo[m][1], pk_lo[m][2], pk_lo[m][3]), acc[db]);
             }
+        return false;
+    };
+
+    // ---- the rest of the walk judged at once -------------------------------------------------------
+    // True (for the whole workgroup) if no key of tiles 0 .. kt can carry a weight above 2^kPfSkipLog2 of
+    // any row's sum so far, so that every one of these tiles would be skipped by the test in softmax_pv
+    // anyway.  By Cauchy-Schwarz |q.k| <= |q||k|, so key j is out of the question for a row if
+    //     |scale2| |q| |k_j| + slope2 * (j - pos) - m_ref  <=  log2(lsum) + kPfSkipLog2,
+    // i.e. |k_j| <= A + B * (k0 - j) with k0 the nearest of the keys, A = (log2(lsum) + kPfSkipLog2 + m_ref
+    // + slope2 * (pos - k0)) / (|scale2||q|), B = slope2 / (|scale2||q|) (any sign), the least A and B of
+    // all rows.  The workgroup then reads the keys once, without V, LDS, MFMAs or exponentials.
+    // A norm that is not a number, or infinite, fails the test.
+    auto rest_negligible = [&](int kt, bool wave_skips) __attribute__((always_inline)) -> bool {
+        const int k0 = kt * kPfKeys + kPfKeys - 1;
+        float a = -1.f, bb = 0.f;
+        if (wave_skips) {
+            float q2 = 0.f;
+#pragma unroll
+            for (int m = 0; m < kQ; ++m) {
+                q2 = dot2<DT>(qb[m].x, qb[m].x, q2);
+                q2 = dot2<DT>(qb[m].y, qb[m].y, q2);
+                q2 = dot2<DT>(qb[m].z, qb[m].z, q2);
+                q2 = dot2<DT>(qb[m].w, qb[m].w, q2);
+            }
+            q2 += __shfl_xor(q2, 32);                            // a row's dims live in 2 lanes (h2)
+            const float qs = 1.001f * fabsf(scale2) * __builtin_amdgcn_sqrtf(q2) + 0x1p-100f;    // (margins cover the rounding of the norms)
+            const float room = __builtin_amdgcn_logf(lsum) + (kPfSkipLog2 - 0.01f);
+            a = (room + m_ref + slope2 * (posf - (float)k0)) / qs;
+            bb = slope2 / qs;
+            const bool bad = !(a > 0.f && q2 < 0x1p100f);
+            if (__builtin_amdgcn_ballot_w64(bad) != 0) a = -1.f;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                a = fminf(a, __shfl_xor(a, off));
+                bb = fminf(bb, __shfl_xor(bb, off));
+            }
+        }
+        if (lane == 0) {
+            vote[0][wave] = a;
+            vote[1][wave] = bb;
+        }
+        __syncthreads();
+        a = vote[0][0], bb = vote[1][0];
+#pragma unroll
+        for (int i = 1; i < kPfWaves; ++i) a = fminf(a, vote[0][i]), bb = fminf(bb, vote[1][i]);
+        if (!(a > 0.f)) return false;                            // workgroup-uniform
+        // thread -> (key, 16-byte column piece): kPfWaves * 64 / kCPR keys a pass, nearest first
+        constexpr int kScanKeys = kPfWaves * 64 / kCPR, kBatch = 8;
+        int s_tid = tid;
+        asm volatile("" : "+v"(s_tid));                          // (keeps this rare code's addresses out of the registers of the loop around it)
+        const int s_key = s_tid / kCPR, s_piece = s_tid % kCPR;
+        const unsigned char* const s_lane = kc + 8 * s_piece * ES;
+        auto scan_key = [&](int i) __attribute__((always_inline)) { return max(k0 - i * kScanKeys - s_key, 0); };
+        const int passes = (k0 + kScanKeys) / kScanKeys;
+        int blks[kBatch];
+        auto load_blks = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) blks[u] = CONTIG ? 0 : table[scan_key(i + u) >> bs_shift];
+        };
+        load_blks(0);
+        bool bad = false;
+        for (int i = 0; i < passes; i += kBatch) {
+            StageT x[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const int key = scan_key(i + u);
+                const unsigned char* src;
+                if (CONTIG) src = s_lane + (uint64_t)(uint32_t)key * (uint32_t)(p.k_in_stride * 2);
+                else src = s_lane + (uint64_t)(uint32_t)blks[u] * (uint32_t)(block_stride * ES) + (uint32_t)((key & (bs - 1)) * (D * ES));
+                if (STEP && key >= pos0) src = kin + 16 * s_piece + (uint64_t)(uint32_t)(key - pos0) * (uint32_t)(p.k_in_stride * 2);
+                x[u] = *reinterpret_cast<const StageT*>(src);
+            }
+            load_blks(i + kBatch);
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                uint4 y;
+                if constexpr (KV8) y = widen8_e4m3<DT>(x[u][0], x[u][1]);
+                else y = __builtin_bit_cast(uint4, x[u]);
+                float n2 = dot2<DT>(y.x, y.x, 0.f);
+                n2 = dot2<DT>(y.y, y.y, n2);
+                n2 = dot2<DT>(y.z, y.z, n2);
+                n2 = dot2<DT>(y.w, y.w, n2);
+                n2 = row_group_sum<kCPR>(n2);
+                const float most = fmaf(bb, (float)(k0 - scan_key(i + u)), a);
+                bad = bad || !(most > 0.f && n2 * 1.001f <= most * most);
+            }
+            if (__builtin_amdgcn_ballot_w64(bad) != 0) break;
+        }
+        __syncthreads();                                         // the votes above have been read
+        if (lane == 0) vote[0][wave] = __builtin_amdgcn_ballot_w64(bad) != 0 ? -1.f : 1.f;
+        __syncthreads();
+        a = vote[0][0];
+#pragma unroll
+        for (int i = 1; i < kPfWaves; ++i) a = fminf(a, vote[0][i]);
+        return a > 0.f;                                          // (the next call's votes are barriers away)
     };
 
     const int pos_min = pos0 + tq0;                             // tiles ending at or below it need no causal mask
@@ -537,9 +637,10 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // (two steps per trip with the two score registers swapping roles, so that no trip copies the
     // look-ahead scores into place)
     f32x16 st_other;
+    bool wave_skips = false;                                     // this wave skipped its last tile (wave-uniform)
     auto one_tile = [&](int j, const f32x16& st_cur, f32x16& st_ahead, auto masked) __attribute__((always_inline)) {
         st_ahead = scores(j + 1);
-        softmax_pv(last_tile - j, j, st_cur, masked);
+        wave_skips = softmax_pv(last_tile - j, j, st_cur, masked);
         store_tile(stage, j + 1 + l_ahead);
         fetch_tile(stage, j + 2 + l_ahead);
         __syncthreads();
@@ -561,8 +662,16 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // from the diagonal backwards: the tiles the causal mask cuts come first, those that some
     // row's window start cuts (if there is a window) last
     run_tiles(0, ntiles - plain_end, std::true_type{});
-    run_tiles(ntiles - plain_end, ntiles - cut_end, std::false_type{});
-    run_tiles(ntiles - cut_end, nt, std::true_type{});
+    // (Without slopes no weight is ever out of the question for its position alone: no checks.)
+    int until_check = !WIN && p.slopes ? kPfCheckTiles : nt;
+    for (int j = ntiles - plain_end; j < ntiles - cut_end;) {
+        const int to = min(j + until_check, ntiles - cut_end);
+        run_tiles(j, to, std::false_type{});
+        j = to;
+        if constexpr (!WIN)
+            if (ntiles - j >= kPfCheckTiles && rest_negligible(ntiles - 1 - j, wave_skips)) break;
+    }
+    if constexpr (WIN) run_tiles(ntiles - cut_end, nt, std::true_type{});
 
     // ---- normalise and write: this lane holds dims 32db + 8i + 4h2 + (0..3) of its row -----------
     uint16_t* __restrict__ op = static_cast<uint16_t*>(p.out);
