@@ -62,10 +62,8 @@ namespace optgqa {
 #define OPTGQA_PF_SKIP_LOG2 (-24.f)
 #endif
 constexpr float kPfSkipLog2 = OPTGQA_PF_SKIP_LOG2;
-#ifndef OPTGQA_PF_CHECK_TILES
-#define OPTGQA_PF_CHECK_TILES 4
-#endif
-constexpr int kPfCheckTiles = OPTGQA_PF_CHECK_TILES;
+// tiles between a look at whether the rest of the walk still matters, at the least (2, 4 and 8 measure the same)
+constexpr int kPfCheckTiles = 4;
 
 struct PrefillParams {
     void* out;                  // [T][Hq][D] dtype
@@ -174,7 +172,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // two tile buffers, each a K tile [32][kPfKRow] followed by a V tile [32][kPfVRow]
     constexpr int kKTile = kPfKeys * kPfKRow, kBuf = kKTile + kPfKeys * kPfVRow;
     extern __shared__ __attribute__((aligned(16))) uint16_t tile_lds[];          // PfTile<D>::kLdsBytes
-    __shared__ float vote[2][kPfWaves];                          // rest_negligible
+    __shared__ float vote[3][kPfWaves];                          // rest_judged
 
     // ---- which rows -----------------------------------------------------------------------
     // XCD-aware order: workgroups go to XCD (flat id % 8); all query tiles of one (sequence, KV
@@ -282,8 +280,11 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     bool row_ok, started;
     int64_t out_off;
     {
-        const int row = 32 * wave + n32;
-        const int ti = tq0 + (row >> gshift), head = row & ((1 << gshift) - 1);
+        // row block of 32: waves w and w + 4 share a SIMD, so with 8 waves the upper four take theirs in
+        // reverse order (the first head's rows, with the steepest slope, beside the last head's)
+        const int row = 32 * (WAVES == 8 && wave >= 4 ? 11 - wave : wave) + n32;
+        const int tshift = __builtin_ctz(tokens_per_wg);
+        const int ti = tq0 + (row & (tokens_per_wg - 1)), head = row >> tshift;
         row_ok = ti < n_b && head < GH;
         const int tc = min(ti, n_b - 1), hc = min(head, GH - 1);
         const int64_t qrow = ((int64_t)(cu0 + tc) * Hq + h0 + hc) * D;
@@ -291,10 +292,11 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         const int pos = pos0 + tc;
         posf = (float)pos;
         lof = W > 0 ? (float)(pos - W) : -1.f;                   // keys above this one are inside the window
-        slope2 = p.slopes ? p.slopes[h0 + hc] * kLog2e : 0.f;
+        slope2 = p.slopes && row_ok ? p.slopes[h0 + hc] * kLog2e : 0.f;
         m_ref = 0.f;                                             // set by the first tile in which the row sees a key
-        started = false;
-        lsum = 0.f;
+        // a row that does not exist never wants a tile: its sum is already beyond anything
+        started = !row_ok;
+        lsum = row_ok ? 0.f : INFINITY;
         const uint32_t keep = row_ok ? 0xffffffffu : 0u;
 #pragma unroll
         for (int m = 0; m < kQ; ++m) {
@@ -507,48 +509,58 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     };
 
     // ---- the rest of the walk judged at once -------------------------------------------------------
-    // True (for the whole workgroup) if no key of tiles 0 .. kt can carry a weight above 2^kPfSkipLog2 of
+    // 0 (for the whole workgroup) if no key of tiles 0 .. kt can carry a weight above 2^kPfSkipLog2 of
     // any row's sum so far, so that every one of these tiles would be skipped by the test in softmax_pv
-    // anyway.  By Cauchy-Schwarz |q.k| <= |q||k|, so key j is out of the question for a row if
+    // anyway; else the number of tiles after which it is worth asking again.
+    // By Cauchy-Schwarz |q.k| <= |q||k|, so key j is out of the question for a row if
     //     |scale2| |q| |k_j| + slope2 * (j - pos) - m_ref  <=  log2(lsum) + kPfSkipLog2,
     // i.e. |k_j| <= A + B * (k0 - j) with k0 the nearest of the keys, A = (log2(lsum) + kPfSkipLog2 + m_ref
     // + slope2 * (pos - k0)) / (|scale2||q|), B = slope2 / (|scale2||q|) (any sign), the least A and B of
     // all rows.  The workgroup then reads the keys once, without V, LDS, MFMAs or exponentials.
     // A norm that is not a number, or infinite, fails the test.
-    auto rest_negligible = [&](int kt, bool wave_skips) __attribute__((always_inline)) -> bool {
+    // When to ask: A grows by 32 B a tile, and the keys' norms - not known before they are read - are
+    // taken to be like the queries', |k| = |q| (a wrong guess costs time only).
+    auto rest_judged = [&](int kt, bool wave_skips) __attribute__((always_inline)) -> int {
         const int k0 = kt * kPfKeys + kPfKeys - 1;
-        float a = -1.f, bb = 0.f;
-        if (wave_skips) {
-            float q2 = 0.f;
+        float q2 = 0.f;
 #pragma unroll
-            for (int m = 0; m < kQ; ++m) {
-                q2 = dot2<DT>(qb[m].x, qb[m].x, q2);
-                q2 = dot2<DT>(qb[m].y, qb[m].y, q2);
-                q2 = dot2<DT>(qb[m].z, qb[m].z, q2);
-                q2 = dot2<DT>(qb[m].w, qb[m].w, q2);
-            }
-            q2 += __shfl_xor(q2, 32);                            // a row's dims live in 2 lanes (h2)
-            const float qs = 1.001f * fabsf(scale2) * __builtin_amdgcn_sqrtf(q2) + 0x1p-100f;    // (margins cover the rounding of the norms)
-            const float room = __builtin_amdgcn_logf(lsum) + (kPfSkipLog2 - 0.01f);
-            a = (room + m_ref + slope2 * (posf - (float)k0)) / qs;
-            bb = slope2 / qs;
-            const bool bad = !(a > 0.f && q2 < 0x1p100f);
-            if (__builtin_amdgcn_ballot_w64(bad) != 0) a = -1.f;
+        for (int m = 0; m < kQ; ++m) {
+            q2 = dot2<DT>(qb[m].x, qb[m].x, q2);
+            q2 = dot2<DT>(qb[m].y, qb[m].y, q2);
+            q2 = dot2<DT>(qb[m].z, qb[m].z, q2);
+            q2 = dot2<DT>(qb[m].w, qb[m].w, q2);
+        }
+        q2 += __shfl_xor(q2, 32);                                // a row's dims live in 2 lanes (h2)
+        const float qn = __builtin_amdgcn_sqrtf(q2);
+        const float qs = 1.001f * fabsf(scale2) * qn + 0x1p-100f;    // (margins cover the rounding of the norms)
+        const float room = __builtin_amdgcn_logf(lsum) + (kPfSkipLog2 - 0.01f);
+        float a = (room + m_ref + slope2 * (posf - (float)k0)) / qs;
+        float bb = row_ok ? slope2 / qs : INFINITY;
+        float wait = a >= qn ? 0.f : fminf((qn - a) / (bb * (float)kPfKeys), 1e6f);
+        wait = wait >= 0.f ? wait : 1e6f;                        // (no slope, or a negative one)
+        const bool no = !(a > 0.f && q2 < 0x1p100f);
+        if (!wave_skips || __builtin_amdgcn_ballot_w64(no) != 0) a = -1.f;
 #pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                a = fminf(a, __shfl_xor(a, off));
-                bb = fminf(bb, __shfl_xor(bb, off));
-            }
+        for (int off = 1; off < 64; off <<= 1) {
+            a = fminf(a, __shfl_xor(a, off));
+            bb = fminf(bb, __shfl_xor(bb, off));
+            wait = fmaxf(wait, __shfl_xor(wait, off));
         }
         if (lane == 0) {
             vote[0][wave] = a;
             vote[1][wave] = bb;
+            vote[2][wave] = wait;
         }
         __syncthreads();
-        a = vote[0][0], bb = vote[1][0];
+        a = vote[0][0], bb = vote[1][0], wait = vote[2][0];
 #pragma unroll
-        for (int i = 1; i < kPfWaves; ++i) a = fminf(a, vote[0][i]), bb = fminf(bb, vote[1][i]);
-        if (!(a > 0.f)) return false;                            // workgroup-uniform
+        for (int i = 1; i < kPfWaves; ++i) {
+            a = fminf(a, vote[0][i]);
+            bb = fminf(bb, vote[1][i]);
+            wait = fmaxf(wait, vote[2][i]);
+        }
+        const int ask = max(kPfCheckTiles, __builtin_amdgcn_readfirstlane((int)wait + 1));
+        if (!(a > 0.f) || ask > kPfCheckTiles) return ask;       // workgroup-uniform
         // thread -> (key, 16-byte column piece): kPfWaves * 64 / kCPR keys a pass, nearest first
         constexpr int kScanKeys = kPfWaves * 64 / kCPR, kBatch = 8;
         int s_tid = tid;
@@ -597,7 +609,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         a = vote[0][0];
 #pragma unroll
         for (int i = 1; i < kPfWaves; ++i) a = fminf(a, vote[0][i]);
-        return a > 0.f;                                          // (the next call's votes are barriers away)
+        return a > 0.f ? 0 : 2 * kPfCheckTiles;                  // (the next call's votes are barriers away)
     };
 
     const int pos_min = pos0 + tq0;                             // tiles ending at or below it need no causal mask
@@ -663,13 +675,15 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // row's window start cuts (if there is a window) last
     run_tiles(0, ntiles - plain_end, std::true_type{});
     // (Without slopes no weight is ever out of the question for its position alone: no checks.)
-    int until_check = !WIN && p.slopes ? kPfCheckTiles : nt;
+    int ask = !WIN && p.slopes ? kPfCheckTiles : nt;
     for (int j = ntiles - plain_end; j < ntiles - cut_end;) {
-        const int to = min(j + until_check, ntiles - cut_end);
+        const int to = min(j + ask, ntiles - cut_end);
         run_tiles(j, to, std::false_type{});
         j = to;
-        if constexpr (!WIN)
-            if (ntiles - j >= kPfCheckTiles && rest_negligible(ntiles - 1 - j, wave_skips)) break;
+        if constexpr (!WIN) {
+            if (ntiles - j < kPfCheckTiles) ask = kPfCheckTiles;
+            else if ((ask = rest_judged(ntiles - 1 - j, wave_skips)) == 0) break;
+        }
     }
     if constexpr (WIN) run_tiles(ntiles - cut_end, nt, std::true_type{});
 
