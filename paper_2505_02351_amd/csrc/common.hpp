@@ -90,14 +90,34 @@ constexpr int kDppRowRor4 = 0x124;    // row_ror:4
 constexpr int kDppRowRor8 = 0x128;
 constexpr int kDppRowRor12 = 0x12C;
 
-// Sum over the LPR (8 or 16) consecutive lanes that share a token row; every lane gets the sum.
+// Sum over the LPR (4, 8 or 16) consecutive lanes that share a token row; every lane gets the sum.
 template <int LPR> __device__ __forceinline__ float row_group_sum(float x)
 {
     x += dpp<kDppXor1>(x);
     x += dpp<kDppXor2>(x);
-    x += dpp<kDppHalfMirror>(x);
+    if (LPR >= 8) x += dpp<kDppHalfMirror>(x);
     if (LPR == 16) x += dpp<kDppMirror>(x);
     return x;
+}
+
+// Sum over the wave, the same in every lane (a scalar).
+__device__ __forceinline__ int wave_sum(int x)
+{
+    x += __builtin_amdgcn_update_dpp(0, x, kDppXor1, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, kDppXor2, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, kDppHalfMirror, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, kDppMirror, 0xf, 0xf, true);
+    return __builtin_amdgcn_readlane(x, 0) + __builtin_amdgcn_readlane(x, 16) + __builtin_amdgcn_readlane(x, 32) + __builtin_amdgcn_readlane(x, 48);
+}
+
+__device__ __forceinline__ int wave_max(int x)
+{
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, kDppXor1, 0xf, 0xf, true));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, kDppXor2, 0xf, 0xf, true));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, kDppHalfMirror, 0xf, 0xf, true));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, kDppMirror, 0xf, 0xf, true));
+    return max(max(__builtin_amdgcn_readlane(x, 0), __builtin_amdgcn_readlane(x, 16)),
+               max(__builtin_amdgcn_readlane(x, 32), __builtin_amdgcn_readlane(x, 48)));
 }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }

@@ -361,51 +361,37 @@ int launch_decode_flat(int dtype, int head_dim, const DecodeParams& p, int workg
 
 // The tiled prefill kernel takes its LDS as dynamic shared memory (more than the 64 KiB a kernel
 // gets by default); the limit is raised once per instantiation.
-template <int DT, bool KV8, bool WIN, bool CONTIG, int D, int WAVES>
-int launch_prefill_mma_w(const PrefillParams& p, dim3 grid, hipStream_t st)
+// Shapes of a prefill workgroup (see prefill_kernels.hpp): 128 rows, 256 rows, or 128 rows whose keys are
+// shared out between two groups of four waves.
+enum class PrefillShape { k4Waves, k8Waves, k8WavesTwoGroups };
+
+template <int DT, bool KV8, bool WIN, bool CONTIG, bool STEP, int D, int WAVES, int KS>
+int launch_prefill_w(const PrefillParams& p, dim3 grid, hipStream_t st)
 {
-    constexpr int kBytes = PfTile<D>::kLdsBytes;
-    static const hipError_t attr = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&paged_prefill_mma_kernel<DT, KV8, WIN, CONTIG, D, WAVES>),
-        hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
+    void (*kernel)(PrefillParams);
+    if constexpr (STEP) kernel = paged_prefill_step_kernel<DT, D, WAVES, KS>;
+    else kernel = paged_prefill_mma_kernel<DT, KV8, WIN, CONTIG, D, WAVES, KS>;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, KS * PfTile<D>::kLdsBytes);
     if (attr != hipSuccess) return OPTGQA_ERR_LAUNCH;
-    return launch(paged_prefill_mma_kernel<DT, KV8, WIN, CONTIG, D, WAVES>, grid, dim3(WAVES * 64), kBytes, st, p);
+    return launch(kernel, grid, dim3(WAVES * 64), KS * PfTile<D>::kLdsBytes, st, p);
 }
 
-template <int DT, bool KV8, bool WIN, bool CONTIG, int D>
-int launch_prefill_mma_d(const PrefillParams& p, dim3 grid, int waves, hipStream_t st)
+template <int DT, bool KV8, bool WIN, bool CONTIG, bool STEP, int D>
+int launch_prefill_d(const PrefillParams& p, dim3 grid, PrefillShape shape, hipStream_t st)
 {
     if constexpr (!WIN) {
-        if (waves == 8) return launch_prefill_mma_w<DT, KV8, WIN, CONTIG, D, 8>(p, grid, st);
+        if (shape == PrefillShape::k8Waves) return launch_prefill_w<DT, KV8, WIN, CONTIG, STEP, D, 8, 1>(p, grid, st);
+        if (shape == PrefillShape::k8WavesTwoGroups) return launch_prefill_w<DT, KV8, WIN, CONTIG, STEP, D, 8, 2>(p, grid, st);
     }
-    return launch_prefill_mma_w<DT, KV8, WIN, CONTIG, D, 4>(p, grid, st);
+    return launch_prefill_w<DT, KV8, WIN, CONTIG, STEP, D, 4, 1>(p, grid, st);
 }
 
-template <int DT, bool KV8, bool WIN, bool CONTIG>
-int launch_prefill_mma(const PrefillParams& p, int head_dim, dim3 grid, int waves, hipStream_t st)
+template <int DT, bool KV8, bool WIN, bool CONTIG, bool STEP>
+int launch_prefill_mma(const PrefillParams& p, int head_dim, dim3 grid, PrefillShape shape, hipStream_t st)
 {
-    if (head_dim == 64) return launch_prefill_mma_d<DT, KV8, WIN, CONTIG, 64>(p, grid, waves, st);
-    return launch_prefill_mma_d<DT, KV8, WIN, CONTIG, 128>(p, grid, waves, st);
-}
-
-// The one-call prefill step (cache write inside the prefill kernel).
-template <int DT, int D, int WAVES>
-int launch_prefill_step_w(const PrefillParams& p, dim3 grid, hipStream_t st)
-{
-    constexpr int kBytes = PfTile<D>::kLdsBytes;
-    static const hipError_t attr = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&paged_prefill_step_kernel<DT, D, WAVES>),
-        hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
-    if (attr != hipSuccess) return OPTGQA_ERR_LAUNCH;
-    return launch(paged_prefill_step_kernel<DT, D, WAVES>, grid, dim3(WAVES * 64), kBytes, st, p);
-}
-
-template <int DT>
-int launch_prefill_step(const PrefillParams& p, int head_dim, dim3 grid, int waves, hipStream_t st)
-{
-    if (head_dim == 64)
-        return waves == 8 ? launch_prefill_step_w<DT, 64, 8>(p, grid, st) : launch_prefill_step_w<DT, 64, 4>(p, grid, st);
-    return waves == 8 ? launch_prefill_step_w<DT, 128, 8>(p, grid, st) : launch_prefill_step_w<DT, 128, 4>(p, grid, st);
+    if (head_dim == 64) return launch_prefill_d<DT, KV8, WIN, CONTIG, STEP, 64>(p, grid, shape, st);
+    return launch_prefill_d<DT, KV8, WIN, CONTIG, STEP, 128>(p, grid, shape, st);
 }
 
 // The tiled prefill kernel carries the tile-invariant part of the ALiBi term inside the score
@@ -432,13 +418,27 @@ int launch_prefill(PrefillParams p, int num_seqs, int max_q_len, int head_dim, i
     p.heads_per_wg = gh;
     p.heads_pow2_shift = shift;
     p.units = num_seqs * p.num_kv_heads * (group / gh);
-    // 8 waves per workgroup when that still leaves two rounds of workgroups per CU, else 4 (and 4
-    // with a sliding window): see prefill_kernels.hpp
     const int64_t units8 = (p.units + 7) / 8 * 8;
     const int tokens_per_wg8 = (8 * 32) >> shift;
     const int64_t blocks8 = units8 * ((max_q_len + tokens_per_wg8 - 1) / tokens_per_wg8);
-    const int waves = (p.window > 0 || blocks8 < 2 * num_cus()) ? 4 : 8;
-    const int tokens_per_wg = (waves * 32) >> shift;
+    const int tokens_per_wg4 = (4 * 32) >> shift;
+    const int64_t blocks4 = units8 * ((max_q_len + tokens_per_wg4 - 1) / tokens_per_wg4);
+    // Which shape (measured on both sides of each line; see also prefill_kernels.hpp):
+    //   a sliding window: 128 rows (a workgroup's rows should span few keys; 8 waves 9 % slower);
+    //   128-row workgroups do not even fill the CUs once: two key groups, which halve the longest
+    //     walk (634 new tokens behind 1 723 over 8-bit caches: 43.4 -> 38.1 us; at twice as many
+    //     workgroups the two tie);
+    //   256-row workgroups would not fill them twice - five times for whole prompts, whose walks are
+    //     short against what a workgroup costs before and behind its walk, which two resident
+    //     workgroups overlap (8 prompts of 1 024: 94 -> 84 us, 8 of 1 280: 148 -> 143, 8 of 2 560:
+    //     395 -> 415): 128 rows;
+    //   else 256 rows, half the loads and LDS stores per row (chunks of 512 behind 2 048: 124 us, 147 at
+    //     128 rows).
+    PrefillShape shape = PrefillShape::k8Waves;
+    if (p.window > 0) shape = PrefillShape::k4Waves;
+    else if (blocks4 <= num_cus()) shape = PrefillShape::k8WavesTwoGroups;
+    else if (blocks8 < 2 * num_cus() || (contig && blocks8 <= 5 * num_cus())) shape = PrefillShape::k4Waves;
+    const int tokens_per_wg = ((shape == PrefillShape::k8Waves ? 8 : 4) * 32) >> shift;
     p.q_tiles = (max_q_len + tokens_per_wg - 1) / tokens_per_wg;
     const int64_t blocks = units8 * p.q_tiles;
     if (blocks > 0x7fffffffLL) return OPTGQA_ERR_SHAPE;
@@ -447,24 +447,24 @@ int launch_prefill(PrefillParams p, int num_seqs, int max_q_len, int head_dim, i
     const bool f16 = dtype == OPTGQA_F16;
     if (step) {
         if (kv8 || contig || p.window > 0) return OPTGQA_ERR_UNSUPPORTED;
-        return f16 ? launch_prefill_step<kF16>(p, head_dim, grid, waves, st)
-                   : launch_prefill_step<kBF16>(p, head_dim, grid, waves, st);
+        return f16 ? launch_prefill_mma<kF16, false, false, false, true>(p, head_dim, grid, shape, st)
+                   : launch_prefill_mma<kBF16, false, false, false, true>(p, head_dim, grid, shape, st);
     }
     if (contig) {
         if (kv8 || p.window > 0) return OPTGQA_ERR_UNSUPPORTED;
-        return f16 ? launch_prefill_mma<kF16, false, false, true>(p, head_dim, grid, waves, st)
-                   : launch_prefill_mma<kBF16, false, false, true>(p, head_dim, grid, waves, st);
+        return f16 ? launch_prefill_mma<kF16, false, false, true, false>(p, head_dim, grid, shape, st)
+                   : launch_prefill_mma<kBF16, false, false, true, false>(p, head_dim, grid, shape, st);
     }
     if (p.window > 0) {
         if (kv8) return OPTGQA_ERR_UNSUPPORTED;
-        return f16 ? launch_prefill_mma<kF16, false, true, false>(p, head_dim, grid, waves, st)
-                   : launch_prefill_mma<kBF16, false, true, false>(p, head_dim, grid, waves, st);
+        return f16 ? launch_prefill_mma<kF16, false, true, false, false>(p, head_dim, grid, shape, st)
+                   : launch_prefill_mma<kBF16, false, true, false, false>(p, head_dim, grid, shape, st);
     }
     if (kv8)
-        return f16 ? launch_prefill_mma<kF16, true, false, false>(p, head_dim, grid, waves, st)
-                   : launch_prefill_mma<kBF16, true, false, false>(p, head_dim, grid, waves, st);
-    return f16 ? launch_prefill_mma<kF16, false, false, false>(p, head_dim, grid, waves, st)
-               : launch_prefill_mma<kBF16, false, false, false>(p, head_dim, grid, waves, st);
+        return f16 ? launch_prefill_mma<kF16, true, false, false, false>(p, head_dim, grid, shape, st)
+                   : launch_prefill_mma<kBF16, true, false, false, false>(p, head_dim, grid, shape, st);
+    return f16 ? launch_prefill_mma<kF16, false, false, false, false>(p, head_dim, grid, shape, st)
+               : launch_prefill_mma<kBF16, false, false, false, false>(p, head_dim, grid, shape, st);
 }
 
 }  // namespace

@@ -65,6 +65,7 @@ constexpr float kPfSkipLog2 = OPTGQA_PF_SKIP_LOG2;
 // tiles between a look at whether the rest of the walk still matters, at the least (2, 4 and 8 measure the same)
 constexpr int kPfCheckTiles = 4;
 
+
 struct PrefillParams {
     void* out;                  // [T][Hq][D] dtype
     const void* q;              // [T][Hq][D]
@@ -93,11 +94,14 @@ struct PrefillParams {
     void* v_cache_w;
 };
 
-// Waves per workgroup (a template parameter, 32 rows per wave): 8 - 256 rows against one K/V tile,
-// half the loader work and LDS stores per row, measured 4 % on the causal kernel - when that still
-// gives every CU two rounds of workgroups; else 4, and always 4 with a sliding window, where a
-// workgroup's rows should span few keys because every tile that some row's window start or causal
-// end cuts needs the masked path (measured: 8 waves 9 % slower there).
+// Workgroup shapes (template parameters WAVES and KS; 32 rows per wave, chosen in launch_prefill):
+//   8 waves            256 rows against one K/V tile, half the loader work and LDS stores per row;
+//   4 waves            128 rows, two workgroups to a CU: one's start and end under the other's walk;
+//   8 waves, KS = 2    128 rows, the walk's tiles dealt to two groups of four waves (each its own tile
+//                      buffers), whose sums are merged through LDS at the end: half as long a walk where
+//                      there are too few workgroups to fill the chip.
+// With a sliding window always 4 waves: a workgroup's rows should span few keys, because every tile that
+// some row's window start or causal end cuts needs the masked path (measured: 8 waves 9 % slower there).
 constexpr int kPfKeys = 32;                              // keys per tile
 // LDS rows, elements: K rows padded by 8 (16-byte reads of 16 keys then cover all 64 banks), V rows
 // by 16 (so do the rows a transposing load touches) - head_dim 128: 272 / 288 bytes, 64: 144 / 160
@@ -155,11 +159,11 @@ template <> struct PfSoftmax<kBF16> {
 // inputs - chosen per key, both addresses are always valid - and, as with CONTIG, the workgroups of
 // a KV head's first head chunk store their own tokens' rows into the caches.  No workgroup reads
 // a cache row that this launch writes.
-template <int DT, bool KV8, bool WIN, bool CONTIG, int D, int WAVES, bool STEP>
+template <int DT, bool KV8, bool WIN, bool CONTIG, int D, int WAVES, int KS, bool STEP>
 __device__ __forceinline__ void prefill_body(const PrefillParams& p)
 {
-    static_assert(WAVES == 4 || (WAVES == 8 && !WIN), "4 waves, or 8 without a window");
-    constexpr int kPfWaves = WAVES, kPfRows = WAVES * 32;
+    static_assert((WAVES == 4 && KS == 1) || (WAVES == 8 && !WIN && (KS == 1 || KS == 2)), "4 waves; without a window also 8, or 8 in two key groups");
+    constexpr int kPfWaves = WAVES / KS, kPfRows = kPfWaves * 32;   // of one key group: its waves, and the workgroup's rows
     static_assert(!(CONTIG && (KV8 || WIN)), "the whole-prompt variant reads 2-byte inputs, full causal mask");
     static_assert(!(STEP && (KV8 || WIN || CONTIG)), "the one-call step runs over 2-byte caches, full causal mask");
     static_assert(D == 128 || D == 64, "head_dim 64 or 128");
@@ -170,9 +174,9 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     constexpr int kKPT = kPfKeys * (D / 8) / (kPfWaves * 32);   // consecutive keys a loader thread moves per tile (half the threads per tensor)
     constexpr int ES = KV8 ? 1 : 2;                     // bytes per cache element
     // two tile buffers, each a K tile [32][kPfKRow] followed by a V tile [32][kPfVRow]
-    constexpr int kKTile = kPfKeys * kPfKRow, kBuf = kKTile + kPfKeys * kPfVRow;
-    extern __shared__ __attribute__((aligned(16))) uint16_t tile_lds[];          // PfTile<D>::kLdsBytes
-    __shared__ float vote[3][kPfWaves];                          // rest_judged
+    constexpr int kKTile = kPfKeys * kPfKRow, kBuf = kKTile + kPfKeys * kPfVRow;   // (of each key group)
+    extern __shared__ __attribute__((aligned(16))) uint16_t tile_lds[];          // KS * PfTile<D>::kLdsBytes
+    __shared__ float vote[3][WAVES];                          // rest_judged
 
     // ---- which rows -----------------------------------------------------------------------
     // XCD-aware order: workgroups go to XCD (flat id % 8); all query tiles of one (sequence, KV
@@ -190,24 +194,57 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     const int GH = p.heads_per_wg, gshift = p.heads_pow2_shift;
     const int G = Hq / Hkv, chunks = G / GH;
     const int units_per_seq = Hkv * chunks;
-    // (without slopes nothing is skipped and only the query tile decides the length: query tiles first)
+    const int tokens_per_wg = kPfRows >> gshift;
+    // Without slopes nothing is skipped and the query tile's position alone decides the length: with up to
+    // 64 sequences (a lane each) workgroup number n takes the (n / units per sequence)-th of all (sequence,
+    // query tile) pairs in falling order of their last position, counted in query tiles.  (Ragged chunks, 6
+    // sequences of 333-777 new tokens behind 5-2999 cached: by query tile alone the launch's longest
+    // workgroup started in its middle.)
     const bool by_head = p.slopes != nullptr;
-    const int units8 = (p.units + 7) >> 3;
-    const int urow = by_head ? w / p.q_tiles : w % units8;
-    const int qt = p.q_tiles - 1 - (by_head ? w % p.q_tiles : w / units8);
-    const int ui = urow * 8 + ((xcd - urow) & 7);
-    if (ui >= p.units) return;
-    const int b = by_head ? ui % p.num_seqs : ui / units_per_seq;
-    const int gu = by_head ? units_per_seq - 1 - ui / p.num_seqs : ui - b * units_per_seq;
+    int b, gu, qt, cu0, n_b, ctx_len;
+    if (!WIN && !by_head && p.num_seqs <= 64) {
+        const int rank = blockIdx.x / units_per_seq;
+        const int l = threadIdx.x & 63, lc = min(l, p.num_seqs - 1);
+        const int c0 = p.cu_q_lens[lc], n = p.cu_q_lens[lc + 1] - c0, len = CONTIG ? n : p.context_lens[lc];
+        const int tiles = l < p.num_seqs && n > 0 ? (n + tokens_per_wg - 1) / tokens_per_wg : 0;
+        const int before = max(len - n, 0) / tokens_per_wg;      // query tiles' worth of cached tokens
+        // the pairs that end at or beyond position x (in query tiles): tile q of a sequence ends at before + q + 1
+        auto count = [&](int x) __attribute__((always_inline)) {
+            return wave_sum(min(tiles, max(before + tiles - x + 1, 0)));
+        };
+        if (count(1) <= rank) return;
+        int lo = 1, hi = wave_max(tiles > 0 ? before + tiles : 0) + 1;   // count(lo) > rank >= count(hi) = 0
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (count(mid) > rank) lo = mid;
+            else hi = mid;
+        }
+        // the rank's pair ends at lo: of those that do, in order of the sequences
+        uint64_t at = __builtin_amdgcn_ballot_w64(before < lo && lo <= before + tiles);
+        for (int skip = rank - count(lo + 1); skip > 0; --skip) at &= at - 1;
+        b = __builtin_ctzll(at);
+        qt = lo - 1 - __builtin_amdgcn_readlane(before, b);
+        cu0 = __builtin_amdgcn_readlane(c0, b);
+        n_b = __builtin_amdgcn_readlane(n, b);
+        ctx_len = __builtin_amdgcn_readlane(len, b);
+        gu = blockIdx.x - rank * units_per_seq;
+    } else {
+        const int units8 = (p.units + 7) >> 3;
+        const int urow = by_head ? w / p.q_tiles : w % units8;
+        qt = p.q_tiles - 1 - (by_head ? w % p.q_tiles : w / units8);
+        const int ui = urow * 8 + ((xcd - urow) & 7);
+        if (ui >= p.units) return;
+        b = by_head ? ui % p.num_seqs : ui / units_per_seq;
+        gu = by_head ? units_per_seq - 1 - ui / p.num_seqs : ui - b * units_per_seq;
+        cu0 = p.cu_q_lens[b];
+        n_b = p.cu_q_lens[b + 1] - cu0;
+        ctx_len = CONTIG ? n_b : p.context_lens[b];
+    }
     const int g = gu / chunks;
     const int h0 = g * G + (gu - g * chunks) * GH;
-    const int tokens_per_wg = kPfRows >> gshift;
-
-    const int cu0 = p.cu_q_lens[b];
-    const int n_b = p.cu_q_lens[b + 1] - cu0;
     const int tq0 = qt * tokens_per_wg;
     if (tq0 >= n_b) return;
-    const int L = CONTIG ? n_b : p.context_lens[b];
+    const int L = ctx_len;
     const int pos0 = L - n_b;                                   // position of the sequence's first new token
     const int kmax = pos0 + min(tq0 + tokens_per_wg, n_b);      // keys 0 .. kmax-1 are visible to some row
     const int ntiles = (kmax + kPfKeys - 1) / kPfKeys;
@@ -219,8 +256,11 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     const int kmin = W > 0 ? max(pos0 + tq0 - W + 1, 0) : 0;
     const int kt0 = kmin / kPfKeys;
 
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // wg_wave: the wave's number in the workgroup; kw: its key group; wave, tid: its and its thread's number in that
+    const int lane = threadIdx.x & 63;
+    const int wg_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int kw = KS == 1 ? 0 : wg_wave / kPfWaves, wave = KS == 1 ? wg_wave : wg_wave % kPfWaves;
+    const int tid = KS == 1 ? threadIdx.x : threadIdx.x % (kPfWaves * 64);
     const int n32 = lane & 31, h2 = lane >> 5;
 
     const uint16_t* __restrict__ qp = static_cast<const uint16_t*>(p.q);
@@ -262,65 +302,6 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         const int64_t dst = blk * block_stride + (int64_t)g * bs * D + (int64_t)(tok & (bs - 1)) * D + 8 * piece;
         return reinterpret_cast<own_u32x4*>((is_v ? static_cast<uint16_t*>(p.v_cache_w) : static_cast<uint16_t*>(p.k_cache_w)) + dst);
     };
-    own_u32x4 own[kOwnBatch];
-    int own_blk[kOwnBatch];
-    if (n_own > 0) {                                             // workgroup-uniform
-#pragma unroll
-        for (int c = 0; c < kOwnBatch; ++c) {
-            const int ic = min((int)threadIdx.x + c * kPfWaves * 64, n_own - 1);
-            own[c] = *reinterpret_cast<const own_u32x4*>(own_src(ic));
-            own_blk[c] = own_blk_of(ic);
-        }
-    }
-
-    // This lane's query row (row n32 of the wave's 32): B operand of the score MFMAs (dims
-    // 16m + 8h2 .. +7, m = 0..7), its position, slope and validity.
-    uint4 qb[kQ];
-    float posf, lof, slope2, m_ref, lsum;
-    bool row_ok, started;
-    int64_t out_off;
-    {
-        // row block of 32: waves w and w + 4 share a SIMD, so with 8 waves the upper four take theirs in
-        // reverse order (the first head's rows, with the steepest slope, beside the last head's)
-        const int row = 32 * (WAVES == 8 && wave >= 4 ? 11 - wave : wave) + n32;
-        const int tshift = __builtin_ctz(tokens_per_wg);
-        const int ti = tq0 + (row & (tokens_per_wg - 1)), head = row >> tshift;
-        row_ok = ti < n_b && head < GH;
-        const int tc = min(ti, n_b - 1), hc = min(head, GH - 1);
-        const int64_t qrow = ((int64_t)(cu0 + tc) * Hq + h0 + hc) * D;
-        out_off = qrow;
-        const int pos = pos0 + tc;
-        posf = (float)pos;
-        lof = W > 0 ? (float)(pos - W) : -1.f;                   // keys above this one are inside the window
-        slope2 = p.slopes && row_ok ? p.slopes[h0 + hc] * kLog2e : 0.f;
-        m_ref = 0.f;                                             // set by the first tile in which the row sees a key
-        // a row that does not exist never wants a tile: its sum is already beyond anything
-        started = !row_ok;
-        lsum = row_ok ? 0.f : INFINITY;
-        const uint32_t keep = row_ok ? 0xffffffffu : 0u;
-#pragma unroll
-        for (int m = 0; m < kQ; ++m) {
-            const uint4 x = *reinterpret_cast<const uint4*>(qp + qrow + 16 * m + 8 * h2);
-            qb[m] = make_uint4(x.x & keep, x.y & keep, x.z & keep, x.w & keep);
-        }
-    }
-    // score scale (base 2) and output scale of this workgroup's KV head
-    const float scale2 = KV8 && p.k_scales ? p.scale2 * p.k_scales[g] : p.scale2;
-    const float out_scale = KV8 && p.v_scales ? p.v_scales[g] : p.out_scale;
-    // slope * (offset of the lane's e-th key from its first key in a tile) / score scale: the part of
-    // the ALiBi term that does not change from tile to tile, as the score MFMAs' starting value
-    f32x16 key_bias;
-    {
-        const float per_key = slope2 / scale2;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) key_bias[e] = per_key * (float)(8 * (e >> 2) + (e & 3));
-    }
-    f32x16 acc[kDB];                                             // O^T: dims 32db + 8i + 4h2 + j of row n32 in element 4i + j
-#pragma unroll
-    for (int db = 0; db < kDB; ++db)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[db][e] = 0.f;
-
     // ---- tile staging: threads 0..127 fetch K, 128..255 fetch V; either way a thread moves the
     // same 16-byte column piece of kKPT consecutive keys (kCPR lanes cover one row) ----------------
     const bool k_loader = wave < kPfWaves / 2;                   // wave-uniform (first half of the waves: K; second: V)
@@ -343,11 +324,14 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     typedef typename std::conditional<KV8, u32x2, u32x4>::type StageT;   // 8 elements of one key
     StageT stage[kKPT];
-    const int last_tile = ntiles - 1;                             // >= kt0
-    const int nt = ntiles - kt0;                                  // tiles this workgroup walks
-    // the i-th tile of the walk (i past the end: the last one again)
+    // KS key groups: of every KS consecutive tiles of the walk each group takes one.  The walk is made a
+    // multiple of KS long by starting it beyond the diagonal, where the causal mask hides every key.
+    const int pad = KS == 1 ? 0 : (ntiles - kt0) & (KS - 1);
+    const int last_tile = ntiles - 1 + pad;                       // >= kt0
+    const int nt = ntiles - kt0 + pad;                            // tiles this workgroup walks
+    // the tile of the walk's i-th step (i past the end: the last one again)
     auto tile_of = [&](int i) __attribute__((always_inline)) {
-        const int ic = min(i, nt - 1);
+        const int ic = min(i * KS + kw, nt - KS + kw);
         return last_tile - ic;                                    // from the diagonal backwards
     };
     auto load_blk = [&](int i) __attribute__((always_inline)) {
@@ -356,19 +340,23 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         const int key = min(tile_of(i) * kPfKeys + kKPT * l_group, kmax - 1);
         return table[key >> bs_shift];
     };
-    int blk_next = load_blk(0);
+
+    // Everything a workgroup starts with is asked for before anything is waited for: the block numbers of
+    // the first tiles, the query rows, this workgroup's own new rows, then the first two tiles.
+    const int blk_first = load_blk(0), blk_second = load_blk(1);
+    int blk_next = load_blk(2);
 
     // (address arithmetic kept short on purpose - this loop pays for every instruction: one 64-bit
     // multiply-add for the block, one shift-add for the first row, then per key a clamp and a shift-add;
     // rows past the sequence's last key re-read that key, which lies in the same block)
     const unsigned char* const l_lane = l_src + 8 * l_chunk * ES;                 // this lane's column piece
     const uint32_t l_blk_bytes = (uint32_t)(block_stride * ES);                   // < 2^32: one block of all KV heads
-    auto fetch_tile = [&](StageT (&stage)[kKPT], int i) __attribute__((always_inline)) {
+    auto fetch_from = [&](StageT (&stage)[kKPT], int i, int blk) __attribute__((always_inline)) {
         const int key0 = min(tile_of(i) * kPfKeys + kKPT * l_group, kmax - 1);
         const int rmax = kmax - 1 - key0;                         // >= 0; < kKPT - 1 only at the sequence's end
         const unsigned char* base;
         if (CONTIG) base = l_lane + (uint64_t)(uint32_t)key0 * (uint32_t)l_row;
-        else base = l_lane + (uint64_t)(uint32_t)blk_next * l_blk_bytes + (uint32_t)((key0 & (bs - 1)) * (D * ES));
+        else base = l_lane + (uint64_t)(uint32_t)blk * l_blk_bytes + (uint32_t)((key0 & (bs - 1)) * (D * ES));
         // STEP: a tile that ends below the first new position is all cache (the plain path: most
         // tiles); otherwise the keys from that position on come from the inputs, chosen per key (the
         // clamped key, so that rows past the last visible key re-read it from wherever it lives)
@@ -385,11 +373,15 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
             for (int j = 0; j < kKPT; ++j)
                 stage[j] = *reinterpret_cast<const StageT*>(base + (uint32_t)(min(j, rmax) * (CONTIG ? (int)l_row : D * ES)));
         }
+    };
+    auto fetch_tile = [&](StageT (&stage)[kKPT], int i) __attribute__((always_inline)) {
+        fetch_from(stage, i, blk_next);
         blk_next = load_blk(i + 1);
     };
     // A tile's place in LDS: the j-th tile of the walk sits in buffer j % 2.
-    auto tile_base = [&](int j) __attribute__((always_inline)) { return (j & 1) * kBuf; };
-    auto tile_base_v = [&](int j) __attribute__((always_inline)) { return (j & 1) * kBuf + kKTile; };
+    const int group_base = kw * 2 * kBuf;
+    auto tile_base = [&](int j) __attribute__((always_inline)) { return group_base + (j & 1) * kBuf; };
+    auto tile_base_v = [&](int j) __attribute__((always_inline)) { return group_base + (j & 1) * kBuf + kKTile; };
     auto store_tile = [&](const StageT (&stage)[kKPT], int buf) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < kKPT; ++j) {
@@ -403,6 +395,70 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
             *reinterpret_cast<u32x4*>(&tile_lds[(k_loader ? tile_base(buf) : tile_base_v(buf)) + l_dst + j * l_pitch]) = w;
         }
     };
+
+    own_u32x4 own[kOwnBatch];
+    int own_blk[kOwnBatch];
+    if (n_own > 0) {                                             // workgroup-uniform
+#pragma unroll
+        for (int c = 0; c < kOwnBatch; ++c) {
+            const int ic = min((int)threadIdx.x + c * WAVES * 64, n_own - 1);
+            own[c] = *reinterpret_cast<const own_u32x4*>(own_src(ic));
+            own_blk[c] = own_blk_of(ic);
+        }
+    }
+
+    // This lane's query row (row n32 of the wave's 32): B operand of the score MFMAs (dims
+    // 16m + 8h2 .. +7, m = 0..7), its position, slope and validity.
+    // Waves w and w + 4 of a workgroup share a SIMD, so with 8 waves the upper four take the row blocks in
+    // reverse order (the first head's rows, with the steepest slope, beside the last head's).
+    const int row_block = wg_wave < 4 ? wg_wave : KS == 1 ? 11 - wg_wave : 7 - wg_wave;
+    uint4 qb[kQ];
+    float posf, lof, slope2, m_ref, lsum;
+    bool row_ok, started;
+    int64_t out_off;
+    {
+        const int row = 32 * row_block + n32;
+        const int tshift = __builtin_ctz(tokens_per_wg);
+        const int ti = tq0 + (row & (tokens_per_wg - 1)), head = row >> tshift;
+        row_ok = ti < n_b && head < GH;
+        const int tc = min(ti, n_b - 1), hc = min(head, GH - 1);
+        const int64_t qrow = ((int64_t)(cu0 + tc) * Hq + h0 + hc) * D;
+        out_off = qrow;
+        const int pos = pos0 + tc;
+        posf = (float)pos;
+        lof = W > 0 ? (float)(pos - W) : -1.f;                   // keys above this one are inside the window
+        slope2 = p.slopes && row_ok ? p.slopes[h0 + hc] * kLog2e : 0.f;
+        m_ref = 0.f;                                             // set by the first tile in which the row sees a key
+        // a row that does not exist never wants a tile: its sum is already beyond anything
+        started = !row_ok;
+        lsum = row_ok ? 0.f : INFINITY;
+#pragma unroll
+        for (int m = 0; m < kQ; ++m) qb[m] = *reinterpret_cast<const uint4*>(qp + qrow + 16 * m + 8 * h2);
+    }
+    StageT stage_first[kKPT];
+    fetch_from(stage_first, 0, blk_first);
+    fetch_from(stage, 1, blk_second);
+    {
+        const uint32_t keep = row_ok ? 0xffffffffu : 0u;
+#pragma unroll
+        for (int m = 0; m < kQ; ++m) qb[m] = make_uint4(qb[m].x & keep, qb[m].y & keep, qb[m].z & keep, qb[m].w & keep);
+    }
+    // score scale (base 2) and output scale of this workgroup's KV head
+    const float scale2 = KV8 && p.k_scales ? p.scale2 * p.k_scales[g] : p.scale2;
+    const float out_scale = KV8 && p.v_scales ? p.v_scales[g] : p.out_scale;
+    // slope * (offset of the lane's e-th key from its first key in a tile) / score scale: the part of
+    // the ALiBi term that does not change from tile to tile, as the score MFMAs' starting value
+    f32x16 key_bias;
+    {
+        const float per_key = slope2 / scale2;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) key_bias[e] = per_key * (float)(8 * (e >> 2) + (e & 3));
+    }
+    f32x16 acc[kDB];                                             // O^T: dims 32db + 8i + 4h2 + j of row n32 in element 4i + j
+#pragma unroll
+    for (int db = 0; db < kDB; ++db)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[db][e] = 0.f;
 
     // ---- S^T = K Q^T : element 4i + j = score of key 32kt + 8i + 4h2 + j against row n32
     // (the accumulator starts from the tile-invariant part of the ALiBi term, already divided by the
@@ -442,7 +498,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
             // below 2^kPfSkipLog2 of the row's sum (this lane's half of it, which is no more) for
             // every row of the wave, the tile changes no bit that the accumulators keep.
             const float room = __builtin_amdgcn_logf(lsum) + kPfSkipLog2;        // log2; -inf before the row's first key
-            if (__builtin_amdgcn_ballot_w64(mx > room) == 0) return true;
+            if (__builtin_amdgcn_ballot_w64(mx > room) == 0) return;
         }
         // Has the row seen a key yet?  Walking backwards from the diagonal, a row's first visible key
         // may lie in a later tile of the walk than another row's.
@@ -505,7 +561,6 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
                 if (PfSoftmax<DT>::kSplitWeights)
                     acc[db] = mfma32<DT>(va, make_uint4(pk_lo[m][0], pk_lo[m][1], pk_lo[m][2], pk_lo[m][3]), acc[db]);
             }
-        return false;
     };
 
     // ---- the rest of the walk judged at once -------------------------------------------------------
@@ -519,8 +574,8 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // all rows.  The workgroup then reads the keys once, without V, LDS, MFMAs or exponentials.
     // A norm that is not a number, or infinite, fails the test.
     // When to ask: A grows by 32 B a tile, and the keys' norms - not known before they are read - are
-    // taken to be like the queries', |k| = |q| (a wrong guess costs time only).
-    auto rest_judged = [&](int kt, bool wave_skips) __attribute__((always_inline)) -> int {
+    // taken to be like the queries', at most 1.25 |q| (a wrong guess costs time only).
+    auto rest_judged = [&](int kt) __attribute__((always_inline)) -> int {
         const int k0 = kt * kPfKeys + kPfKeys - 1;
         float q2 = 0.f;
 #pragma unroll
@@ -533,13 +588,13 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         q2 += __shfl_xor(q2, 32);                                // a row's dims live in 2 lanes (h2)
         const float qn = __builtin_amdgcn_sqrtf(q2);
         const float qs = 1.001f * fabsf(scale2) * qn + 0x1p-100f;    // (margins cover the rounding of the norms)
-        const float room = __builtin_amdgcn_logf(lsum) + (kPfSkipLog2 - 0.01f);
+        const float room = __builtin_amdgcn_logf(lsum + __shfl_xor(lsum, 32)) + (kPfSkipLog2 - 0.01f);
         float a = (room + m_ref + slope2 * (posf - (float)k0)) / qs;
         float bb = row_ok ? slope2 / qs : INFINITY;
-        float wait = a >= qn ? 0.f : fminf((qn - a) / (bb * (float)kPfKeys), 1e6f);
-        wait = wait >= 0.f ? wait : 1e6f;                        // (no slope, or a negative one)
+        float wait = a >= 1.25f * qn ? 0.f : fminf((1.25f * qn - a) / (bb * (float)kPfKeys) + 1.f, 1e6f);
+        wait = room == -INFINITY ? 1.f : wait >= 0.f ? wait : 1e6f;  // (no key seen yet; no slope, or a negative one)
         const bool no = !(a > 0.f && q2 < 0x1p100f);
-        if (!wave_skips || __builtin_amdgcn_ballot_w64(no) != 0) a = -1.f;
+        if (__builtin_amdgcn_ballot_w64(no) != 0) a = -1.f;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
             a = fminf(a, __shfl_xor(a, off));
@@ -547,68 +602,89 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
             wait = fmaxf(wait, __shfl_xor(wait, off));
         }
         if (lane == 0) {
-            vote[0][wave] = a;
-            vote[1][wave] = bb;
-            vote[2][wave] = wait;
+            vote[0][wg_wave] = a;
+            vote[1][wg_wave] = bb;
+            vote[2][wg_wave] = wait;
         }
         __syncthreads();
         a = vote[0][0], bb = vote[1][0], wait = vote[2][0];
 #pragma unroll
-        for (int i = 1; i < kPfWaves; ++i) {
+        for (int i = 1; i < WAVES; ++i) {
             a = fminf(a, vote[0][i]);
             bb = fminf(bb, vote[1][i]);
             wait = fmaxf(wait, vote[2][i]);
         }
-        const int ask = max(kPfCheckTiles, __builtin_amdgcn_readfirstlane((int)wait + 1));
-        if (!(a > 0.f) || ask > kPfCheckTiles) return ask;       // workgroup-uniform
-        // thread -> (key, 16-byte column piece): kPfWaves * 64 / kCPR keys a pass, nearest first
-        constexpr int kScanKeys = kPfWaves * 64 / kCPR, kBatch = 8;
-        int s_tid = tid;
-        asm volatile("" : "+v"(s_tid));                          // (keeps this rare code's addresses out of the registers of the loop around it)
-        const int s_key = s_tid / kCPR, s_piece = s_tid % kCPR;
-        const unsigned char* const s_lane = kc + 8 * s_piece * ES;
-        auto scan_key = [&](int i) __attribute__((always_inline)) { return max(k0 - i * kScanKeys - s_key, 0); };
-        const int passes = (k0 + kScanKeys) / kScanKeys;
-        int blks[kBatch];
-        auto load_blks = [&](int i) __attribute__((always_inline)) {
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) blks[u] = CONTIG ? 0 : table[scan_key(i + u) >> bs_shift];
-        };
-        load_blks(0);
+        if (!(a > 0.f) || wait > 0.f) return max(kPfCheckTiles / 2, __builtin_amdgcn_readfirstlane((int)wait));    // workgroup-uniform
+        // Nearest first, the waves take groups of 16 keys in turn: one block each, kLoads 16-byte loads per
+        // lane, kRowLanes lanes to a key.  A lane holds the block number of one of the wave's next 64 groups.
+        constexpr int kRowLanes = D * ES / 16, kRowsPerLoad = 64 / kRowLanes, kLoads = 16 / kRowsPerLoad;
+        int s_lane = lane;
+        asm volatile("" : "+v"(s_lane));                         // (keeps this rare code's addresses out of the registers of the loop around it)
+        const int s_row = s_lane / kRowLanes, s_piece = s_lane % kRowLanes;
+        const uint32_t row_bytes = CONTIG ? (uint32_t)(p.k_in_stride * 2) : D * ES;
+        const int groups = (k0 + 1) / 16;
+        const float far_end = bb < 0.f ? 15.f : 0.f;             // offset of a group's key with the least bound
         bool bad = false;
-        for (int i = 0; i < passes; i += kBatch) {
-            StageT x[kBatch];
+        for (int g0 = 0; g0 < groups; g0 += 64 * WAVES) {
+            const int mine = min((groups - g0 - wg_wave + WAVES - 1) / WAVES, 64);     // this wave's groups here
+            if (mine <= 0) break;
+            auto base_key = [&](int i) __attribute__((always_inline)) { return k0 - 15 - 16 * (g0 + i * WAVES + wg_wave); };
+            const int blks = CONTIG ? 0 : table[max(base_key(s_lane), 0) >> bs_shift];
+            auto load_keys = [&](uint4 (&x)[kLoads], int i) __attribute__((always_inline)) {
+                i = min(i, mine - 1);
+                const int key = base_key(i);
+                const int blk = CONTIG ? 0 : __builtin_amdgcn_readlane(blks, i);
+                if (STEP && key + 15 >= pos0) {                  // some of its keys are new: from the inputs, chosen per key
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                const int key = scan_key(i + u);
-                const unsigned char* src;
-                if (CONTIG) src = s_lane + (uint64_t)(uint32_t)key * (uint32_t)(p.k_in_stride * 2);
-                else src = s_lane + (uint64_t)(uint32_t)blks[u] * (uint32_t)(block_stride * ES) + (uint32_t)((key & (bs - 1)) * (D * ES));
-                if (STEP && key >= pos0) src = kin + 16 * s_piece + (uint64_t)(uint32_t)(key - pos0) * (uint32_t)(p.k_in_stride * 2);
-                x[u] = *reinterpret_cast<const StageT*>(src);
-            }
-            load_blks(i + kBatch);
+                    for (int r = 0; r < kLoads; ++r) {
+                        const int kk = key + kRowsPerLoad * r + s_row;
+                        const unsigned char* src = kc + (uint64_t)(uint32_t)blk * l_blk_bytes + (uint32_t)((kk & (bs - 1)) * (D * ES));
+                        if (kk >= pos0) src = kin + (uint64_t)(uint32_t)(kk - pos0) * (uint32_t)(p.k_in_stride * 2);
+                        x[r] = *reinterpret_cast<const uint4*>(src + 16 * s_piece);
+                    }
+                    return;
+                }
+                const unsigned char* src = CONTIG ? kc + (uint64_t)(uint32_t)key * row_bytes
+                                                  : kc + (uint64_t)(uint32_t)blk * l_blk_bytes + (uint32_t)((key & (bs - 1)) * (D * ES));
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                uint4 y;
-                if constexpr (KV8) y = widen8_e4m3<DT>(x[u][0], x[u][1]);
-                else y = __builtin_bit_cast(uint4, x[u]);
-                float n2 = dot2<DT>(y.x, y.x, 0.f);
+                for (int r = 0; r < kLoads; ++r)
+                    x[r] = *reinterpret_cast<const uint4*>(src + (uint64_t)(uint32_t)(kRowsPerLoad * r + s_row) * row_bytes + 16 * s_piece);
+            };
+            auto norm2 = [&](uint4 y, float n2) __attribute__((always_inline)) {
+                n2 = dot2<DT>(y.x, y.x, n2);
                 n2 = dot2<DT>(y.y, y.y, n2);
                 n2 = dot2<DT>(y.z, y.z, n2);
-                n2 = dot2<DT>(y.w, y.w, n2);
-                n2 = row_group_sum<kCPR>(n2);
-                const float most = fmaf(bb, (float)(k0 - scan_key(i + u)), a);
-                bad = bad || !(most > 0.f && n2 * 1.001f <= most * most);
+                return dot2<DT>(y.w, y.w, n2);
+            };
+            auto judge = [&](const uint4 (&x)[kLoads], int i) __attribute__((always_inline)) {
+                const float most = fmaf(bb, (float)(k0 - 15 - base_key(min(i, mine - 1))) + far_end, a);
+                const float most2 = most > 0.f ? most * most * 0.999f : -1.f;
+#pragma unroll
+                for (int r = 0; r < kLoads; ++r) {
+                    float n2;
+                    if constexpr (KV8) n2 = norm2(widen8_e4m3<DT>(x[r].z, x[r].w), norm2(widen8_e4m3<DT>(x[r].x, x[r].y), 0.f));
+                    else n2 = norm2(x[r], 0.f);
+                    n2 = row_group_sum<kRowLanes>(n2);
+                    bad = bad || !(n2 <= most2);
+                }
+            };
+            uint4 x0[kLoads], x1[kLoads];
+            load_keys(x0, 0);
+            for (int i = 0; i < mine; i += 2) {
+                load_keys(x1, i + 1);
+                judge(x0, i);
+                load_keys(x0, i + 2);
+                judge(x1, i + 1);
+                if (__builtin_amdgcn_ballot_w64(bad) != 0) break;
             }
             if (__builtin_amdgcn_ballot_w64(bad) != 0) break;
         }
         __syncthreads();                                         // the votes above have been read
-        if (lane == 0) vote[0][wave] = __builtin_amdgcn_ballot_w64(bad) != 0 ? -1.f : 1.f;
+        if (lane == 0) vote[0][wg_wave] = __builtin_amdgcn_ballot_w64(bad) != 0 ? -1.f : 1.f;
         __syncthreads();
         a = vote[0][0];
 #pragma unroll
-        for (int i = 1; i < kPfWaves; ++i) a = fminf(a, vote[0][i]);
+        for (int i = 1; i < WAVES; ++i) a = fminf(a, vote[0][i]);
         return a > 0.f ? 0 : 2 * kPfCheckTiles;                  // (the next call's votes are barriers away)
     };
 
@@ -619,20 +695,18 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // (measured: 3 % on the kernel).  For that the K tiles run one tile ahead of the V tiles: at the
     // start of step j, K tiles j and j + 1 and V tile j are in LDS, K tile j + 2 and V tile j + 1 are
     // on their way to registers.  Prologue:
-    fetch_tile(stage, 0);
-    store_tile(stage, 0);
-    if (n_own > 0) {                                             // the rows loaded at the top have landed with tile 0
+    store_tile(stage_first, 0);
+    if (k_loader) {                                              // wave-uniform
+        store_tile(stage, 1);
+        fetch_tile(stage, 2);
+    }
+    if (n_own > 0) {                                             // the rows loaded at the top have landed with the tiles
 #pragma unroll
         for (int c = 0; c < kOwnBatch; ++c) {
-            const int idx = (int)threadIdx.x + c * kPfWaves * 64;
+            const int idx = (int)threadIdx.x + c * WAVES * 64;
             if (idx < n_own) *own_dst(idx, own_blk[c]) = own[c];
         }
     }
-    if (k_loader) {                                              // wave-uniform
-        fetch_tile(stage, 1);
-        store_tile(stage, 1);
-    }
-    fetch_tile(stage, 1 + l_ahead);
     __syncthreads();
     f32x16 st_next = scores(0);
     __syncthreads();                                             // buffer 0's K tile is overwritten during step 0
@@ -649,10 +723,9 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // (two steps per trip with the two score registers swapping roles, so that no trip copies the
     // look-ahead scores into place)
     f32x16 st_other;
-    bool wave_skips = false;                                     // this wave skipped its last tile (wave-uniform)
     auto one_tile = [&](int j, const f32x16& st_cur, f32x16& st_ahead, auto masked) __attribute__((always_inline)) {
         st_ahead = scores(j + 1);
-        wave_skips = softmax_pv(last_tile - j, j, st_cur, masked);
+        softmax_pv(last_tile - (j * KS + kw), j, st_cur, masked);
         store_tile(stage, j + 1 + l_ahead);
         fetch_tile(stage, j + 2 + l_ahead);
         __syncthreads();
@@ -673,19 +746,62 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     const int plain_end = max(cut_end, n_unmasked);                // tiles no mask touches
     // from the diagonal backwards: the tiles the causal mask cuts come first, those that some
     // row's window start cuts (if there is a window) last
-    run_tiles(0, ntiles - plain_end, std::true_type{});
-    // (Without slopes no weight is ever out of the question for its position alone: no checks.)
-    int ask = !WIN && p.slopes ? kPfCheckTiles : nt;
-    for (int j = ntiles - plain_end; j < ntiles - cut_end;) {
-        const int to = min(j + ask, ntiles - cut_end);
+    // (in steps of KS tiles: a step that any mask touches takes the masked path)
+    const int steps = nt / KS;
+    const int from_plain = min((ntiles + pad - plain_end + KS - 1) / KS, steps);
+    const int to_plain = WIN ? max(from_plain, (ntiles + pad - cut_end) / KS) : steps;
+    run_tiles(0, from_plain, std::true_type{});
+    // Without slopes no weight is ever out of the question for its position alone: no checks.
+    int ask = nt;
+    for (int j = from_plain; j < to_plain;) {
+        if constexpr (!WIN)
+            if (p.slopes && nt - j * KS >= kPfCheckTiles && (ask = rest_judged(last_tile - j * KS)) == 0) break;
+        const int to = min(j + (ask + KS - 1) / KS, to_plain);
         run_tiles(j, to, std::false_type{});
         j = to;
-        if constexpr (!WIN) {
-            if (ntiles - j < kPfCheckTiles) ask = kPfCheckTiles;
-            else if ((ask = rest_judged(ntiles - 1 - j, wave_skips)) == 0) break;
-        }
     }
-    if constexpr (WIN) run_tiles(ntiles - cut_end, nt, std::true_type{});
+    if constexpr (WIN) run_tiles(to_plain, steps, std::true_type{});
+
+    // ---- two key groups: merge (max / rescale / add), each wave of a pair finishing half of the dims ----
+    // The waves of a row block hold the same rows in the same lanes; each leaves its reference, its sum
+    // and the other's half of its output block in LDS, over the tile buffers.
+    constexpr int kDBW = kDB / KS;                               // 32-dim blocks that this wave writes
+    f32x16 (&res)[kDB] = acc;
+    const int db0 = kw * kDBW;
+    if constexpr (KS == 2) {
+        constexpr int kPieces = kDBW * 4;                        // 16-byte pieces per lane and wave, and a pair of floats
+        static_assert(WAVES * 64 * (kPieces * 16 + 8) <= KS * PfTile<D>::kLdsBytes, "the exchange fits the tile buffers");
+        float4* const xch = reinterpret_cast<float4*>(tile_lds);
+        float2* const xch_ml = reinterpret_cast<float2*>(xch + WAVES * 64 * kPieces);
+        const int pair_mine = kw * kPfWaves + row_block, pair_theirs = (1 - kw) * kPfWaves + row_block;
+        const int mine = pair_mine * kPieces * 64 + lane, theirs = pair_theirs * kPieces * 64 + lane;
+        __syncthreads();
+        const float m_mine = started ? m_ref : -INFINITY;        // (a group need not have seen a key of the row)
+        xch_ml[pair_mine * 64 + lane] = make_float2(m_mine, lsum);
+#pragma unroll
+        for (int i = 0; i < kDBW; ++i) {
+            const f32x16 send = kw == 0 ? acc[kDBW + i] : acc[i];
+            if (kw != 0) res[i] = acc[kDBW + i];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                xch[mine + 64 * (4 * i + e)] = make_float4(send[4 * e], send[4 * e + 1], send[4 * e + 2], send[4 * e + 3]);
+        }
+        __syncthreads();
+        const float2 t = xch_ml[pair_theirs * 64 + lane];
+        const float m_all = fmaxf(m_mine, t.x);
+        const float f0 = fast_exp2(m_mine - m_all), f1 = fast_exp2(t.x - m_all);
+        lsum = lsum * f0 + t.y * f1;
+#pragma unroll
+        for (int i = 0; i < kDBW; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float4 o = xch[theirs + 64 * (4 * i + e)];
+                res[i][4 * e] = fmaf(o.x, f1, res[i][4 * e] * f0);
+                res[i][4 * e + 1] = fmaf(o.y, f1, res[i][4 * e + 1] * f0);
+                res[i][4 * e + 2] = fmaf(o.z, f1, res[i][4 * e + 2] * f0);
+                res[i][4 * e + 3] = fmaf(o.w, f1, res[i][4 * e + 3] * f0);
+            }
+    }
 
     // ---- normalise and write: this lane holds dims 32db + 8i + 4h2 + (0..3) of its row -----------
     uint16_t* __restrict__ op = static_cast<uint16_t*>(p.out);
@@ -694,32 +810,32 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     if (row_ok) {
         const float inv = out_scale / lt;
 #pragma unroll
-        for (int db = 0; db < kDB; ++db)
+        for (int db = 0; db < kDBW; ++db)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 u32x2 packed;
-                packed.x = narrow2<DT>(acc[db][4 * i] * inv, acc[db][4 * i + 1] * inv);
-                packed.y = narrow2<DT>(acc[db][4 * i + 2] * inv, acc[db][4 * i + 3] * inv);
-                *reinterpret_cast<u32x2*>(op + out_off + 32 * db + 8 * i + 4 * h2) = packed;
+                packed.x = narrow2<DT>(res[db][4 * i] * inv, res[db][4 * i + 1] * inv);
+                packed.y = narrow2<DT>(res[db][4 * i + 2] * inv, res[db][4 * i + 3] * inv);
+                *reinterpret_cast<u32x2*>(op + out_off + 32 * (db0 + db) + 8 * i + 4 * h2) = packed;
             }
     }
     // own rows beyond the first batch (stores inside the walk would delay the tile loads behind
     // them - loads and stores complete in issue order; measured twice as costly as this)
-    for (int idx = threadIdx.x + kOwnBatch * kPfWaves * 64; idx < n_own; idx += kPfWaves * 64)
+    for (int idx = threadIdx.x + kOwnBatch * WAVES * 64; idx < n_own; idx += WAVES * 64)
         *own_dst(idx, own_blk_of(idx)) = *reinterpret_cast<const own_u32x4*>(own_src(idx));
 }
 
-template <int DT, bool KV8 = false, bool WIN = false, bool CONTIG = false, int D = 128, int WAVES = 4>
+template <int DT, bool KV8, bool WIN, bool CONTIG, int D, int WAVES, int KS>
 __global__ __launch_bounds__(WAVES * 64, OPTGQA_PF_WAVES_PER_SIMD) void paged_prefill_mma_kernel(const PrefillParams p)
 {
-    prefill_body<DT, KV8, WIN, CONTIG, D, WAVES, false>(p);
+    prefill_body<DT, KV8, WIN, CONTIG, D, WAVES, KS, false>(p);
 }
 
 // cache write + prefill over the cached context in one launch (see STEP above)
-template <int DT, int D = 128, int WAVES = 4>
+template <int DT, int D, int WAVES, int KS>
 __global__ __launch_bounds__(WAVES * 64, OPTGQA_PF_WAVES_PER_SIMD) void paged_prefill_step_kernel(const PrefillParams p)
 {
-    prefill_body<DT, false, false, false, D, WAVES, true>(p);
+    prefill_body<DT, false, false, false, D, WAVES, KS, true>(p);
 }
 
 }  // namespace optgqa
