@@ -680,7 +680,8 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
             if (__builtin_amdgcn_ballot_w64(bad) != 0) break;
         }
         __syncthreads();                                         // the votes above have been read
-        if (lane == 0) vote[0][wg_wave] = __builtin_amdgcn_ballot_w64(bad) != 0 ? -1.f : 1.f;
+        const float verdict = __builtin_amdgcn_ballot_w64(bad) != 0 ? -1.f : 1.f;     // (with all lanes active)
+        if (lane == 0) vote[0][wg_wave] = verdict;
         __syncthreads();
         a = vote[0][0];
 #pragma unroll

@@ -1,0 +1,108 @@
+"""GPU parity of how the tiled prefill kernel ends, orders and shares out its walks: the rest of a walk that
+is judged at once from the keys' norms, ragged launches ordered by length, walks shared by two key groups."""
+import numpy as np
+import pytest
+
+import workloads as W
+from test_gpu_parity import U, fp8_caches, oracle_filled  # noqa: F401  (U: a fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def outlier_case(dtype, D, q_len, t0, slope, like, ctx=705, batch=2, seed=1):
+    """Steep slopes, under which every key far back is out of the question - except the one at t0 of
+    sequence 0, whose K row points along the last query (of head 1): its score outweighs its bias by 3."""
+    cfg = W.small_config(name="outlier", kind="prefill", dtype=dtype, batch=batch, num_heads=8, num_kv_heads=2,
+                         head_dim=D, block_size=16, num_blocks=batch * 45 + 3, ctx_lo=ctx, ctx_hi=ctx, q_len=q_len, seed=seed)
+    case = W.make_case(cfg, slopes=np.full(8, slope, np.float32))
+    q = W.from_bits(case.q[case.cu_q_lens[1] - 1, 1], dtype)
+    want = slope * (ctx - 1 - t0) + 3.0
+    row = np.sign(q) * 5.6 if like == "sign" else q * (want / (float(case.scale) * float(q @ q)))
+    assert float(case.scale) * float(row @ q) > want - 0.5
+    bits = W.to_bits(row.astype(np.float32), dtype)
+    new = t0 - (ctx - q_len)
+    if new >= 0:
+        case.k_new[new, 0] = bits
+    else:
+        case.k_cache[case.block_tables[0, t0 // 16], 0, t0 % 16] = bits
+    return case
+
+
+@pytest.mark.parametrize("t0", [0, 15, 16, 333, 511])
+@pytest.mark.parametrize("dtype,D", [(W.BF16, 128), (W.F16, 64)])
+@pytest.mark.parametrize("batch", [2, 70])      # two key groups; one group of four waves
+def test_a_far_key_that_matters_is_not_judged_away(U, oracle, batch, dtype, D, t0):
+    case = outlier_case(dtype, D, 24 if batch == 2 else 70, t0, 0.25, "q", batch=batch)
+    dev = U.DevCase(case)
+    step = dev.prefill_step()
+    kc, vc = oracle_filled(oracle, case)
+    rows = slice(None, case.cu_q_lens[2])       # sequences 0 and 1
+    ref = oracle.paged_prefill(case.q[rows], kc, vc, case.block_tables[:2], case.context_lens[:2], case.cu_q_lens[:3],
+                               case.slopes, case.scale, dtype)
+    U.check_scaled(step[rows], ref, dtype, f"prefill step, outlier at {t0}")
+    U.check_scaled(dev.prefill()[rows], ref, dtype, f"paged prefill, outlier at {t0}")
+
+
+@pytest.mark.parametrize("t0", [0, 16, 511, 640])
+@pytest.mark.parametrize("dtype,D", [(W.BF16, 128), (W.F16, 64)])
+def test_a_far_key_of_a_whole_prompt(U, oracle, dtype, D, t0):
+    import torch
+    import oracle as O
+    import paper_2505_02351_amd as G
+    case = outlier_case(dtype, D, 705, t0, 0.25, "q")
+    dev = U.DevCase(case)
+    G.prompt_prefill(dev.out, dev.q, dev.k_new, dev.v_new, dev.k_cache, dev.v_cache, dev.block_tables, dev.cu_q_lens,
+                     dev.slopes, float(case.scale), case.max_q_len)
+    torch.cuda.synchronize()
+    dev.check_canaries()
+    ref = O.prompt_attention(case.q, case.k_new, case.v_new, case.cu_q_lens, case.slopes, case.scale, dtype)
+    U.check_scaled(U.to_host(dev.out), ref, dtype, f"whole prompt, outlier at {t0}")
+
+
+@pytest.mark.parametrize("t0", [0, 16, 511])
+@pytest.mark.parametrize("D", [128, 64])
+def test_a_far_key_of_an_8_bit_cache(U, oracle, D, t0):
+    import torch
+    import oracle as O
+    import paper_2505_02351_amd as G
+    case = outlier_case(W.BF16, D, 24, t0, 1 / 16 if D == 128 else 1 / 32, "sign")
+    kc8, vc8, dk, dv = fp8_caches(U, case, 0.0125, 0.02)
+    qd = U.to_dev(case.q, W.BF16)
+    out = torch.full_like(qd, float("nan"))
+    G.paged_prefill_fp8(out, qd, dk, dv, torch.from_numpy(case.block_tables).cuda(),
+                        torch.from_numpy(case.context_lens).cuda(), torch.from_numpy(case.cu_q_lens).cuda(),
+                        torch.from_numpy(case.slopes).cuda(), float(case.scale), 0.0125, 0.02, case.max_q_len)
+    torch.cuda.synchronize()
+    ref = O.paged_prefill_e4m3(case.q, kc8, vc8, case.block_tables, case.context_lens, case.cu_q_lens,
+                               case.slopes, case.scale, 0.0125, 0.02, W.BF16)
+    U.check_scaled(U.to_host(out), ref, W.BF16, f"E4M3 caches, outlier at {t0}")
+
+
+# (sequences, heads, KV heads, head_dim): 1 and odd numbers of them, a lane's worth, one more (the plain order);
+# few enough workgroups for two key groups, and enough for one group of four and of eight waves
+@pytest.mark.parametrize("B,Hq,Hkv,D", [(1, 8, 2, 128), (3, 6, 2, 64), (7, 40, 8, 128), (64, 4, 1, 64), (65, 4, 1, 128),
+                                        (17, 16, 16, 128), (60, 16, 16, 64)])
+def test_ragged_launches_in_order_of_length(U, oracle, B, Hq, Hkv, D):
+    """No slopes; chunks of up to 90 new tokens behind 0 to 200 cached ones, one sequence without any."""
+    import torch
+    import paper_2505_02351_amd as G
+    cfg = W.small_config(name="ragged", kind="prefill", dtype=W.BF16, batch=B, num_heads=Hq, num_kv_heads=Hkv, head_dim=D,
+                         block_size=16, num_blocks=B * 13 + 5, ctx_lo=1, ctx_hi=200, q_len=90, seed=77 + B)
+    case = W.make_case(cfg)
+    kc, vc = oracle_filled(oracle, case)
+    cu = case.cu_q_lens.copy()
+    if B > 2:
+        cu[2] = cu[1]                           # sequence 1 without new tokens, its rows sequence 2's: more of them
+        case.context_lens[2] = min(case.context_lens[2], case.block_tables.shape[1] * 16)
+    q_lens = np.diff(cu)
+    if B > 2 and q_lens[2] > case.context_lens[2]:
+        cu = case.cu_q_lens.copy()              # (they do not fit behind its context: leave the batch as it was)
+    ref = oracle.paged_prefill(case.q, kc, vc, case.block_tables, case.context_lens, cu, None, case.scale, W.BF16)
+    dev = U.DevCase(case)
+    dev.write_cache()
+    dev.out.fill_(float("nan"))
+    G.paged_prefill(dev.out, dev.q, dev.k_cache, dev.v_cache, dev.block_tables, dev.context_lens,
+                    torch.from_numpy(cu).cuda(), None, float(case.scale), int(np.diff(cu).max()))
+    torch.cuda.synchronize()
+    dev.check_canaries()
+    U.check_scaled(U.to_host(dev.out), ref, W.BF16, f"ragged {B}")
