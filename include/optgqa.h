@@ -109,9 +109,10 @@ int optgqa_reshape_and_cache(const void *k, const void *v, void *k_cache, void *
  *   max_context_len an upper bound on context_lens (used for sizing only)
  *   partition_size  0: the library decides whether and how to split the context;
  *                   >0: split the context into partitions of this many tokens (multiple of
- *                       block_size and of 16) whose results are computed separately and then
- *                       combined (the waves of the launch still get equal shares: a share
- *                       boundary may cut a partition into two separately computed pieces);
+ *                       block_size and of 16) whose results are carried forward and combined: the
+ *                       waves of the launch get equal shares of no less than a partition; the
+ *                       partitions of a sequence inside one share are merged as they are streamed
+ *                       (a share boundary may cut a partition in two), the shares' results afterwards;
  *                   OPTGQA_SPLIT_BALANCED: split by equal work - every wave of the launch gets
  *                       the same number of 16-token tiles, whatever the mix of context
  *                       lengths, and the pieces are combined afterwards; this is also what

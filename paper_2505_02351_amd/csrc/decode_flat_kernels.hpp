@@ -202,14 +202,11 @@ __device__ __forceinline__ FlatSeg flat_seg(const DecodeParams& p, int v)
 //
 // SHARED: shared prefixes are read once per bundle of sequences (above).  2-byte caches, no window.
 //
-// PARTS: fixed partitions (Section III-A: the context is cut into partitions of a given size whose
-// results are merged) on the equal-work machinery: pieces end where a unit or a segment ends AND
-// at every multiple of part_tiles tiles inside a segment, so no piece spans two partitions.  The
-// waves still stream equal shares, with the prefetch chained from one partition to the next.  A
-// unit is at least one partition long, so a unit boundary cuts a partition into at most two
-// fragments: partition pi of segment (b, y) leaves its partial results in slots
-// ((b * Y + y) * num_partitions + pi) * 2 + (0: the fragment that starts the partition, 1: the
-// rest, if a unit boundary fell inside).  Plain attention over 2-byte caches only.
+// Fixed partitions (Section III-A: the context is cut into partitions of a given size whose results are
+// merged): a unit is at least one partition long (min_unit_tiles), and the partitions of a segment that one
+// unit streams are merged as they are streamed, in registers: a piece is the unit's whole run in a segment.
+// (Writing one partial result per partition and merging them in the combine kernel: 4 sequences of 32 768
+// tokens, 64 / 8 heads, partitions of 512: 96.4 us for cache write, streaming and combine; one per run: 90.7.)
 //
 // Head dimension D (128 or 64).  A K row is D / 32 sixteen-byte pieces per lane group hg, one score MFMA each;
 // a V tile (16 rows of D elements) is fetched D / 8 lanes to a row, 512 / D rows per load, D / 32 loads;
@@ -223,12 +220,11 @@ template <int D> struct FlatTile8 {
     uint2 v[D / 32];    // V: as above, 8 one-byte codes
 };
 
-template <int DT, bool FUSED, bool KV8 = false, bool SHARED = false, bool PARTS = false, int D = 128>
+template <int DT, bool FUSED, bool KV8 = false, bool SHARED = false, int D = 128>
 __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8 : OPTGQA_FLAT_WAVES_PER_SIMD) void paged_decode_flat_kernel(const DecodeParams p)
 {
     static_assert(D == 128 || D == 64, "head_dim 128 or 64");
     static_assert(!(SHARED && KV8), "shared prefixes: 2-byte caches");
-    static_assert(!(PARTS && (FUSED || KV8 || SHARED)), "fixed partitions: plain attention over 2-byte caches");
     constexpr bool NEW_TILE = FUSED && !KV8;            // the new token is a tile of its own, read from k_new / v_new
     typedef typename std::conditional<KV8, FlatTile8<D>, FlatTile<D>>::type Tile;
     constexpr int ES = KV8 ? 1 : 2;                     // bytes per cache element
@@ -266,7 +262,6 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
     const int u = blockIdx.x * kDecodeWaves + wave;
     const int32_t* __restrict__ ctx = p.context_lens;
     const int W = p.window;
-    const int tp = PARTS ? p.part_tiles : 0;            // tiles per fixed partition
 
     // ---- where does this unit start?  level 1: lane i sums the tiles of sequences [i*k, (i+1)*k)
     const int k = (NV + 63) >> 6;
@@ -283,7 +278,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
     const int incl = wave_inclusive_scan(mine, lane);
     const int P_total = __builtin_amdgcn_readlane(incl, 63);
     const int T = Y * P_total;
-    const int c = max(PARTS ? tp : 1, (T + p.num_units - 1) / p.num_units);     // (PARTS: at least one partition)
+    const int c = max(p.min_unit_tiles, (T + p.num_units - 1) / p.num_units);
     const int f0 = u * c;
     const int f1 = min(f0 + c, T);
     if (f0 >= f1) return;                                   // no workgroup-wide barrier below
@@ -483,14 +478,12 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
     };
     int staged = 0, staged_cols = 0;    // pieces parked in LDS, and the columns they take
     bool chained = false;         // buf[0] / d0 were filled by the previous piece
-    bool same_q = false;          // ... and it was a piece of the same segment (PARTS): qa, slope2, q_pos still hold
     int f = f0;
     for (;;) {
         // ---- one piece: tiles [tau, tau_end) of segment (v, y) -------------------------------
         const int n = seg.n, L = seg.L, lo = seg.lo;
         const bool has_new = NEW_TILE && !(SHARED && seg.shared);   // the segment's last tile is the new token
-        // (PARTS: a piece also ends where its partition ends)
-        const int tau_end = min(PARTS ? min(n, (tau / tp + 1) * tp) : n, tau + (f1 - f));
+        const int tau_end = min(n, tau + (f1 - f));
         const int ntw = tau_end - tau;                      // >= 1
         const int j_last = ntw - 1;
         const int Lm1 = L - 1;
@@ -508,7 +501,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
         const int64_t new_k = NEW_TILE ? seg.b * p.k_new_stride + (int64_t)g * D : 0;
         const int64_t new_v = NEW_TILE ? seg.b * p.v_new_stride + (int64_t)g * D : 0;
 
-        if (!(PARTS && same_q)) load_q(qa, slope2, q_pos, seg.b, seg.L, seg.shared != 0, y);
+        load_q(qa, slope2, q_pos, seg.b, seg.L, seg.shared != 0, y);
         if (!chained) {
             d0 = tile_src(table, head_off, lo, L, n, has_new, reg_end, new_k, new_v, tau);
             load_tile(buf[0], d0);
@@ -533,13 +526,10 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
         // ---- the piece after this one (same unit), so that its first tile is on its way before this
         // piece ends.  Without one, the spare prefetch slot re-reads this piece's last tile (a cache
         // hit, never consumed).
-        bool has_next = f + ntw < f1;                        // (not PARTS: then this piece ends its segment)
+        bool has_next = f + ntw < f1;                        // (then this piece ends its segment)
         int nv = v, ny = y;
-        int ntau = 0;                                        // first tile of the next piece in its segment
         FlatSeg nseg = seg;
-        if (PARTS && has_next && tau_end < n) {
-            ntau = tau_end;                                  // the next partition of the same segment
-        } else if (has_next) {
+        if (has_next) {
             if (++ny == Y) {
                 ny = 0;
                 do {                                         // skip sequences without tiles
@@ -556,7 +546,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
         // (nothing follows) this piece's last one again
         const int nn = nseg.n;
         const bool n_has_new = NEW_TILE && !(SHARED && nseg.shared);
-        const int n_tau_end = min(PARTS ? min(nn, (ntau / tp + 1) * tp) : nn, ntau + f1 - (f + ntw));
+        const int n_tau_end = min(nn, f1 - (f + ntw));
         const int32_t* x_table = has_next ? p.block_tables + (int64_t)nseg.tb * p.max_blocks_per_seq : table;
         const int64_t x_head_off = has_next ? (int64_t)(ny / chunks) * bs * D : head_off;
         const int x_L = has_next ? nseg.L : L, x_n = has_next ? nn : n, x_lo = has_next ? nseg.lo : lo;
@@ -566,7 +556,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
                               : min(nseg.hi, ((n_has_new && n_tau_end == nn ? n_tau_end - 1 : n_tau_end) + n_first) * TILE);
         const int64_t x_new_k = !has_next ? new_k : NEW_TILE ? nseg.b * p.k_new_stride + (int64_t)(ny / chunks) * D : 0;
         const int64_t x_new_v = !has_next ? new_v : NEW_TILE ? nseg.b * p.v_new_stride + (int64_t)(ny / chunks) * D : 0;
-        const int x_ti = has_next ? ntau : tau + j_last;
+        const int x_ti = has_next ? 0 : tau + j_last;
 
         // ---- both contractions on 16-bit MFMAs, transposed so that nothing is transposed in registers:
         //   S^T[token][head] = K Q^T : A = the K tile as fetched (lane (token j16, slab hg)), B = the query
@@ -705,8 +695,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
 
         // ---- the piece's partial result belongs in slot u + s (s = v * Y + y): this lane holds dims
         // 16db + 4hg + v of column j16 ---------------------------------------------------------------
-        const int64_t slot = PARTS ? ((((int64_t)v * Y + y) * p.num_partitions + tau / tp) << 1) + (tau % tp != 0)
-                                   : (int64_t)u + (int64_t)v * Y + y;
+        const int64_t slot = (int64_t)u + (int64_t)v * Y + y;
         const int ncols = SHARED && seg.shared ? CS : GH;    // (a shared prefix fills all 16 columns of its slots)
         if (has_next) {
             if (staged == kStagePieces || staged_cols + ncols > kStageCols) {    // no room: write out what is parked
@@ -756,8 +745,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
         if (ny != y || nv != v) {                            // the next piece starts a segment
             if (y + 1 == Y) P_v += n;                        // sequences skipped on the way have no tiles
         }
-        same_q = nv == v && ny == y;
-        v = nv, y = ny, seg = nseg, tau = ntau;
+        v = nv, y = ny, seg = nseg, tau = 0;
         chained = true;
     }
 }
@@ -776,13 +764,22 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
 // SHARED: a head's partial results lie in two staircases - the pieces of its own segment (virtual
 // sequence 2b + 1, column = the head) and, if the sequence takes part in its bundle's shared
 // prefix, the pieces of that segment (virtual sequence 2 * leader, column = member * GH + head).
-template <int DT, bool NEWTOK = false, bool SHARED = false, int D = 128>
-__global__ __launch_bounds__(kReduceThreads) void paged_decode_flat_reduce_kernel(const DecodeParams p)
+//
+// GROUPS: a head's partial results are read by that many groups of D / 4 threads, each every GROUPS-th
+// batch of them, and merged through LDS.  1: a workgroup serves several heads.  8: one head; for segments
+// of many pieces (few sequences, long contexts), whose batches would otherwise be a chain of memory
+// round trips.  The host picks by the pieces a segment has on average.
+constexpr int kReduceGroups = 8;
+
+template <int DT, bool NEWTOK, bool SHARED, int D, int GROUPS>
+__global__ __launch_bounds__(GROUPS == 1 ? kReduceThreads : GROUPS * (D / 4)) void paged_decode_flat_reduce_kernel(const DecodeParams p)
 {
     static_assert(!(NEWTOK && SHARED), "shared prefixes: 2-byte caches");
     constexpr int kVecPerHead = D / 4;
-    constexpr int kHeads = kReduceThreads / kVecPerHead;
-    const int h = blockIdx.y * kHeads + threadIdx.x / kVecPerHead;
+    constexpr int kHeads = GROUPS == 1 ? kReduceThreads / kVecPerHead : 1;
+    constexpr int kBatch = GROUPS == 1 ? 8 : 4;             // partial results in flight per thread
+    const int grp = GROUPS == 1 ? 0 : threadIdx.x / kVecPerHead;
+    const int h = GROUPS == 1 ? blockIdx.y * kHeads + threadIdx.x / kVecPerHead : blockIdx.y;
     const int od = (threadIdx.x % kVecPerHead) * 4;
     const int b = blockIdx.x;                                // (sequences along x: no 16-bit limit)
     if (h >= p.num_heads) return;
@@ -837,8 +834,8 @@ __global__ __launch_bounds__(kReduceThreads) void paged_decode_flat_reduce_kerne
         n_own = NEWTOK ? flat_tiles<true, true>(L, p.window)
                        : p.k_new ? flat_tiles<true>(L, p.window) : flat_tiles<false>(L, p.window);
     }
-    // One pass in batches of 8 partial results with a running reference (a segment rarely has more
-    // than 8 pieces, so this is one memory round trip; a separate pass for the maximum would be
+    // One pass in batches of partial results with a running reference (with one group a segment rarely has
+    // more than the 8 pieces of a batch, so this is one memory round trip; a separate pass for the maximum would be
     // a second chain of them).
     float M = -INFINITY;
     float den = 0.f;
@@ -856,11 +853,11 @@ __global__ __launch_bounds__(kReduceThreads) void paged_decode_flat_reduce_kerne
             np = n > 0 ? min(max((F0 + n - 1) / c - u0 + 1, 1), p.num_units - u0) : 0;
             base = ((int64_t)u0 + (int64_t)vv * Y + y) * CS + col;          // slot stride between units: CS
         }
-        for (int i0 = 0; i0 < np; i0 += 8) {
-            float mm[8], ll[8];
-            float4 x[8];
+        for (int i0 = grp * kBatch; i0 < np; i0 += GROUPS * kBatch) {
+            float mm[kBatch], ll[kBatch];
+            float4 x[kBatch];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
+            for (int k = 0; k < kBatch; ++k) {
                 const int64_t e = base + (int64_t)min(i0 + k, np - 1) * CS;
                 mm[k] = p.ws_m[e];
                 ll[k] = p.ws_l[e];
@@ -868,7 +865,7 @@ __global__ __launch_bounds__(kReduceThreads) void paged_decode_flat_reduce_kerne
             }
             float Mn = M;                                            // clamped repeats of the last piece do not change it
 #pragma unroll
-            for (int k = 0; k < 8; ++k) Mn = fmaxf(Mn, mm[k]);
+            for (int k = 0; k < kBatch; ++k) Mn = fmaxf(Mn, mm[k]);
             const float keep = any ? fast_exp2(M - Mn) : 0.f;        // nothing accumulated before the first batch
             any = true;
             M = Mn;
@@ -878,7 +875,7 @@ __global__ __launch_bounds__(kReduceThreads) void paged_decode_flat_reduce_kerne
             num.z *= keep;
             num.w *= keep;
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
+            for (int k = 0; k < kBatch; ++k) {
                 const float fct = i0 + k < np ? fast_exp2(mm[k] - M) : 0.f;
                 den = fmaf(fct, ll[k], den);
                 num.x = fmaf(fct, x[k].x, num.x);
@@ -890,6 +887,32 @@ __global__ __launch_bounds__(kReduceThreads) void paged_decode_flat_reduce_kerne
     };
     collect(v_own, n_own, plan_own, hh);
     if constexpr (SHARED) collect(v_shared, n_shared, plan_shared, col_shared);
+    if constexpr (GROUPS > 1) {
+        __shared__ float s_m[GROUPS][kVecPerHead], s_den[GROUPS][kVecPerHead];
+        __shared__ float4 s_num[GROUPS][kVecPerHead];
+        const int l = threadIdx.x % kVecPerHead;
+        s_m[grp][l] = any ? M : -INFINITY;
+        s_den[grp][l] = den;
+        s_num[grp][l] = num;
+        __syncthreads();                                     // (every return above is the whole workgroup's)
+        if (grp != 0) return;
+        M = -INFINITY;
+#pragma unroll
+        for (int k = 0; k < GROUPS; ++k) M = fmaxf(M, s_m[k][l]);
+        any = M > -INFINITY;
+        den = 0.f;
+        num = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int k = 0; k < GROUPS; ++k) {
+            const float mk = s_m[k][l], fct = mk > -INFINITY ? fast_exp2(mk - M) : 0.f;
+            const float4 nk = s_num[k][l];
+            den = fmaf(fct, s_den[k][l], den);
+            num.x = fmaf(fct, nk.x, num.x);
+            num.y = fmaf(fct, nk.y, num.y);
+            num.z = fmaf(fct, nk.z, num.z);
+            num.w = fmaf(fct, nk.w, num.w);
+        }
+    }
     // E4M3 caches with per-KV-head scales: this head's pair
     const float k_scale_g = p.k_scales ? p.k_scales[g] : 1.f, v_scale_g = p.v_scales ? p.v_scales[g] : 1.f;
     if constexpr (NEWTOK) {
@@ -926,108 +949,6 @@ __global__ __launch_bounds__(kReduceThreads) void paged_decode_flat_reduce_kerne
     uint2 packed;
     packed.x = narrow2<DT>(num.x * inv, num.y * inv);
     packed.y = narrow2<DT>(num.z * inv, num.w * inv);
-    *reinterpret_cast<uint2*>(o) = packed;
-}
-
-// Combine for fixed partitions run by the equal-work kernel (PARTS): head h of sequence b has two
-// slots per partition, ((b * Y + y) * num_partitions + pi) * 2 + fragment; fragment 0 (the piece that
-// starts the partition) always exists, fragment 1 only if a unit boundary - a multiple of c in the
-// flat order - fell strictly inside the partition.  One workgroup per (head, sequence): eight groups of
-// head_dim / 4 threads (4 output dims each) take every eighth slot with all their loads in flight at once,
-// then the eight partial sums are merged through LDS - a long context has dozens of partitions and
-// a single chain of memory round trips over them would cost more than the streaming they merge.
-constexpr int kPartsReduceGroups = 8;
-
-template <int DT, int D = 128>
-__global__ __launch_bounds__(kPartsReduceGroups * (D / 4)) void paged_decode_parts_reduce_kernel(const DecodeParams p)
-{
-    constexpr int GW = D / 4;                                          // threads per group: 4 output dims each
-    __shared__ float s_m[kPartsReduceGroups][GW], s_den[kPartsReduceGroups][GW];
-    __shared__ float4 s_num[kPartsReduceGroups][GW];
-    const int h = blockIdx.y, b = blockIdx.x;
-    const int l32 = threadIdx.x % GW, grp = threadIdx.x / GW;
-    const int od = l32 * 4;
-    uint16_t* o = static_cast<uint16_t*>(p.out) + ((int64_t)b * p.num_heads + h) * D + od;
-    const int L = p.context_lens[b];
-    const int c = max(p.plan[p.num_seqs], 1), P = p.plan[b];          // readable garbage where nobody wrote them
-    if (L <= 0) {                                                      // (uniform over the workgroup)
-        if (grp == 0) *reinterpret_cast<uint2*>(o) = make_uint2(0u, 0u);
-        return;
-    }
-    const int GH = p.heads_per_wg;
-    const int G = p.num_heads / p.num_kv_heads;
-    const int chunks = G / GH;
-    const int g = h / G;
-    const int within = h - g * G;
-    const int chunk = within / GH;
-    const int hh = within - chunk * GH;
-    const int Y = p.segs_per_seq;
-    const int y = g * chunks + chunk;
-    const int tp = p.part_tiles;
-    const int n = flat_tiles<false>(L, 0);
-    const int parts = min((n + tp - 1) / tp, p.num_partitions);
-    const int64_t first = (((int64_t)b * Y + y) * p.num_partitions) << 1;
-    const int64_t F0 = (int64_t)Y * P + (int64_t)y * n;
-    float M = -INFINITY, den = 0.f;
-    float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int i0 = grp; i0 < 2 * parts; i0 += 8 * kPartsReduceGroups) {
-        float mm[8], ll[8];
-        float4 x[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int i = i0 + k * kPartsReduceGroups, pi = i >> 1;
-            const int64_t start = F0 + (int64_t)pi * tp, len = min(tp, n - pi * tp);
-            const bool there = i < 2 * parts && ((i & 1) == 0 || (start / c + 1) * c < start + len);
-            const int64_t e = (first + i) * GH + hh;
-            mm[k] = there ? p.ws_m[e] : -INFINITY;
-            ll[k] = there ? p.ws_l[e] : 0.f;
-            x[k] = there ? *reinterpret_cast<const float4*>(p.ws_o + e * D + od) : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-        float Mn = M;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) Mn = fmaxf(Mn, mm[k]);
-        const float keep = Mn > -INFINITY ? fast_exp2(M - Mn) : 0.f;      // (M = -inf before the first slot: keep 0)
-        M = Mn;
-        den *= keep;
-        num.x *= keep;
-        num.y *= keep;
-        num.z *= keep;
-        num.w *= keep;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const float fct = mm[k] > -INFINITY ? fast_exp2(mm[k] - M) : 0.f;
-            den = fmaf(fct, ll[k], den);
-            num.x = fmaf(fct, x[k].x, num.x);
-            num.y = fmaf(fct, x[k].y, num.y);
-            num.z = fmaf(fct, x[k].z, num.z);
-            num.w = fmaf(fct, x[k].w, num.w);
-        }
-    }
-    s_m[grp][l32] = M;
-    s_den[grp][l32] = den;
-    s_num[grp][l32] = num;
-    __syncthreads();
-    if (grp != 0) return;
-    float Mt = -INFINITY;
-#pragma unroll
-    for (int k = 0; k < kPartsReduceGroups; ++k) Mt = fmaxf(Mt, s_m[k][l32]);
-    float dt = 0.f;
-    float4 nt = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-    for (int k = 0; k < kPartsReduceGroups; ++k) {
-        const float mk = s_m[k][l32];
-        const float fct = mk > -INFINITY ? fast_exp2(mk - Mt) : 0.f;
-        const float4 nk = s_num[k][l32];
-        dt = fmaf(fct, s_den[k][l32], dt);
-        nt.x = fmaf(fct, nk.x, nt.x);
-        nt.y = fmaf(fct, nk.y, nt.y);
-        nt.z = fmaf(fct, nk.z, nt.z);
-        nt.w = fmaf(fct, nk.w, nt.w);
-    }
-    const float inv = p.out_scale / dt;
-    uint2 packed;
-    packed.x = narrow2<DT>(nt.x * inv, nt.y * inv);
-    packed.y = narrow2<DT>(nt.z * inv, nt.w * inv);
     *reinterpret_cast<uint2*>(o) = packed;
 }
 

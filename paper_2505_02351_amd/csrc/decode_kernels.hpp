@@ -27,7 +27,6 @@ struct DecodeParams {
     const float* slopes;        // [Hq] or nullptr
     float scale2;               // scale * log2(e)
     int num_heads, num_kv_heads, block_size, max_blocks_per_seq;
-    int num_partitions;         // fixed partitions on the equal-work kernel: partitions per segment, else 1
     int num_seqs;
     int row_offset;             // first row handled by this launch (grid.z/y counts from here)
     int heads_per_wg;           // query heads one workgroup serves (divides the group size)
@@ -58,10 +57,7 @@ struct DecodeParams {
     // entries of sequence b are the bundle leader's (sequence b - b % bundle), 0 that b shares nothing.
     const int32_t* shared_blocks;   // [num_seqs] or nullptr
     int bundle;                     // sequences whose heads fit the score tile together: 16 / heads_per_wg
-    // Fixed partitions through the equal-work kernel: pieces also end at every multiple of part_tiles
-    // tiles of 16 tokens (partition_size / 16) inside a segment, and num_partitions bounds the
-    // partitions of a segment; 0 = pieces end only where a unit or a segment ends.
-    int part_tiles;
+    int min_unit_tiles;             // tiles of 16 tokens a unit has at least: 1, or a fixed partition (partition_size / 16)
 };
 
 // Sequence and number of visible keys of one output row (decode: row = sequence).

@@ -147,7 +147,7 @@ constexpr int kMaxRowsPerLaunch = 65535;
 
 struct SplitPlan {
     int partition_size;   // 0 = unsplit, OPTGQA_SPLIT_BALANCED = equal-work split
-    int num_partitions;
+    int max_units;        // waves that may get work (equal-work kernel)
     size_t bytes;
     // equal-work kernel only (the equal-work split, and fixed partitions that are multiples of 16 tokens)
     int workgroups;
@@ -190,7 +190,7 @@ bool plan_flat(SplitPlan& s, int num_seqs, int num_heads, int num_kv_heads, int 
     if (wgs > flat_max_workgroups()) wgs = flat_max_workgroups();
     if (wgs < 1) wgs = 1;
     s.partition_size = OPTGQA_SPLIT_BALANCED;
-    s.num_partitions = 1;
+    s.max_units = (int)wgs * kDecodeWaves;
     s.workgroups = (int)wgs;
     s.segs_per_seq = (int)Y;
     const size_t slots = (size_t)wgs * kDecodeWaves + (size_t)segs;
@@ -202,9 +202,9 @@ bool plan_flat(SplitPlan& s, int num_seqs, int num_heads, int num_kv_heads, int 
     return true;
 }
 
-// Fixed partitions of P tokens (a multiple of 16) run by the equal-work kernel: two partial-result
-// slots per partition of every (sequence, KV head / head chunk) segment (a unit boundary may cut a
-// partition in two).
+// Fixed partitions of P tokens (a multiple of 16) run by the equal-work kernel: no more units than
+// partitions, a unit at least one partition long, one partial result per (unit, segment) that occur - fewer
+// than the two slots per partition that are asked for.
 bool plan_flat_parts(SplitPlan& s, int num_seqs, int num_heads, int num_kv_heads, int head_dim, int max_context_len, int P)
 {
     const int group = num_heads / num_kv_heads;
@@ -216,7 +216,7 @@ bool plan_flat_parts(SplitPlan& s, int num_seqs, int num_heads, int num_kv_heads
     int64_t wgs = (parts + kDecodeWaves - 1) / kDecodeWaves;  // no more units than partitions
     if (wgs > flat_workgroups(false)) wgs = flat_workgroups(false);
     s.partition_size = P;
-    s.num_partitions = np;
+    s.max_units = (int)(parts < wgs * kDecodeWaves ? parts : wgs * kDecodeWaves);
     s.workgroups = (int)wgs;
     s.segs_per_seq = (int)Y;
     s.slots = 2 * parts;
@@ -230,7 +230,7 @@ bool plan_flat_parts(SplitPlan& s, int num_seqs, int num_heads, int num_kv_heads
 SplitPlan plan_split(int num_seqs, int num_heads, int num_kv_heads, int head_dim, int block_size,
                      int max_context_len, int partition_size, int window = 0, bool shared = false)
 {
-    SplitPlan s{0, 1, 0, 0, 0, 0, 0, 0, false};
+    SplitPlan s{0, 0, 0, 0, 0, 0, 0, 0, false};
     int P = partition_size;
     if (P == 0) P = auto_partition(num_seqs, num_heads, num_kv_heads, head_dim, block_size, max_context_len);
     // The library's own choice is the equal-work split whenever splitting pays.
@@ -308,12 +308,12 @@ int launch_decode_any(int dtype, int head_dim, A... args)
 // Equal-work kernel: `workgroups` was sized for the work; it is also capped by what
 // the device keeps resident at once, because a unit that has to wait for a free slot would start
 // when every other unit is nearly done.
-template <int DT, int D, bool FUSED, bool KV8 = false, bool SHARED = false, bool PARTS = false>
+template <int DT, int D, bool FUSED, bool KV8 = false, bool SHARED = false>
 int launch_decode_flat_dt(DecodeParams p, int workgroups, hipStream_t st)
 {
     static const int resident = [] {
         int per_cu = 0, dev = 0, cus = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, paged_decode_flat_kernel<DT, FUSED, KV8, SHARED, PARTS, D>, kDecodeWaves * 64, 0) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, paged_decode_flat_kernel<DT, FUSED, KV8, SHARED, D>, kDecodeWaves * 64, 0) != hipSuccess ||
             hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
             return 0;
@@ -323,24 +323,29 @@ int launch_decode_flat_dt(DecodeParams p, int workgroups, hipStream_t st)
     if (workgroups > resident) workgroups = resident;
     const int group = p.num_heads / p.num_kv_heads;
     p.heads_per_wg = mfma_heads_per_workgroup(group);
-    p.num_units = workgroups * kDecodeWaves;
+    p.num_units = std::min(workgroups * kDecodeWaves, p.num_units);      // (num_units came in as the plan's most)
     int rc;
     {
         KernelEvents ev(st);
-        rc = launch(paged_decode_flat_kernel<DT, FUSED, KV8, SHARED, PARTS, D>, dim3(workgroups), dim3(kDecodeWaves * 64), 0, st, p);
+        rc = launch(paged_decode_flat_kernel<DT, FUSED, KV8, SHARED, D>, dim3(workgroups), dim3(kDecodeWaves * 64), 0, st, p);
     }
     if (rc != OPTGQA_OK) return rc;
-    if constexpr (PARTS)
-        return launch(paged_decode_parts_reduce_kernel<DT, D>, dim3(p.num_seqs, p.num_heads), dim3(kPartsReduceGroups * (D / 4)), 0, st, p);
+    // More than four pieces to a segment on average: eight groups of threads to a head - unless that makes
+    // more than four workgroups per CU, where the launch costs what the shorter chain saves.  (Steps, 16
+    // sequences of 255 - 2 047 tokens, 32 / 8 heads, 8 pieces, 512 workgroups: 22.9 -> 22.1 us; 4 of 32 768,
+    // 64 / 8 heads, 32 pieces: 92.9 -> 90.7; but 64 sequences over 8-bit caches, 8 pieces, 2 048 workgroups:
+    // 66.9 -> 68.2; 64 with a window, 4 pieces: 32.5 -> 33.9.)
+    if (p.num_units > (int64_t)4 * p.num_seqs * p.segs_per_seq && (int64_t)p.num_seqs * p.num_heads <= 4 * num_cus())
+        return launch(paged_decode_flat_reduce_kernel<DT, FUSED && KV8, SHARED, D, kReduceGroups>, dim3(p.num_seqs, p.num_heads),
+                      dim3(kReduceGroups * (D / 4)), 0, st, p);
     constexpr int kHeadsPerWg = kReduceThreads / (D / 4);
-    return launch(paged_decode_flat_reduce_kernel<DT, FUSED && KV8, SHARED, D>, dim3(p.num_seqs, (p.num_heads + kHeadsPerWg - 1) / kHeadsPerWg),
+    return launch(paged_decode_flat_reduce_kernel<DT, FUSED && KV8, SHARED, D, 1>, dim3(p.num_seqs, (p.num_heads + kHeadsPerWg - 1) / kHeadsPerWg),
                   dim3(kReduceThreads), 0, st, p);
 }
 
 template <int DT, int D>
 int launch_decode_flat_d(const DecodeParams& p, int workgroups, hipStream_t st, bool kv8)
 {
-    if (p.part_tiles > 0) return launch_decode_flat_dt<DT, D, false, false, false, true>(p, workgroups, st);
     if (p.shared_blocks && p.k_new) return launch_decode_flat_dt<DT, D, true, false, true>(p, workgroups, st);
     if (p.shared_blocks) return launch_decode_flat_dt<DT, D, false, false, true>(p, workgroups, st);
     if (kv8 && p.k_new) return launch_decode_flat_dt<DT, D, true, true>(p, workgroups, st);
@@ -634,7 +639,7 @@ int attention_impl(void* out, const void* q, const void* k_cache, const void* v_
         const bool have = workspace && workspace_bytes >= s.bytes && aligned16(workspace);
         if (!have) {
             if (partition_size != 0) return OPTGQA_ERR_WORKSPACE;
-            s = SplitPlan{0, 1, 0, 0, 0, 0, 0, 0, false};          // library's own choice: fall back to unsplit
+            s = SplitPlan{0, 0, 0, 0, 0, 0, 0, 0, false};          // library's own choice: fall back to unsplit
         }
     }
 
@@ -660,7 +665,7 @@ int attention_impl(void* out, const void* q, const void* k_cache, const void* v_
     p.window = window > 0 ? window : 0;
     p.new_token_in_combine = 0;
     p.k_inv_scale = p.v_inv_scale = 1.f;
-    p.part_tiles = 0;
+    p.min_unit_tiles = 1;
     p.shared_blocks = shared_blocks;
     p.bundle = shared_blocks ? kMmaMaxHeads / mfma_heads_per_workgroup(num_heads / num_kv_heads) : 1;
     p.k_scales = p.v_scales = nullptr;
@@ -695,11 +700,8 @@ int attention_impl(void* out, const void* q, const void* k_cache, const void* v_
         p.ws_m = static_cast<float*>(workspace) + s.plan_floats;
         p.ws_l = p.ws_m + s.ml_floats;
         p.ws_o = p.ws_l + s.ml_floats;
-        p.num_partitions = 1;
-        if (s.partition_size > 0) {                          // fixed partitions
-            p.part_tiles = s.partition_size / kMmaTile;
-            p.num_partitions = s.num_partitions;
-        }
+        p.num_units = s.max_units;
+        if (s.partition_size > 0) p.min_unit_tiles = s.partition_size / kMmaTile;        // fixed partitions
         p.segs_per_seq = s.segs_per_seq;
         if (fused) {
             p.k_new = step->k_new;
@@ -716,7 +718,6 @@ int attention_impl(void* out, const void* q, const void* k_cache, const void* v_
     p.plan = nullptr;
     p.num_units = p.segs_per_seq = 0;
     p.ws_m = p.ws_l = p.ws_o = nullptr;
-    p.num_partitions = 1;
     return launch_decode_any(dtype, head_dim, p, num_seqs, st);
 }
 
