@@ -177,9 +177,10 @@ int optgqa_set_kernel_events(void *start_event, void *stop_event);
  * Same result, bit for bit in the caches and to rounding in `out`, as
  * optgqa_reshape_and_cache with that slot mapping followed by optgqa_paged_attention with
  * partition_size 0; sequences with context_lens[b] == 0 write nothing and give a row of +0.
- * Where the equal-work split applies (a context worth splitting, workspace given) the cache write happens
- * inside the attention kernel - one launch less per step; otherwise the library issues the
- * two launches itself.
+ * The cache write happens inside the attention kernel - one launch less per step - where the equal-work
+ * split applies (a context worth splitting, workspace given), and without a split where one workgroup
+ * serves a whole group; always provided that the new rows are 16-byte aligned with strides that are
+ * multiples of 8 elements.  Otherwise the library issues the two launches itself.
  *
  *   k_new, v_new    [num_seqs][num_kv_heads][head_dim]; sequence b starts at element
  *                   b * k_token_stride (resp. v_token_stride), strides >= num_kv_heads * head_dim

@@ -681,12 +681,14 @@ int attention_impl(void* out, const void* q, const void* k_cache, const void* v_
         p.new_token_in_combine = step != nullptr;
     }
 
-    // The cache write rides inside the equal-work kernel when that kernel runs and the new rows
-    // can be moved as 16-byte pieces; otherwise it is a launch of its own ahead of the attention.
+    // The cache write rides inside the attention kernel when the new rows can be moved as 16-byte pieces
+    // and that kernel is the equal-work one, or an unsplit one with one workgroup for a whole group (with
+    // several, one would read the row that another writes); otherwise it is a launch of its own.
     bool fused = false;
     if (step) {
-        fused = s.flat && s.partition_size == OPTGQA_SPLIT_BALANCED && aligned16(step->k_new) && aligned16(step->v_new) &&
-                step->k_stride % 8 == 0 && step->v_stride % 8 == 0;
+        const int group = num_heads / num_kv_heads;
+        fused = (s.flat ? s.partition_size == OPTGQA_SPLIT_BALANCED : heads_per_workgroup(group, head_dim) == group) &&
+                aligned16(step->k_new) && aligned16(step->v_new) && step->k_stride % 8 == 0 && step->v_stride % 8 == 0;
         if (!fused && kv_scales) return OPTGQA_ERR_UNSUPPORTED;   // 8-bit step: new rows must move as 16-byte pieces
         if (!fused) {
             const int rc = write_new_tokens(*step, nullptr, block_tables, context_lens, num_seqs, num_kv_heads,
@@ -695,6 +697,14 @@ int attention_impl(void* out, const void* q, const void* k_cache, const void* v_
         }
     }
 
+    if (fused) {
+        p.k_new = step->k_new;
+        p.v_new = step->v_new;
+        p.k_new_stride = step->k_stride;
+        p.v_new_stride = step->v_stride;
+        p.k_cache_w = step->k_cache_w;
+        p.v_cache_w = step->v_cache_w;
+    }
     if (s.flat) {
         p.plan = static_cast<int32_t*>(workspace);
         p.ws_m = static_cast<float*>(workspace) + s.plan_floats;
@@ -703,14 +713,6 @@ int attention_impl(void* out, const void* q, const void* k_cache, const void* v_
         p.num_units = s.max_units;
         if (s.partition_size > 0) p.min_unit_tiles = s.partition_size / kMmaTile;        // fixed partitions
         p.segs_per_seq = s.segs_per_seq;
-        if (fused) {
-            p.k_new = step->k_new;
-            p.v_new = step->v_new;
-            p.k_new_stride = step->k_stride;
-            p.v_new_stride = step->v_stride;
-            p.k_cache_w = step->k_cache_w;
-            p.v_cache_w = step->v_cache_w;
-        }
         const int cap = flat_workgroups(kv_scales != nullptr);
         return launch_decode_flat(dtype, head_dim, p, s.workgroups < cap ? s.workgroups : cap, st, kv_scales != nullptr);
     }

@@ -1,0 +1,47 @@
+"""GPU parity of the one-call decode step where the context is not split: the kernel that attends stores the
+new row itself (one workgroup per KV head), or a launch in front of it does."""
+import numpy as np
+import pytest
+
+import workloads as W
+from test_gpu_parity import U, oracle_filled  # noqa: F401  (U: a fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,D", [
+    (W.F16, 8, 2, 64), (W.BF16, 16, 2, 64),                  # group 4 and 8: ring kernel
+    (W.F16, 6, 3, 64), (W.BF16, 3, 3, 64),                   # group 2 and 1: general kernel
+    (W.F16, 6, 2, 64), (W.BF16, 32, 2, 64),                  # group 3 and 16: several workgroups a group, own launch
+    (W.BF16, 8, 2, 128), (W.F16, 3, 1, 128), (W.BF16, 16, 1, 128), (W.F16, 20, 1, 128),   # 20: two workgroups
+])
+def test_unsplit_step(U, oracle, dtype, Hq, Hkv, D):
+    """Lengths at block and tile edges, 1 and 0; new rows dense and as strided views; caches bit for bit
+    (the new rows hold NaN patterns until the step stores them)."""
+    import torch
+    import paper_2505_02351_amd as G
+    lens = np.array([128, 1, 16, 17, 0, 31, 33, 127, 256], np.int32)
+    B = len(lens)
+    cfg = W.small_config(name="unsplit", dtype=dtype, batch=B, num_heads=Hq, num_kv_heads=Hkv, head_dim=D, block_size=16,
+                         num_blocks=B * 17, ctx_lo=1, ctx_hi=256, seed=Hq + D)
+    case = W.make_case(cfg, context_lens=lens)
+    kc, vc = oracle_filled(oracle, case)
+
+    def full(a):
+        z = np.zeros((B,) + a.shape[1:], np.uint16)
+        z[lens > 0] = a
+        return z
+    k_new, v_new = full(case.k_new), full(case.v_new)
+    case.q = full(case.q)
+    ref = oracle.paged_attention(case.q, kc, vc, case.block_tables, case.context_lens, case.slopes, case.scale, dtype)
+    assert G.paged_attention_workspace_bytes(B, Hq, Hkv, D, 16, 256, 0) == (0, 0)
+    for pad in (0, 8, 1):                                    # token strides: dense, a multiple of 8 elements, odd
+        dev = U.DevCase(case)
+        rows = []
+        for a in (k_new, v_new):
+            wide = torch.zeros(B, Hkv * D + pad, dtype=dev.q.dtype, device="cuda")
+            wide[:, :Hkv * D] = U.to_dev(a, dtype).reshape(B, Hkv * D)
+            rows.append(wide[:, :Hkv * D].unflatten(1, (Hkv, D)))
+        dev.k_new, dev.v_new = rows
+        assert U.max_abs_err(dev.step(None), ref, dtype) <= U.TOL[dtype], pad
+        assert np.array_equal(U.to_host(dev.k_cache), kc) and np.array_equal(U.to_host(dev.v_cache), vc), pad
