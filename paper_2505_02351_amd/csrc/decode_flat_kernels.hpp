@@ -266,15 +266,73 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
     // ---- where does this unit start?  level 1: lane i sums the tiles of sequences [i*k, (i+1)*k)
     const int k = (NV + 63) >> 6;
     int mine = 0, my_len = 0;
-    for (int i = 0; i < k; ++i) {
-        const int idx = lane * k + i;
+    // Up to 64 sequences: lane i holds sequence i's length (and, SHARED, how many of its tokens are its
+    // bundle's shared prefix), so that a segment's extent - here and at every later piece - costs lane
+    // reads instead of dependent memory round trips.  (Shared prefixes, where an extent is four or five
+    // dependent loads: 35 sequences of 42-423 tokens, 24 / 8 heads, kernel 15.1 -> 12.6 us; 64 of
+    // 1 023-8 191 in pairs, step 84.7 -> 82.6 us.)
+    const bool in_lanes = B <= 64;
+    int my_shared = 0, my_even = 0;
+    if (in_lanes) {
+        my_len = lane < B ? ctx[lane] : 0;
         if constexpr (SHARED) {
-            if (idx < NV) mine += flat_seg<FUSED, KV8, true, false>(p, idx).n;
+            const int my_sb = lane < B ? p.shared_blocks[lane] : 0;
+            const int b0 = lane - lane % p.bundle;
+            // (shared_prefix_tokens and flat_seg, over the lanes)
+            const int L0 = __shfl(my_len, b0);
+            int S = 0x7fffffff;
+            bool any = false;
+            for (int i = 1; i < p.bundle; ++i) {
+                const int s = __shfl(my_sb, (b0 + i) & 63), Li = __shfl(my_len, (b0 + i) & 63);
+                if (b0 + i < B && s > 0 && Li > 0) {
+                    any = true;
+                    S = min(S, min(s * bs, Li - (FUSED ? 1 : 0)));
+                }
+            }
+            S = !any || L0 <= 0 ? 0 : max(min(S, L0 - (FUSED ? 1 : 0)), 0) & ~(TILE - 1);
+            my_shared = S > 0 && (lane == b0 || my_sb > 0) ? S : 0;
+            my_even = lane == b0 ? my_shared / TILE : 0;
+            const int hi = FUSED ? my_len - 1 : my_len;
+            mine = my_even + (my_len <= 0 ? 0 : (hi > my_shared ? (hi + TILE - 1) / TILE - my_shared / TILE : 0) + (FUSED && !KV8 ? 1 : 0));
         } else {
-            my_len = idx < B ? ctx[idx] : 0;
-            mine += flat_tiles<FUSED, KV8>(my_len, W);
+            mine = flat_tiles<FUSED, KV8>(my_len, W);
+        }
+    } else {
+        for (int i = 0; i < k; ++i) {
+            const int idx = lane * k + i;
+            if constexpr (SHARED) {
+                if (idx < NV) mine += flat_seg<FUSED, KV8, true, false>(p, idx).n;
+            } else {
+                mine += flat_tiles<FUSED, KV8>(idx < B ? ctx[idx] : 0, W);
+            }
         }
     }
+    // the segments of (virtual) sequence v, a scalar
+    auto seg_at = [&](int v) __attribute__((always_inline)) {
+        if (!in_lanes) return flat_seg<FUSED, KV8, SHARED, true>(p, v);
+        FlatSeg s;
+        s.b = s.tb = SHARED ? v >> 1 : v;
+        s.L = __builtin_amdgcn_readlane(my_len, s.b);
+        s.hi = FUSED ? s.L - 1 : s.L;
+        s.shared = 0;
+        if constexpr (!SHARED) {
+            s.lo = flat_first_token(s.L, W);
+            s.n = flat_tiles<FUSED, KV8>(s.L, W);
+        } else {
+            const int S = __builtin_amdgcn_readlane(my_shared, s.b);
+            if ((v & 1) == 0) {
+                s.shared = 1;
+                s.tb = s.b - s.b % p.bundle;
+                s.lo = 0;
+                s.hi = s.b == s.tb ? S : 0;
+                s.n = s.hi / TILE;
+            } else {
+                s.lo = S;
+                s.n = s.L <= 0 ? 0 : (s.hi > S ? (s.hi + TILE - 1) / TILE - S / TILE : 0) + (FUSED && !KV8 ? 1 : 0);
+            }
+        }
+        return s;
+    };
     const int incl = wave_inclusive_scan(mine, lane);
     const int P_total = __builtin_amdgcn_readlane(incl, 63);
     const int T = Y * P_total;
@@ -285,20 +343,18 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
 
     // the lane whose chunk holds flat tile f0: the last one whose chunk starts at or before it
     const int cl = __builtin_popcountll(__builtin_amdgcn_ballot_w64(Y * (incl - mine) <= f0)) - 1;
-    int v = cl * k;                                         // (virtual) sequence of the piece at hand
+    int v = in_lanes && SHARED ? 2 * cl : cl * k;           // (virtual) sequence of the piece at hand
     int P_v = __builtin_amdgcn_readlane(incl - mine, cl);
     FlatSeg seg;
-    if (k == 1) {
-        if constexpr (SHARED) {
-            seg = flat_seg<FUSED, KV8, true, true>(p, v);
-        } else {
-            seg.b = seg.tb = v;
-            seg.n = __builtin_amdgcn_readlane(mine, cl);
-            seg.L = __builtin_amdgcn_readlane(my_len, cl);
-            seg.lo = flat_first_token(seg.L, W);
-            seg.hi = FUSED ? seg.L - 1 : seg.L;
-            seg.shared = 0;
+    if (in_lanes) {
+        if constexpr (SHARED) {                             // the bundle's shared prefix (2 cl), or what cl reads alone
+            const int even = __builtin_amdgcn_readlane(my_even, cl);
+            if (Y * (P_v + even) <= f0) {
+                ++v;
+                P_v += even;
+            }
         }
+        seg = seg_at(v);
     } else {
         // level 2: the k sequences of that chunk, 64 at a time
         int n = 0;
@@ -534,7 +590,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
                 ny = 0;
                 do {                                         // skip sequences without tiles
                     ++nv;
-                    nseg = flat_seg<FUSED, KV8, SHARED, true>(p, nv);
+                    nseg = seg_at(nv);
                 } while (nseg.n == 0 && nv + 1 < NV);
                 if (nseg.n == 0) {                           // cannot happen for consistent lengths
                     has_next = false;

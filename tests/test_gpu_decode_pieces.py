@@ -75,3 +75,28 @@ def test_many_pieces_behind_a_shared_prefix(U, oracle):
     dev = U.DevCase(case)
     assert U.max_abs_err(dev.decode_shared(shared, fused=True), ref, W.BF16) <= U.TOL[W.BF16]
     assert U.max_abs_err(dev.decode_shared(shared), ref, W.BF16) <= U.TOL[W.BF16]
+
+
+@pytest.mark.parametrize("B", [1, 63, 64, 65, 130])
+@pytest.mark.parametrize("Hq,Hkv,D", [(8, 2, 128), (6, 2, 64), (8, 8, 64)])      # bundles of 4, 5 and 16
+def test_shared_prefixes_at_the_lane_limit(U, oracle, B, Hq, Hkv, D):
+    """Up to 64 sequences keep their extents in lanes, more read them from memory: random shares,
+    members that share nothing."""
+    rng = np.random.default_rng(B + D)
+    lens = rng.integers(1, 150, B).astype(np.int32)
+    cfg = W.small_config(name="lanes", dtype=W.F16, batch=B, num_heads=Hq, num_kv_heads=Hkv, head_dim=D, block_size=16,
+                         num_blocks=B * 11, ctx_lo=1, ctx_hi=150, seed=B)
+    case = W.make_case(cfg, context_lens=lens)
+    bundle = 16 // (Hq // Hkv)
+    shared = np.zeros(B, np.int32)
+    for b in range(B):
+        b0 = b - b % bundle
+        if b != b0 and rng.random() < 0.7:
+            shared[b] = rng.integers(0, min(lens[b] - 1, lens[b0] - 1) // 16 + 1)
+            case.block_tables[b, :shared[b]] = case.block_tables[b0, :shared[b]]
+    kc, vc = oracle_filled(oracle, case)
+    ref = oracle.paged_attention(case.q, kc, vc, case.block_tables, case.context_lens, case.slopes, case.scale, W.F16)
+    dev = U.DevCase(case)
+    assert U.max_abs_err(dev.decode_shared(shared, fused=True), ref, W.F16) <= U.TOL[W.F16]
+    assert np.array_equal(U.to_host(dev.k_cache), kc) and np.array_equal(U.to_host(dev.v_cache), vc)
+    assert U.max_abs_err(dev.decode_shared(shared), ref, W.F16) <= U.TOL[W.F16]
