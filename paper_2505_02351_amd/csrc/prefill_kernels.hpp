@@ -3,8 +3,9 @@
 //
 // Workgroup (4 or 8 waves, see WAVES below) = 32 (query token, head) rows per wave of one
 // (sequence, KV head [x chunk of the group]) against the whole visible context, in 32-key tiles
-// staged through LDS and shared by the waves.  Heads vary fastest inside the rows, so all heads of the group consume the same K/V
-// tile (Section II: a group shares one key-value pair).
+// staged through LDS and shared by the waves.  The rows are the same tokens of every head of the group,
+// head by head, so all heads of the group consume the same K/V tile (Section II: a group shares one
+// key-value pair).
 //
 // A wave owns 32 rows.  Both contractions are computed transposed, with v_mfma_f32_32x32x16, so that
 // no operand has to be transposed in registers:
@@ -64,6 +65,10 @@ namespace optgqa {
 constexpr float kPfSkipLog2 = OPTGQA_PF_SKIP_LOG2;
 // tiles between a look at whether the rest of the walk still matters, at the least (2, 4 and 8 measure the same)
 constexpr int kPfCheckTiles = 4;
+// ... and tiles that must be left for the look to pay (rest_judged costs about 2 us; 4 prompts of 205-351 over
+// 8-bit caches, 24 / 8 heads, at most 11 tiles: 27.3 us when looking from 4 tiles on, 24.9 from 12; 5 chunks
+// of up to 1 419 behind 630: 115 from 4, 117 from 12, 121 from 16)
+constexpr int kPfJudgeTiles = 12;
 
 
 struct PrefillParams {
@@ -82,7 +87,7 @@ struct PrefillParams {
     int num_heads, num_kv_heads, block_size, max_blocks_per_seq;
     int num_seqs;
     int heads_per_wg;           // GH: query heads per workgroup (divides the group size, <= 16)
-    int heads_pow2_shift;       // log2 of GH rounded up to a power of two (row = token * 2^shift + head)
+    int heads_pow2_shift;       // log2 of GH rounded up to a power of two (rows per workgroup >> shift: its tokens)
     int q_tiles;                // ceil(max_q_len / tokens per workgroup)
     int units;                  // num_seqs * num_kv_heads * (group / GH)
     int window;                 // > 0: the query at position pos sees keys pos - window < j <= pos only
@@ -417,6 +422,8 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     bool row_ok, started;
     int64_t out_off;
     {
+        // (a wave's rows are consecutive tokens of one head, so that it skips by that head's slope and not
+        // by the shallowest of the group's)
         const int row = 32 * row_block + n32;
         const int tshift = __builtin_ctz(tokens_per_wg);
         const int ti = tq0 + (row & (tokens_per_wg - 1)), head = row >> tshift;
@@ -567,6 +574,9 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // 0 (for the whole workgroup) if no key of tiles 0 .. kt can carry a weight above 2^kPfSkipLog2 of
     // any row's sum so far, so that every one of these tiles would be skipped by the test in softmax_pv
     // anyway; else the number of tiles after which it is worth asking again.
+    // (A skipped tile still costs its fetch, LDS stores, score MFMAs and barrier, 0.45 us; the keys read here
+    // cost 0.1.  8 chunks of 512 behind 2 048, 32 / 8 heads: step 156 -> 125 us together with the rows by
+    // head below; 8 prompts of 2 560: 452 -> 403.)
     // By Cauchy-Schwarz |q.k| <= |q||k|, so key j is out of the question for a row if
     //     |scale2| |q| |k_j| + slope2 * (j - pos) - m_ref  <=  log2(lsum) + kPfSkipLog2,
     // i.e. |k_j| <= A + B * (k0 - j) with k0 the nearest of the keys, A = (log2(lsum) + kPfSkipLog2 + m_ref
@@ -756,7 +766,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     int ask = nt;
     for (int j = from_plain; j < to_plain;) {
         if constexpr (!WIN)
-            if (p.slopes && nt - j * KS >= kPfCheckTiles && (ask = rest_judged(last_tile - j * KS)) == 0) break;
+            if (p.slopes && nt - j * KS >= kPfJudgeTiles && (ask = rest_judged(last_tile - j * KS)) == 0) break;
         const int to = min(j + (ask + KS - 1) / KS, to_plain);
         run_tiles(j, to, std::false_type{});
         j = to;
