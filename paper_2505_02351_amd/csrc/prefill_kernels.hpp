@@ -207,7 +207,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // workgroup started in its middle.)
     const bool by_head = p.slopes != nullptr;
     int b, gu, qt, cu0, n_b, ctx_len;
-    if (!WIN && !by_head && p.num_seqs <= 64) {
+    if (KS == 1 && !WIN && !by_head && p.num_seqs <= 64) {       // (two key groups: all workgroups start at once anyway)
         const int rank = blockIdx.x / units_per_seq;
         const int l = threadIdx.x & 63, lc = min(l, p.num_seqs - 1);
         const int c0 = p.cu_q_lens[lc], n = p.cu_q_lens[lc + 1] - c0, len = CONTIG ? n : p.context_lens[lc];
