@@ -179,8 +179,10 @@ int optgqa_set_kernel_events(void *start_event, void *stop_event);
  * partition_size 0; sequences with context_lens[b] == 0 write nothing and give a row of +0.
  * The cache write happens inside the attention kernel - one launch less per step - where the equal-work
  * split applies (a context worth splitting, workspace given), and without a split where one workgroup
- * serves a whole group; always provided that the new rows are 16-byte aligned with strides that are
- * multiples of 8 elements.  Otherwise the library issues the two launches itself.
+ * serves a whole group of at most 32 sequences; always provided that the new rows are 16-byte aligned with
+ * strides that are multiples of 8 elements.  Otherwise the library issues the two launches itself.
+ * Where the split applies, the slot of a sequence's new token must not be among the positions of another
+ * sequence of the batch (successive tokens of one sequence as several batch entries: use the two calls).
  *
  *   k_new, v_new    [num_seqs][num_kv_heads][head_dim]; sequence b starts at element
  *                   b * k_token_stride (resp. v_token_stride), strides >= num_kv_heads * head_dim

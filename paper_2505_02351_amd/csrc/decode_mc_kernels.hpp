@@ -145,7 +145,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, 2) void paged_decode_mc_kernel(c
         for (int i = threadIdx.x; i < GH * D; i += NW * 64) o[i] = 0;
         return;
     }
-    store_new_row<D>(p, b, g, L);
+    store_new_rows<D>(p, g);
     const uint16_t* __restrict__ qp = static_cast<const uint16_t*>(p.q);
     const uint16_t* __restrict__ kc = static_cast<const uint16_t*>(p.k_cache);
     const uint16_t* __restrict__ vc = static_cast<const uint16_t*>(p.v_cache);

@@ -682,12 +682,13 @@ int attention_impl(void* out, const void* q, const void* k_cache, const void* v_
     }
 
     // The cache write rides inside the attention kernel when the new rows can be moved as 16-byte pieces
-    // and that kernel is the equal-work one, or an unsplit one with one workgroup for a whole group (with
-    // several, one would read the row that another writes); otherwise it is a launch of its own.
+    // and that kernel is the equal-work one, or an unsplit one with one workgroup for a whole group and few
+    // sequences (store_new_rows); otherwise it is a launch of its own.
     bool fused = false;
     if (step) {
         const int group = num_heads / num_kv_heads;
-        fused = (s.flat ? s.partition_size == OPTGQA_SPLIT_BALANCED : heads_per_workgroup(group, head_dim) == group) &&
+        fused = (s.flat ? s.partition_size == OPTGQA_SPLIT_BALANCED
+                        : num_seqs <= kMaxFusedSeqs && heads_per_workgroup(group, head_dim) == group) &&
                 aligned16(step->k_new) && aligned16(step->v_new) && step->k_stride % 8 == 0 && step->v_stride % 8 == 0;
         if (!fused && kv_scales) return OPTGQA_ERR_UNSUPPORTED;   // 8-bit step: new rows must move as 16-byte pieces
         if (!fused) {

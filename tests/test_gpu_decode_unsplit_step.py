@@ -1,5 +1,5 @@
 """GPU parity of the one-call decode step where the context is not split: the kernel that attends stores the
-new row itself (one workgroup per KV head), or a launch in front of it does."""
+new rows itself (one workgroup per KV head, few sequences), or a launch in front of it does."""
 import numpy as np
 import pytest
 
@@ -45,3 +45,24 @@ def test_unsplit_step(U, oracle, dtype, Hq, Hkv, D):
         dev.k_new, dev.v_new = rows
         assert U.max_abs_err(dev.step(None), ref, dtype) <= U.TOL[dtype], pad
         assert np.array_equal(U.to_host(dev.k_cache), kc) and np.array_equal(U.to_host(dev.v_cache), vc), pad
+
+
+@pytest.mark.parametrize("n", [2, 32, 33, 40])                 # 32 sequences: the most that one launch serves
+@pytest.mark.parametrize("dtype,Hq,Hkv,D", [(W.F16, 8, 2, 64), (W.BF16, 4, 2, 64), (W.BF16, 8, 2, 128)])
+def test_tokens_of_one_sequence_as_batch_entries(U, oracle, dtype, Hq, Hkv, D, n):
+    """The step's n new tokens are successive tokens of ONE sequence (same block table, lengths one apart): every
+    entry sees the new rows of those before it, as if all rows had been written first."""
+    lens = np.arange(61, 61 + n, dtype=np.int32)
+    cfg = W.small_config(name="successive", dtype=dtype, batch=n, num_heads=Hq, num_kv_heads=Hkv, head_dim=D, block_size=16,
+                         num_blocks=n * 8, ctx_lo=1, ctx_hi=128, seed=n + D)
+    case = W.make_case(cfg, context_lens=lens)
+    case.block_tables[:] = case.block_tables[-1]
+    pos = lens - 1
+    blk, row = case.block_tables[0, pos // 16], pos % 16
+    case.k_cache[blk, :, row] = case.v_cache[blk, :, row] = W.NAN_BITS[dtype]
+    case.slot_mapping = blk.astype(np.int64) * 16 + row
+    kc, vc = oracle_filled(oracle, case)
+    ref = oracle.paged_attention(case.q, kc, vc, case.block_tables, case.context_lens, case.slopes, case.scale, dtype)
+    dev = U.DevCase(case)
+    assert U.max_abs_err(dev.step(None), ref, dtype) <= U.TOL[dtype]
+    assert np.array_equal(U.to_host(dev.k_cache), kc) and np.array_equal(U.to_host(dev.v_cache), vc)
