@@ -60,6 +60,19 @@ struct DecodeParams {
     int min_unit_tiles;             // tiles of 16 tokens a unit has at least: 1, or a fixed partition (partition_size / 16)
 };
 
+// A uniform pointer whose contents no workgroup of the launch changes: its loads stay scalar loads in a kernel that
+// also stores (the address space), and the pointer stays in scalar registers whatever else is made of its parts (the
+// asm; taken ahead of the stores).  Without this the stores to the caches ahead of the walk turned the block
+// numbers into vector loads, each waited for, with every tile in flight, ahead of its own tile's loads: 64 sequences
+// of 300-1 500 tokens, unsplit plain attention, 16 / 4 heads, head_dim 128: 28.1 -> 38.4 us; 8 / 8, head_dim 64: 36.0
+// -> 51.5.  For the same reason, and for its registers, plain attention is an instantiation without the store (STEP).
+typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
+__device__ __forceinline__ const_i32_ptr launch_constant(const int32_t* q)
+{
+    asm volatile("" : "+s"(q));
+    return (const_i32_ptr)(uintptr_t)q;
+}
+
 // Sequence and number of visible keys of one output row (decode: row = sequence).
 __device__ __forceinline__ bool row_to_seq(const DecodeParams& p, int row, int& b, int& L)
 {
@@ -70,21 +83,20 @@ __device__ __forceinline__ bool row_to_seq(const DecodeParams& p, int row, int& 
 
 constexpr int kDecodeWaves = 4;
 
-// The step's cache write inside the unsplit kernels (k_new set: one workgroup per sequence and KV head): the
-// workgroup stores its KV head's new rows of EVERY sequence, in 16-byte pieces, and nobody in it reads the cache
-// before they have landed.  Tables may name a block twice - the successive tokens of one sequence as several
+// The step's cache write inside the unsplit kernels (their STEP instantiations: one workgroup per sequence and KV
+// head): the workgroup stores its KV head's new rows of EVERY sequence, in 16-byte pieces, and nobody in it reads the
+// cache before they have landed.  Tables may name a block twice - the successive tokens of one sequence as several
 // batch entries, say - so another sequence's new row may be among the keys read here, and its own workgroup may
 // be late; the same bytes stored by several workgroups are no conflict, and none reads a row that it has not
 // stored itself.  Saves the launch that a step of a few short contexts otherwise spends a third of its time on
 // (cache write and attention, then one launch, GPU time: batch 1, 128 tokens, 8 / 2 heads, head_dim 64: 7.2 -> 5.7
 // us), and costs num_seqs rows per workgroup, so the host fuses up to kMaxFusedSeqs sequences (16 / 4 heads,
-// head_dim 128, 128 tokens: 16 sequences 8.3 -> 7.2 us, 32: 8.4 -> 8.2, 64: 8.4 -> 10.1).
+// head_dim 128, 128 tokens: 16 sequences 8.3 -> 7.0 us, 32: 8.3 -> 8.0, 64: 8.4 -> 10.1).
 constexpr int kMaxFusedSeqs = 32;
 
 template <int D> __device__ __forceinline__ void store_new_rows(const DecodeParams& p, int g)
 {
     constexpr int LPR = D / 8;
-    if (p.k_new == nullptr) return;                     // launch-uniform
     for (int i = threadIdx.x; i < p.num_seqs * 2 * LPR; i += kDecodeWaves * 64) {
         const int b = i / (2 * LPR), bs = p.block_size;
         const bool is_v = i / LPR & 1;
@@ -102,7 +114,7 @@ template <int D> __device__ __forceinline__ void store_new_rows(const DecodePara
     __syncthreads();
 }
 
-template <int DT, int D, int GH>
+template <int DT, int D, int GH, bool STEP>
 __global__ __launch_bounds__(kDecodeWaves * 64) void paged_decode_kernel(const DecodeParams p)
 {
     constexpr int LPR = D / 8;            // lanes per token row
@@ -132,7 +144,8 @@ __global__ __launch_bounds__(kDecodeWaves * 64) void paged_decode_kernel(const D
         for (int i = threadIdx.x; i < GH * D; i += NW * 64) o[i] = 0;
         return;
     }
-    store_new_rows<D>(p, g);
+    const const_i32_ptr table = launch_constant(p.block_tables + (int64_t)b * p.max_blocks_per_seq);
+    if constexpr (STEP) store_new_rows<D>(p, g);
 
     // q for the GH heads, this lane's 8 dims, still packed (consumed by 2-way dot products).
     uint4 qv[GH];
@@ -152,7 +165,6 @@ __global__ __launch_bounds__(kDecodeWaves * 64) void paged_decode_kernel(const D
         for (int e = 0; e < 8; ++e) acc[i][e] = 0.f;
     }
 
-    const int32_t* __restrict__ table = p.block_tables + (int64_t)b * p.max_blocks_per_seq;
     const int nsteps = (t_end - t_begin + TPS - 1) / TPS;
     for (int s = wave; s < nsteps; s += NW) {
         const int t0 = t_begin + s * TPS;                 // wave-uniform, never straddles a block

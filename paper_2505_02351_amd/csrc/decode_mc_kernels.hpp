@@ -103,7 +103,7 @@ struct McSmem {
     static constexpr int kBytes = kBulkBytes + 2 * kStreams * GH * 4;
 };
 
-template <int DT, int D, int GH>
+template <int DT, int D, int GH, bool STEP>
 __global__ __launch_bounds__(kDecodeWaves * 64, 2) void paged_decode_mc_kernel(const DecodeParams p)
 {
     static_assert(GH == 4 || GH == 8, "heads per workgroup must be 4 or 8");
@@ -145,11 +145,11 @@ __global__ __launch_bounds__(kDecodeWaves * 64, 2) void paged_decode_mc_kernel(c
         for (int i = threadIdx.x; i < GH * D; i += NW * 64) o[i] = 0;
         return;
     }
-    store_new_rows<D>(p, g);
+    const int32_t* const table = (const int32_t*)launch_constant(p.block_tables + (int64_t)b * p.max_blocks_per_seq);
+    if constexpr (STEP) store_new_rows<D>(p, g);
     const uint16_t* __restrict__ qp = static_cast<const uint16_t*>(p.q);
     const uint16_t* __restrict__ kc = static_cast<const uint16_t*>(p.k_cache);
     const uint16_t* __restrict__ vc = static_cast<const uint16_t*>(p.v_cache);
-    const int32_t* __restrict__ table = p.block_tables + (int64_t)b * p.max_blocks_per_seq;
 
     // q, this lane's 8 dims, still packed, in a lane-dependent head order: slot 4i+k holds head
     // 4i + (u ^ k).  With that order the transposing reduction needs no selects: slot 0 is the

@@ -72,7 +72,7 @@ __device__ __forceinline__ float row16_max(float x)
     return dpp_max<kDppMirror>(x);
 }
 
-template <int DT>
+template <int DT, bool STEP>
 __global__ __launch_bounds__(kDecodeWaves * 64, OPTGQA_MMA_WAVES_PER_SIMD) void paged_decode_mma_kernel(const DecodeParams p)
 {
     constexpr int D = 128;
@@ -108,11 +108,11 @@ __global__ __launch_bounds__(kDecodeWaves * 64, OPTGQA_MMA_WAVES_PER_SIMD) void 
         for (int i = threadIdx.x; i < GH * D; i += NW * 64) o[i] = 0;
         return;
     }
-    store_new_rows<D>(p, g);
+    const const_i32_ptr table = launch_constant(p.block_tables + (int64_t)b * p.max_blocks_per_seq);
+    if constexpr (STEP) store_new_rows<D>(p, g);
     const uint16_t* __restrict__ qp = static_cast<const uint16_t*>(p.q);
     const uint16_t* __restrict__ kc = static_cast<const uint16_t*>(p.k_cache);
     const uint16_t* __restrict__ vc = static_cast<const uint16_t*>(p.v_cache);
-    const int32_t* __restrict__ table = p.block_tables + (int64_t)b * p.max_blocks_per_seq;
 
     const float scale2 = p.scale2;
     const int Lm1 = L - 1;

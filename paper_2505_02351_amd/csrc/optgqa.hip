@@ -247,32 +247,32 @@ SplitPlan plan_split(int num_seqs, int num_heads, int num_kv_heads, int head_dim
 
 // The fast decode kernel takes its LDS as dynamic shared memory (the ring may exceed the 64 KiB
 // a kernel gets by default); the size limit is raised once per kernel instantiation.
-template <int DT, int D, int GH>
+template <int DT, int D, int GH, bool STEP>
 int launch_decode_mc(const DecodeParams& p, dim3 grid, dim3 block, hipStream_t st)
 {
     constexpr int kBytes = McSmem<D, GH>::kBytes;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&paged_decode_mc_kernel<DT, D, GH>),
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&paged_decode_mc_kernel<DT, D, GH, STEP>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
     if (attr != hipSuccess) return OPTGQA_ERR_LAUNCH;
-    return launch(paged_decode_mc_kernel<DT, D, GH>, grid, block, kBytes, st, p);
+    return launch(paged_decode_mc_kernel<DT, D, GH, STEP>, grid, block, kBytes, st, p);
 }
 
-template <int DT, int D>
+template <int DT, int D, bool STEP>
 int launch_decode_gh(const DecodeParams& p, int gh, dim3 grid, hipStream_t st)
 {
     const dim3 block(kDecodeWaves * 64);
     if (D == 128) {
-        return launch(paged_decode_mma_kernel<DT>, grid, block, 0, st, p);
+        return launch(paged_decode_mma_kernel<DT, STEP>, grid, block, 0, st, p);
     }
 #ifndef OPTGQA_VALU_ONLY_DECODE
-    if (gh == 8) return launch_decode_mc<DT, D, 8>(p, grid, block, st);
-    if (gh == 4) return launch_decode_mc<DT, D, 4>(p, grid, block, st);
+    if (gh == 8) return launch_decode_mc<DT, D, 8, STEP>(p, grid, block, st);
+    if (gh == 4) return launch_decode_mc<DT, D, 4, STEP>(p, grid, block, st);
 #endif
     switch (gh) {
-    case 8: return launch(paged_decode_kernel<DT, D, 8>, grid, block, 0, st, p);
-    case 4: return launch(paged_decode_kernel<DT, D, 4>, grid, block, 0, st, p);
-    case 2: return launch(paged_decode_kernel<DT, D, 2>, grid, block, 0, st, p);
-    default: return launch(paged_decode_kernel<DT, D, 1>, grid, block, 0, st, p);
+    case 8: return launch(paged_decode_kernel<DT, D, 8, STEP>, grid, block, 0, st, p);
+    case 4: return launch(paged_decode_kernel<DT, D, 4, STEP>, grid, block, 0, st, p);
+    case 2: return launch(paged_decode_kernel<DT, D, 2, STEP>, grid, block, 0, st, p);
+    default: return launch(paged_decode_kernel<DT, D, 1, STEP>, grid, block, 0, st, p);
     }
 }
 
@@ -290,7 +290,7 @@ int launch_decode(DecodeParams p, int num_rows, hipStream_t st)
         int rc;
         {
             KernelEvents ev(st);
-            rc = launch_decode_gh<DT, D>(p, gh, grid, st);
+            rc = p.k_new ? launch_decode_gh<DT, D, true>(p, gh, grid, st) : launch_decode_gh<DT, D, false>(p, gh, grid, st);
         }
         if (rc != OPTGQA_OK) return rc;
     }
