@@ -320,8 +320,9 @@ size_t optgqa_paged_attention_workspace_bytes(int num_seqs, int num_heads, int n
  * rounding, the row sum taken over the rounded weights; bf16: a bf16 head plus a bf16 tail, two
  * contractions, so that the weights keep 16 significant bits).  Keys are
  * visited from the query's own position backwards; a 32-key tile in which every weight, for
- * every query row a wave holds, is below 2^-24 of that row's sum so far is dropped (less than
- * half an ulp of the fp32 sum per tile: with ALiBi slopes the far keys of steep heads).
+ * every query row a wave holds, is below 2^-24 of that row's sum so far is dropped (each weight less than
+ * half an ulp of the fp32 sum: with ALiBi slopes the far keys of steep heads), and so is the rest of the context
+ * where a bound from the keys' norms shows this of all its tiles.
  *
  *   out, q          [total_q_tokens][num_heads][head_dim], total_q_tokens = cu_q_lens[num_seqs]
  *   cu_q_lens       [num_seqs + 1] int32, non-decreasing prefix sums of the n_b, cu_q_lens[0] = 0

@@ -46,9 +46,10 @@
 // row's sum so far - half an ulp of that fp32 sum, a fact read off the scores, not assumed from
 // the slopes - the tile's exponentials, weight packing and output MFMAs are skipped.  Each dropped
 // weight is one that an fp32 "sum += w" would have rounded away by itself; a tile drops at most
-// 32 of them per row (2^-19 of the row sum), and since skipping only sets in where the weights
-// keep falling, the total stays within a few 2^-19 - three orders of magnitude below the compute
-// budget of the stated tolerance.  (The definition, eq. (3)-(4), still sums every key; heads with a
+// 32 of them per row (2^-19 of the row sum).  Under a positive slope the weights that could lie at the threshold
+// fall from tile to tile, and the total stays within a few 2^-19 - three orders of magnitude below the compute
+// budget of the stated tolerance; without one it is bounded by 2^-24 a key (2^-9 of the sum if all of 32 768
+// keys lie just below the threshold).  (The definition, eq. (3)-(4), still sums every key; heads with a
 // steep slope simply give most keys a weight that no fp32 sum can see.)
 #pragma once
 #include <type_traits>
@@ -572,14 +573,15 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
 
     // ---- the rest of the walk judged at once -------------------------------------------------------
     // 0 (for the whole workgroup) if no key of tiles 0 .. kt can carry a weight above 2^kPfSkipLog2 of
-    // any row's sum so far, so that every one of these tiles would be skipped by the test in softmax_pv
-    // anyway; else the number of tiles after which it is worth asking again.
+    // any row's sum so far - of the smaller of the two lanes' halves of it, which is what the test in softmax_pv
+    // compares with - so that every one of these tiles would be skipped by that test anyway; else the number of
+    // tiles after which it is worth asking again.
     // (A skipped tile still costs its fetch, LDS stores, score MFMAs and barrier, 0.45 us; the keys read here
     // cost 0.1.  8 chunks of 512 behind 2 048, 32 / 8 heads: step 156 -> 125 us together with the rows by
     // head below; 8 prompts of 2 560: 452 -> 403.)
     // By Cauchy-Schwarz |q.k| <= |q||k|, so key j is out of the question for a row if
-    //     |scale2| |q| |k_j| + slope2 * (j - pos) - m_ref  <=  log2(lsum) + kPfSkipLog2,
-    // i.e. |k_j| <= A + B * (k0 - j) with k0 the nearest of the keys, A = (log2(lsum) + kPfSkipLog2 + m_ref
+    //     |scale2| |q| |k_j| + slope2 * (j - pos) - m_ref  <=  log2(sum) + kPfSkipLog2,
+    // i.e. |k_j| <= A + B * (k0 - j) with k0 the nearest of the keys, A = (log2(sum) + kPfSkipLog2 + m_ref
     // + slope2 * (pos - k0)) / (|scale2||q|), B = slope2 / (|scale2||q|) (any sign), the least A and B of
     // all rows.  The workgroup then reads the keys once, without V, LDS, MFMAs or exponentials.
     // A norm that is not a number, or infinite, fails the test.
@@ -598,7 +600,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         q2 += __shfl_xor(q2, 32);                                // a row's dims live in 2 lanes (h2)
         const float qn = __builtin_amdgcn_sqrtf(q2);
         const float qs = 1.001f * fabsf(scale2) * qn + 0x1p-100f;    // (margins cover the rounding of the norms)
-        const float room = __builtin_amdgcn_logf(lsum + __shfl_xor(lsum, 32)) + (kPfSkipLog2 - 0.01f);
+        const float room = __builtin_amdgcn_logf(fminf(lsum, __shfl_xor(lsum, 32))) + (kPfSkipLog2 - 0.01f);
         float a = (room + m_ref + slope2 * (posf - (float)k0)) / qs;
         float bb = row_ok ? slope2 / qs : INFINITY;
         float wait = a >= 1.25f * qn ? 0.f : fminf((1.25f * qn - a) / (bb * (float)kPfKeys) + 1.f, 1e6f);

@@ -78,6 +78,35 @@ def test_a_far_key_of_an_8_bit_cache(U, oracle, D, t0):
     U.check_scaled(U.to_host(out), ref, W.BF16, f"E4M3 caches, outlier at {t0}")
 
 
+# (two key groups; 8 waves)
+@pytest.mark.parametrize("B,Hq,Hkv,D", [(2, 8, 2, 128), (64, 8, 8, 64)])
+def test_half_a_rows_sum_does_not_judge_the_other_halfs_keys(U, oracle, B, Hq, Hkv, D):
+    """A row's sum is held by two lanes, of keys 8i .. 8i + 3 and 8i + 4 .. 8i + 7.  Two near keys of the first kind weigh
+    2^23 times the others, so the far keys lie below 2^-24 of the whole sum, but not of the second lane's half of it:
+    a tile of them is kept, and so must be the rest of the walk (their values are large: without them the output is
+    off by 0.4 or more)."""
+    ctx, q_len = 2616, 24
+    cfg = W.small_config(name="halves", kind="prefill", dtype=W.BF16, batch=B, num_heads=Hq, num_kv_heads=Hkv, head_dim=D,
+                         block_size=16, num_blocks=B * 164, ctx_lo=ctx, ctx_hi=ctx, q_len=q_len, seed=3)
+    case = W.make_case(cfg, slopes=np.full(Hq, 2.0 ** -9, np.float32))
+    pos0, u = ctx - q_len, np.full(D, D ** -0.5, np.float32)
+    case.q[:] = W.to_bits(u, W.BF16)
+    case.k_cache[:] = case.k_new[:] = 0
+    loud = W.to_bits(u * np.float32(23 * np.log(2) / case.scale), W.BF16)
+    for b in range(B):                      # positions 2 592 and 2 584: in the first tile of either key group
+        case.k_new[b * q_len] = loud
+        case.k_cache[case.block_tables[b, (pos0 - 8) // 16], :, (pos0 - 8) % 16] = loud
+        for t in range(0, pos0 - 400, 16):
+            case.v_cache[case.block_tables[b, t // 16]] = W.to_bits(np.float32(3e4), W.BF16)
+    dev = U.DevCase(case)
+    step = dev.prefill_step()
+    kc, vc = oracle_filled(oracle, case)
+    rows = slice(None, case.cu_q_lens[2])
+    ref = oracle.paged_prefill(case.q[rows], kc, vc, case.block_tables[:2], case.context_lens[:2], case.cu_q_lens[:3],
+                               case.slopes, case.scale, W.BF16)
+    U.check_scaled(step[rows], ref, W.BF16, "halves", max_exempt=1.0)
+
+
 # (sequences, heads, KV heads, head_dim): 1 and odd numbers of them, a lane's worth, one more (the plain order);
 # few enough workgroups for two key groups, and enough for one group of four and of eight waves
 @pytest.mark.parametrize("B,Hq,Hkv,D", [(1, 8, 2, 128), (3, 6, 2, 64), (7, 40, 8, 128), (64, 4, 1, 64), (65, 4, 1, 128),
