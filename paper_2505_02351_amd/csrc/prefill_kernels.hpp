@@ -598,14 +598,16 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
             q2 = dot2<DT>(qb[m].w, qb[m].w, q2);
         }
         q2 += __shfl_xor(q2, 32);                                // a row's dims live in 2 lanes (h2)
-        const float qn = __builtin_amdgcn_sqrtf(q2);
-        const float qs = 1.001f * fabsf(scale2) * qn + 0x1p-100f;    // (margins cover the rounding of the norms)
+        // (margins cover the rounding of the norms, 2^-58 the squares below 2^-126 that are lost in them: as many in the
+        // keys' norms, which is why qs is bounded below)
+        const float qn = __builtin_amdgcn_sqrtf(q2) + 0x1p-58f;
+        const float qs = 1.001f * fabsf(scale2) * qn + 0x1p-100f;
         const float room = __builtin_amdgcn_logf(fminf(lsum, __shfl_xor(lsum, 32))) + (kPfSkipLog2 - 0.01f);
         float a = (room + m_ref + slope2 * (posf - (float)k0)) / qs;
         float bb = row_ok ? slope2 / qs : INFINITY;
         float wait = a >= 1.25f * qn ? 0.f : fminf((1.25f * qn - a) / (bb * (float)kPfKeys) + 1.f, 1e6f);
         wait = room == -INFINITY ? 1.f : wait >= 0.f ? wait : 1e6f;  // (no key seen yet; no slope, or a negative one)
-        const bool no = !(a > 0.f && q2 < 0x1p100f);
+        const bool no = !(a > 0.f && qs < 0x1p40f);
         if (__builtin_amdgcn_ballot_w64(no) != 0) a = -1.f;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
@@ -670,7 +672,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
             };
             auto judge = [&](const uint4 (&x)[kLoads], int i) __attribute__((always_inline)) {
                 const float most = fmaf(bb, (float)(k0 - 15 - base_key(min(i, mine - 1))) + far_end, a);
-                const float most2 = most > 0.f ? most * most * 0.999f : -1.f;
+                const float most2 = most > 0.f ? fminf(most * most * 0.999f, 0x1p126f) : -1.f;
 #pragma unroll
                 for (int r = 0; r < kLoads; ++r) {
                     float n2;

@@ -107,6 +107,25 @@ def test_half_a_rows_sum_does_not_judge_the_other_halfs_keys(U, oracle, B, Hq, H
     U.check_scaled(step[rows], ref, W.BF16, "halves", max_exempt=1.0)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,D", [(2, 8, 2, 128), (64, 8, 8, 64)])
+def test_a_key_whose_norm_overflows_is_not_judged_away(U, oracle, B, Hq, Hkv, D):
+    """Queries so small that their norms' squares vanish, one far key so large that its norm's square is infinite: the
+    score between them is the row's largest by far."""
+    cfg = W.small_config(name="huge", kind="prefill", dtype=W.BF16, batch=B, num_heads=Hq, num_kv_heads=Hkv, head_dim=D,
+                         block_size=16, num_blocks=B * 45, ctx_lo=705, ctx_hi=705, q_len=24, seed=4)
+    case = W.make_case(cfg, slopes=np.full(Hq, 0.25, np.float32))
+    u = np.full(D, D ** -0.5, np.float32)
+    case.q[:] = W.to_bits(u * np.float32(2.0 ** -70), W.BF16)
+    case.k_cache[case.block_tables[0, 6], :, 4] = W.to_bits(u * np.float32(2.0 ** 100), W.BF16)
+    dev = U.DevCase(case)
+    step = dev.prefill_step()
+    kc, vc = oracle_filled(oracle, case)
+    rows = slice(None, case.cu_q_lens[2])
+    ref = oracle.paged_prefill(case.q[rows], kc, vc, case.block_tables[:2], case.context_lens[:2], case.cu_q_lens[:3],
+                               case.slopes, case.scale, W.BF16)
+    U.check_scaled(step[rows], ref, W.BF16, "huge")
+
+
 # (sequences, heads, KV heads, head_dim): 1 and odd numbers of them, a lane's worth, one more (the plain order);
 # few enough workgroups for two key groups, and enough for one group of four and of eight waves
 @pytest.mark.parametrize("B,Hq,Hkv,D", [(1, 8, 2, 128), (3, 6, 2, 64), (7, 40, 8, 128), (64, 4, 1, 64), (65, 4, 1, 128),
