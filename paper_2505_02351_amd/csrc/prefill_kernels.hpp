@@ -70,8 +70,8 @@ constexpr int kPfCheckTiles = 4;
 // 8-bit caches, 24 / 8 heads, at most 11 tiles: 27.3 us when looking from 4 tiles on, 24.9 from 12; 5 chunks
 // of up to 1 419 behind 630: 115 from 4, 117 from 12, 121 from 16)
 constexpr int kPfJudgeTiles = 12;
-
-
+// tiles that a look which fails further on must have passed for the walk to leave them out (starting it anew costs about 3 us)
+constexpr int kPfJumpTiles = 8;
 struct PrefillParams {
     void* out;                  // [T][Hq][D] dtype
     const void* q;              // [T][Hq][D]
@@ -183,6 +183,8 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     constexpr int kKTile = kPfKeys * kPfKRow, kBuf = kKTile + kPfKeys * kPfVRow;   // (of each key group)
     extern __shared__ __attribute__((aligned(16))) uint16_t tile_lds[];          // KS * PfTile<D>::kLdsBytes
     __shared__ float vote[3][WAVES];                          // rest_judged
+    __shared__ int nearest_bad;
+    __shared__ uint32_t least_norm2;
 
     // ---- which rows -----------------------------------------------------------------------
     // XCD-aware order: workgroups go to XCD (flat id % 8); all query tiles of one (sequence, KV
@@ -577,8 +579,8 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // compares with - so that every one of these tiles would be skipped by that test anyway; else the number of
     // tiles after which it is worth asking again.
     // (A skipped tile still costs its fetch, LDS stores, score MFMAs and barrier, 0.45 us; the keys read here
-    // cost 0.1.  8 chunks of 512 behind 2 048, 32 / 8 heads: step 156 -> 125 us together with the rows by
-    // head below; 8 prompts of 2 560: 452 -> 403.)
+    // cost 0.1.  8 chunks of 512 behind 2 048, 32 / 8 heads: step 156 -> 120 us together with the rows by
+    // head above; 8 prompts of 2 560: 452 -> 403.)
     // By Cauchy-Schwarz |q.k| <= |q||k|, so key j is out of the question for a row if
     //     |scale2| |q| |k_j| + slope2 * (j - pos) - m_ref  <=  log2(sum) + kPfSkipLog2,
     // i.e. |k_j| <= A + B * (k0 - j) with k0 the nearest of the keys, A = (log2(sum) + kPfSkipLog2 + m_ref
@@ -587,6 +589,14 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // A norm that is not a number, or infinite, fails the test.
     // When to ask: A grows by 32 B a tile, and the keys' norms - not known before they are read - are
     // taken to be like the queries', at most 1.25 |q| (a wrong guess costs time only).
+    // A key that fails fails every later look too (but for the growth of the sum) until the walk is past it.  So a
+    // look ends, for all waves, where the nearest failing key lies; the walk leaves out the tiles before it (restart)
+    // and looks again behind it, when the bound has grown to the least norm of the key's group (all keys may be louder
+    // than the queries) and after twice as many tiles each time (they may be loud here and there).  Chunks of 512
+    // behind 32 000, 32 / 8 heads, one key of 10 times the norm at distance 2 000 / 20 000: 1 614 / 10 000 us when
+    // every look read on past it and the next came 8 tiles later, 396 / 403 now, 718 without looks (none loud: 460, 387 and
+    // 720); all of 10 times the norm: 1 396, 642 and 752.
+    int pause = 2 * kPfCheckTiles, passed = 0;                   // passed: tiles kt, kt - 1, ... that a failing look has judged away
     auto rest_judged = [&](int kt) __attribute__((always_inline)) -> int {
         const int k0 = kt * kPfKeys + kPfKeys - 1;
         float q2 = 0.f;
@@ -619,6 +629,8 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
             vote[0][wg_wave] = a;
             vote[1][wg_wave] = bb;
             vote[2][wg_wave] = wait;
+            nearest_bad = -1;                                    // (the last call's have been read, barriers ago)
+            least_norm2 = 0x7f800000u;
         }
         __syncthreads();
         a = vote[0][0], bb = vote[1][0], wait = vote[2][0];
@@ -628,6 +640,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
             bb = fminf(bb, vote[1][i]);
             wait = fmaxf(wait, vote[2][i]);
         }
+        passed = 0;
         if (!(a > 0.f) || wait > 0.f) return max(kPfCheckTiles / 2, __builtin_amdgcn_readfirstlane((int)wait));    // workgroup-uniform
         // Nearest first, the waves take groups of 16 keys in turn: one block each, kLoads 16-byte loads per
         // lane, kRowLanes lanes to a key.  A lane holds the block number of one of the wave's next 64 groups.
@@ -638,8 +651,8 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         const uint32_t row_bytes = CONTIG ? (uint32_t)(p.k_in_stride * 2) : D * ES;
         const int groups = (k0 + 1) / 16;
         const float far_end = bb < 0.f ? 15.f : 0.f;             // offset of a group's key with the least bound
-        bool bad = false;
-        for (int g0 = 0; g0 < groups; g0 += 64 * WAVES) {
+        bool stop = false;                                       // wave-uniform
+        for (int g0 = 0; g0 < groups && !stop; g0 += 64 * WAVES) {
             const int mine = min((groups - g0 - wg_wave + WAVES - 1) / WAVES, 64);     // this wave's groups here
             if (mine <= 0) break;
             auto base_key = [&](int i) __attribute__((always_inline)) { return k0 - 15 - 16 * (g0 + i * WAVES + wg_wave); };
@@ -670,9 +683,12 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
                 n2 = dot2<DT>(y.z, y.z, n2);
                 return dot2<DT>(y.w, y.w, n2);
             };
-            auto judge = [&](const uint4 (&x)[kLoads], int i) __attribute__((always_inline)) {
+            // (least: of the norms' squares)
+            auto judge = [&](const uint4 (&x)[kLoads], int i, float& least) __attribute__((always_inline)) -> bool {
                 const float most = fmaf(bb, (float)(k0 - 15 - base_key(min(i, mine - 1))) + far_end, a);
                 const float most2 = most > 0.f ? fminf(most * most * 0.999f, 0x1p126f) : -1.f;
+                bool bad = false;
+                least = INFINITY;
 #pragma unroll
                 for (int r = 0; r < kLoads; ++r) {
                     float n2;
@@ -680,27 +696,43 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
                     else n2 = norm2(x[r], 0.f);
                     n2 = row_group_sum<kRowLanes>(n2);
                     bad = bad || !(n2 <= most2);
+                    least = fminf(least, n2);
                 }
+                return bad;
             };
             uint4 x0[kLoads], x1[kLoads];
             load_keys(x0, 0);
-            for (int i = 0; i < mine; i += 2) {
+            for (int i = 0; i < mine && !stop; i += 2) {
                 load_keys(x1, i + 1);
-                judge(x0, i);
+                const int others = *static_cast<volatile int*>(&nearest_bad);
+                float least0, least1;
+                const bool bad0 = judge(x0, i, least0);
                 load_keys(x0, i + 2);
-                judge(x1, i + 1);
-                if (__builtin_amdgcn_ballot_w64(bad) != 0) break;
-            }
-            if (__builtin_amdgcn_ballot_w64(bad) != 0) break;
-        }
-        __syncthreads();                                         // the votes above have been read
-        const float verdict = __builtin_amdgcn_ballot_w64(bad) != 0 ? -1.f : 1.f;     // (with all lanes active)
-        if (lane == 0) vote[0][wg_wave] = verdict;
-        __syncthreads();
-        a = vote[0][0];
+                const bool bad1 = judge(x1, i + 1, least1);
+                if (__builtin_amdgcn_ballot_w64(bad0 || bad1) != 0) {
+                    const bool first = __builtin_amdgcn_ballot_w64(bad0) != 0;
+                    float least = first ? least0 : least1;
 #pragma unroll
-        for (int i = 1; i < WAVES; ++i) a = fminf(a, vote[0][i]);
-        return a > 0.f ? 0 : 2 * kPfCheckTiles;                  // (the next call's votes are barriers away)
+                    for (int off = kRowLanes; off < 64; off <<= 1) least = fminf(least, __shfl_xor(least, off));
+                    if (lane == 0) {
+                        atomicMax(&nearest_bad, base_key(first ? i : min(i + 1, mine - 1)));
+                        atomicMin(&least_norm2, __builtin_bit_cast(uint32_t, least));
+                    }
+                    stop = true;
+                }
+                // (another wave's key that fails: nothing beyond it counts)
+                stop = stop || __builtin_amdgcn_readfirstlane(others) > base_key(i);
+            }
+        }
+        __syncthreads();
+        const int nearest = __builtin_amdgcn_readfirstlane(nearest_bad);
+        if (nearest < 0) return 0;
+        const float quiet = __builtin_amdgcn_sqrtf(__builtin_bit_cast(float, least_norm2));
+        const float grown = bb > 0.f ? fminf((quiet - a) / (bb * (float)kPfKeys) + 1.f, 1e6f) : 0.f;
+        passed = kt - nearest / kPfKeys;
+        const int next = max(passed + pause, __builtin_amdgcn_readfirstlane((int)grown));
+        pause *= 2;
+        return next;                                             // (the next call's votes are barriers away)
     };
 
     const int pos_min = pos0 + tq0;                             // tiles ending at or below it need no causal mask
@@ -757,6 +789,20 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
             st_next = st_other;
         }
     };
+    // The walk goes on at step j, wherever it was (every wave has passed a barrier since it last read a tile).
+    auto restart = [&](int j) __attribute__((always_inline)) {
+        blk_next = load_blk(j);
+        fetch_tile(stage, j);
+        store_tile(stage, j);
+        if (k_loader) {
+            fetch_tile(stage, j + 1);
+            store_tile(stage, j + 1);
+        }
+        fetch_tile(stage, j + 1 + l_ahead);
+        __syncthreads();
+        st_next = scores(j);
+        __syncthreads();
+    };
     const int cut_end = max(kt0, min(n_window_cut, n_unmasked));   // tiles cut by some row's window start
     const int plain_end = max(cut_end, n_unmasked);                // tiles no mask touches
     // from the diagonal backwards: the tiles the causal mask cuts come first, those that some
@@ -770,7 +816,15 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     int ask = nt;
     for (int j = from_plain; j < to_plain;) {
         if constexpr (!WIN)
-            if (p.slopes && nt - j * KS >= kPfJudgeTiles && (ask = rest_judged(last_tile - j * KS)) == 0) break;
+            if (p.slopes && nt - j * KS >= kPfJudgeTiles) {
+                ask = rest_judged(last_tile - j * KS);
+                if (ask == 0) break;
+                if (passed >= kPfJumpTiles) {                    // workgroup-uniform
+                    j += passed / KS;
+                    ask -= passed / KS * KS;
+                    restart(j);
+                }
+            }
         const int to = min(j + (ask + KS - 1) / KS, to_plain);
         run_tiles(j, to, std::false_type{});
         j = to;

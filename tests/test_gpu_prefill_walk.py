@@ -154,3 +154,31 @@ def test_ragged_launches_in_order_of_length(U, oracle, B, Hq, Hkv, D):
     torch.cuda.synchronize()
     dev.check_canaries()
     U.check_scaled(U.to_host(dev.out), ref, W.BF16, f"ragged {B}")
+
+
+@pytest.mark.parametrize("distance", [2000, 8000])
+def test_one_loud_far_key_does_not_cost_a_look_every_few_tiles(U, distance):
+    """Chunks of 512 behind 32 000 cached tokens, slopes 2^(-8h/32): with one key of ten times the norm in every sequence the
+    step takes 1.02 (1.01) of its time without, and took 3.5 (9.7) when every look read the context up to that key and
+    beyond, and the next one came eight tiles later."""
+    import torch
+    import paper_2505_02351_amd as G
+    from test_gpu_decode_unsplit_step import microseconds
+    B, Hq, Hkv, D, bs, ctx, new = 4, 32, 8, 128, 16, 32000, 512
+    blocks = (ctx + new) // bs
+    gen = torch.Generator("cuda").manual_seed(8)
+    q, k, v = (torch.randn(B * new, h, D, generator=gen, device="cuda", dtype=torch.bfloat16) for h in (Hq, Hkv, Hkv))
+    kc, vc = (torch.randn(B * blocks, Hkv, bs, D, generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    table = torch.randperm(B * blocks, generator=gen, device="cuda").to(torch.int32).view(B, blocks)
+    lens = torch.full((B,), ctx + new, dtype=torch.int32, device="cuda")
+    cu = torch.arange(0, B * new + 1, new, dtype=torch.int32, device="cuda")
+    slopes = torch.exp2(-8.0 * torch.arange(1, Hq + 1, device="cuda") / Hq)
+    out = torch.empty_like(q)
+
+    def us():
+        return microseconds(lambda: G.prefill_step(out, q, k, v, kc, vc, table, lens, cu, slopes, D ** -0.5, new))
+    quiet = us()
+    at = ctx + new - distance
+    kc[table[:, at // bs].long(), :, at % bs] *= 10
+    loud = us()
+    assert loud <= 1.5 * quiet, (loud, quiet)
