@@ -72,6 +72,7 @@ constexpr int kPfCheckTiles = 4;
 constexpr int kPfJudgeTiles = 12;
 // tiles that a look which fails further on must have passed for the walk to leave them out (starting it anew costs about 3 us)
 constexpr int kPfJumpTiles = 8;
+
 struct PrefillParams {
     void* out;                  // [T][Hq][D] dtype
     const void* q;              // [T][Hq][D]
