@@ -139,10 +139,13 @@ template <int DT> struct PfSoftmax;
 template <> struct PfSoftmax<kF16> {
     static constexpr float kThreshold = 14.f, kHeadroom = 2.f;
     static constexpr bool kSplitWeights = false;
+    static constexpr float kFirstSum = 0x1p-32f;             // 2^-30 of the first maximum's weight 2^-kHeadroom, see softmax_pv
 };
 template <> struct PfSoftmax<kBF16> {
     static constexpr float kThreshold = kRescaleThreshold, kHeadroom = kRescaleHeadroom;
     static constexpr bool kSplitWeights = true;
+    static constexpr float kFirstSum = 0x1p-90f;
+    static_assert(kHeadroom == 60.f, "2^-30 of 2^-kHeadroom");
 };
 
 #ifndef OPTGQA_PF_WAVES_PER_SIMD
@@ -519,13 +522,17 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
             // The first keys a row sees put its reference kHeadroom above their maximum, wherever
             // that is (nothing has been accumulated yet); afterwards the reference only moves up
             // (rows with no visible key in the tile, or with lower scores, keep theirs).
+            // The sums start at 2^-30 of the row's weight so far, which no fp32 sum shows: where a row's first
+            // visible keys are all the other lane's, this lane's half would stay zero as long as its weights
+            // round to zero (fp16, a steep slope, and with two key groups 36 keys or more to the next of them), and
+            // a row without a sum wants every tile of the walk.
             const bool sees = mx > -INFINITY;
             const float delta = first ? (sees ? mx + PfSoftmax<DT>::kHeadroom : 0.f)
                                       : fmaxf(mx + PfSoftmax<DT>::kHeadroom, 0.f);
             const float alpha = first ? 1.f : fast_exp2(-delta);
             started = started || sees;
             m_ref += delta;
-            lsum *= alpha;
+            lsum = first && sees ? PfSoftmax<DT>::kFirstSum : lsum * alpha;
 #pragma unroll
             for (int e = 0; e < 16; ++e) x[e] -= delta;
 #pragma unroll

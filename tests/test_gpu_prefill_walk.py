@@ -182,3 +182,25 @@ def test_one_loud_far_key_does_not_cost_a_look_every_few_tiles(U, distance):
     kc[table[:, at // bs].long(), :, at % bs] *= 10
     loud = us()
     assert loud <= 1.5 * quiet, (loud, quiet)
+
+
+def test_fp16_rows_skip_their_far_tiles(U):
+    """Chunks of 16 behind 2 048, 16 / 4 heads, slopes 2^(-8h/16), two key groups: fp16 (one output product a tile) takes
+    0.84 of bf16's time (two), and took 1.5 of it when a row half of whose sum was zero wanted every tile."""
+    import torch
+    import paper_2505_02351_amd as G
+    from test_gpu_decode_unsplit_step import microseconds
+    B, Hq, Hkv, D, bs, ctx, new = 2, 16, 4, 64, 16, 2048, 16
+    blocks = (ctx + new) // bs
+    us = {}
+    for dtype in (torch.float16, torch.bfloat16):
+        gen = torch.Generator("cuda").manual_seed(9)
+        q, k, v = (torch.randn(B * new, h, D, generator=gen, device="cuda").to(dtype) for h in (Hq, Hkv, Hkv))
+        kc, vc = (torch.randn(B * blocks, Hkv, bs, D, generator=gen, device="cuda").to(dtype) for _ in range(2))
+        table = torch.randperm(B * blocks, generator=gen, device="cuda").to(torch.int32).view(B, blocks)
+        lens = torch.full((B,), ctx + new, dtype=torch.int32, device="cuda")
+        cu = torch.arange(0, B * new + 1, new, dtype=torch.int32, device="cuda")
+        slopes = torch.exp2(-8.0 * torch.arange(1, Hq + 1, device="cuda") / Hq)
+        out = torch.empty_like(q)
+        us[dtype] = microseconds(lambda: G.prefill_step(out, q, k, v, kc, vc, table, lens, cu, slopes, D ** -0.5, new))
+    assert us[torch.float16] <= 1.2 * us[torch.bfloat16], us
