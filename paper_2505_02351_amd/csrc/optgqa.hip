@@ -432,7 +432,7 @@ int launch_prefill(PrefillParams p, int num_seqs, int max_q_len, int head_dim, i
     //   a sliding window: 128 rows (a workgroup's rows should span few keys; 8 waves 9 % slower);
     //   128-row workgroups do not even fill the CUs once: two key groups, which halve the longest
     //     walk (634 new tokens behind 1 723 over 8-bit caches: 43.4 -> 38.1 us; at twice as many
-    //     workgroups the two tie);
+    //     workgroups the two tie; a workgroup whose walk is short uses one of them, kPfTwoGroupTiles);
     //   256-row workgroups would not fill them twice - five times for whole prompts, whose walks are
     //     short against what a workgroup costs before and behind its walk, which two resident
     //     workgroups overlap (8 prompts of 1 024: 94 -> 84 us, 8 of 1 280: 148 -> 143, 8 of 2 560:

@@ -72,6 +72,12 @@ constexpr int kPfCheckTiles = 4;
 constexpr int kPfJudgeTiles = 12;
 // tiles that a look which fails further on must have passed for the walk to leave them out (starting it anew costs about 3 us)
 constexpr int kPfJumpTiles = 8;
+// tiles that a walk must have for two key groups to share it: below, the second group's waves end at once and the
+// first walks alone.  (Sharing costs a tile beyond the diagonal, a merge through LDS and two barriers.  Two groups
+// over one, GPU time of prompts and of chunks behind a cache, both types: head_dim 128 1.2-1.3 at 1 to 4 tiles, 0.99-1.14
+// at 9 and 10, 0.95-1.03 at 16, 0.9 at 24; head_dim 64 1.0-1.25, 0.82-1.08, 0.86-0.94, 0.8-0.9.  One prompt of 64 tokens,
+// 32 / 8 heads, head_dim 128: 8.4 us shared, 6.7 alone; a launch of 128-row workgroups of one group: 6.7.)
+template <int D> constexpr int kPfTwoGroupTiles = D == 128 ? 16 : 11;
 
 struct PrefillParams {
     void* out;                  // [T][Hq][D] dtype
@@ -106,7 +112,8 @@ struct PrefillParams {
 //   4 waves            128 rows, two workgroups to a CU: one's start and end under the other's walk;
 //   8 waves, KS = 2    128 rows, the walk's tiles dealt to two groups of four waves (each its own tile
 //                      buffers), whose sums are merged through LDS at the end: half as long a walk where
-//                      there are too few workgroups to fill the chip.
+//                      there are too few workgroups to fill the chip (a workgroup with a short walk uses
+//                      one group only, kPfTwoGroupTiles).
 // With a sliding window always 4 waves: a workgroup's rows should span few keys, because every tile that
 // some row's window start or causal end cuts needs the masked path (measured: 8 waves 9 % slower there).
 constexpr int kPfKeys = 32;                              // keys per tile
@@ -274,6 +281,10 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     const int kw = KS == 1 ? 0 : wg_wave / kPfWaves, wave = KS == 1 ? wg_wave : wg_wave % kPfWaves;
     const int tid = KS == 1 ? threadIdx.x : threadIdx.x % (kPfWaves * 64);
     const int n32 = lane & 31, h2 = lane >> 5;
+    // two key groups: whether they share the walk (log2 of the groups that do), and the waves that stay
+    const int share = KS == 1 ? 0 : ntiles >= kPfTwoGroupTiles<D> ? 1 : 0;        // workgroup-uniform
+    const int nwaves = kPfWaves << share;
+    if (KS == 2 && wg_wave >= nwaves) return;
 
     const uint16_t* __restrict__ qp = static_cast<const uint16_t*>(p.q);
     // paged: the KV head's offset inside a block; CONTIG: the sequence's token 0, KV head g
@@ -336,14 +347,14 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     typedef typename std::conditional<KV8, u32x2, u32x4>::type StageT;   // 8 elements of one key
     StageT stage[kKPT];
-    // KS key groups: of every KS consecutive tiles of the walk each group takes one.  The walk is made a
-    // multiple of KS long by starting it beyond the diagonal, where the causal mask hides every key.
-    const int pad = KS == 1 ? 0 : (ntiles - kt0) & (KS - 1);
+    // Key groups: of every two consecutive tiles of the walk each group takes one.  The walk is made a
+    // multiple of two long by starting it beyond the diagonal, where the causal mask hides every key.
+    const int pad = KS == 1 ? 0 : (ntiles - kt0) & share;
     const int last_tile = ntiles - 1 + pad;                       // >= kt0
     const int nt = ntiles - kt0 + pad;                            // tiles this workgroup walks
     // the tile of the walk's i-th step (i past the end: the last one again)
     auto tile_of = [&](int i) __attribute__((always_inline)) {
-        const int ic = min(i * KS + kw, nt - KS + kw);
+        const int ic = min((i << share) + kw, nt - (1 << share) + kw);
         return last_tile - ic;                                    // from the diagonal backwards
     };
     auto load_blk = [&](int i) __attribute__((always_inline)) {
@@ -413,7 +424,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     if (n_own > 0) {                                             // workgroup-uniform
 #pragma unroll
         for (int c = 0; c < kOwnBatch; ++c) {
-            const int ic = min((int)threadIdx.x + c * WAVES * 64, n_own - 1);
+            const int ic = min((int)threadIdx.x + c * nwaves * 64, n_own - 1);
             own[c] = *reinterpret_cast<const own_u32x4*>(own_src(ic));
             own_blk[c] = own_blk_of(ic);
         }
@@ -644,6 +655,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         a = vote[0][0], bb = vote[1][0], wait = vote[2][0];
 #pragma unroll
         for (int i = 1; i < WAVES; ++i) {
+            if (KS == 2 && i >= nwaves) break;
             a = fminf(a, vote[0][i]);
             bb = fminf(bb, vote[1][i]);
             wait = fmaxf(wait, vote[2][i]);
@@ -660,10 +672,10 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         const int groups = (k0 + 1) / 16;
         const float far_end = bb < 0.f ? 15.f : 0.f;             // offset of a group's key with the least bound
         bool stop = false;                                       // wave-uniform
-        for (int g0 = 0; g0 < groups && !stop; g0 += 64 * WAVES) {
-            const int mine = min((groups - g0 - wg_wave + WAVES - 1) / WAVES, 64);     // this wave's groups here
+        for (int g0 = 0; g0 < groups && !stop; g0 += 64 * nwaves) {
+            const int mine = min((groups - g0 - wg_wave + nwaves - 1) / nwaves, 64);     // this wave's groups here
             if (mine <= 0) break;
-            auto base_key = [&](int i) __attribute__((always_inline)) { return k0 - 15 - 16 * (g0 + i * WAVES + wg_wave); };
+            auto base_key = [&](int i) __attribute__((always_inline)) { return k0 - 15 - 16 * (g0 + i * nwaves + wg_wave); };
             const int blks = CONTIG ? 0 : table[max(base_key(s_lane), 0) >> bs_shift];
             auto load_keys = [&](uint4 (&x)[kLoads], int i) __attribute__((always_inline)) {
                 i = min(i, mine - 1);
@@ -758,7 +770,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     if (n_own > 0) {                                             // the rows loaded at the top have landed with the tiles
 #pragma unroll
         for (int c = 0; c < kOwnBatch; ++c) {
-            const int idx = (int)threadIdx.x + c * WAVES * 64;
+            const int idx = (int)threadIdx.x + c * nwaves * 64;
             if (idx < n_own) *own_dst(idx, own_blk[c]) = own[c];
         }
     }
@@ -780,7 +792,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     f32x16 st_other;
     auto one_tile = [&](int j, const f32x16& st_cur, f32x16& st_ahead, auto masked) __attribute__((always_inline)) {
         st_ahead = scores(j + 1);
-        softmax_pv(last_tile - (j * KS + kw), j, st_cur, masked);
+        softmax_pv(last_tile - ((j << share) + kw), j, st_cur, masked);
         store_tile(stage, j + 1 + l_ahead);
         fetch_tile(stage, j + 2 + l_ahead);
         __syncthreads();
@@ -815,25 +827,25 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     const int plain_end = max(cut_end, n_unmasked);                // tiles no mask touches
     // from the diagonal backwards: the tiles the causal mask cuts come first, those that some
     // row's window start cuts (if there is a window) last
-    // (in steps of KS tiles: a step that any mask touches takes the masked path)
-    const int steps = nt / KS;
-    const int from_plain = min((ntiles + pad - plain_end + KS - 1) / KS, steps);
-    const int to_plain = WIN ? max(from_plain, (ntiles + pad - cut_end) / KS) : steps;
+    // (in steps of a tile for each group: a step that any mask touches takes the masked path)
+    const int steps = nt >> share;
+    const int from_plain = min((ntiles + pad - plain_end + share) >> share, steps);
+    const int to_plain = WIN ? max(from_plain, ntiles - cut_end) : steps;
     run_tiles(0, from_plain, std::true_type{});
     // Without slopes no weight is ever out of the question for its position alone: no checks.
     int ask = nt;
     for (int j = from_plain; j < to_plain;) {
         if constexpr (!WIN)
-            if (p.slopes && nt - j * KS >= kPfJudgeTiles) {
-                ask = rest_judged(last_tile - j * KS);
+            if (p.slopes && nt - (j << share) >= kPfJudgeTiles) {
+                ask = rest_judged(last_tile - (j << share));
                 if (ask == 0) break;
                 if (passed >= kPfJumpTiles) {                    // workgroup-uniform
-                    j += passed / KS;
-                    ask -= passed / KS * KS;
+                    j += passed >> share;
+                    ask -= passed >> share << share;
                     restart(j);
                 }
             }
-        const int to = min(j + (ask + KS - 1) / KS, to_plain);
+        const int to = min(j + ((ask + share) >> share), to_plain);
         run_tiles(j, to, std::false_type{});
         j = to;
     }
@@ -845,7 +857,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     constexpr int kDBW = kDB / KS;                               // 32-dim blocks that this wave writes
     f32x16 (&res)[kDB] = acc;
     const int db0 = kw * kDBW;
-    if constexpr (KS == 2) {
+    if constexpr (KS == 2) if (share) {
         constexpr int kPieces = kDBW * 4;                        // 16-byte pieces per lane and wave, and a pair of floats
         static_assert(WAVES * 64 * (kPieces * 16 + 8) <= KS * PfTile<D>::kLdsBytes, "the exchange fits the tile buffers");
         float4* const xch = reinterpret_cast<float4*>(tile_lds);
@@ -895,10 +907,21 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
                 packed.y = narrow2<DT>(res[db][4 * i + 2] * inv, res[db][4 * i + 3] * inv);
                 *reinterpret_cast<u32x2*>(op + out_off + 32 * (db0 + db) + 8 * i + 4 * h2) = packed;
             }
+        if constexpr (KS == 2) if (!share) {                           // (alone: the other half as well)
+#pragma unroll
+            for (int db = kDBW; db < kDB; ++db)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    u32x2 packed;
+                    packed.x = narrow2<DT>(acc[db][4 * i] * inv, acc[db][4 * i + 1] * inv);
+                    packed.y = narrow2<DT>(acc[db][4 * i + 2] * inv, acc[db][4 * i + 3] * inv);
+                    *reinterpret_cast<u32x2*>(op + out_off + 32 * db + 8 * i + 4 * h2) = packed;
+                }
+        }
     }
     // own rows beyond the first batch (stores inside the walk would delay the tile loads behind
     // them - loads and stores complete in issue order; measured twice as costly as this)
-    for (int idx = threadIdx.x + kOwnBatch * WAVES * 64; idx < n_own; idx += WAVES * 64)
+    for (int idx = threadIdx.x + kOwnBatch * nwaves * 64; idx < n_own; idx += nwaves * 64)
         *own_dst(idx, own_blk_of(idx)) = *reinterpret_cast<const own_u32x4*>(own_src(idx));
 }
 

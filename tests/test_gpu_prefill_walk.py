@@ -204,3 +204,33 @@ def test_fp16_rows_skip_their_far_tiles(U):
         out = torch.empty_like(q)
         us[dtype] = microseconds(lambda: G.prefill_step(out, q, k, v, kc, vc, table, lens, cu, slopes, D ** -0.5, new))
     assert us[torch.float16] <= 1.2 * us[torch.bfloat16], us
+
+
+@pytest.mark.parametrize("D,new,ctx", [(128, 40, 0), (128, 100, 100), (64, 40, 0)])
+def test_a_short_walk_is_not_shared_by_two_key_groups(U, D, new, ctx):
+    """Walks of 2, 7 and 2 tiles in a launch of few workgroups, against the windowed kernel under a window that hides nothing
+    (which always runs one group of four waves): 0.99-1.01 of its time; 1.29, 1.12 and 1.20 when two key groups shared
+    such walks.  GPU time: 20 calls in a graph."""
+    import torch
+    import paper_2505_02351_amd as G
+    from test_gpu_decode_unsplit_step import microseconds
+    B, Hq, Hkv, bs = 2, 32, 8, 16
+    blocks = -(-(ctx + new) // bs)
+    q = torch.randn(B * new, Hq, D, device="cuda", dtype=torch.bfloat16)
+    kc, vc = (torch.randn(B * blocks, Hkv, bs, D, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    table = torch.arange(B * blocks, dtype=torch.int32, device="cuda").view(B, blocks)
+    lens = torch.full((B,), ctx + new, dtype=torch.int32, device="cuda")
+    cu = torch.arange(0, B * new + 1, new, dtype=torch.int32, device="cuda")
+    out = torch.empty_like(q)
+
+    def us(call):
+        call()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(20):
+                call()
+        return microseconds(graph.replay, reps=1, runs=15) / 20
+    plain = us(lambda: G.paged_prefill(out, q, kc, vc, table, lens, cu, None, D ** -0.5, new))
+    windowed = us(lambda: G.paged_prefill_window(out, q, kc, vc, table, lens, cu, None, D ** -0.5, 4096, new))
+    assert plain <= 1.08 * windowed, (plain, windowed)
