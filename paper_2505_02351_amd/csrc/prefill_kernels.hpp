@@ -146,13 +146,10 @@ template <int DT> struct PfSoftmax;
 template <> struct PfSoftmax<kF16> {
     static constexpr float kThreshold = 14.f, kHeadroom = 2.f;
     static constexpr bool kSplitWeights = false;
-    static constexpr float kFirstSum = 0x1p-32f;             // 2^-30 of the first maximum's weight 2^-kHeadroom, see softmax_pv
 };
 template <> struct PfSoftmax<kBF16> {
     static constexpr float kThreshold = kRescaleThreshold, kHeadroom = kRescaleHeadroom;
     static constexpr bool kSplitWeights = true;
-    static constexpr float kFirstSum = 0x1p-90f;
-    static_assert(kHeadroom == 60.f, "2^-30 of 2^-kHeadroom");
 };
 
 #ifndef OPTGQA_PF_WAVES_PER_SIMD
@@ -533,17 +530,13 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
             // The first keys a row sees put its reference kHeadroom above their maximum, wherever
             // that is (nothing has been accumulated yet); afterwards the reference only moves up
             // (rows with no visible key in the tile, or with lower scores, keep theirs).
-            // The sums start at 2^-30 of the row's weight so far, which no fp32 sum shows: where a row's first
-            // visible keys are all the other lane's, this lane's half would stay zero as long as its weights
-            // round to zero (fp16, a steep slope, and with two key groups 36 keys or more to the next of them), and
-            // a row without a sum wants every tile of the walk.
             const bool sees = mx > -INFINITY;
             const float delta = first ? (sees ? mx + PfSoftmax<DT>::kHeadroom : 0.f)
                                       : fmaxf(mx + PfSoftmax<DT>::kHeadroom, 0.f);
             const float alpha = first ? 1.f : fast_exp2(-delta);
             started = started || sees;
             m_ref += delta;
-            lsum = first && sees ? PfSoftmax<DT>::kFirstSum : lsum * alpha;
+            lsum *= alpha;
 #pragma unroll
             for (int e = 0; e < 16; ++e) x[e] -= delta;
 #pragma unroll
@@ -596,7 +589,10 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // 0 (for the whole workgroup) if no key of tiles 0 .. kt can carry a weight above 2^kPfSkipLog2 of
     // any row's sum so far - of the smaller of the two lanes' halves of it, which is what the test in softmax_pv
     // compares with - so that every one of these tiles would be skipped by that test anyway; else the number of
-    // tiles after which it is worth asking again.
+    // tiles after which it is worth asking again.  (A half below 2^-30 of the other counts as that much: where a row's
+    // first visible keys are all one lane's, the other's half stays zero as long as its weights round to zero -
+    // fp16, a steep slope, with two key groups 36 keys or more to the next of them - and a row without a sum wants
+    // every tile.  What this leaves out is below 2^-54 of the row's sum a key.)
     // (A skipped tile still costs its fetch, LDS stores, score MFMAs and barrier, 0.45 us; the keys read here
     // cost 0.1.  8 chunks of 512 behind 2 048, 32 / 8 heads: step 156 -> 120 us together with the rows by
     // head above; 8 prompts of 2 560: 452 -> 403.)
@@ -631,10 +627,15 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         // keys' norms, which is why qs is bounded below)
         const float qn = __builtin_amdgcn_sqrtf(q2) + 0x1p-58f;
         const float qs = 1.001f * fabsf(scale2) * qn + 0x1p-100f;
-        const float room = __builtin_amdgcn_logf(fminf(lsum, __shfl_xor(lsum, 32))) + (kPfSkipLog2 - 0.01f);
+        const float other = __shfl_xor(lsum, 32);
+        const float half = row_ok ? fmaxf(fminf(lsum, other), 0x1p-30f * fmaxf(lsum, other)) : INFINITY;
+        const float room = __builtin_amdgcn_logf(half) + (kPfSkipLog2 - 0.01f);
         float a = (room + m_ref + slope2 * (posf - (float)k0)) / qs;
         float bb = row_ok ? slope2 / qs : INFINITY;
-        float wait = a >= 1.25f * qn ? 0.f : fminf((1.25f * qn - a) / (bb * (float)kPfKeys) + 1.f, 1e6f);
+        // (predicted from the whole sum first: near the diagonal one half may have hardly begun)
+        const float ahead = row_ok ? (__builtin_amdgcn_logf(0.5f * (lsum + other)) - __builtin_amdgcn_logf(half)) / qs : 0.f;
+        const float lack = 1.25f * qn - (a + ahead > 1.25f * qn ? a : a + ahead);
+        float wait = lack <= 0.f ? 0.f : fminf(lack / (bb * (float)kPfKeys) + 1.f, 1e6f);
         wait = room == -INFINITY ? 1.f : wait >= 0.f ? wait : 1e6f;  // (no key seen yet; no slope, or a negative one)
         const bool no = !(a > 0.f && qs < 0x1p40f);
         if (__builtin_amdgcn_ballot_w64(no) != 0) a = -1.f;
