@@ -3,8 +3,8 @@
 //
 // Workgroup (4 or 8 waves, see WAVES below) = 32 (query token, head) rows per wave of one
 // (sequence, KV head [x chunk of the group]) against the whole visible context, in 32-key tiles
-// staged through LDS and shared by the waves.  The rows are the same tokens of every head of the group,
-// head by head, so all heads of the group consume the same K/V tile (Section II: a group shares one
+// staged through LDS and shared by the waves.  The rows are the same tokens of every head of the group
+// (head by head, or token by token: kPfByHeadTiles), so all heads of the group consume the same K/V tile (Section II: a group shares one
 // key-value pair).
 //
 // A wave owns 32 rows.  Both contractions are computed transposed, with v_mfma_f32_32x32x16, so that
@@ -72,6 +72,10 @@ constexpr int kPfCheckTiles = 4;
 constexpr int kPfJudgeTiles = 12;
 // tiles that a look which fails further on must have passed for the walk to leave them out (starting it anew costs about 3 us)
 constexpr int kPfJumpTiles = 8;
+// tiles that a walk must have for a wave's rows to be one head's; below, a token's heads are neighbouring rows, as they are
+// in memory (slopes, 8 prompts of 170-512, 32 / 8 heads, head_dim 128: 30.8 us by head, 29.4 by token; 24 / 8 heads over
+// 8-bit caches, 528: 28.4 and 28.3; longer walks skip more by head: 8 chunks of 512 behind 2 048: 117 and 122)
+constexpr int kPfByHeadTiles = 16;
 // tiles that a walk must have for two key groups to share it: below, the second group's waves end at once and the
 // first walks alone.  (Sharing costs a tile beyond the diagonal, a merge through LDS and two barriers.  Two groups
 // over one, GPU time of prompts and of chunks behind a cache, both types: head_dim 128 1.2-1.3 at 1 to 4 tiles, 0.99-1.14
@@ -437,11 +441,12 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     bool row_ok, started;
     int64_t out_off;
     {
-        // (a wave's rows are consecutive tokens of one head, so that it skips by that head's slope and not
-        // by the shallowest of the group's)
+        // (with slopes, where the walk is worth it, a wave's rows are consecutive tokens of one head, so that it skips by
+        // that head's slope and not by the shallowest of the group's)
         const int row = 32 * row_block + n32;
-        const int tshift = __builtin_ctz(tokens_per_wg);
-        const int ti = tq0 + (row & (tokens_per_wg - 1)), head = row >> tshift;
+        const bool rows_by_head = by_head && ntiles >= kPfByHeadTiles;
+        const int ti = tq0 + (rows_by_head ? row & (tokens_per_wg - 1) : row >> gshift);
+        const int head = rows_by_head ? row >> __builtin_ctz(tokens_per_wg) : row & ((1 << gshift) - 1);
         row_ok = ti < n_b && head < GH;
         const int tc = min(ti, n_b - 1), hc = min(head, GH - 1);
         const int64_t qrow = ((int64_t)(cu0 + tc) * Hq + h0 + hc) * D;
