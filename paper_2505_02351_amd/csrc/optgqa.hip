@@ -370,33 +370,39 @@ int launch_decode_flat(int dtype, int head_dim, const DecodeParams& p, int workg
 // shared out between two groups of four waves.
 enum class PrefillShape { k4Waves, k8Waves, k8WavesTwoGroups };
 
-template <int DT, bool KV8, bool WIN, bool CONTIG, bool STEP, int D, int WAVES, int KS>
+template <int DT, bool KV8, bool WIN, bool CONTIG, bool STEP, bool JUDGE, int D, int WAVES, int KS>
 int launch_prefill_w(const PrefillParams& p, dim3 grid, hipStream_t st)
 {
     void (*kernel)(PrefillParams);
-    if constexpr (STEP) kernel = paged_prefill_step_kernel<DT, D, WAVES, KS>;
-    else kernel = paged_prefill_mma_kernel<DT, KV8, WIN, CONTIG, D, WAVES, KS>;
+    if constexpr (STEP) kernel = paged_prefill_step_kernel<DT, JUDGE, D, WAVES, KS>;
+    else kernel = paged_prefill_mma_kernel<DT, KV8, WIN, CONTIG, JUDGE, D, WAVES, KS>;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, KS * PfTile<D>::kLdsBytes);
     if (attr != hipSuccess) return OPTGQA_ERR_LAUNCH;
     return launch(kernel, grid, dim3(WAVES * 64), KS * PfTile<D>::kLdsBytes, st, p);
 }
 
-template <int DT, bool KV8, bool WIN, bool CONTIG, bool STEP, int D>
+template <int DT, bool KV8, bool WIN, bool CONTIG, bool STEP, bool JUDGE, int D>
 int launch_prefill_d(const PrefillParams& p, dim3 grid, PrefillShape shape, hipStream_t st)
 {
     if constexpr (!WIN) {
-        if (shape == PrefillShape::k8Waves) return launch_prefill_w<DT, KV8, WIN, CONTIG, STEP, D, 8, 1>(p, grid, st);
-        if (shape == PrefillShape::k8WavesTwoGroups) return launch_prefill_w<DT, KV8, WIN, CONTIG, STEP, D, 8, 2>(p, grid, st);
+        if (shape == PrefillShape::k8Waves) return launch_prefill_w<DT, KV8, WIN, CONTIG, STEP, JUDGE, D, 8, 1>(p, grid, st);
+        if (shape == PrefillShape::k8WavesTwoGroups)
+            return launch_prefill_w<DT, KV8, WIN, CONTIG, STEP, JUDGE, D, 8, 2>(p, grid, st);
     }
-    return launch_prefill_w<DT, KV8, WIN, CONTIG, STEP, D, 4, 1>(p, grid, st);
+    return launch_prefill_w<DT, KV8, WIN, CONTIG, STEP, JUDGE, D, 4, 1>(p, grid, st);
 }
 
+// judge: slopes are given and some walk may have kPfJudgeLongest tiles (JUDGE)
 template <int DT, bool KV8, bool WIN, bool CONTIG, bool STEP>
-int launch_prefill_mma(const PrefillParams& p, int head_dim, dim3 grid, PrefillShape shape, hipStream_t st)
+int launch_prefill_mma(const PrefillParams& p, int head_dim, dim3 grid, PrefillShape shape, bool judge, hipStream_t st)
 {
-    if (head_dim == 64) return launch_prefill_d<DT, KV8, WIN, CONTIG, STEP, 64>(p, grid, shape, st);
-    return launch_prefill_d<DT, KV8, WIN, CONTIG, STEP, 128>(p, grid, shape, st);
+    if constexpr (!WIN) {
+        if (judge && head_dim == 64) return launch_prefill_d<DT, KV8, WIN, CONTIG, STEP, true, 64>(p, grid, shape, st);
+        if (judge) return launch_prefill_d<DT, KV8, WIN, CONTIG, STEP, true, 128>(p, grid, shape, st);
+    }
+    if (head_dim == 64) return launch_prefill_d<DT, KV8, WIN, CONTIG, STEP, false, 64>(p, grid, shape, st);
+    return launch_prefill_d<DT, KV8, WIN, CONTIG, STEP, false, 128>(p, grid, shape, st);
 }
 
 // The tiled prefill kernel carries the tile-invariant part of the ALiBi term inside the score
@@ -450,26 +456,28 @@ int launch_prefill(PrefillParams p, int num_seqs, int max_q_len, int head_dim, i
     const dim3 grid((unsigned)blocks);
     KernelEvents ev(st);
     const bool f16 = dtype == OPTGQA_F16;
+    const int64_t longest = contig ? max_q_len : (int64_t)p.max_blocks_per_seq * p.block_size;
+    const bool judge = p.slopes != nullptr && longest >= kPfJudgeLongest * kPfKeys;
     if (step) {
         if (kv8 || contig || p.window > 0) return OPTGQA_ERR_UNSUPPORTED;
-        return f16 ? launch_prefill_mma<kF16, false, false, false, true>(p, head_dim, grid, shape, st)
-                   : launch_prefill_mma<kBF16, false, false, false, true>(p, head_dim, grid, shape, st);
+        return f16 ? launch_prefill_mma<kF16, false, false, false, true>(p, head_dim, grid, shape, judge, st)
+                   : launch_prefill_mma<kBF16, false, false, false, true>(p, head_dim, grid, shape, judge, st);
     }
     if (contig) {
         if (kv8 || p.window > 0) return OPTGQA_ERR_UNSUPPORTED;
-        return f16 ? launch_prefill_mma<kF16, false, false, true, false>(p, head_dim, grid, shape, st)
-                   : launch_prefill_mma<kBF16, false, false, true, false>(p, head_dim, grid, shape, st);
+        return f16 ? launch_prefill_mma<kF16, false, false, true, false>(p, head_dim, grid, shape, judge, st)
+                   : launch_prefill_mma<kBF16, false, false, true, false>(p, head_dim, grid, shape, judge, st);
     }
     if (p.window > 0) {
         if (kv8) return OPTGQA_ERR_UNSUPPORTED;
-        return f16 ? launch_prefill_mma<kF16, false, true, false, false>(p, head_dim, grid, shape, st)
-                   : launch_prefill_mma<kBF16, false, true, false, false>(p, head_dim, grid, shape, st);
+        return f16 ? launch_prefill_mma<kF16, false, true, false, false>(p, head_dim, grid, shape, judge, st)
+                   : launch_prefill_mma<kBF16, false, true, false, false>(p, head_dim, grid, shape, judge, st);
     }
     if (kv8)
-        return f16 ? launch_prefill_mma<kF16, true, false, false, false>(p, head_dim, grid, shape, st)
-                   : launch_prefill_mma<kBF16, true, false, false, false>(p, head_dim, grid, shape, st);
-    return f16 ? launch_prefill_mma<kF16, false, false, false, false>(p, head_dim, grid, shape, st)
-               : launch_prefill_mma<kBF16, false, false, false, false>(p, head_dim, grid, shape, st);
+        return f16 ? launch_prefill_mma<kF16, true, false, false, false>(p, head_dim, grid, shape, judge, st)
+                   : launch_prefill_mma<kBF16, true, false, false, false>(p, head_dim, grid, shape, judge, st);
+    return f16 ? launch_prefill_mma<kF16, false, false, false, false>(p, head_dim, grid, shape, judge, st)
+               : launch_prefill_mma<kBF16, false, false, false, false>(p, head_dim, grid, shape, judge, st);
 }
 
 }  // namespace

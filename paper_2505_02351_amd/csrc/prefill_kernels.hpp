@@ -70,6 +70,8 @@ constexpr int kPfCheckTiles = 4;
 // 8-bit caches, 24 / 8 heads, at most 11 tiles: 27.3 us when looking from 4 tiles on, 24.9 from 12; 5 chunks
 // of up to 1 419 behind 630: 115 from 4, 117 from 12, 121 from 16)
 constexpr int kPfJudgeTiles = 12;
+// tiles that a launch's longest possible walk must have for the kernel that looks to be taken (JUDGE)
+constexpr int kPfJudgeLongest = 24;
 // tiles that a look which fails further on must have passed for the walk to leave them out (starting it anew costs about 3 us)
 constexpr int kPfJumpTiles = 8;
 // tiles that a walk must have for a wave's rows to be one head's; below, a token's heads are neighbouring rows, as they are
@@ -177,9 +179,16 @@ template <> struct PfSoftmax<kBF16> {
 // inputs - chosen per key, both addresses are always valid - and, as with CONTIG, the workgroups of
 // a KV head's first head chunk store their own tokens' rows into the caches.  No workgroup reads
 // a cache row that this launch writes.
-template <int DT, bool KV8, bool WIN, bool CONTIG, int D, int WAVES, int KS, bool STEP>
+//
+// JUDGE: slopes are given and walks may be long enough to be ended early (rest_judged).  A switch because the code of it,
+// even where it never runs, costs the loop around it its instruction order (no slopes, 5 prompts of 512, 16 / 4 heads,
+// head_dim 64, bf16: 15.3 us without it in the kernel, 16.4 with; 3 of 1 024: 24.3 and 27.1; 8 chunks of 512 behind 2 048,
+// 32 / 8 heads, head_dim 128: 217.8 and 220.2), and because a look costs what walks of up to kPfJudgeLongest tiles cannot
+// earn back (slopes, prompts of 512: 3 with 16 / 4 heads, head_dim 64, 13.6 and 15.6; 8 with 32 / 8, head_dim 128, 43.2 and 44.8).
+template <int DT, bool KV8, bool WIN, bool CONTIG, bool JUDGE, int D, int WAVES, int KS, bool STEP>
 __device__ __forceinline__ void prefill_body(const PrefillParams& p)
 {
+    static_assert(!(JUDGE && WIN), "a windowed walk is short: never judged");
     static_assert((WAVES == 4 && KS == 1) || (WAVES == 8 && !WIN && (KS == 1 || KS == 2)), "4 waves; without a window also 8, or 8 in two key groups");
     constexpr int kPfWaves = WAVES / KS, kPfRows = kPfWaves * 32;   // of one key group: its waves, and the workgroup's rows
     static_assert(!(CONTIG && (KV8 || WIN)), "the whole-prompt variant reads 2-byte inputs, full causal mask");
@@ -838,11 +847,11 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     const int from_plain = min((ntiles + pad - plain_end + share) >> share, steps);
     const int to_plain = WIN ? max(from_plain, ntiles - cut_end) : steps;
     run_tiles(0, from_plain, std::true_type{});
-    // Without slopes no weight is ever out of the question for its position alone: no checks.
+    // (Without slopes no weight is ever out of the question for its position alone: no JUDGE.)
     int ask = nt;
     for (int j = from_plain; j < to_plain;) {
-        if constexpr (!WIN)
-            if (p.slopes && nt - (j << share) >= kPfJudgeTiles) {
+        if constexpr (JUDGE)
+            if (nt - (j << share) >= kPfJudgeTiles) {
                 ask = rest_judged(last_tile - (j << share));
                 if (ask == 0) break;
                 if (passed >= kPfJumpTiles) {                    // workgroup-uniform
@@ -931,17 +940,17 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         *own_dst(idx, own_blk_of(idx)) = *reinterpret_cast<const own_u32x4*>(own_src(idx));
 }
 
-template <int DT, bool KV8, bool WIN, bool CONTIG, int D, int WAVES, int KS>
+template <int DT, bool KV8, bool WIN, bool CONTIG, bool JUDGE, int D, int WAVES, int KS>
 __global__ __launch_bounds__(WAVES * 64, OPTGQA_PF_WAVES_PER_SIMD) void paged_prefill_mma_kernel(const PrefillParams p)
 {
-    prefill_body<DT, KV8, WIN, CONTIG, D, WAVES, KS, false>(p);
+    prefill_body<DT, KV8, WIN, CONTIG, JUDGE, D, WAVES, KS, false>(p);
 }
 
 // cache write + prefill over the cached context in one launch (see STEP above)
-template <int DT, int D, int WAVES, int KS>
+template <int DT, bool JUDGE, int D, int WAVES, int KS>
 __global__ __launch_bounds__(WAVES * 64, OPTGQA_PF_WAVES_PER_SIMD) void paged_prefill_step_kernel(const PrefillParams p)
 {
-    prefill_body<DT, false, false, false, D, WAVES, KS, true>(p);
+    prefill_body<DT, false, false, false, JUDGE, D, WAVES, KS, true>(p);
 }
 
 }  // namespace optgqa
