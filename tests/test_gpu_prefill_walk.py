@@ -9,12 +9,30 @@ from test_gpu_parity import U, fp8_caches, oracle_filled  # noqa: F401  (U: a fi
 pytestmark = pytest.mark.gpu
 
 
-def outlier_case(dtype, D, q_len, t0, slope, like, ctx=705, batch=2, seed=1):
+def launch_shape(batch, Hq, Hkv, max_q_len, whole_prompt=False):
+    """The workgroup shape that a prefill launch takes on this card (launch_prefill's rule): "two" key groups of four
+    waves, "4" waves, or "8" waves; and its query tiles."""
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    group = Hq // Hkv
+    gh = max(h for h in range(1, 17) if group % h == 0)
+    pow2 = 1 << (gh - 1).bit_length()
+    units = -(-batch * Hkv * (group // gh) // 8) * 8
+    tiles4, tiles8 = -(-max_q_len // (128 // pow2)), -(-max_q_len // (256 // pow2))
+    if units * tiles4 <= cus:
+        return "two", tiles4
+    if units * tiles8 < 2 * cus or (whole_prompt and units * tiles8 <= 5 * cus):
+        return "4", tiles4
+    return "8", tiles8
+
+
+def outlier_case(dtype, D, q_len, t0, slope, like, ctx=705, batch=2, seed=1, heads=(8, 2), block_size=16):
     """Steep slopes, under which every key far back is out of the question - except the one at t0 of
     sequence 0, whose K row points along the last query (of head 1): its score outweighs its bias by 3."""
-    cfg = W.small_config(name="outlier", kind="prefill", dtype=dtype, batch=batch, num_heads=8, num_kv_heads=2,
-                         head_dim=D, block_size=16, num_blocks=batch * 45 + 3, ctx_lo=ctx, ctx_hi=ctx, q_len=q_len, seed=seed)
-    case = W.make_case(cfg, slopes=np.full(8, slope, np.float32))
+    cfg = W.small_config(name="outlier", kind="prefill", dtype=dtype, batch=batch, num_heads=heads[0], num_kv_heads=heads[1],
+                         head_dim=D, block_size=block_size, num_blocks=batch * -(-ctx // block_size) + 3, ctx_lo=ctx, ctx_hi=ctx, q_len=q_len, seed=seed)
+    case = W.make_case(cfg, slopes=np.full(heads[0], slope, np.float32))
+    g = 1 * heads[1] // heads[0]                # head 1's KV head
     q = W.from_bits(case.q[case.cu_q_lens[1] - 1, 1], dtype)
     want = slope * (ctx - 1 - t0) + 3.0
     row = np.sign(q) * 5.6 if like == "sign" else q * (want / (float(case.scale) * float(q @ q)))
@@ -22,17 +40,19 @@ def outlier_case(dtype, D, q_len, t0, slope, like, ctx=705, batch=2, seed=1):
     bits = W.to_bits(row.astype(np.float32), dtype)
     new = t0 - (ctx - q_len)
     if new >= 0:
-        case.k_new[new, 0] = bits
+        case.k_new[new, g] = bits
     else:
-        case.k_cache[case.block_tables[0, t0 // 16], 0, t0 % 16] = bits
+        case.k_cache[case.block_tables[0, t0 // block_size], g, t0 % block_size] = bits
     return case
 
 
 @pytest.mark.parametrize("t0", [0, 15, 16, 333, 511])
 @pytest.mark.parametrize("dtype,D", [(W.BF16, 128), (W.F16, 64)])
-@pytest.mark.parametrize("batch", [2, 70])      # two key groups; one group of four waves
-def test_a_far_key_that_matters_is_not_judged_away(U, oracle, batch, dtype, D, t0):
-    case = outlier_case(dtype, D, 24 if batch == 2 else 70, t0, 0.25, "q", batch=batch)
+@pytest.mark.parametrize("batch,heads,q_len,shape", [(2, (8, 2), 24, "two"), (70, (8, 2), 70, "4"), (64, (8, 8), 70, "8")])
+@pytest.mark.parametrize("block_size", [16, 64])
+def test_a_far_key_that_matters_is_not_judged_away(U, oracle, block_size, batch, heads, q_len, shape, dtype, D, t0):
+    assert launch_shape(batch, *heads, q_len)[0] == shape
+    case = outlier_case(dtype, D, q_len, t0, 0.25, "q", batch=batch, heads=heads, block_size=block_size)
     dev = U.DevCase(case)
     step = dev.prefill_step()
     kc, vc = oracle_filled(oracle, case)
@@ -44,28 +64,33 @@ def test_a_far_key_that_matters_is_not_judged_away(U, oracle, batch, dtype, D, t
 
 
 @pytest.mark.parametrize("t0", [0, 16, 511, 640])
+@pytest.mark.parametrize("batch,heads,shape", [(2, (8, 2), "two"), (6, (8, 2), "4"), (54, (8, 8), "8")])
 @pytest.mark.parametrize("dtype,D", [(W.BF16, 128), (W.F16, 64)])
-def test_a_far_key_of_a_whole_prompt(U, oracle, dtype, D, t0):
+def test_a_far_key_of_a_whole_prompt(U, oracle, dtype, D, batch, heads, shape, t0):
     import torch
     import oracle as O
     import paper_2505_02351_amd as G
-    case = outlier_case(dtype, D, 705, t0, 0.25, "q")
+    assert launch_shape(batch, *heads, 705, True)[0] == shape
+    case = outlier_case(dtype, D, 705, t0, 0.25, "q", batch=batch, heads=heads)
     dev = U.DevCase(case)
     G.prompt_prefill(dev.out, dev.q, dev.k_new, dev.v_new, dev.k_cache, dev.v_cache, dev.block_tables, dev.cu_q_lens,
                      dev.slopes, float(case.scale), case.max_q_len)
     torch.cuda.synchronize()
     dev.check_canaries()
-    ref = O.prompt_attention(case.q, case.k_new, case.v_new, case.cu_q_lens, case.slopes, case.scale, dtype)
-    U.check_scaled(U.to_host(dev.out), ref, dtype, f"whole prompt, outlier at {t0}")
+    rows = slice(None, case.cu_q_lens[2])       # sequences 0 and 1
+    ref = O.prompt_attention(case.q[rows], case.k_new[rows], case.v_new[rows], case.cu_q_lens[:3], case.slopes, case.scale, dtype)
+    U.check_scaled(U.to_host(dev.out)[rows], ref, dtype, f"whole prompt, outlier at {t0}")
 
 
 @pytest.mark.parametrize("t0", [0, 16, 511])
+@pytest.mark.parametrize("batch,heads,q_len,shape", [(2, (8, 2), 24, "two"), (70, (8, 2), 70, "4"), (64, (8, 8), 24, "8")])
 @pytest.mark.parametrize("D", [128, 64])
-def test_a_far_key_of_an_8_bit_cache(U, oracle, D, t0):
+def test_a_far_key_of_an_8_bit_cache(U, oracle, D, batch, heads, q_len, shape, t0):
     import torch
     import oracle as O
     import paper_2505_02351_amd as G
-    case = outlier_case(W.BF16, D, 24, t0, 1 / 16 if D == 128 else 1 / 32, "sign")
+    assert launch_shape(batch, *heads, q_len)[0] == shape
+    case = outlier_case(W.BF16, D, q_len, t0, 1 / 16 if D == 128 else 1 / 32, "sign", batch=batch, heads=heads)
     kc8, vc8, dk, dv = fp8_caches(U, case, 0.0125, 0.02)
     qd = U.to_dev(case.q, W.BF16)
     out = torch.full_like(qd, float("nan"))
@@ -73,9 +98,46 @@ def test_a_far_key_of_an_8_bit_cache(U, oracle, D, t0):
                         torch.from_numpy(case.context_lens).cuda(), torch.from_numpy(case.cu_q_lens).cuda(),
                         torch.from_numpy(case.slopes).cuda(), float(case.scale), 0.0125, 0.02, case.max_q_len)
     torch.cuda.synchronize()
-    ref = O.paged_prefill_e4m3(case.q, kc8, vc8, case.block_tables, case.context_lens, case.cu_q_lens,
+    rows = slice(None, case.cu_q_lens[2])       # sequences 0 and 1
+    ref = O.paged_prefill_e4m3(case.q[rows], kc8, vc8, case.block_tables[:2], case.context_lens[:2], case.cu_q_lens[:3],
                                case.slopes, case.scale, 0.0125, 0.02, W.BF16)
-    U.check_scaled(U.to_host(out), ref, W.BF16, f"E4M3 caches, outlier at {t0}")
+    U.check_scaled(U.to_host(out)[rows], ref, W.BF16, f"E4M3 caches, outlier at {t0}")
+
+
+@pytest.mark.parametrize("t0", [None, 5, 1000, 2000])
+@pytest.mark.parametrize("block_size", [16, 32])
+@pytest.mark.parametrize("batch,heads,shape", [(2, (8, 2), "two"), (64, (8, 8), "8")])
+def test_a_far_key_under_a_negative_slope(U, oracle, batch, heads, shape, block_size, t0):
+    """Biases that grow with the distance, by 20 over the context; near keys whose scores lie 60 above the others' end the
+    walk all the same - unless one far key's score makes up for what its bias leaves."""
+    ctx, q_len, D, slope = 2616, 24, 64, -2.0 ** -7
+    assert launch_shape(batch, *heads, q_len)[0] == shape
+    cfg = W.small_config(name="negative", kind="prefill", dtype=W.BF16, batch=batch, num_heads=heads[0], num_kv_heads=heads[1],
+                         head_dim=D, block_size=block_size, num_blocks=batch * -(-ctx // block_size), ctx_lo=ctx, ctx_hi=ctx,
+                         q_len=q_len, seed=6)
+    case = W.make_case(cfg, slopes=np.full(heads[0], slope, np.float32))
+    pos0, u = ctx - q_len, np.full(D, D ** -0.5, np.float32)
+
+    def put(b, t, score):
+        row = W.to_bits(u * np.float32(score / case.scale), W.BF16)
+        if t >= pos0:
+            case.k_new[b * q_len + t - pos0] = row
+        else:
+            case.k_cache[case.block_tables[b, t // block_size], :, t % block_size] = row
+    case.q[:] = W.to_bits(u, W.BF16)
+    case.k_cache[:] = case.k_new[:] = 0
+    for b in range(batch):
+        for t in (pos0, pos0 - 4, pos0 - 8):
+            put(b, t, 60.0)
+    if t0 is not None:
+        put(0, t0, 60.0 + 2.0 + slope * (ctx - t0))
+    dev = U.DevCase(case)
+    step = dev.prefill_step()
+    kc, vc = oracle_filled(oracle, case)
+    rows = slice(None, case.cu_q_lens[2])
+    ref = oracle.paged_prefill(case.q[rows], kc, vc, case.block_tables[:2], case.context_lens[:2], case.cu_q_lens[:3],
+                               case.slopes, case.scale, W.BF16)
+    U.check_scaled(step[rows], ref, W.BF16, f"negative slope, outlier at {t0}", max_exempt=1.0)
 
 
 # (two key groups; 8 waves)
@@ -126,25 +188,28 @@ def test_a_key_whose_norm_overflows_is_not_judged_away(U, oracle, B, Hq, Hkv, D)
     U.check_scaled(step[rows], ref, W.BF16, "huge")
 
 
-# (sequences, heads, KV heads, head_dim): 1 and odd numbers of them, a lane's worth, one more (the plain order);
-# few enough workgroups for two key groups, and enough for one group of four and of eight waves
-@pytest.mark.parametrize("B,Hq,Hkv,D", [(1, 8, 2, 128), (3, 6, 2, 64), (7, 40, 8, 128), (64, 4, 1, 64), (65, 4, 1, 128),
-                                        (17, 16, 16, 128), (60, 16, 16, 64)])
-def test_ragged_launches_in_order_of_length(U, oracle, B, Hq, Hkv, D):
-    """No slopes; chunks of up to 90 new tokens behind 0 to 200 cached ones, one sequence without any."""
+# (sequences, heads, KV heads, head_dim): 1 and odd numbers of them, a lane's worth, one more (the plain order), in
+# every shape - the order by length is that of one group of four or of eight waves
+@pytest.mark.parametrize("B,Hq,Hkv,D,shape", [
+    (1, 8, 2, 128, "two"), (3, 6, 2, 64, "two"), (7, 40, 8, 128, "4"), (17, 16, 16, 128, "4"), (60, 16, 16, 64, "8"),
+    (64, 8, 2, 128, "4"), (65, 8, 2, 64, "4"), (64, 16, 4, 64, "8"), (65, 16, 4, 128, "8")])
+def test_ragged_launches_in_order_of_length(U, oracle, B, Hq, Hkv, D, shape):
+    """No slopes; chunks of up to 90 new tokens (one of up to 180) behind 0 to 200 cached ones, one sequence without any."""
     import torch
     import paper_2505_02351_amd as G
+    lens = np.random.default_rng(77 + B).integers(1, 201, B).astype(np.int32)
+    if B > 2:
+        lens[2] = 200
     cfg = W.small_config(name="ragged", kind="prefill", dtype=W.BF16, batch=B, num_heads=Hq, num_kv_heads=Hkv, head_dim=D,
                          block_size=16, num_blocks=B * 13 + 5, ctx_lo=1, ctx_hi=200, q_len=90, seed=77 + B)
-    case = W.make_case(cfg)
+    case = W.make_case(cfg, context_lens=lens)
     kc, vc = oracle_filled(oracle, case)
     cu = case.cu_q_lens.copy()
     if B > 2:
         cu[2] = cu[1]                           # sequence 1 without new tokens, its rows sequence 2's: more of them
-        case.context_lens[2] = min(case.context_lens[2], case.block_tables.shape[1] * 16)
-    q_lens = np.diff(cu)
-    if B > 2 and q_lens[2] > case.context_lens[2]:
-        cu = case.cu_q_lens.copy()              # (they do not fit behind its context: leave the batch as it was)
+        assert np.diff(cu)[1] == 0 and 90 < np.diff(cu)[2] <= 180 <= lens[2]
+    got, tiles = launch_shape(B, Hq, Hkv, int(np.diff(cu).max()))
+    assert got == shape and (tiles > 1 or B == 1 or Hq == Hkv)
     ref = oracle.paged_prefill(case.q, kc, vc, case.block_tables, case.context_lens, cu, None, case.scale, W.BF16)
     dev = U.DevCase(case)
     dev.write_cache()
