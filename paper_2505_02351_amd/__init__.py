@@ -149,9 +149,15 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()              # (the argument types are declared: an int will do)
 
 
+# (private names: where a torch build has other ones, the public call serves, at about 1 us)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) if hasattr(torch._C, "_cuda_getDevice") else None
+
+
 def _stream(stream) -> int:
     if stream is None:                                       # the current stream of the current device
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if _raw_stream is None:
+            return torch.cuda.current_stream().cuda_stream
+        return _raw_stream(torch._C._cuda_getDevice())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 

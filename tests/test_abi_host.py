@@ -358,3 +358,15 @@ def test_per_head_scale_entry_points_reject_missing_arrays(G):
                                               16, 8, 4, 0, None) == -1
     assert lib.optgqa_paged_prefill_fp8_heads(one, one, one, one, one, one, one, None, 0.1, one, one, 2, 8, 2, 96,
                                               16, 8, 4, 0, None) == -3
+
+
+def test_the_current_stream_without_torchs_private_names(G, monkeypatch):
+    """The handle comes from torch's raw call where there is one, else from the public stream object."""
+    import torch
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("S", (), {"cuda_stream": 1234})())
+    monkeypatch.setattr(G, "_raw_stream", None)
+    assert G._stream(None) == 1234
+    monkeypatch.setattr(G, "_raw_stream", lambda device: 100 + device)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+    assert G._stream(None) == 103
+    assert G._stream(7) == 7
