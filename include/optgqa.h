@@ -108,11 +108,13 @@ int optgqa_reshape_and_cache(const void *k, const void *v, void *k_cache, void *
  *   alibi_slopes    [num_heads] fp32, or NULL for no bias
  *   max_context_len an upper bound on context_lens (used for sizing only)
  *   partition_size  0: the library decides whether and how to split the context;
- *                   >0: split the context into partitions of this many tokens (multiple of
- *                       block_size and of 16) whose results are carried forward and combined: the
- *                       waves of the launch get equal shares of no less than a partition; the
- *                       partitions of a sequence inside one share are merged as they are streamed
- *                       (a share boundary may cut a partition in two), the shares' results afterwards;
+ *                   >0: partitions of this many tokens (multiple of block_size and of 16): an upper
+ *                       bound on how finely the context is split, not a place to cut it.  The waves of
+ *                       the launch get equal shares of no less than a partition, wherever a share
+ *                       begins; what a wave streams of a sequence is carried forward in registers, the
+ *                       shares' results are combined afterwards.  Where equal shares are longer
+ *                       than a partition anyway the size has no effect.  (The workspace asked for
+ *                       is that of two results per partition, as ever, more than is used);
  *                   OPTGQA_SPLIT_BALANCED: split by equal work - every wave of the launch gets
  *                       the same number of 16-token tiles, whatever the mix of context
  *                       lengths, and the pieces are combined afterwards; this is also what

@@ -198,13 +198,14 @@ __device__ __forceinline__ FlatSeg flat_seg(const DecodeParams& p, int v)
 // v_scale into the combine kernel's normalisation.  A token row is then 128 bytes; a lane's
 // 16-byte K piece holds 16 consecutive dims and feeds two score MFMAs after widening to DT
 // (exact: every E4M3 value is an fp16 and a bf16 number), a lane's 8-byte V piece widens to 8 DT
-// values on its way into the LDS copy.  Not combined with FUSED.
+// values on its way into the LDS copy.  With FUSED the new token has no tile here: the combine
+// kernel quantises and stores its row and adds its term.
 //
 // SHARED: shared prefixes are read once per bundle of sequences (above).  2-byte caches, no window.
 //
 // Fixed partitions (Section III-A: the context is cut into partitions of a given size whose results are
-// merged): a unit is at least one partition long (min_unit_tiles), and the partitions of a segment that one
-// unit streams are merged as they are streamed, in registers: a piece is the unit's whole run in a segment.
+// merged): a unit is at least one partition long (min_unit_tiles) and cuts nothing at their multiples: a piece is the
+// unit's whole run in a segment, carried forward in registers.
 // (Writing one partial result per partition and merging them in the combine kernel: 4 sequences of 32 768
 // tokens, 64 / 8 heads, partitions of 512: 96.4 us for cache write, streaming and combine; one per run: 90.7.)
 //

@@ -121,7 +121,7 @@ struct PrefillParams {
 //                      there are too few workgroups to fill the chip (a workgroup with a short walk uses
 //                      one group only, kPfTwoGroupTiles).
 // With a sliding window always 4 waves: a workgroup's rows should span few keys, because every tile that
-// some row's window start or causal end cuts needs the masked path (measured: 8 waves 9 % slower there).
+// some row's window start or causal end cuts needs the masked path (launch_prefill has both sides' times).
 constexpr int kPfKeys = 32;                              // keys per tile
 // LDS rows, elements: K rows padded by 8 (16-byte reads of 16 keys then cover all 64 banks), V rows
 // by 16 (so do the rows a transposing load touches) - head_dim 128: 272 / 288 bytes, 64: 144 / 160
@@ -209,7 +209,11 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
 
     // ---- which rows -----------------------------------------------------------------------
     // XCD-aware order: workgroups go to XCD (flat id % 8); all query tiles of one (sequence, KV
-    // head) unit are given the same residue so that its K/V stay in one XCD's L2.
+    // head) unit are given the same residue so that its K/V stay in one XCD's L2 (but for the order by
+    // length below, where that holds with a multiple of 8 KV heads x head chunks only: with 2, 3 or 4 a unit's tiles lie
+    // on 4, 8 or 2 XCDs, and its keys are read from memory more than once, which a kernel bound by its matrix
+    // instructions does not show - 24 ragged chunks without slopes, 8 / 2 heads: 235 -> 155 us, 24 / 3: 542 -> 449,
+    // 16 / 4: 416 -> 295, 32 / 8: 681 -> 586 with the order by length).
     // Longest first: the hardware hands workgroups to free slots in id order, so the workgroups that
     // will run longest should have the lowest ids and the short ones fill the tail of the launch.
     // A later query tile sees more keys; and, walking backwards from the diagonal, a head with a
