@@ -81,8 +81,8 @@ constexpr int kPfByHeadTiles = 16;
 // tiles that a walk must have for two key groups to share it: below, the second group's waves end at once and the
 // first walks alone.  (Sharing costs a tile beyond the diagonal, a merge through LDS and two barriers.  Two groups
 // over one, GPU time of prompts and of chunks behind a cache, both types: head_dim 128 1.2-1.3 at 1 to 4 tiles, 0.99-1.14
-// at 9 and 10, 0.95-1.03 at 16, 0.9 at 24; head_dim 64 1.0-1.25, 0.82-1.08, 0.86-0.94, 0.8-0.9.  One prompt of 64 tokens,
-// 32 / 8 heads, head_dim 128: 8.4 us shared, 6.7 alone; a launch of 128-row workgroups of one group: 6.7.)
+// at 9 and 10, 0.95-1.03 at 16, 0.9 at 24; head_dim 64 1.0-1.25, 0.82-1.08, 0.86-0.94, 0.8-0.9.  One prompt of 48 tokens,
+// 32 / 8 heads, head_dim 128: 10.4 us shared, 8.1 alone; a launch of 128-row workgroups of one group: 8.1.)
 template <int D> constexpr int kPfTwoGroupTiles = D == 128 ? 16 : 11;
 
 struct PrefillParams {
