@@ -76,7 +76,8 @@ constexpr int kPfJudgeLongest = 24;
 constexpr int kPfJumpTiles = 8;
 // tiles that a walk must have for a wave's rows to be one head's; below, a token's heads are neighbouring rows, as they are
 // in memory (slopes, 8 prompts of 170-512, 32 / 8 heads, head_dim 128: 30.8 us by head, 29.4 by token; 24 / 8 heads over
-// 8-bit caches, 528: 28.4 and 28.3; longer walks skip more by head: 8 chunks of 512 behind 2 048: 117 and 122)
+// 8-bit caches, 528: 28.4 and 28.3; 5 prompts of 657-1 972 with a window of 84, 16 / 4: 39.6 and 37.5; longer walks skip more
+// by head: 8 chunks of 512 behind 2 048: 117 and 122)
 constexpr int kPfByHeadTiles = 16;
 // tiles that a walk must have for two key groups to share it: below, the second group's waves end at once and the
 // first walks alone.  (Sharing costs a tile beyond the diagonal, a merge through LDS and two barriers.  Two groups
@@ -457,7 +458,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         // (with slopes, where the walk is worth it, a wave's rows are consecutive tokens of one head, so that it skips by
         // that head's slope and not by the shallowest of the group's)
         const int row = 32 * row_block + n32;
-        const bool rows_by_head = by_head && ntiles >= kPfByHeadTiles;
+        const bool rows_by_head = by_head && ntiles - kt0 >= kPfByHeadTiles;
         const int ti = tq0 + (rows_by_head ? row & (tokens_per_wg - 1) : row >> gshift);
         const int head = rows_by_head ? row >> __builtin_ctz(tokens_per_wg) : row & ((1 << gshift) - 1);
         row_ok = ti < n_b && head < GH;
