@@ -459,7 +459,7 @@ int launch_prefill(PrefillParams p, int num_seqs, int max_q_len, int head_dim, i
     KernelEvents ev(st);
     const bool f16 = dtype == OPTGQA_F16;
     const int64_t longest = contig ? max_q_len : (int64_t)p.max_blocks_per_seq * p.block_size;
-    const bool judge = p.slopes != nullptr && longest >= kPfJudgeLongest * kPfKeys;
+    const bool judge = p.slopes != nullptr && longest >= (head_dim == 128 ? kPfJudgeLongest<128> : kPfJudgeLongest<64>) * kPfKeys;
     if (step) {
         if (kv8 || contig || p.window > 0) return OPTGQA_ERR_UNSUPPORTED;
         return f16 ? launch_prefill_mma<kF16, false, false, false, true>(p, head_dim, grid, shape, judge, st)

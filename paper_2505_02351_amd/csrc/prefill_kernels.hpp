@@ -70,8 +70,11 @@ constexpr int kPfCheckTiles = 4;
 // 8-bit caches, 24 / 8 heads, at most 11 tiles: 27.3 us when looking from 4 tiles on, 24.9 from 12; 5 chunks
 // of up to 1 419 behind 630: 115 from 4, 117 from 12, 121 from 16)
 constexpr int kPfJudgeTiles = 12;
-// tiles that a launch's longest possible walk must have for the kernel that looks to be taken (JUDGE)
-constexpr int kPfJudgeLongest = 24;
+// tiles that a launch's longest possible walk must have for the kernel that looks to be taken (JUDGE).  (GPU time with it
+// and without, slopes: head_dim 64, 16 / 4 heads, 3 prompts of 1 024 27.2 and 25.4 us, 3 of 1 280 33.5 and 29.3, 12 of 1 280
+// 64.7 and 66.1, 3 of 2 560 69.5 and 81.2; head_dim 128, up to 1 093 over 8-bit caches, 32 / 4 heads, 50.5 and 46.7, 5 of
+// 1 024, 32 / 8, 68.3 and 71.1, 5 of 1 280 91.5 and 95.9, 5 chunks of up to 1 419 behind 630 112 and 121.)
+template <int D> constexpr int kPfJudgeLongest = D == 128 ? 36 : 48;
 // tiles that a look which fails further on must have passed for the walk to leave them out (starting it anew costs about 3 us)
 constexpr int kPfJumpTiles = 8;
 // tiles that a walk must have for a wave's rows to be one head's; below, a token's heads are neighbouring rows, as they are
