@@ -26,6 +26,17 @@ def launch_shape(batch, Hq, Hkv, max_q_len, whole_prompt=False):
     return "8", tiles8
 
 
+LONGEST = 1600          # tokens that a launch's longest possible walk must have for its kernel to look at the rest of walks (48 tiles)
+
+
+def widen(case):
+    """Block tables as wide as a serving program's, for sequences of up to LONGEST tokens: what the launch goes by."""
+    bs = case.cfg.block_size
+    more = -(-LONGEST // bs) - case.block_tables.shape[1]
+    case.block_tables = np.pad(case.block_tables, ((0, 0), (0, max(more, 0))), constant_values=-1)
+    assert case.block_tables.shape[1] * bs >= 48 * 32
+
+
 def outlier_case(dtype, D, q_len, t0, slope, like, ctx=705, batch=2, seed=1, heads=(8, 2), block_size=16):
     """Steep slopes, under which every key far back is out of the question - except the one at t0 of
     sequence 0, whose K row points along the last query (of head 1): its score outweighs its bias by 3."""
@@ -43,6 +54,7 @@ def outlier_case(dtype, D, q_len, t0, slope, like, ctx=705, batch=2, seed=1, hea
         case.k_new[new, g] = bits
     else:
         case.k_cache[case.block_tables[0, t0 // block_size], g, t0 % block_size] = bits
+    widen(case)
     return case
 
 
@@ -64,17 +76,17 @@ def test_a_far_key_that_matters_is_not_judged_away(U, oracle, block_size, batch,
 
 
 @pytest.mark.parametrize("t0", [0, 16, 511, 640])
-@pytest.mark.parametrize("batch,heads,shape", [(2, (8, 2), "two"), (6, (8, 2), "4"), (54, (8, 8), "8")])
+@pytest.mark.parametrize("batch,heads,shape", [(2, (8, 8), "two"), (6, (8, 2), "4"), (54, (8, 8), "8")])
 @pytest.mark.parametrize("dtype,D", [(W.BF16, 128), (W.F16, 64)])
 def test_a_far_key_of_a_whole_prompt(U, oracle, dtype, D, batch, heads, shape, t0):
     import torch
     import oracle as O
     import paper_2505_02351_amd as G
-    assert launch_shape(batch, *heads, 705, True)[0] == shape
+    assert launch_shape(batch, *heads, LONGEST, True)[0] == shape
     case = outlier_case(dtype, D, 705, t0, 0.25, "q", batch=batch, heads=heads)
     dev = U.DevCase(case)
     G.prompt_prefill(dev.out, dev.q, dev.k_new, dev.v_new, dev.k_cache, dev.v_cache, dev.block_tables, dev.cu_q_lens,
-                     dev.slopes, float(case.scale), case.max_q_len)
+                     dev.slopes, float(case.scale), LONGEST)
     torch.cuda.synchronize()
     dev.check_canaries()
     rows = slice(None, case.cu_q_lens[2])       # sequences 0 and 1
@@ -179,6 +191,7 @@ def test_a_key_whose_norm_overflows_is_not_judged_away(U, oracle, B, Hq, Hkv, D)
     u = np.full(D, D ** -0.5, np.float32)
     case.q[:] = W.to_bits(u * np.float32(2.0 ** -70), W.BF16)
     case.k_cache[case.block_tables[0, 6], :, 4] = W.to_bits(u * np.float32(2.0 ** 100), W.BF16)
+    widen(case)
     dev = U.DevCase(case)
     step = dev.prefill_step()
     kc, vc = oracle_filled(oracle, case)
