@@ -378,9 +378,9 @@ int launch_prefill_w(const PrefillParams& p, dim3 grid, hipStream_t st)
     if constexpr (STEP) kernel = paged_prefill_step_kernel<DT, JUDGE, D, WAVES, KS>;
     else kernel = paged_prefill_mma_kernel<DT, KV8, WIN, CONTIG, JUDGE, D, WAVES, KS>;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, KS * PfTile<D>::kLdsBytes);
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, PfTile<D>::lds_bytes(WAVES, KS));
     if (attr != hipSuccess) return OPTGQA_ERR_LAUNCH;
-    return launch(kernel, grid, dim3(WAVES * 64), KS * PfTile<D>::kLdsBytes, st, p);
+    return launch(kernel, grid, dim3(WAVES * 64), PfTile<D>::lds_bytes(WAVES, KS), st, p);
 }
 
 template <int DT, bool KV8, bool WIN, bool CONTIG, bool STEP, bool JUDGE, int D>

@@ -132,6 +132,9 @@ constexpr int kPfKeys = 32;                              // keys per tile
 template <int D> struct PfTile {
     static constexpr int kKRow = D + 8, kVRow = D + 16;
     static constexpr int kLdsBytes = 2 * kPfKeys * (kKRow + kVRow) * 2;   // two buffers of one K and one V tile
+    static constexpr int kWaveBytes = 32 * kKRow * 2;                     // a wave's 32 query (output) rows, pitched as K rows
+    // a workgroup of `waves` waves in `groups` key groups
+    static constexpr int lds_bytes(int waves, int groups) { return groups * kLdsBytes + waves * kWaveBytes; }
 };
 
 template <int DT> __device__ __forceinline__ uint32_t pack2(float lo, float hi) { return narrow2<DT>(lo, hi); }
@@ -150,6 +153,14 @@ template <> __device__ __forceinline__ f32x16 mfma32<kBF16>(uint4 a, uint4 b, f3
 {
     typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// what this wave wrote to LDS is there for its other lanes (LDS instructions of a wave complete in order; the compiler
+// keeps theirs across this)
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
 template <int DT> struct PfSoftmax;
@@ -206,7 +217,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     constexpr int ES = KV8 ? 1 : 2;                     // bytes per cache element
     // two tile buffers, each a K tile [32][kPfKRow] followed by a V tile [32][kPfVRow]
     constexpr int kKTile = kPfKeys * kPfKRow, kBuf = kKTile + kPfKeys * kPfVRow;   // (of each key group)
-    extern __shared__ __attribute__((aligned(16))) uint16_t tile_lds[];          // KS * PfTile<D>::kLdsBytes
+    extern __shared__ __attribute__((aligned(16))) uint16_t tile_lds[];          // PfTile<D>::lds_bytes(WAVES, KS)
     __shared__ float vote[3][WAVES];                          // rest_judged
     __shared__ int nearest_bad;
     __shared__ uint32_t least_norm2;
@@ -456,19 +467,30 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     uint4 qb[kQ];
     float posf, lof, slope2, m_ref, lsum;
     bool row_ok, started;
-    int64_t out_off;
-    {
-        // (with slopes, where the walk is worth it, a wave's rows are consecutive tokens of one head, so that it skips by
-        // that head's slope and not by the shallowest of the group's)
-        const int row = 32 * row_block + n32;
-        const bool rows_by_head = by_head && ntiles - kt0 >= kPfByHeadTiles;
+    // (with slopes, where the walk is worth it, a wave's rows are consecutive tokens of one head, so that it skips by
+    // that head's slope and not by the shallowest of the group's)
+    const bool rows_by_head = by_head && ntiles - kt0 >= kPfByHeadTiles;
+    struct Row { int token, head; bool ok; };                    // new token (clamped), head of the chunk (clamped), whether it exists
+    auto row_at = [&](int r) __attribute__((always_inline)) {    // row r of the wave's 32
+        const int row = 32 * row_block + r;
         const int ti = tq0 + (rows_by_head ? row & (tokens_per_wg - 1) : row >> gshift);
         const int head = rows_by_head ? row >> __builtin_ctz(tokens_per_wg) : row & ((1 << gshift) - 1);
-        row_ok = ti < n_b && head < GH;
-        const int tc = min(ti, n_b - 1), hc = min(head, GH - 1);
-        const int64_t qrow = ((int64_t)(cu0 + tc) * Hq + h0 + hc) * D;
-        out_off = qrow;
-        const int pos = pos0 + tc;
+        return Row{min(ti, n_b - 1), min(head, GH - 1), ti < n_b && head < GH};
+    };
+    auto row_offset = [&](const Row& row) __attribute__((always_inline)) {   // elements, of q and of out
+        return ((int64_t)(cu0 + row.token) * Hq + h0 + row.head) * D;
+    };
+    // The query rows come, and the output rows leave, whole rows at a time through an LDS strip of the wave's own:
+    // kCPR lanes to a row.  (From and to the operand layout directly, 64 lanes touch 32 rows of 16 or 32 bytes each:
+    // a line per lane, and the memory pipeline's time for such lines is what a workgroup pays before and behind its walk.
+    // 32 / 8 heads, head_dim 128: 8 chunks of 512 behind 2 048 121.1 -> 114.0 us, 8 prompts of 2 560 398.8 -> 383.9, 8 chunks
+    // of 512 with a window of 512 74.6 -> 71.2; 5 prompts of 3-301, 16 / 4 heads, head_dim 64: 9.6 -> 9.3.)
+    uint16_t* const strip = tile_lds + KS * (2 * kBuf) + wg_wave * (kPfKeys * kPfKRow);
+    uint4 q_stage[kQ];
+    {
+        const Row mine = row_at(n32);
+        row_ok = mine.ok;
+        const int pos = pos0 + mine.token, hc = mine.head;
         posf = (float)pos;
         lof = W > 0 ? (float)(pos - W) : -1.f;                   // keys above this one are inside the window
         slope2 = p.slopes && row_ok ? p.slopes[h0 + hc] * kLog2e : 0.f;
@@ -477,12 +499,19 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         started = !row_ok;
         lsum = row_ok ? 0.f : INFINITY;
 #pragma unroll
-        for (int m = 0; m < kQ; ++m) qb[m] = *reinterpret_cast<const uint4*>(qp + qrow + 16 * m + 8 * h2);
+        for (int m = 0; m < kQ; ++m)
+            q_stage[m] = *reinterpret_cast<const uint4*>(qp + row_offset(row_at((64 / kCPR) * m + lane / kCPR)) + 8 * (lane % kCPR));
     }
     StageT stage_first[kKPT];
     fetch_from(stage_first, 0, blk_first);
     fetch_from(stage, 1, blk_second);
     {
+#pragma unroll
+        for (int m = 0; m < kQ; ++m)
+            *reinterpret_cast<uint4*>(strip + ((64 / kCPR) * m + lane / kCPR) * kPfKRow + 8 * (lane % kCPR)) = q_stage[m];
+        wave_lds_fence();
+#pragma unroll
+        for (int m = 0; m < kQ; ++m) qb[m] = *reinterpret_cast<const uint4*>(strip + n32 * kPfKRow + 16 * m + 8 * h2);
         const uint32_t keep = row_ok ? 0xffffffffu : 0u;
 #pragma unroll
         for (int m = 0; m < kQ; ++m) qb[m] = make_uint4(qb[m].x & keep, qb[m].y & keep, qb[m].z & keep, qb[m].w & keep);
@@ -919,28 +948,42 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     uint16_t* __restrict__ op = static_cast<uint16_t*>(p.out);
     float lt = lsum;
     lt += __shfl_xor(lt, 32);
-    if (row_ok) {
-        const float inv = out_scale / lt;
+    const float inv = out_scale / lt;
+    // (addresses are worked out anew here: kept from the top, or this code moved into the walk's last trip, they would take
+    // the walk's registers)
+    int e_lane = lane;
+    asm volatile("" : "+v"(e_lane));
+    // dims 32 * block .. +31 of the lane's row, into the wave's strip
+    auto put = [&](int block, const f32x16& x) __attribute__((always_inline)) {
 #pragma unroll
-        for (int db = 0; db < kDBW; ++db)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                u32x2 packed;
-                packed.x = narrow2<DT>(res[db][4 * i] * inv, res[db][4 * i + 1] * inv);
-                packed.y = narrow2<DT>(res[db][4 * i + 2] * inv, res[db][4 * i + 3] * inv);
-                *reinterpret_cast<u32x2*>(op + out_off + 32 * (db0 + db) + 8 * i + 4 * h2) = packed;
-            }
-        if constexpr (KS == 2) if (!share) {                           // (alone: the other half as well)
-#pragma unroll
-            for (int db = kDBW; db < kDB; ++db)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    u32x2 packed;
-                    packed.x = narrow2<DT>(acc[db][4 * i] * inv, acc[db][4 * i + 1] * inv);
-                    packed.y = narrow2<DT>(acc[db][4 * i + 2] * inv, acc[db][4 * i + 3] * inv);
-                    *reinterpret_cast<u32x2*>(op + out_off + 32 * db + 8 * i + 4 * h2) = packed;
-                }
+        for (int i = 0; i < 4; ++i) {
+            u32x2 packed;
+            packed.x = narrow2<DT>(x[4 * i] * inv, x[4 * i + 1] * inv);
+            packed.y = narrow2<DT>(x[4 * i + 2] * inv, x[4 * i + 3] * inv);
+            *reinterpret_cast<u32x2*>(strip + (e_lane & 31) * kPfKRow + 32 * block + 8 * i + 4 * (e_lane >> 5)) = packed;
         }
+    };
+    // the strip's rows that exist, pieces col0 .. col0 + PIECES - 1 of 16 bytes each
+    auto write_rows = [&](auto pieces, int col0) __attribute__((always_inline)) {
+        constexpr int PIECES = decltype(pieces)::value, kRows = 64 / PIECES;
+        wave_lds_fence();
+        const int piece = col0 + e_lane % PIECES;
+#pragma unroll
+        for (int m = 0; m < 32 / kRows; ++m) {
+            const int r = kRows * m + e_lane / PIECES;
+            const Row row = row_at(r);
+            const u32x4 x = *reinterpret_cast<const u32x4*>(strip + r * kPfKRow + 8 * piece);
+            if (row.ok) *reinterpret_cast<u32x4*>(op + row_offset(row) + 8 * piece) = x;
+        }
+    };
+#pragma unroll
+    for (int db = 0; db < kDBW; ++db) put(db0 + db, res[db]);
+    if (KS == 2 && share) {
+        write_rows(std::integral_constant<int, kCPR / KS>{}, db0 * 4);
+    } else {                                                     // (alone: the other half as well)
+#pragma unroll
+        for (int db = kDBW; db < kDB; ++db) put(db, acc[db]);
+        write_rows(std::integral_constant<int, kCPR>{}, 0);
     }
     // own rows beyond the first batch (stores inside the walk would delay the tile loads behind
     // them - loads and stores complete in issue order; measured twice as costly as this)
