@@ -453,6 +453,15 @@ int launch_prefill(PrefillParams p, int num_seqs, int max_q_len, int head_dim, i
     else if (blocks8 < 2 * num_cus() || (contig && blocks8 <= 5 * num_cus())) shape = PrefillShape::k4Waves;
     const int tokens_per_wg = ((shape == PrefillShape::k8Waves ? 8 : 4) * 32) >> shift;
     p.q_tiles = (max_q_len + tokens_per_wg - 1) / tokens_per_wg;
+    p.group = group;
+    p.chunks = group / gh;
+    p.units_per_seq = p.num_kv_heads * p.chunks;
+    p.tiles_div = p.slopes ? p.q_tiles : (int)(units8 / 8);
+    p.units_div = p.slopes ? num_seqs : p.units_per_seq;
+    p.by_tiles.set(std::max(p.tiles_div, 1));
+    p.by_units.set(std::max(p.units_div, 1));
+    p.by_units_per_seq.set(p.units_per_seq);
+    p.by_chunks.set(p.chunks);
     const int64_t blocks = units8 * p.q_tiles;
     if (blocks > 0x7fffffffLL) return OPTGQA_ERR_SHAPE;
     const dim3 grid((unsigned)blocks);

@@ -89,6 +89,26 @@ constexpr int kPfByHeadTiles = 16;
 // 32 / 8 heads, head_dim 128: 10.4 us shared, 8.1 alone; a launch of 128-row workgroups of one group: 8.1.)
 template <int D> constexpr int kPfTwoGroupTiles = D == 128 ? 16 : 11;
 
+// n / d for 0 <= n < 2^31 and a d that the host knows: multiply, subtract, two shifts (Granlund and Montgomery, "Division by
+// invariant integers using multiplication").  The compiler's own division by a register is 25 dependent instructions;
+// a workgroup's place in the launch takes six of them.
+struct FastDiv {
+    uint32_t mul, shift1, shift2;
+    __host__ void set(uint32_t d)
+    {
+        uint32_t l = 0;
+        while ((1ull << l) < d) ++l;
+        mul = (uint32_t)((((1ull << l) - d) << 32) / d + 1);
+        shift1 = l < 1 ? l : 1;
+        shift2 = l < 1 ? 0 : l - 1;
+    }
+    __host__ __device__ __forceinline__ int div(int n) const
+    {
+        const uint32_t t = (uint32_t)(((uint64_t)mul * (uint32_t)n) >> 32);
+        return (int)((t + (((uint32_t)n - t) >> shift1)) >> shift2);
+    }
+};
+
 struct PrefillParams {
     void* out;                  // [T][Hq][D] dtype
     const void* q;              // [T][Hq][D]
@@ -108,6 +128,12 @@ struct PrefillParams {
     int heads_pow2_shift;       // log2 of GH rounded up to a power of two (rows per workgroup >> shift: its tokens)
     int q_tiles;                // ceil(max_q_len / tokens per workgroup)
     int units;                  // num_seqs * num_kv_heads * (group / GH)
+    int group;                  // query heads per KV head
+    int chunks;                 // group / GH
+    int units_per_seq;          // num_kv_heads * chunks
+    FastDiv by_units_per_seq, by_chunks;
+    FastDiv by_tiles, by_units;                     // with slopes: q_tiles and num_seqs, else ceil(units / 8) and units_per_seq
+    int tiles_div, units_div;                       // those divisors
     int window;                 // > 0: the query at position pos sees keys pos - window < j <= pos only
     // whole-prompt variant (CONTIG): K/V come from the step's contiguous inputs, not from the cache
     const void* k_in;           // [T][Hkv][D] with token strides (elements)
@@ -240,9 +266,8 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     const int Hq = p.num_heads, Hkv = p.num_kv_heads, bs = p.block_size;
     const int bs_shift = __builtin_ctz(bs);
     const int GH = p.heads_per_wg, gshift = p.heads_pow2_shift;
-    const int G = Hq / Hkv, chunks = G / GH;
-    const int units_per_seq = Hkv * chunks;
-    const int tokens_per_wg = kPfRows >> gshift;
+    const int G = p.group, chunks = p.chunks, units_per_seq = p.units_per_seq;
+    const int tshift = __builtin_ctz(kPfRows) - gshift, tokens_per_wg = 1 << tshift;
     // Without slopes nothing is skipped and the query tile's position alone decides the length: with up to
     // 64 sequences (a lane each) workgroup number n takes the (n / units per sequence)-th of all (sequence,
     // query tile) pairs in falling order of their last position, counted in query tiles.  (Ragged chunks, 6
@@ -251,11 +276,11 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     const bool by_head = p.slopes != nullptr;
     int b, gu, qt, cu0, n_b, ctx_len;
     if (KS == 1 && !WIN && !by_head && p.num_seqs <= 64) {       // (two key groups: all workgroups start at once anyway)
-        const int rank = blockIdx.x / units_per_seq;
+        const int rank = p.by_units_per_seq.div(blockIdx.x);
         const int l = threadIdx.x & 63, lc = min(l, p.num_seqs - 1);
         const int c0 = p.cu_q_lens[lc], n = p.cu_q_lens[lc + 1] - c0, len = CONTIG ? n : p.context_lens[lc];
-        const int tiles = l < p.num_seqs && n > 0 ? (n + tokens_per_wg - 1) / tokens_per_wg : 0;
-        const int before = max(len - n, 0) / tokens_per_wg;      // query tiles' worth of cached tokens
+        const int tiles = l < p.num_seqs && n > 0 ? (n + tokens_per_wg - 1) >> tshift : 0;
+        const int before = max(len - n, 0) >> tshift;      // query tiles' worth of cached tokens
         // the pairs that end at or beyond position x (in query tiles): tile q of a sequence ends at before + q + 1
         auto count = [&](int x) __attribute__((always_inline)) {
             return wave_sum(min(tiles, max(before + tiles - x + 1, 0)));
@@ -277,18 +302,20 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         ctx_len = __builtin_amdgcn_readlane(len, b);
         gu = blockIdx.x - rank * units_per_seq;
     } else {
-        const int units8 = (p.units + 7) >> 3;
-        const int urow = by_head ? w / p.q_tiles : w % units8;
-        qt = p.q_tiles - 1 - (by_head ? w % p.q_tiles : w / units8);
+        // w: row of eight units, query tile; the unit: sequence, KV head x chunk (by head: the units of a KV head in a row)
+        const int quot = p.by_tiles.div(w), rest = w - quot * p.tiles_div;
+        const int urow = by_head ? quot : rest;
+        qt = p.q_tiles - 1 - (by_head ? rest : quot);
         const int ui = urow * 8 + ((xcd - urow) & 7);
         if (ui >= p.units) return;
-        b = by_head ? ui % p.num_seqs : ui / units_per_seq;
-        gu = by_head ? units_per_seq - 1 - ui / p.num_seqs : ui - b * units_per_seq;
+        const int uq = p.by_units.div(ui), ur = ui - uq * p.units_div;
+        b = by_head ? ur : uq;
+        gu = by_head ? units_per_seq - 1 - uq : ur;
         cu0 = p.cu_q_lens[b];
         n_b = p.cu_q_lens[b + 1] - cu0;
         ctx_len = CONTIG ? n_b : p.context_lens[b];
     }
-    const int g = gu / chunks;
+    const int g = p.by_chunks.div(gu);
     const int h0 = g * G + (gu - g * chunks) * GH;
     const int tq0 = qt * tokens_per_wg;
     if (tq0 >= n_b) return;
@@ -315,7 +342,6 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     const int nwaves = kPfWaves << share;
     if (KS == 2 && wg_wave >= nwaves) return;
 
-    const uint16_t* __restrict__ qp = static_cast<const uint16_t*>(p.q);
     // paged: the KV head's offset inside a block; CONTIG: the sequence's token 0, KV head g
     const unsigned char* __restrict__ kc = CONTIG
         ? static_cast<const unsigned char*>(p.k_in) + (cu0 * p.k_in_stride + (int64_t)g * D) * 2
@@ -333,26 +359,36 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         : static_cast<const unsigned char*>(p.v_in) + (cu0 * p.v_in_stride + (int64_t)g * D) * 2;
 
     // CONTIG / STEP: this workgroup's own tokens' K / V rows of head g go into the caches, as 16-byte
-    // pieces (kCPR per row and tensor; piece idx = ((token * 2 + is_v) * kCPR + column piece)).  The
-    // first kOwnBatch pieces of every thread are loaded here, in front of the first tile fetch, and
+    // pieces (kCPR per row and tensor; 2 * kCPR threads to a token, K row then V row).  The first kOwnBatch
+    // tokens of every thread are loaded here, in front of the first tile fetch, and
     // stored once that tile has landed - one memory latency shared with the fetch instead of a
     // load-then-store loop of its own in front of or behind the walk (each workgroup has the CU to
     // itself, so such a loop is not overlapped by anything: measured 2 us per workgroup round);
     // whatever is left (more than 64 tokens per workgroup) goes out behind the output.
     constexpr int kOwnBatch = 4;
     typedef uint32_t own_u32x4 __attribute__((ext_vector_type(4)));
-    const int n_own = ((CONTIG || STEP) && p.k_cache_w && gu == g * chunks) ? min(tokens_per_wg, n_b - tq0) * 2 * kCPR : 0;
-    auto own_src = [&](int idx) __attribute__((always_inline)) {
-        const int ti = tq0 + idx / (2 * kCPR), is_v = (idx / kCPR) & 1, piece = idx % kCPR;
-        return (is_v ? vin + (int64_t)ti * p.v_in_stride * 2 : kin + (int64_t)ti * p.k_in_stride * 2) + 16 * piece;
+    const int own_tokens = ((CONTIG || STEP) && p.k_cache_w && gu == g * chunks) ? min(tokens_per_wg, n_b - tq0) : 0;
+    const int own_step = nwaves * 64 / (2 * kCPR);
+    // token t of the workgroup's, the piece of thread `thread`
+    auto own_src = [&](int thread, int t) __attribute__((always_inline)) {
+        const bool is_v = (thread / kCPR) & 1;
+        const uint32_t row = (uint32_t)((is_v ? p.v_in_stride : p.k_in_stride) * 2);
+        return reinterpret_cast<const own_u32x4*>((is_v ? vin : kin) + 16 * (thread % kCPR) + (uint64_t)(uint32_t)(tq0 + t) * row);
     };
-    auto own_blk_of = [&](int idx) __attribute__((always_inline)) {
-        return table[(pos0 + tq0 + idx / (2 * kCPR)) >> bs_shift];   // position in the sequence (CONTIG: pos0 == 0)
+    auto own_blk_of = [&](int t) __attribute__((always_inline)) {
+        return table[(pos0 + tq0 + t) >> bs_shift];              // position in the sequence (CONTIG: pos0 == 0)
     };
-    auto own_dst = [&](int idx, int blk) __attribute__((always_inline)) {
-        const int tok = pos0 + tq0 + idx / (2 * kCPR), is_v = (idx / kCPR) & 1, piece = idx % kCPR;
-        const int64_t dst = blk * block_stride + (int64_t)g * bs * D + (int64_t)(tok & (bs - 1)) * D + 8 * piece;
-        return reinterpret_cast<own_u32x4*>((is_v ? static_cast<uint16_t*>(p.v_cache_w) : static_cast<uint16_t*>(p.k_cache_w)) + dst);
+    // this thread's piece of row 0 of block 0, KV head g
+    auto own_cache = [&](int thread) __attribute__((always_inline)) {
+        uint64_t k = reinterpret_cast<uint64_t>(p.k_cache_w), v = reinterpret_cast<uint64_t>(p.v_cache_w);
+        asm volatile("" : "+s"(k), "+s"(v));                     // (both by scalar loads: a choice of arguments is fetched like data, behind the tiles)
+        const bool is_v = (thread / kCPR) & 1;
+        return reinterpret_cast<unsigned char*>(is_v ? v : k) + (int64_t)g * bs * D * 2 + 16 * (thread % kCPR);
+    };
+    auto own_dst = [&](unsigned char* cache, int t, int blk) __attribute__((always_inline)) {
+        const int tok = pos0 + tq0 + t;
+        return reinterpret_cast<own_u32x4*>(cache + (uint64_t)(uint32_t)blk * (uint32_t)(block_stride * 2)
+                                            + (uint32_t)((tok & (bs - 1)) * (D * 2)));
     };
     // ---- tile staging: threads 0..127 fetch K, 128..255 fetch V; either way a thread moves the
     // same 16-byte column piece of kKPT consecutive keys (kCPR lanes cover one row) ----------------
@@ -394,7 +430,11 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     };
 
     // Everything a workgroup starts with is asked for before anything is waited for: the block numbers of
-    // the first tiles, the query rows, this workgroup's own new rows, then the first two tiles.
+    // the first tiles, the query rows, this workgroup's own new rows, then the first two tiles.  (What the source
+    // says here the compiler does not keep by itself: a value that it widens, scales or selects where it is loaded is
+    // waited for there, and a load may sink to its use.  The few lines of asm below hold such places: one memory round trip
+    // before the first tile instead of three, five where new rows are stored - 8 prompts of 2 560 383.9 -> 371.6 us, with the
+    // divisions by FastDiv.)
     const int blk_first = load_blk(0), blk_second = load_blk(1);
     int blk_next = load_blk(2);
 
@@ -403,7 +443,9 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // rows past the sequence's last key re-read that key, which lies in the same block)
     const unsigned char* const l_lane = l_src + 8 * l_chunk * ES;                 // this lane's column piece
     const uint32_t l_blk_bytes = (uint32_t)(block_stride * ES);                   // < 2^32: one block of all KV heads
-    auto fetch_from = [&](StageT (&stage)[kKPT], int i, int blk) __attribute__((always_inline)) {
+    // (head: one of the first two tiles, always chosen per key - behind a branch the compiler would have the fetch wait
+    // for everything asked for before it)
+    auto fetch_from = [&](StageT (&stage)[kKPT], int i, int blk, auto head) __attribute__((always_inline)) {
         const int key0 = min(tile_of(i) * kPfKeys + kKPT * l_group, kmax - 1);
         const int rmax = kmax - 1 - key0;                         // >= 0; < kKPT - 1 only at the sequence's end
         const unsigned char* base;
@@ -412,7 +454,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         // STEP: a tile that ends below the first new position is all cache (the plain path: most
         // tiles); otherwise the keys from that position on come from the inputs, chosen per key (the
         // clamped key, so that rows past the last visible key re-read it from wherever it lives)
-        if (STEP && tile_of(i) * kPfKeys + kPfKeys > pos0) {     // workgroup-uniform
+        if (STEP && (decltype(head)::value || tile_of(i) * kPfKeys + kPfKeys > pos0)) {     // workgroup-uniform
 #pragma unroll
             for (int j = 0; j < kKPT; ++j) {
                 const unsigned char* a = base + (uint32_t)(min(j, rmax) * (D * ES));
@@ -427,7 +469,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         }
     };
     auto fetch_tile = [&](StageT (&stage)[kKPT], int i) __attribute__((always_inline)) {
-        fetch_from(stage, i, blk_next);
+        fetch_from(stage, i, blk_next, std::false_type{});
         blk_next = load_blk(i + 1);
     };
     // A tile's place in LDS: the j-th tile of the walk sits in buffer j % 2.
@@ -450,12 +492,12 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
 
     own_u32x4 own[kOwnBatch];
     int own_blk[kOwnBatch];
-    if (n_own > 0) {                                             // workgroup-uniform
+    if (own_tokens > 0) {                                        // workgroup-uniform
 #pragma unroll
         for (int c = 0; c < kOwnBatch; ++c) {
-            const int ic = min((int)threadIdx.x + c * nwaves * 64, n_own - 1);
-            own[c] = *reinterpret_cast<const own_u32x4*>(own_src(ic));
-            own_blk[c] = own_blk_of(ic);
+            const int t = min((int)threadIdx.x / (2 * kCPR) + c * own_step, own_tokens - 1);
+            own[c] = *own_src(threadIdx.x, t);
+            own_blk[c] = own_blk_of(t);
         }
     }
 
@@ -470,15 +512,18 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // (with slopes, where the walk is worth it, a wave's rows are consecutive tokens of one head, so that it skips by
     // that head's slope and not by the shallowest of the group's)
     const bool rows_by_head = by_head && ntiles - kt0 >= kPfByHeadTiles;
+    const int row_tshift = rows_by_head ? 0 : gshift, row_tmask = rows_by_head ? tokens_per_wg - 1 : -1;
+    const int row_hshift = rows_by_head ? tshift : 0, row_hmask = rows_by_head ? -1 : (1 << gshift) - 1;
     struct Row { int token, head; bool ok; };                    // new token (clamped), head of the chunk (clamped), whether it exists
     auto row_at = [&](int r) __attribute__((always_inline)) {    // row r of the wave's 32
         const int row = 32 * row_block + r;
-        const int ti = tq0 + (rows_by_head ? row & (tokens_per_wg - 1) : row >> gshift);
-        const int head = rows_by_head ? row >> __builtin_ctz(tokens_per_wg) : row & ((1 << gshift) - 1);
+        const int ti = tq0 + ((row >> row_tshift) & row_tmask);
+        const int head = (row >> row_hshift) & row_hmask;
         return Row{min(ti, n_b - 1), min(head, GH - 1), ti < n_b && head < GH};
     };
-    auto row_offset = [&](const Row& row) __attribute__((always_inline)) {   // elements, of q and of out
-        return ((int64_t)(cu0 + row.token) * Hq + h0 + row.head) * D;
+    const int64_t rows_base = ((int64_t)cu0 * Hq + h0) * (D * 2);              // bytes, of q and of out: the sequence's first new token
+    auto row_offset = [&](const Row& row) __attribute__((always_inline)) {   // bytes, from there
+        return (uint64_t)(uint32_t)row.token * (uint32_t)(Hq * (D * 2)) + (uint32_t)(row.head * (D * 2));
     };
     // The query rows come, and the output rows leave, whole rows at a time through an LDS strip of the wave's own:
     // kCPR lanes to a row.  (From and to the operand layout directly, 64 lanes touch 32 rows of 16 or 32 bytes each:
@@ -486,29 +531,31 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // 32 / 8 heads, head_dim 128: 8 chunks of 512 behind 2 048 121.1 -> 114.0 us, 8 prompts of 2 560 398.8 -> 383.9, 8 chunks
     // of 512 with a window of 512 74.6 -> 71.2; 5 prompts of 3-301, 16 / 4 heads, head_dim 64: 9.6 -> 9.3.)
     uint16_t* const strip = tile_lds + KS * (2 * kBuf) + wg_wave * (kPfKeys * kPfKRow);
-    uint4 q_stage[kQ];
+    const unsigned char* const qp = static_cast<const unsigned char*>(p.q) + rows_base;
+    u32x4 q_stage[kQ];
     {
         const Row mine = row_at(n32);
         row_ok = mine.ok;
         const int pos = pos0 + mine.token, hc = mine.head;
         posf = (float)pos;
         lof = W > 0 ? (float)(pos - W) : -1.f;                   // keys above this one are inside the window
-        slope2 = p.slopes && row_ok ? p.slopes[h0 + hc] * kLog2e : 0.f;
+        slope2 = by_head ? p.slopes[h0 + hc] : 0.f;              // (scaled below: here that would wait for it)
         m_ref = 0.f;                                             // set by the first tile in which the row sees a key
         // a row that does not exist never wants a tile: its sum is already beyond anything
         started = !row_ok;
         lsum = row_ok ? 0.f : INFINITY;
 #pragma unroll
         for (int m = 0; m < kQ; ++m)
-            q_stage[m] = *reinterpret_cast<const uint4*>(qp + row_offset(row_at((64 / kCPR) * m + lane / kCPR)) + 8 * (lane % kCPR));
+            q_stage[m] = *reinterpret_cast<const u32x4*>(qp + row_offset(row_at((64 / kCPR) * m + lane / kCPR)) + 16 * (lane % kCPR));
     }
+    asm volatile("" ::: "memory");                               // (asked for here, before the tiles' block numbers are waited for)
     StageT stage_first[kKPT];
-    fetch_from(stage_first, 0, blk_first);
-    fetch_from(stage, 1, blk_second);
+    fetch_from(stage_first, 0, blk_first, std::true_type{});
+    fetch_from(stage, 1, blk_second, std::true_type{});
     {
 #pragma unroll
         for (int m = 0; m < kQ; ++m)
-            *reinterpret_cast<uint4*>(strip + ((64 / kCPR) * m + lane / kCPR) * kPfKRow + 8 * (lane % kCPR)) = q_stage[m];
+            *reinterpret_cast<u32x4*>(strip + ((64 / kCPR) * m + lane / kCPR) * kPfKRow + 8 * (lane % kCPR)) = q_stage[m];
         wave_lds_fence();
 #pragma unroll
         for (int m = 0; m < kQ; ++m) qb[m] = *reinterpret_cast<const uint4*>(strip + n32 * kPfKRow + 16 * m + 8 * h2);
@@ -516,6 +563,8 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
 #pragma unroll
         for (int m = 0; m < kQ; ++m) qb[m] = make_uint4(qb[m].x & keep, qb[m].y & keep, qb[m].z & keep, qb[m].w & keep);
     }
+    asm volatile("" : "+v"(slope2));
+    slope2 = row_ok ? slope2 * kLog2e : 0.f;
     // score scale (base 2) and output scale of this workgroup's KV head
     const float scale2 = KV8 && p.k_scales ? p.scale2 * p.k_scales[g] : p.scale2;
     const float out_scale = KV8 && p.v_scales ? p.v_scales[g] : p.out_scale;
@@ -819,11 +868,14 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         store_tile(stage, 1);
         fetch_tile(stage, 2);
     }
-    if (n_own > 0) {                                             // the rows loaded at the top have landed with the tiles
+    if (own_tokens > 0) {                                        // the rows loaded at the top have landed with the tiles
+        unsigned char* const cache = own_cache(threadIdx.x);
 #pragma unroll
         for (int c = 0; c < kOwnBatch; ++c) {
-            const int idx = (int)threadIdx.x + c * nwaves * 64;
-            if (idx < n_own) *own_dst(idx, own_blk[c]) = own[c];
+            const int t = (int)threadIdx.x / (2 * kCPR) + c * own_step;
+            int blk = own_blk[c];
+            asm volatile("" : "+v"(blk));                        // (widened here and no earlier: at its load the widening waits for it)
+            if (t < own_tokens) *own_dst(cache, t, blk) = own[c];
         }
     }
     __syncthreads();
@@ -945,7 +997,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     }
 
     // ---- normalise and write: this lane holds dims 32db + 8i + 4h2 + (0..3) of its row -----------
-    uint16_t* __restrict__ op = static_cast<uint16_t*>(p.out);
+    unsigned char* const op = static_cast<unsigned char*>(p.out) + rows_base;
     float lt = lsum;
     lt += __shfl_xor(lt, 32);
     const float inv = out_scale / lt;
@@ -973,7 +1025,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
             const int r = kRows * m + e_lane / PIECES;
             const Row row = row_at(r);
             const u32x4 x = *reinterpret_cast<const u32x4*>(strip + r * kPfKRow + 8 * piece);
-            if (row.ok) *reinterpret_cast<u32x4*>(op + row_offset(row) + 8 * piece) = x;
+            if (row.ok) *reinterpret_cast<u32x4*>(op + row_offset(row) + 16 * piece) = x;
         }
     };
 #pragma unroll
@@ -987,8 +1039,13 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     }
     // own rows beyond the first batch (stores inside the walk would delay the tile loads behind
     // them - loads and stores complete in issue order; measured twice as costly as this)
-    for (int idx = threadIdx.x + kOwnBatch * nwaves * 64; idx < n_own; idx += nwaves * 64)
-        *own_dst(idx, own_blk_of(idx)) = *reinterpret_cast<const own_u32x4*>(own_src(idx));
+    if (own_tokens > kOwnBatch * own_step) {                     // workgroup-uniform
+        int thread = threadIdx.x;
+        asm volatile("" : "+v"(thread));
+        unsigned char* const cache = own_cache(thread);
+        for (int t = thread / (2 * kCPR) + kOwnBatch * own_step; t < own_tokens; t += own_step)
+            *own_dst(cache, t, own_blk_of(t)) = *own_src(thread, t);
+    }
 }
 
 template <int DT, bool KV8, bool WIN, bool CONTIG, bool JUDGE, int D, int WAVES, int KS>
