@@ -77,6 +77,26 @@ __device__ __forceinline__ void split_bf16(float w0, float w1, uint32_t& head, u
     tail = narrow2<kBF16>(w0 - __uint_as_float(b0 & 0xffff0000u), w1 - __uint_as_float(b1 & 0xffff0000u));
 }
 
+// n / d for 0 <= n < 2^31 and a d that the host knows: multiply, subtract, two shifts (Granlund and Montgomery, "Division by
+// invariant integers using multiplication").  The compiler's own division by a register is 25 dependent instructions;
+// a workgroup's place in the launch takes six of them.
+struct FastDiv {
+    uint32_t mul, shift1, shift2;
+    __host__ void set(uint32_t d)
+    {
+        uint32_t l = 0;
+        while ((1ull << l) < d) ++l;
+        mul = (uint32_t)((((1ull << l) - d) << 32) / d + 1);
+        shift1 = l < 1 ? l : 1;
+        shift2 = l < 1 ? 0 : l - 1;
+    }
+    __host__ __device__ __forceinline__ int div(int n) const
+    {
+        const uint32_t t = (uint32_t)(((uint64_t)mul * (uint32_t)n) >> 32);
+        return (int)((t + (((uint32_t)n - t) >> shift1)) >> shift2);
+    }
+};
+
 // Data-parallel-primitive lane exchange inside a row of 16 lanes (full VALU rate, no LDS).
 template <int CTRL> __device__ __forceinline__ float dpp(float x)
 {

@@ -95,12 +95,13 @@ template <bool FUSED, bool KV8 = false> __device__ __forceinline__ int flat_tile
 
 __device__ __forceinline__ int wave_inclusive_scan(int x, int lane)
 {
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int y = __shfl_up(x, off);
-        if (lane >= off) x += y;
-    }
-    return x;
+    // (DPP: each row of 16 lanes, then row ends to the rows behind; six shuffles through LDS are six waits in a chain)
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);       // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);       // row_shr:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);       // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);       // row_shr:8
+    const int e0 = __builtin_amdgcn_readlane(x, 15), e1 = __builtin_amdgcn_readlane(x, 31), e2 = __builtin_amdgcn_readlane(x, 47);
+    return x + (lane < 16 ? 0 : lane < 32 ? e0 : lane < 48 ? e0 + e1 : e0 + e1 + e2);
 }
 
 // ---- shared prefixes (Section III-B: cached key-value blocks are shared and reused) --------------
@@ -228,6 +229,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
     static_assert(!(SHARED && KV8), "shared prefixes: 2-byte caches");
     constexpr bool NEW_TILE = FUSED && !KV8;            // the new token is a tile of its own, read from k_new / v_new
     typedef typename std::conditional<KV8, FlatTile8<D>, FlatTile<D>>::type Tile;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     constexpr int ES = KV8 ? 1 : 2;                     // bytes per cache element
     constexpr int TILE = kMmaTile;
     constexpr int kFlatVRow = FlatRow<D>::kV;
@@ -257,8 +259,8 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
     const int Hq = p.num_heads, Hkv = p.num_kv_heads, bs = p.block_size;
     const int bs_shift = __builtin_ctz(bs);
     const int GH = p.heads_per_wg;
-    const int G = Hq / Hkv;
-    const int chunks = G / GH;
+    const FastDiv by_chunks = p.by_chunks;
+    const int G = p.group, chunks = p.chunks;
     const int CS = SHARED ? 16 : GH;                    // columns (query heads) per partial-result slot
     const int u = blockIdx.x * kDecodeWaves + wave;
     const int32_t* __restrict__ ctx = p.context_lens;
@@ -337,7 +339,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
     const int incl = wave_inclusive_scan(mine, lane);
     const int P_total = __builtin_amdgcn_readlane(incl, 63);
     const int T = Y * P_total;
-    const int c = max(p.min_unit_tiles, (T + p.num_units - 1) / p.num_units);
+    const int c = max(p.min_unit_tiles, p.by_units.div(T + p.num_units - 1));
     const int f0 = u * c;
     const int f1 = min(f0 + c, T);
     if (f0 >= f1) return;                                   // no workgroup-wide barrier below
@@ -460,11 +462,12 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
     // 32i + 8hg .. +7 of its column's query row, unused columns zero - with that head's slope (base 2)
     // and the position of that query (the ALiBi term is relative to it).  A column is head j16 of the
     // segment's GH heads; in a shared prefix, head j16 % GH of the bundle's member j16 / GH.
-    auto load_q = [&](uint4 (&qd)[NQ], float& sd, int& pos, int sg_b, int sg_L, bool sg_shared, int yy) __attribute__((always_inline)) {
-        const int gg = yy / chunks;
+    // (as loaded: what turns them into operands comes once the piece's second tile has been asked for, below)
+    auto load_q = [&](u32x4 (&qd)[NQ], float& sd, int& pos, bool& ok, int sg_b, int sg_L, bool sg_shared, int yy) __attribute__((always_inline)) {
+        const int gg = by_chunks.div(yy);
         const int hh0 = gg * G + (yy - gg * chunks) * GH;
         int col_b = sg_b, col_h = min(j16, GH - 1);
-        bool ok = j16 < GH;
+        ok = j16 < GH;
         pos = sg_L - 1;
         if constexpr (SHARED) {
             if (sg_shared) {
@@ -472,29 +475,32 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
                 col_h = j16 - i * GH;
                 ok = i < p.bundle && sg_b + i < B;
                 col_b = min(sg_b + i, B - 1);
-                const int Li = ctx[col_b];
-                if (i > 0) ok = ok && p.shared_blocks[col_b] > 0 && Li > 0;
-                pos = Li - 1;
+                if (in_lanes) {                              // (a member that takes part has the bundle's shared prefix)
+                    const int Li = __shfl(my_len, col_b), Si = __shfl(my_shared, col_b);
+                    if (i > 0) ok = ok && Si > 0;
+                    pos = Li - 1;
+                } else {
+                    const int Li = ctx[col_b];
+                    if (i > 0) ok = ok && p.shared_blocks[col_b] > 0 && Li > 0;
+                    pos = Li - 1;
+                }
             }
         }
         // (2-byte caches: MFMA i contracts dims 32i + 8hg .. +7; E4M3 caches: dims
         // 64(i/2) + 16hg + 8(i%2) .. +7, the order in which a lane's 16-byte K pieces arrive)
         const uint16_t* qrow = qp + ((int64_t)col_b * Hq + hh0 + col_h) * D + (KV8 ? 16 : 8) * hg;
-        const uint32_t keep = ok ? 0xffffffffu : 0u;
 #pragma unroll
-        for (int i = 0; i < NQ; ++i) {
-            const uint4 x = *reinterpret_cast<const uint4*>(qrow + (KV8 ? 64 * (i >> 1) + 8 * (i & 1) : 32 * i));
-            qd[i] = make_uint4(x.x & keep, x.y & keep, x.z & keep, x.w & keep);
-        }
-        float sl = 0.f;
-        if (p.slopes) sl = p.slopes[hh0 + col_h];
-        sd = ok ? sl * kLog2e : 0.f;
+        for (int i = 0; i < NQ; ++i)
+            qd[i] = *reinterpret_cast<const u32x4*>(qrow + (KV8 ? 64 * (i >> 1) + 8 * (i & 1) : 32 * i));
+        sd = 0.f;
+        if (p.slopes) sd = p.slopes[hh0 + col_h];
     };
 
     Tile buf[2];
     TileSrc d0, d1;               // what buf[0] / buf[1] hold (or are receiving)
-    uint4 qa[NQ];
+    u32x4 qa[NQ];
     float slope2;                 // ALiBi slope (base 2) of column j16
+    bool col_ok;                  // column j16 is a head
     int q_pos;                    // position of column j16's query: its sequence's last token
     // (see "side effects" in the piece loop)
     auto side_effects = [&](int fx, int64_t row, int64_t new_k, int64_t new_v, int vv, int P_vv) __attribute__((always_inline)) {
@@ -547,7 +553,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
         // regular (cached) tokens the piece covers end here
         const int first = lo / TILE;                        // the segment's tiles start at this tile of the cache
         const int reg_end = min(seg.hi, ((has_new && tau_end == n ? tau_end - 1 : tau_end) + first) * TILE);
-        const int g = y / chunks;
+        const int g = by_chunks.div(y);
         // score scale (base 2); E4M3 caches with per-KV-head scales: times this KV head's k_scale
         float scale2 = p.scale2;
         if constexpr (KV8) {
@@ -558,7 +564,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
         const int64_t new_k = NEW_TILE ? seg.b * p.k_new_stride + (int64_t)g * D : 0;
         const int64_t new_v = NEW_TILE ? seg.b * p.v_new_stride + (int64_t)g * D : 0;
 
-        load_q(qa, slope2, q_pos, seg.b, seg.L, seg.shared != 0, y);
+        load_q(qa, slope2, q_pos, col_ok, seg.b, seg.L, seg.shared != 0, y);
         if (!chained) {
             d0 = tile_src(table, head_off, lo, L, n, has_new, reg_end, new_k, new_v, tau);
             load_tile(buf[0], d0);
@@ -572,11 +578,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
         // parked in LDS (results) and in a header (the rest) and written after the unit's last tile.
         int fx = 0;
         int64_t fx_row = 0;                                  // element offset of the new token's cache row
-        if (has_new && tau_end == n && y == g * chunks) {
-            const int blk = scalar_load_i32(table + (Lm1 >> bs_shift));
-            fx_row = blk * block_stride + head_off + (int64_t)(Lm1 & (bs - 1)) * D;
-            fx |= 1;
-        }
+        if (has_new && tau_end == n && y == g * chunks) fx |= 1;
         if (y == 0 && tau == 0) fx |= 2;                     // plan[v] = P_v
         if (f == 0) fx |= 4;                                 // plan[NV] = c
 
@@ -605,14 +607,14 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
         const bool n_has_new = NEW_TILE && !(SHARED && nseg.shared);
         const int n_tau_end = min(nn, f1 - (f + ntw));
         const int32_t* x_table = has_next ? p.block_tables + (int64_t)nseg.tb * p.max_blocks_per_seq : table;
-        const int64_t x_head_off = has_next ? (int64_t)(ny / chunks) * bs * D : head_off;
+        const int64_t x_head_off = has_next ? (int64_t)by_chunks.div(ny) * bs * D : head_off;
         const int x_L = has_next ? nseg.L : L, x_n = has_next ? nn : n, x_lo = has_next ? nseg.lo : lo;
         const bool x_has_new = has_next ? n_has_new : has_new;
         const int n_first = nseg.lo / TILE;
         const int x_reg_end = !has_next ? reg_end
                               : min(nseg.hi, ((n_has_new && n_tau_end == nn ? n_tau_end - 1 : n_tau_end) + n_first) * TILE);
-        const int64_t x_new_k = !has_next ? new_k : NEW_TILE ? nseg.b * p.k_new_stride + (int64_t)(ny / chunks) * D : 0;
-        const int64_t x_new_v = !has_next ? new_v : NEW_TILE ? nseg.b * p.v_new_stride + (int64_t)(ny / chunks) * D : 0;
+        const int64_t x_new_k = !has_next ? new_k : NEW_TILE ? nseg.b * p.k_new_stride + (int64_t)by_chunks.div(ny) * D : 0;
+        const int64_t x_new_v = !has_next ? new_v : NEW_TILE ? nseg.b * p.v_new_stride + (int64_t)by_chunks.div(ny) * D : 0;
         const int x_ti = has_next ? 0 : tau + j_last;
 
         // ---- both contractions on 16-bit MFMAs, transposed so that nothing is transposed in registers:
@@ -682,9 +684,9 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
             for (int i = 0; i < NQ; ++i) {
                 if constexpr (KV8) {
                     const uint4 kk = Tl.k[i >> 1];
-                    S = mfma_qk<DT>((i & 1) ? widen8_e4m3<DT>(kk.z, kk.w) : widen8_e4m3<DT>(kk.x, kk.y), qa[i], S);
+                    S = mfma_qk<DT>((i & 1) ? widen8_e4m3<DT>(kk.z, kk.w) : widen8_e4m3<DT>(kk.x, kk.y), __builtin_bit_cast(uint4, qa[i]), S);
                 } else {
-                    S = mfma_qk<DT>(Tl.k[i], qa[i], S);
+                    S = mfma_qk<DT>(Tl.k[i], __builtin_bit_cast(uint4, qa[i]), S);
                 }
             }
             const int t0 = src.tok0 + 4 * hg;
@@ -732,6 +734,26 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
             const int j = 2 * it;
             d1 = tile_src(table, head_off, lo, L, n, has_new, reg_end, new_k, new_v, tau + min(j + 1, j_last));
             load_tile(buf[1], d1);
+            if (it == 0) {
+                // The piece's query rows and slopes become operands only now: where they are loaded, the wave would wait for
+                // them, and for the tile that is on its way, before it asked for the next one.  (A memory round trip less
+                // before the first tile and at each later piece; with it the divisions by the host's numbers, the scan
+                // without shuffles and the combine kernel's loads all ahead of its first branch: 16 sequences of 255-2 047
+                // 22.0 -> 20.5 us, 64 of 1 023-8 191 109.1 -> 107.3, over 8-bit caches 67.1 -> 65.6, in pairs 83.2 -> 80.6,
+                // with a window of 1 024 32.4 -> 31.0, 4 of 32 768 in partitions of 512 90.9 -> 89.5.)
+                const uint32_t keep = col_ok ? 0xffffffffu : 0u;
+#pragma unroll
+                for (int i = 0; i < NQ; ++i) {
+                    asm volatile("" : "+v"(qa[i]));
+                    qa[i] &= keep;
+                }
+                if (fx & 1) {                                // (one more dependent load that must not hold up the second tile's)
+                    const int blk = scalar_load_i32(table + (Lm1 >> bs_shift));
+                    fx_row = blk * block_stride + head_off + (int64_t)(Lm1 & (bs - 1)) * D;
+                }
+                asm volatile("" : "+v"(slope2));
+                slope2 = col_ok ? slope2 * kLog2e : 0.f;
+            }
             compute_tile(buf[0], d0, std::false_type{});
             const bool more = j + 2 <= j_last;
             d0 = tile_src(more ? table : x_table, more ? head_off : x_head_off, more ? lo : x_lo, more ? L : x_L,
@@ -845,17 +867,24 @@ __global__ __launch_bounds__(GROUPS == 1 ? kReduceThreads : GROUPS * (D / 4)) vo
     const int v_own = SHARED ? 2 * b + 1 : b;
     // (this kernel is a few dependent memory round trips and little else: the three values that
     // everything else depends on are fetched together, before the first branch)
-    const int L = p.context_lens[b];
-    const int plan_total = p.plan[NV], plan_own = p.plan[v_own];      // readable garbage where nobody wrote them
+    int L = p.context_lens[b];
+    int plan_total = p.plan[NV], plan_own = p.plan[v_own];            // readable garbage where nobody wrote them
+    const int b0 = SHARED ? b - b % p.bundle : b;
+    int plan_first = SHARED ? p.plan[2 * b0] : 0;                     // (of the bundle's shared prefix)
+    // (all of them, and the arguments used below, before the branch: the compiler moves loads to where they are used,
+    // a memory round trip after the other)
+    asm volatile("" : "+s"(L), "+s"(plan_total), "+s"(plan_own), "+s"(plan_first)
+                    : "s"(p.ws_m), "s"(p.ws_l), "s"(p.ws_o), "s"(p.num_units), "s"(p.segs_per_seq), "s"(p.group), "s"(p.chunks),
+                      "s"(p.heads_per_wg), "s"(p.window), "s"(p.k_new), "s"(p.by_group.mul), "s"(p.by_heads_per_wg.mul),
+                      "s"(p.k_scales), "s"(p.v_scales), "s"(p.out_scale));
     if (L <= 0) {
         *reinterpret_cast<uint2*>(o) = make_uint2(0u, 0u);
         return;
     }
     const int GH = p.heads_per_wg;
     const int CS = SHARED ? 16 : GH;                         // columns per slot
-    const int G = p.num_heads / p.num_kv_heads;
-    const int chunks = G / GH;
-    const int g = h / G;
+    const int G = p.group, chunks = p.chunks;
+    const int g = p.by_group.div(h);
     // NEWTOK: the new token's rows, the query and the block of the new row are fetched first, so that
     // they arrive while the partial results are being read
     uint2 kw = make_uint2(0u, 0u), vw = kw, qw = kw;
@@ -864,19 +893,24 @@ __global__ __launch_bounds__(GROUPS == 1 ? kReduceThreads : GROUPS * (D / 4)) vo
         kw = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(p.k_new) + (int64_t)b * p.k_new_stride + (int64_t)g * D + od);
         vw = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(p.v_new) + (int64_t)b * p.v_new_stride + (int64_t)g * D + od);
         qw = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(p.q) + ((int64_t)b * p.num_heads + h) * D + od);
-        new_blk = p.block_tables[(int64_t)b * p.max_blocks_per_seq + (L - 1) / p.block_size];
+        new_blk = p.block_tables[(int64_t)b * p.max_blocks_per_seq + ((L - 1) >> __builtin_ctz(p.block_size))];
     }
     const int within = h - g * G;
-    const int chunk = within / GH;
+    const int chunk = p.by_heads_per_wg.div(within);
     const int hh = within - chunk * GH;
     const int Y = p.segs_per_seq;
     const int y = g * chunks + chunk;
     const int c = max(plan_total, 1);
+    // n / c for n >= 0 (the quotient is a unit's number, far below 2^20: one off at most before it is mended)
+    const float c_inv = __builtin_amdgcn_rcpf((float)c);
+    auto by_c = [&](int n) __attribute__((always_inline)) {
+        const int x = (int)((float)n * c_inv), r = n - x * c;
+        return r < 0 ? x - 1 : r >= c ? x + 1 : x;
+    };
     // the numbering the main kernel used
     int n_own, n_shared = 0, col_shared = 0, plan_shared = 0, v_shared = 0;
     if constexpr (SHARED) {
         const bool fused = p.k_new != nullptr;
-        const int b0 = b - b % p.bundle;
         const int S = shared_prefix_tokens<false>(p, b0, fused ? 1 : 0);
         const bool takes_part = S > 0 && (b == b0 || p.shared_blocks[b] > 0);
         const int lo = takes_part ? S : 0, hi = fused ? L - 1 : L;
@@ -885,7 +919,7 @@ __global__ __launch_bounds__(GROUPS == 1 ? kReduceThreads : GROUPS * (D / 4)) vo
             n_shared = S / kMmaTile;
             v_shared = 2 * b0;
             col_shared = (b - b0) * GH + hh;
-            plan_shared = p.plan[v_shared];
+            plan_shared = plan_first;
         }
     } else {
         n_own = NEWTOK ? flat_tiles<true, true>(L, p.window)
@@ -906,8 +940,8 @@ __global__ __launch_bounds__(GROUPS == 1 ? kReduceThreads : GROUPS * (D / 4)) vo
             // (the clamps only matter if the lengths changed under the kernels: they keep every read
             // inside the workspace; n == 0: nothing was streamed, nobody wrote the plan entry)
             const int F0 = n > 0 ? Y * P + y * n : 0;
-            const int u0 = min(max(F0 / c, 0), p.num_units - 1);
-            np = n > 0 ? min(max((F0 + n - 1) / c - u0 + 1, 1), p.num_units - u0) : 0;
+            const int u0 = min(max(by_c(F0), 0), p.num_units - 1);
+            np = n > 0 ? min(max(by_c(F0 + n - 1) - u0 + 1, 1), p.num_units - u0) : 0;
             base = ((int64_t)u0 + (int64_t)vv * Y + y) * CS + col;          // slot stride between units: CS
         }
         for (int i0 = grp * kBatch; i0 < np; i0 += GROUPS * kBatch) {
@@ -997,7 +1031,7 @@ __global__ __launch_bounds__(GROUPS == 1 ? kReduceThreads : GROUPS * (D / 4)) vo
         num.w = fmaf(num.w, f_old, f_new * v23[1]);
         if (h == g * G) {
             const int pos = L - 1;
-            const int64_t dst = (((int64_t)new_blk * p.num_kv_heads + g) * p.block_size + pos % p.block_size) * D + od;
+            const int64_t dst = (((int64_t)new_blk * p.num_kv_heads + g) * p.block_size + (pos & (p.block_size - 1))) * D + od;
             *reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(p.k_cache_w) + dst) = kcodes;
             *reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(p.v_cache_w) + dst) = vcodes;
         }

@@ -325,6 +325,12 @@ int launch_decode_flat_dt(DecodeParams p, int workgroups, hipStream_t st)
     const int group = p.num_heads / p.num_kv_heads;
     p.heads_per_wg = mfma_heads_per_workgroup(group);
     p.num_units = std::min(workgroups * kDecodeWaves, p.num_units);      // (num_units came in as the plan's most)
+    p.group = group;
+    p.chunks = group / p.heads_per_wg;
+    p.by_group.set(p.group);
+    p.by_chunks.set(p.chunks);
+    p.by_heads_per_wg.set(p.heads_per_wg);
+    p.by_units.set(p.num_units);
     int rc;
     {
         KernelEvents ev(st);

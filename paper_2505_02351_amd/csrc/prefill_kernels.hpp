@@ -89,26 +89,6 @@ constexpr int kPfByHeadTiles = 16;
 // 32 / 8 heads, head_dim 128: 10.4 us shared, 8.1 alone; a launch of 128-row workgroups of one group: 8.1.)
 template <int D> constexpr int kPfTwoGroupTiles = D == 128 ? 16 : 11;
 
-// n / d for 0 <= n < 2^31 and a d that the host knows: multiply, subtract, two shifts (Granlund and Montgomery, "Division by
-// invariant integers using multiplication").  The compiler's own division by a register is 25 dependent instructions;
-// a workgroup's place in the launch takes six of them.
-struct FastDiv {
-    uint32_t mul, shift1, shift2;
-    __host__ void set(uint32_t d)
-    {
-        uint32_t l = 0;
-        while ((1ull << l) < d) ++l;
-        mul = (uint32_t)((((1ull << l) - d) << 32) / d + 1);
-        shift1 = l < 1 ? l : 1;
-        shift2 = l < 1 ? 0 : l - 1;
-    }
-    __host__ __device__ __forceinline__ int div(int n) const
-    {
-        const uint32_t t = (uint32_t)(((uint64_t)mul * (uint32_t)n) >> 32);
-        return (int)((t + (((uint32_t)n - t) >> shift1)) >> shift2);
-    }
-};
-
 struct PrefillParams {
     void* out;                  // [T][Hq][D] dtype
     const void* q;              // [T][Hq][D]
