@@ -51,6 +51,30 @@ int launch(void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t lds_bytes, hi
                ? OPTGQA_OK : OPTGQA_ERR_LAUNCH;
 }
 
+// Launches of a cache store over slices of tokens that have fewer than 2^31 pieces each (one slice, but for inputs of 32 GiB):
+// call(first token, pieces, workgroups).
+template <typename F>
+int for_cache_slices(int num_tokens, int num_kv_heads, int head_dim, int block_size, int elems, F&& call)
+{
+    const int64_t per_token = (int64_t)num_kv_heads * (head_dim / elems);
+    if (per_token > 0x7fffffffLL) return OPTGQA_ERR_SHAPE;
+    CachePieces n;
+    n.per_token = (int)per_token;
+    n.by_token.set((uint32_t)per_token);
+    n.per_head_shift = __builtin_ctz(head_dim / elems);
+    n.num_kv_heads = num_kv_heads;
+    n.block_shift = __builtin_ctz(block_size);
+    const int most = (int)(0x7fffffffLL / per_token);       // >= 1
+    for (int first = 0; first < num_tokens; ) {
+        const int tokens = num_tokens - first < most ? num_tokens - first : most;
+        n.num_pieces = (int)(tokens * per_token);
+        const int rc = call(first, n, dim3((unsigned)(((int64_t)n.num_pieces + 255) / 256)));
+        if (rc != OPTGQA_OK) return rc;
+        first += tokens;
+    }
+    return OPTGQA_OK;
+}
+
 // Compute units of the current device, asked once (every GPU of a box is the same part); 256,
 // the MI355X count, where no device answers (the sizing calls also work on a GPU-less host).
 int num_cus()
@@ -551,9 +575,11 @@ int optgqa_reshape_and_cache(const void* k, const void* v, void* k_cache, void* 
     auto vv = static_cast<const uint16_t*>(v);
     auto kc = static_cast<uint16_t*>(k_cache);
     auto vc = static_cast<uint16_t*>(v_cache);
-    return launch(wide ? reshape_and_cache_kernel<uint4> : reshape_and_cache_kernel<uint16_t>, dim3((unsigned)blocks),
-                  dim3(256), 0, st, kk, vv, kc, vc, slot_mapping, num_tokens, num_kv_heads, head_dim, block_size,
-                  k_token_stride, v_token_stride, nullptr, nullptr, 0);
+    return for_cache_slices(num_tokens, num_kv_heads, head_dim, block_size, elems, [&](int first, const CachePieces& n, dim3 grid) {
+        return launch(wide ? reshape_and_cache_kernel<uint4> : reshape_and_cache_kernel<uint16_t>, grid, dim3(256), 0, st,
+                      kk + first * k_token_stride, vv + first * v_token_stride, kc, vc, slot_mapping + first, n,
+                      k_token_stride, v_token_stride, nullptr, nullptr, 0);
+    });
 }
 
 size_t optgqa_paged_attention_workspace_bytes(int num_seqs, int num_heads, int num_kv_heads,
@@ -611,9 +637,12 @@ int write_new_tokens(const StepInputs& n, const int64_t* slot_mapping, const int
     auto vv = static_cast<const uint16_t*>(n.v_new);
     auto kc = static_cast<uint16_t*>(n.k_cache_w);
     auto vc = static_cast<uint16_t*>(n.v_cache_w);
-    return launch(wide ? reshape_and_cache_kernel<uint4> : reshape_and_cache_kernel<uint16_t>, dim3((unsigned)blocks),
-                  dim3(256), 0, st, kk, vv, kc, vc, slot_mapping, num_tokens, num_kv_heads, head_dim, block_size,
-                  n.k_stride, n.v_stride, block_tables, context_lens, max_blocks_per_seq);
+    return for_cache_slices(num_tokens, num_kv_heads, head_dim, block_size, elems, [&](int first, const CachePieces& pieces, dim3 grid) {
+        return launch(wide ? reshape_and_cache_kernel<uint4> : reshape_and_cache_kernel<uint16_t>, grid, dim3(256), 0, st,
+                      kk + first * n.k_stride, vv + first * n.v_stride, kc, vc, slot_mapping ? slot_mapping + first : nullptr, pieces,
+                      n.k_stride, n.v_stride, slot_mapping ? block_tables : block_tables + (int64_t)first * max_blocks_per_seq,
+                      slot_mapping ? context_lens : context_lens + first, max_blocks_per_seq);
+    });
 }
 
 // Decode attention, optionally preceded by (or fused with) the step's cache write.
@@ -816,9 +845,11 @@ static int reshape_and_cache_fp8_impl(const void* k, const void* v, void* k_cach
     auto vv = static_cast<const uint16_t*>(v);
     auto kc = static_cast<unsigned char*>(k_cache);
     auto vc = static_cast<unsigned char*>(v_cache);
-    return launch(dtype == OPTGQA_F16 ? reshape_and_cache_e4m3_kernel<kF16> : reshape_and_cache_e4m3_kernel<kBF16>,
-                  dim3((unsigned)blocks), dim3(256), 0, st, kk, vv, kc, vc, slot_mapping, num_tokens, num_kv_heads,
-                  head_dim, block_size, k_token_stride, v_token_stride, k_inv, v_inv, sc.k_heads, sc.v_heads);
+    return for_cache_slices(num_tokens, num_kv_heads, head_dim, block_size, 8, [&](int first, const CachePieces& n, dim3 grid) {
+        return launch(dtype == OPTGQA_F16 ? reshape_and_cache_e4m3_kernel<kF16> : reshape_and_cache_e4m3_kernel<kBF16>, grid, dim3(256), 0,
+                      st, kk + first * k_token_stride, vv + first * v_token_stride, kc, vc, slot_mapping + first, n,
+                      k_token_stride, v_token_stride, k_inv, v_inv, sc.k_heads, sc.v_heads);
+    });
 }
 
 int optgqa_reshape_and_cache_fp8(const void* k, const void* v, void* k_cache, void* v_cache,
