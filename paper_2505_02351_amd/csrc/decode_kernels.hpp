@@ -69,6 +69,7 @@ struct DecodeParams {
 // of 300-1 500 tokens, unsplit plain attention, 16 / 4 heads, head_dim 128: 28.1 -> 38.4 us; 8 / 8, head_dim 64: 36.0
 // -> 51.5.  For the same reason, and for its registers, plain attention is an instantiation without the store (STEP).
 typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
+typedef __attribute__((address_space(1))) uint16_t* global_u16_ptr;      // device memory, whatever the compiler knows of where a pointer came from
 __device__ __forceinline__ const_i32_ptr launch_constant(const int32_t* q)
 {
     asm volatile("" : "+s"(q));
@@ -98,18 +99,31 @@ constexpr int kMaxFusedSeqs = 32;
 
 template <int D> __device__ __forceinline__ void store_new_rows(const DecodeParams& p, int g)
 {
+    // (2 * LPR divides the threads: which tensor and which piece of its rows are a thread's own.  The row is asked for together
+    // with the length, the block behind them: two memory round trips ahead of the store.  The asm: a choice between
+    // two arguments would be fetched per lane, as data, a third and a fourth.  GPU time of a step, with
+    // the divisions by the host's reciprocals: one sequence of 128, 8 / 2 heads, head_dim 64, 5.9 -> 5.7 us; 16 of 100-250,
+    // 16 / 4, 7.4 -> 7.2; 32 of 100-250, 32 / 8, head_dim 128, 10.8 -> 10.2.  Asking for the query rows and the first tile's block
+    // ahead of the store as well gave nothing more.)
     constexpr int LPR = D / 8;
-    for (int i = threadIdx.x; i < p.num_seqs * 2 * LPR; i += kDecodeWaves * 64) {
-        const int b = i / (2 * LPR), bs = p.block_size;
-        const bool is_v = i / LPR & 1;
-        const int piece = (i % LPR) * 8, pos = p.context_lens[b] - 1;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    uint64_t kn = reinterpret_cast<uint64_t>(p.k_new), vn = reinterpret_cast<uint64_t>(p.v_new);
+    uint64_t kc = reinterpret_cast<uint64_t>(p.k_cache_w), vc = reinterpret_cast<uint64_t>(p.v_cache_w);
+    int64_t ks = p.k_new_stride, vs = p.v_new_stride;
+    asm volatile("" : "+s"(kn), "+s"(vn), "+s"(kc), "+s"(vc), "+s"(ks), "+s"(vs));
+    const int bs = p.block_size, bs_shift = __builtin_ctz(bs);
+    const bool is_v = threadIdx.x / LPR & 1;
+    const int piece = (threadIdx.x % LPR) * 8;
+    const global_u16_ptr src = (global_u16_ptr)(is_v ? vn : kn) + (int64_t)g * D + piece;
+    const global_u16_ptr cache = (global_u16_ptr)(is_v ? vc : kc) + piece;
+    const int64_t stride = is_v ? vs : ks;
+    for (int b = threadIdx.x / (2 * LPR); b < p.num_seqs; b += kDecodeWaves * 64 / (2 * LPR)) {
+        const u32x4 x = *(const __attribute__((address_space(1))) u32x4*)(src + b * stride);
+        const int pos = p.context_lens[b] - 1;
         if (pos < 0) continue;
-        const uint16_t* src = is_v ? static_cast<const uint16_t*>(p.v_new) + b * p.v_new_stride
-                                   : static_cast<const uint16_t*>(p.k_new) + b * p.k_new_stride;
-        const int64_t blk = p.block_tables[(int64_t)b * p.max_blocks_per_seq + pos / bs];
-        const int64_t dst = ((blk * p.num_kv_heads + g) * bs + pos % bs) * D + piece;
-        uint16_t* cache = static_cast<uint16_t*>(is_v ? p.v_cache_w : p.k_cache_w);
-        *reinterpret_cast<uint4*>(cache + dst) = *reinterpret_cast<const uint4*>(src + (int64_t)g * D + piece);
+        const int64_t blk = p.block_tables[(int64_t)b * p.max_blocks_per_seq + (pos >> bs_shift)];
+        const int64_t dst = ((blk * p.num_kv_heads + g) * bs + (pos & (bs - 1))) * D;
+        *(__attribute__((address_space(1))) u32x4*)(cache + dst) = x;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __threadfence_block();
@@ -128,10 +142,8 @@ __global__ __launch_bounds__(kDecodeWaves * 64) void paged_decode_kernel(const D
 
     const int row = p.row_offset + blockIdx.z;
     const int Hq = p.num_heads, Hkv = p.num_kv_heads, bs = p.block_size;
-    const int G = Hq / Hkv;
-    const int chunks = G / GH;
-    const int g = blockIdx.y / chunks;
-    const int h0 = g * G + (blockIdx.y - g * chunks) * GH;
+    const int g = p.by_chunks.div(blockIdx.y);
+    const int h0 = g * p.group + (blockIdx.y - g * p.chunks) * GH;
 
     int b, L;
     if (!row_to_seq(p, row, b, L)) return;

@@ -132,10 +132,8 @@ __global__ __launch_bounds__(kDecodeWaves * 64, 2) void paged_decode_mc_kernel(c
     const int row = p.row_offset + blockIdx.z;
     const int Hq = p.num_heads, Hkv = p.num_kv_heads, bs = p.block_size;
     const int bs_shift = __builtin_ctz(bs);
-    const int G = Hq / Hkv;
-    const int chunks = G / GH;
-    const int g = blockIdx.y / chunks;
-    const int h0 = g * G + (blockIdx.y - g * chunks) * GH;
+    const int g = p.by_chunks.div(blockIdx.y);
+    const int h0 = g * p.group + (blockIdx.y - g * p.chunks) * GH;
 
     int b, L;
     if (!row_to_seq(p, row, b, L)) return;
@@ -162,7 +160,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, 2) void paged_decode_mc_kernel(c
     f32x4 acc[8][HPL];
 #pragma unroll
     for (int i = 0; i < HPL; ++i) {
-        slope2[i] = p.slopes ? p.slopes[h0 + u + 4 * i] * kLog2e : 0.f;
+        slope2[i] = p.slopes ? p.slopes[h0 + u + 4 * i] : 0.f;     // (scaled below: here that would wait for it)
         m_ref[i] = kNoMax;
         l[i] = 0.f;
 #pragma unroll
@@ -280,6 +278,11 @@ __global__ __launch_bounds__(kDecodeWaves * 64, 2) void paged_decode_mc_kernel(c
     // ---- main loop -------------------------------------------------------------------------
     const uint32_t ring_lane = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)ring + lane * 16;
     for (int j = 0; j < PT && j < ntw; ++j) issue_tile(j);
+#pragma unroll
+    for (int i = 0; i < HPL; ++i) {
+        asm volatile("" : "+v"(slope2[i]));
+        slope2[i] *= kLog2e;
+    }
     for (int j = 0; j < ntw; ++j) {
         if (j + PT < ntw) issue_tile(j + PT);
         const int newer = min(ntw - 1 - j, PT);              // tiles issued after tile j (uniform)

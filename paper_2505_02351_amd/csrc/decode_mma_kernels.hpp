@@ -95,10 +95,8 @@ __global__ __launch_bounds__(kDecodeWaves * 64, OPTGQA_MMA_WAVES_PER_SIMD) void 
     const int Hq = p.num_heads, Hkv = p.num_kv_heads, bs = p.block_size;
     const int bs_shift = __builtin_ctz(bs);
     const int GH = p.heads_per_wg;
-    const int G = Hq / Hkv;
-    const int chunks = G / GH;
-    const int g = blockIdx.y / chunks;
-    const int h0 = g * G + (blockIdx.y - g * chunks) * GH;
+    const int g = p.by_chunks.div(blockIdx.y);
+    const int h0 = g * p.group + (blockIdx.y - g * p.chunks) * GH;
 
     int b, L;
     if (!row_to_seq(p, row, b, L)) return;

@@ -308,6 +308,9 @@ int launch_decode(DecodeParams p, int num_rows, hipStream_t st)
     const int group = p.num_heads / p.num_kv_heads;
     const int gh = heads_per_workgroup(group, D);
     p.heads_per_wg = gh;
+    p.group = group;
+    p.chunks = group / gh;
+    p.by_chunks.set(p.chunks);
     for (int first = 0; first < num_rows; first += kMaxRowsPerLaunch) {
         const int rows = num_rows - first < kMaxRowsPerLaunch ? num_rows - first : kMaxRowsPerLaunch;
         p.row_offset = first;

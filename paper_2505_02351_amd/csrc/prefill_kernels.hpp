@@ -358,16 +358,17 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     auto own_blk_of = [&](int t) __attribute__((always_inline)) {
         return table[(pos0 + tq0 + t) >> bs_shift];              // position in the sequence (CONTIG: pos0 == 0)
     };
+    typedef __attribute__((address_space(1))) unsigned char* global_byte_ptr;   // (device memory, which the asm would hide)
     // this thread's piece of row 0 of block 0, KV head g
     auto own_cache = [&](int thread) __attribute__((always_inline)) {
         uint64_t k = reinterpret_cast<uint64_t>(p.k_cache_w), v = reinterpret_cast<uint64_t>(p.v_cache_w);
         asm volatile("" : "+s"(k), "+s"(v));                     // (both by scalar loads: a choice of arguments is fetched like data, behind the tiles)
         const bool is_v = (thread / kCPR) & 1;
-        return reinterpret_cast<unsigned char*>(is_v ? v : k) + (int64_t)g * bs * D * 2 + 16 * (thread % kCPR);
+        return (global_byte_ptr)(is_v ? v : k) + (int64_t)g * bs * D * 2 + 16 * (thread % kCPR);
     };
-    auto own_dst = [&](unsigned char* cache, int t, int blk) __attribute__((always_inline)) {
+    auto own_dst = [&](global_byte_ptr cache, int t, int blk) __attribute__((always_inline)) {
         const int tok = pos0 + tq0 + t;
-        return reinterpret_cast<own_u32x4*>(cache + (uint64_t)(uint32_t)blk * (uint32_t)(block_stride * 2)
+        return (__attribute__((address_space(1))) own_u32x4*)(cache + (uint64_t)(uint32_t)blk * (uint32_t)(block_stride * 2)
                                             + (uint32_t)((tok & (bs - 1)) * (D * 2)));
     };
     // ---- tile staging: threads 0..127 fetch K, 128..255 fetch V; either way a thread moves the
@@ -849,7 +850,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         fetch_tile(stage, 2);
     }
     if (own_tokens > 0) {                                        // the rows loaded at the top have landed with the tiles
-        unsigned char* const cache = own_cache(threadIdx.x);
+        const global_byte_ptr cache = own_cache(threadIdx.x);
 #pragma unroll
         for (int c = 0; c < kOwnBatch; ++c) {
             const int t = (int)threadIdx.x / (2 * kCPR) + c * own_step;
@@ -1022,7 +1023,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     if (own_tokens > kOwnBatch * own_step) {                     // workgroup-uniform
         int thread = threadIdx.x;
         asm volatile("" : "+v"(thread));
-        unsigned char* const cache = own_cache(thread);
+        const global_byte_ptr cache = own_cache(thread);
         for (int t = thread / (2 * kCPR) + kOwnBatch * own_step; t < own_tokens; t += own_step)
             *own_dst(cache, t, own_blk_of(t)) = *own_src(thread, t);
     }
