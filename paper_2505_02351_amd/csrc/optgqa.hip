@@ -450,6 +450,8 @@ float prefill_scale2(float scale)
     return s * kLog2e;
 }
 
+constexpr int kPfLongPrompt = 2048;      // tokens (launch_prefill)
+
 // Tiled matrix-core prefill (head_dim 128 or 64).
 int launch_prefill(PrefillParams p, int num_seqs, int max_q_len, int head_dim, int dtype, hipStream_t st,
                    bool kv8 = false, bool contig = false, bool step = false)
@@ -476,14 +478,18 @@ int launch_prefill(PrefillParams p, int num_seqs, int max_q_len, int head_dim, i
     //     workgroups the two tie; a workgroup whose walk is short uses one of them, kPfTwoGroupTiles);
     //   256-row workgroups would not fill them twice - five times for whole prompts, whose walks are
     //     short against what a workgroup costs before and behind its walk, which two resident
-    //     workgroups overlap (8 prompts of 1 024: 94 -> 84 us, 8 of 1 280: 148 -> 143, 8 of 2 560:
-    //     395 -> 415): 128 rows;
+    //     workgroups overlap (8 prompts of 768: 71.6 us with 256 rows, 68.9 with 128; 8 of 1 280 without slopes 159.7 and 155.3;
+    //     4 of 2 560, head_dim 64, 128.6 and 114.9; 8 of 1 024 100.8 and 102.4): 128 rows - with
+    //     slopes below 2 048 tokens only at head_dim 128, where a walk of 64 tiles outweighs that (4 prompts of 1 536 95.5 and
+    //     96.0, 5 of 1 800 131.2 and 129.6, 4 of 2 048 137.1 and 140.8, 2 of 2 560 111.9 and 114.7, 4 of 2 560 185.9 and 193.9,
+    //     32 / 4 heads 201 and 213, fp16 165.9 and 170.1; without slopes 317 and 325, but fp16, 3 of 2 200, 152.3 and 149.3);
     //   else 256 rows, half the loads and LDS stores per row (chunks of 512 behind 2 048: 124 us, 147 at
     //     128 rows).
     PrefillShape shape = PrefillShape::k8Waves;
     if (p.window > 0) shape = PrefillShape::k4Waves;
     else if (blocks4 <= num_cus()) shape = PrefillShape::k8WavesTwoGroups;
-    else if (blocks8 < 2 * num_cus() || (contig && blocks8 <= 5 * num_cus())) shape = PrefillShape::k4Waves;
+    else if (blocks8 < 2 * num_cus() || (contig && blocks8 <= 5 * num_cus() && !(p.slopes && head_dim == 128 && max_q_len >= kPfLongPrompt)))
+        shape = PrefillShape::k4Waves;
     const int tokens_per_wg = ((shape == PrefillShape::k8Waves ? 8 : 4) * 32) >> shift;
     p.q_tiles = (max_q_len + tokens_per_wg - 1) / tokens_per_wg;
     p.group = group;

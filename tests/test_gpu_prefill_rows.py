@@ -40,3 +40,28 @@ def test_rows_in_and_out(U, oracle, dtype, D, ctx, alibi, B, Hq, Hkv, q_len, sha
         U.check_scaled(step[rows], ref, dtype, f"prefill step, sequences {first}-{last}")
     assert np.isfinite(W.from_bits(step, dtype)).all()
     assert (dev.prefill() == step).all()        # rows written by a call of its own: the same bits
+
+
+@pytest.mark.parametrize("bound", [2047, 2048])                 # tokens from which launches with slopes take 256 rows (head_dim 128)
+@pytest.mark.parametrize("dtype,D", [(W.BF16, 128), (W.F16, 128), (W.BF16, 64)])
+@pytest.mark.parametrize("alibi", [True, False])
+def test_whole_prompts_on_both_sides_of_the_long_ones(U, dtype, D, alibi, bound):
+    import torch
+    import oracle as O
+    import paper_2505_02351_amd as G
+    B, Hq, Hkv, q_len = 2, 32, 8, 173
+    assert launch_shape(B, Hq, Hkv, bound, True)[0] == "4"      # (head_dim 64, or below the line)
+    cfg = W.small_config(name="long", kind="prefill", dtype=dtype, batch=B, num_heads=Hq, num_kv_heads=Hkv, head_dim=D,
+                         block_size=16, num_blocks=B * 11 + 3, ctx_lo=q_len, ctx_hi=q_len, q_len=q_len, seed=bound)
+    case = W.make_case(cfg)
+    if not alibi:
+        case.slopes = None
+    case.block_tables = np.pad(case.block_tables, ((0, 0), (0, 2048 // 16 - case.block_tables.shape[1])), constant_values=-1)
+    dev = U.DevCase(case)
+    dev.out.fill_(float("nan"))
+    G.prompt_prefill(dev.out, dev.q, dev.k_new, dev.v_new, dev.k_cache, dev.v_cache, dev.block_tables, dev.cu_q_lens,
+                     dev.slopes, float(case.scale), bound)
+    torch.cuda.synchronize()
+    dev.check_canaries()
+    ref = O.prompt_attention(case.q, case.k_new, case.v_new, case.cu_q_lens, case.slopes, case.scale, dtype)
+    U.check_scaled(U.to_host(dev.out), ref, dtype, f"whole prompts, at most {bound} tokens")
