@@ -17,7 +17,7 @@ struct CachePieces {
 
 // Cache store of Alg. 1 / eq. (2).  One thread moves one 16-byte piece (8 elements) of one
 // token's K row and of its V row; pieces of a row are handled by consecutive lanes, so reads and
-// writes are contiguous runs of head_dim * 2 bytes.  The rows are asked for before the slot is there.
+// writes are contiguous runs of head_dim * 2 bytes.  A padding token's rows are not read: they need not exist.
 //   slot_mapping == nullptr (decode step): token t is the newest token of sequence t and goes to
 //   position context_lens[t] - 1, whose slot is read from the block table; empty sequences skip.
 template <typename VecT>
@@ -33,8 +33,6 @@ __global__ __launch_bounds__(256) void reshape_and_cache_kernel(
     if (idx64 >= n.num_pieces) return;
     const int idx = (int)idx64;
     const int t = n.by_token.div(idx), piece = idx - t * n.per_token;
-    const VecT kx = *reinterpret_cast<const VecT*>(k + t * k_token_stride + (int64_t)piece * kElems);
-    const VecT vx = *reinterpret_cast<const VecT*>(v + t * v_token_stride + (int64_t)piece * kElems);
     const int block_size = 1 << n.block_shift;
     int64_t block;
     int row;
@@ -50,6 +48,8 @@ __global__ __launch_bounds__(256) void reshape_and_cache_kernel(
         if (block < 0) return;                              // (no block: nothing to store to)
         row = pos & (block_size - 1);
     }
+    const VecT kx = *reinterpret_cast<const VecT*>(k + t * k_token_stride + (int64_t)piece * kElems);
+    const VecT vx = *reinterpret_cast<const VecT*>(v + t * v_token_stride + (int64_t)piece * kElems);
     const int g = piece >> n.per_head_shift, in_row = piece & ((1 << n.per_head_shift) - 1);
     const int64_t dst = ((((block * n.num_kv_heads + g) << n.block_shift) + row) << n.per_head_shift) * kElems + in_row * kElems;
     *reinterpret_cast<VecT*>(k_cache + dst) = kx;
@@ -74,10 +74,10 @@ __global__ __launch_bounds__(256) void reshape_and_cache_e4m3_kernel(
     if (idx64 >= n.num_pieces) return;
     const int idx = (int)idx64;
     const int t = n.by_token.div(idx), piece = idx - t * n.per_token;
-    const uint4 kx = *reinterpret_cast<const uint4*>(k + t * k_token_stride + (int64_t)piece * 8);
-    const uint4 vx = *reinterpret_cast<const uint4*>(v + t * v_token_stride + (int64_t)piece * 8);
     const int64_t slot = slot_mapping[t];
     if (slot < 0) return;                                   // padding token
+    const uint4 kx = *reinterpret_cast<const uint4*>(k + t * k_token_stride + (int64_t)piece * 8);
+    const uint4 vx = *reinterpret_cast<const uint4*>(v + t * v_token_stride + (int64_t)piece * 8);
     const int g = piece >> n.per_head_shift, in_row = piece & ((1 << n.per_head_shift) - 1);
     const int64_t row = slot & ((1 << n.block_shift) - 1);
     const int64_t dst = (((((slot >> n.block_shift) * n.num_kv_heads + g) << n.block_shift) + row) << n.per_head_shift) * 8 + in_row * 8;

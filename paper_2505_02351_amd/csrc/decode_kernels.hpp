@@ -99,8 +99,8 @@ constexpr int kMaxFusedSeqs = 32;
 
 template <int D> __device__ __forceinline__ void store_new_rows(const DecodeParams& p, int g)
 {
-    // (2 * LPR divides the threads: which tensor and which piece of its rows are a thread's own.  The row is asked for together
-    // with the length, the block behind them: two memory round trips ahead of the store.  The asm: a choice between
+    // (2 * LPR divides the threads: which tensor and which piece of its rows are a thread's own.  The row and its
+    // block are asked for together behind the length: two memory round trips ahead of the store.  The asm: a choice between
     // two arguments would be fetched per lane, as data, a third and a fourth.  GPU time of a step, with
     // the divisions by the host's reciprocals: one sequence of 128, 8 / 2 heads, head_dim 64, 5.9 -> 5.7 us; 16 of 100-250,
     // 16 / 4, 7.4 -> 7.2; 32 of 100-250, 32 / 8, head_dim 128, 10.8 -> 10.2.  Asking for the query rows and the first tile's block
@@ -118,9 +118,9 @@ template <int D> __device__ __forceinline__ void store_new_rows(const DecodePara
     const global_u16_ptr cache = (global_u16_ptr)(is_v ? vc : kc) + piece;
     const int64_t stride = is_v ? vs : ks;
     for (int b = threadIdx.x / (2 * LPR); b < p.num_seqs; b += kDecodeWaves * 64 / (2 * LPR)) {
-        const u32x4 x = *(const __attribute__((address_space(1))) u32x4*)(src + b * stride);
         const int pos = p.context_lens[b] - 1;
-        if (pos < 0) continue;
+        if (pos < 0) continue;                              // (an empty sequence's row is not read)
+        const u32x4 x = *(const __attribute__((address_space(1))) u32x4*)(src + b * stride);
         const int64_t blk = p.block_tables[(int64_t)b * p.max_blocks_per_seq + (pos >> bs_shift)];
         const int64_t dst = ((blk * p.num_kv_heads + g) * bs + (pos & (bs - 1))) * D;
         *(__attribute__((address_space(1))) u32x4*)(cache + dst) = x;
