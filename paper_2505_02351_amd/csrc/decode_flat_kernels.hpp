@@ -279,7 +279,8 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
     if (in_lanes) {
         my_len = lane < B ? ctx[lane] : 0;
         if constexpr (SHARED) {
-            const int my_sb = lane < B ? p.shared_blocks[lane] : 0;
+            const int entry = lane < B ? p.shared_blocks[lane] : 0;
+            const int my_sb = my_len > 0 ? entry : 0;        // (an empty sequence takes no part, whatever its entry says)
             const int b0 = lane - lane % p.bundle;
             // (shared_prefix_tokens and flat_seg, over the lanes)
             const int L0 = __shfl(my_len, b0);
@@ -287,7 +288,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
             bool any = false;
             for (int i = 1; i < p.bundle; ++i) {
                 const int s = __shfl(my_sb, (b0 + i) & 63), Li = __shfl(my_len, (b0 + i) & 63);
-                if (b0 + i < B && s > 0 && Li > 0) {
+                if (b0 + i < B && s > 0) {
                     any = true;
                     S = min(S, min(s * bs, Li - (FUSED ? 1 : 0)));
                 }
