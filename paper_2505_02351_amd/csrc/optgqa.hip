@@ -17,6 +17,7 @@
 #include "decode_mma_kernels.hpp"
 #include "decode_flat_kernels.hpp"
 #include "prefill_kernels.hpp"
+#include "prefill_shape.hpp"
 #include "probe_kernels.hpp"
 
 using namespace optgqa;
@@ -400,10 +401,6 @@ int launch_decode_flat(int dtype, int head_dim, const DecodeParams& p, int workg
 
 // The tiled prefill kernel takes its LDS as dynamic shared memory (more than the 64 KiB a kernel
 // gets by default); the limit is raised once per instantiation.
-// Shapes of a prefill workgroup (see prefill_kernels.hpp): 128 rows, 256 rows, or 128 rows whose keys are
-// shared out between two groups of four waves.
-enum class PrefillShape { k4Waves, k8Waves, k8WavesTwoGroups };
-
 template <int DT, bool KV8, bool WIN, bool CONTIG, bool STEP, bool JUDGE, int D, int WAVES, int KS>
 int launch_prefill_w(const PrefillParams& p, dim3 grid, hipStream_t st)
 {
@@ -450,8 +447,6 @@ float prefill_scale2(float scale)
     return s * kLog2e;
 }
 
-constexpr int kPfLongPrompt = 2048;      // tokens (launch_prefill)
-
 // Tiled matrix-core prefill (head_dim 128 or 64).
 int launch_prefill(PrefillParams p, int num_seqs, int max_q_len, int head_dim, int dtype, hipStream_t st,
                    bool kv8 = false, bool contig = false, bool step = false)
@@ -466,32 +461,8 @@ int launch_prefill(PrefillParams p, int num_seqs, int max_q_len, int head_dim, i
     p.heads_pow2_shift = shift;
     p.units = num_seqs * p.num_kv_heads * (group / gh);
     const int64_t units8 = (p.units + 7) / 8 * 8;
-    const int tokens_per_wg8 = (8 * 32) >> shift;
-    const int64_t blocks8 = units8 * ((max_q_len + tokens_per_wg8 - 1) / tokens_per_wg8);
-    const int tokens_per_wg4 = (4 * 32) >> shift;
-    const int64_t blocks4 = units8 * ((max_q_len + tokens_per_wg4 - 1) / tokens_per_wg4);
-    // Which shape (measured on both sides of each line; see also prefill_kernels.hpp):
-    //   a sliding window: 128 rows (a workgroup's rows should span few keys; 8 chunks of 512, 32 / 8 heads, GPU time with
-    //     128 and 256 rows: window 64 37.9 and 42.9 us, 512 70.8 and 76.9, 1 024 115 and 118, 4 096 386 and 366);
-    //   128-row workgroups do not even fill the CUs once: two key groups, which halve the longest
-    //     walk (634 new tokens behind 1 723 over 8-bit caches: 43.4 -> 38.1 us; at twice as many
-    //     workgroups the two tie; a workgroup whose walk is short uses one of them, kPfTwoGroupTiles);
-    //   256-row workgroups would not fill them twice - five times for whole prompts, whose walks are
-    //     short against what a workgroup costs before and behind its walk, which two resident
-    //     workgroups overlap (8 prompts of 768: 71.6 us with 256 rows, 68.9 with 128; 8 of 1 280 without slopes 159.7 and 155.3;
-    //     4 of 2 560, head_dim 64, 128.6 and 114.9; 8 of 1 024 100.8 and 102.4): 128 rows - with
-    //     slopes below 2 048 tokens only at head_dim 128, where a walk of 64 tiles outweighs that (4 prompts of 1 536 95.5 and
-    //     96.0, 5 of 1 800 131.2 and 129.6, 4 of 2 048 137.1 and 140.8, 2 of 2 560 111.9 and 114.7, 4 of 2 560 185.9 and 193.9,
-    //     32 / 4 heads 201 and 213, fp16 165.9 and 170.1; without slopes 317 and 325, but fp16, 3 of 2 200, 152.3 and 149.3);
-    //   else 256 rows, half the loads and LDS stores per row (chunks of 512 behind 2 048: 124 us, 147 at
-    //     128 rows).
-    PrefillShape shape = PrefillShape::k8Waves;
-    if (p.window > 0) shape = PrefillShape::k4Waves;
-    else if (blocks4 <= num_cus()) shape = PrefillShape::k8WavesTwoGroups;
-    else if (blocks8 < 2 * num_cus() || (contig && blocks8 <= 5 * num_cus() && !(p.slopes && head_dim == 128 && max_q_len >= kPfLongPrompt)))
-        shape = PrefillShape::k4Waves;
-    const int tokens_per_wg = ((shape == PrefillShape::k8Waves ? 8 : 4) * 32) >> shift;
-    p.q_tiles = (max_q_len + tokens_per_wg - 1) / tokens_per_wg;
+    const PrefillShape shape = prefill_shape(units8, shift, max_q_len, p.window > 0, contig, num_cus());
+    p.q_tiles = (int)prefill_q_tiles(shape == PrefillShape::k8Waves ? 8 : 4, shift, max_q_len);
     p.group = group;
     p.chunks = group / gh;
     p.units_per_seq = p.num_kv_heads * p.chunks;

@@ -42,15 +42,15 @@ def test_rows_in_and_out(U, oracle, dtype, D, ctx, alibi, B, Hq, Hkv, q_len, sha
     assert (dev.prefill() == step).all()        # rows written by a call of its own: the same bits
 
 
-@pytest.mark.parametrize("bound", [2047, 2048])                 # tokens from which launches with slopes take 256 rows (head_dim 128)
+@pytest.mark.parametrize("bound", [2047, 2048])                 # far above the lengths
 @pytest.mark.parametrize("dtype,D", [(W.BF16, 128), (W.F16, 128), (W.BF16, 64)])
 @pytest.mark.parametrize("alibi", [True, False])
-def test_whole_prompts_on_both_sides_of_the_long_ones(U, dtype, D, alibi, bound):
+def test_whole_prompts_under_a_loose_bound(U, dtype, D, alibi, bound):
     import torch
     import oracle as O
     import paper_2505_02351_amd as G
     B, Hq, Hkv, q_len = 2, 32, 8, 173
-    assert launch_shape(B, Hq, Hkv, bound, True)[0] == "4"      # (head_dim 64, or below the line)
+    assert launch_shape(B, Hq, Hkv, bound, True)[0] == "4"
     cfg = W.small_config(name="long", kind="prefill", dtype=dtype, batch=B, num_heads=Hq, num_kv_heads=Hkv, head_dim=D,
                          block_size=16, num_blocks=B * 11 + 3, ctx_lo=q_len, ctx_hi=q_len, q_len=q_len, seed=bound)
     case = W.make_case(cfg)
