@@ -1,6 +1,7 @@
 // KV-cache write and the un-paging diagnostic: pure index work and bit copies.
 #pragma once
 #include "common.hpp"
+#include "optgqa.h"
 
 namespace optgqa {
 
@@ -14,6 +15,57 @@ struct CachePieces {
     int per_token, per_head_shift, num_pieces;      // pieces: of a token, of a head (log2), of all tokens
     int num_kv_heads, block_shift;
 };
+
+// What a cache store reads: the new tokens' rows, and where they go - their slots, or (a decode step) the block tables and
+// lengths of the sequences.
+struct StoreRows {
+    const uint16_t *k, *v;
+    int64_t k_stride, v_stride;         // elements from token to token
+    const int64_t* slot_mapping;
+    const int32_t *block_tables, *context_lens;     // (where slot_mapping is nullptr)
+    int max_blocks_per_seq;
+
+    // the same from token `first` on
+    StoreRows from(int first) const
+    {
+        StoreRows s = *this;
+        s.k += first * k_stride;
+        s.v += first * v_stride;
+        if (slot_mapping) {
+            s.slot_mapping += first;
+        } else {
+            s.block_tables += (int64_t)first * max_blocks_per_seq;
+            s.context_lens += first;
+        }
+        return s;
+    }
+};
+
+// Launches of a cache store over slices of tokens of at most most_pieces pieces of `elems` elements each: one, but for K or V
+// rows of 32 GiB (16-byte pieces) or 4 GiB (single elements).  call(rows of the slice, its pieces, its workgroups).
+// Some 2^38 pieces and more are refused: 512 GiB of single elements, which no card holds, rows being a row apart at least.
+template <typename F>
+int for_cache_slices(const StoreRows& rows, int num_tokens, int num_kv_heads, int head_dim, int block_size, int elems, F&& call,
+                     int most_pieces = 0x7fffffff)
+{
+    const int64_t per_token = (int64_t)num_kv_heads * (head_dim / elems);
+    if (per_token > most_pieces || num_tokens * per_token > 128 * 0x7fffffffLL) return OPTGQA_ERR_SHAPE;
+    CachePieces n;
+    n.per_token = (int)per_token;
+    n.by_token.set((uint32_t)per_token);
+    n.per_head_shift = __builtin_ctz(head_dim / elems);
+    n.num_kv_heads = num_kv_heads;
+    n.block_shift = __builtin_ctz(block_size);
+    const int most = (int)(most_pieces / per_token);        // tokens of a slice, >= 1
+    for (int first = 0; first < num_tokens; ) {
+        const int tokens = num_tokens - first < most ? num_tokens - first : most;
+        n.num_pieces = (int)(tokens * per_token);
+        const int rc = call(rows.from(first), n, dim3((unsigned)(((int64_t)n.num_pieces + 255) / 256)));
+        if (rc != OPTGQA_OK) return rc;
+        first += tokens;
+    }
+    return OPTGQA_OK;
+}
 
 // Cache store of Alg. 1 / eq. (2).  One thread moves one 16-byte piece (8 elements) of one
 // token's K row and of its V row; pieces of a row are handled by consecutive lanes, so reads and

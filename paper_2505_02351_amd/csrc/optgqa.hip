@@ -52,28 +52,16 @@ int launch(void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t lds_bytes, hi
                ? OPTGQA_OK : OPTGQA_ERR_LAUNCH;
 }
 
-// Launches of a cache store over slices of tokens that have fewer than 2^31 pieces each (one slice, but for inputs of 32 GiB):
-// call(first token, pieces, workgroups).
-template <typename F>
-int for_cache_slices(int num_tokens, int num_kv_heads, int head_dim, int block_size, int elems, F&& call)
+// Cache store of 2-byte rows; wide: everything lies on 16 bytes and rows move as 16-byte pieces, else element by element.
+int launch_cache_store(const StoreRows& rows, bool wide, void* k_cache, void* v_cache, int num_tokens, int num_kv_heads, int head_dim,
+                       int block_size, hipStream_t st)
 {
-    const int64_t per_token = (int64_t)num_kv_heads * (head_dim / elems);
-    if (per_token > 0x7fffffffLL) return OPTGQA_ERR_SHAPE;
-    CachePieces n;
-    n.per_token = (int)per_token;
-    n.by_token.set((uint32_t)per_token);
-    n.per_head_shift = __builtin_ctz(head_dim / elems);
-    n.num_kv_heads = num_kv_heads;
-    n.block_shift = __builtin_ctz(block_size);
-    const int most = (int)(0x7fffffffLL / per_token);       // >= 1
-    for (int first = 0; first < num_tokens; ) {
-        const int tokens = num_tokens - first < most ? num_tokens - first : most;
-        n.num_pieces = (int)(tokens * per_token);
-        const int rc = call(first, n, dim3((unsigned)(((int64_t)n.num_pieces + 255) / 256)));
-        if (rc != OPTGQA_OK) return rc;
-        first += tokens;
-    }
-    return OPTGQA_OK;
+    auto kc = static_cast<uint16_t*>(k_cache);
+    auto vc = static_cast<uint16_t*>(v_cache);
+    return for_cache_slices(rows, num_tokens, num_kv_heads, head_dim, block_size, wide ? 8 : 1, [&](const StoreRows& r, const CachePieces& n, dim3 grid) {
+        return launch(wide ? reshape_and_cache_kernel<uint4> : reshape_and_cache_kernel<uint16_t>, grid, dim3(256), 0, st, r.k, r.v, kc, vc,
+                      r.slot_mapping, n, r.k_stride, r.v_stride, r.block_tables, r.context_lens, r.max_blocks_per_seq);
+    });
 }
 
 // Compute units of the current device, asked once (every GPU of a box is the same part); 256,
@@ -547,19 +535,9 @@ int optgqa_reshape_and_cache(const void* k, const void* v, void* k_cache, void* 
     hipStream_t st = static_cast<hipStream_t>(stream);
     const bool wide = aligned16(k) && aligned16(v) && aligned16(k_cache) && aligned16(v_cache) &&
                       k_token_stride % 8 == 0 && v_token_stride % 8 == 0;
-    const int elems = wide ? 8 : 1;
-    const int64_t threads = (int64_t)num_tokens * num_kv_heads * (head_dim / elems) * 2;
-    const int64_t blocks = (threads + 255) / 256;
-    if (blocks > 0x7fffffffLL) return OPTGQA_ERR_SHAPE;
-    auto kk = static_cast<const uint16_t*>(k);
-    auto vv = static_cast<const uint16_t*>(v);
-    auto kc = static_cast<uint16_t*>(k_cache);
-    auto vc = static_cast<uint16_t*>(v_cache);
-    return for_cache_slices(num_tokens, num_kv_heads, head_dim, block_size, elems, [&](int first, const CachePieces& n, dim3 grid) {
-        return launch(wide ? reshape_and_cache_kernel<uint4> : reshape_and_cache_kernel<uint16_t>, grid, dim3(256), 0, st,
-                      kk + first * k_token_stride, vv + first * v_token_stride, kc, vc, slot_mapping + first, n,
-                      k_token_stride, v_token_stride, nullptr, nullptr, 0);
-    });
+    const StoreRows rows{static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v), k_token_stride, v_token_stride,
+                         slot_mapping, nullptr, nullptr, 0};
+    return launch_cache_store(rows, wide, k_cache, v_cache, num_tokens, num_kv_heads, head_dim, block_size, st);
 }
 
 size_t optgqa_paged_attention_workspace_bytes(int num_seqs, int num_heads, int num_kv_heads,
@@ -603,26 +581,14 @@ struct StepInputs {
     void* v_cache_w;
 };
 
-int write_new_tokens(const StepInputs& n, const int64_t* slot_mapping, const int32_t* block_tables,
-                     const int32_t* context_lens, int num_tokens, int num_kv_heads, int head_dim, int block_size,
+int write_new_tokens(const StepInputs& n, const int32_t* block_tables, const int32_t* context_lens, int num_tokens, int num_kv_heads, int head_dim, int block_size,
                      int max_blocks_per_seq, hipStream_t st)
 {
     const bool wide = aligned16(n.k_new) && aligned16(n.v_new) && aligned16(n.k_cache_w) && aligned16(n.v_cache_w) &&
                       n.k_stride % 8 == 0 && n.v_stride % 8 == 0;
-    const int elems = wide ? 8 : 1;
-    const int64_t threads = (int64_t)num_tokens * num_kv_heads * (head_dim / elems) * 2;
-    const int64_t blocks = (threads + 255) / 256;
-    if (blocks > 0x7fffffffLL) return OPTGQA_ERR_SHAPE;
-    auto kk = static_cast<const uint16_t*>(n.k_new);
-    auto vv = static_cast<const uint16_t*>(n.v_new);
-    auto kc = static_cast<uint16_t*>(n.k_cache_w);
-    auto vc = static_cast<uint16_t*>(n.v_cache_w);
-    return for_cache_slices(num_tokens, num_kv_heads, head_dim, block_size, elems, [&](int first, const CachePieces& pieces, dim3 grid) {
-        return launch(wide ? reshape_and_cache_kernel<uint4> : reshape_and_cache_kernel<uint16_t>, grid, dim3(256), 0, st,
-                      kk + first * n.k_stride, vv + first * n.v_stride, kc, vc, slot_mapping ? slot_mapping + first : nullptr, pieces,
-                      n.k_stride, n.v_stride, slot_mapping ? block_tables : block_tables + (int64_t)first * max_blocks_per_seq,
-                      slot_mapping ? context_lens : context_lens + first, max_blocks_per_seq);
-    });
+    const StoreRows rows{static_cast<const uint16_t*>(n.k_new), static_cast<const uint16_t*>(n.v_new), n.k_stride, n.v_stride,
+                         nullptr, block_tables, context_lens, max_blocks_per_seq};
+    return launch_cache_store(rows, wide, n.k_cache_w, n.v_cache_w, num_tokens, num_kv_heads, head_dim, block_size, st);
 }
 
 // Decode attention, optionally preceded by (or fused with) the step's cache write.
@@ -726,7 +692,7 @@ int attention_impl(void* out, const void* q, const void* k_cache, const void* v_
                 aligned16(step->k_new) && aligned16(step->v_new) && step->k_stride % 8 == 0 && step->v_stride % 8 == 0;
         if (!fused && kv_scales) return OPTGQA_ERR_UNSUPPORTED;   // 8-bit step: new rows must move as 16-byte pieces
         if (!fused) {
-            const int rc = write_new_tokens(*step, nullptr, block_tables, context_lens, num_seqs, num_kv_heads,
+            const int rc = write_new_tokens(*step, block_tables, context_lens, num_seqs, num_kv_heads,
                                             head_dim, block_size, max_blocks_per_seq, st);
             if (rc != OPTGQA_OK) return rc;
         }
@@ -815,20 +781,16 @@ static int reshape_and_cache_fp8_impl(const void* k, const void* v, void* k_cach
     if (!aligned16(k) || !aligned16(v) || k_token_stride % 8 || v_token_stride % 8 ||
         ((reinterpret_cast<uintptr_t>(k_cache) | reinterpret_cast<uintptr_t>(v_cache)) & 7u))
         return OPTGQA_ERR_UNSUPPORTED;
-    const int64_t threads = (int64_t)num_tokens * num_kv_heads * (head_dim / 8) * 2;
-    const int64_t blocks = (threads + 255) / 256;
-    if (blocks > 0x7fffffffLL) return OPTGQA_ERR_SHAPE;
     // one fp32 division each (per KV head: the same division, in the kernel)
     const float k_inv = sc.per_head() ? 1.f : 1.0f / sc.k, v_inv = sc.per_head() ? 1.f : 1.0f / sc.v;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    auto kk = static_cast<const uint16_t*>(k);
-    auto vv = static_cast<const uint16_t*>(v);
+    const StoreRows rows{static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v), k_token_stride, v_token_stride,
+                         slot_mapping, nullptr, nullptr, 0};
     auto kc = static_cast<unsigned char*>(k_cache);
     auto vc = static_cast<unsigned char*>(v_cache);
-    return for_cache_slices(num_tokens, num_kv_heads, head_dim, block_size, 8, [&](int first, const CachePieces& n, dim3 grid) {
+    return for_cache_slices(rows, num_tokens, num_kv_heads, head_dim, block_size, 8, [&](const StoreRows& r, const CachePieces& n, dim3 grid) {
         return launch(dtype == OPTGQA_F16 ? reshape_and_cache_e4m3_kernel<kF16> : reshape_and_cache_e4m3_kernel<kBF16>, grid, dim3(256), 0,
-                      st, kk + first * k_token_stride, vv + first * v_token_stride, kc, vc, slot_mapping + first, n,
-                      k_token_stride, v_token_stride, k_inv, v_inv, sc.k_heads, sc.v_heads);
+                      st, r.k, r.v, kc, vc, r.slot_mapping, n, r.k_stride, r.v_stride, k_inv, v_inv, sc.k_heads, sc.v_heads);
     });
 }
 

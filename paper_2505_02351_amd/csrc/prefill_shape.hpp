@@ -38,10 +38,9 @@ inline int64_t prefill_q_tiles(int waves, int heads_pow2_shift, int max_q_len)
 //   whole prompts, not five times
 //                         -> 128 rows: the walks are short against what a workgroup costs before and behind its
 //                            walk, which two resident workgroups overlap.  8 prompts:
-//                              tokens               768   1 024   1 280   1 280, no slopes   1 280, head_dim 64   1 536   2 560
-//                              256-row workgroups   768   1 024   1 280   1 280              1 280                1 536   2 560
-//                              256 rows            69.1   105.2   141.3   186.6               97.8                190.1   385.1
-//                              128 rows            65.9   100.7   134.2   177.5               81.6                184.2   395.6
+//                              tokens, and workgroups  768  1 024  1 280   1 280, no slopes   1 280, head_dim 64   1 536   2 560
+//                              256 rows               69.1  105.2  141.3   186.6               97.8                190.1   385.1
+//                              128 rows               65.9  100.7  134.2   177.5               81.6                184.2   395.6
 //   else                  -> 256 rows: half the loads and LDS stores per row.
 // What is counted are workgroups under the caller's bound: most of them may find no tokens, and then the launch is smaller
 // than it looks.  So prompts do not take 256 rows for a large bound alone, though prompts of 2 048 and more that are that

@@ -44,4 +44,4 @@ using std::min;
 #define __builtin_amdgcn_fdot2_f32_bf16(a, b, c, s) (c)
 #define __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(c, s, h) f16x2{}
 #define __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c, s, h) bf16x2{}
-#define __builtin_amdgcn_cvt_pk_fp8_f32(a, b, o, h) (0)
+#define __builtin_amdgcn_cvt_pk_fp8_f32(a, b, o, h) (((int)(a) & 255) | ((int)(b) & 255) << 8)

@@ -6,6 +6,7 @@ import random
 import subprocess
 import types
 
+import numpy as np
 import pytest
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -16,9 +17,106 @@ CSRC = os.path.join(os.path.dirname(HERE), "paper_2505_02351_amd", "csrc")
 def lib(tmp_path_factory):
     out = str(tmp_path_factory.mktemp("rules") / "librules.so")
     clang = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "clang++")
-    subprocess.run([clang, "-std=c++17", "-O1", "-fPIC", "-shared", "-Wno-ignored-attributes", "-I" + os.path.join(HERE, "host_hip"),
-                    "-I" + CSRC, os.path.join(HERE, "host_hip", "rules.cpp"), "-o", out], check=True)
+    # (-O0: a load whose value is not used must stay)
+    subprocess.run([clang, "-std=c++17", "-O0", "-fPIC", "-shared", "-Wno-ignored-attributes", "-I" + os.path.join(HERE, "host_hip"),
+                    "-I" + CSRC, "-I" + os.path.join(os.path.dirname(HERE), "include"), os.path.join(HERE, "host_hip", "rules.cpp"), "-o", out], check=True)
     return ctypes.CDLL(out)
+
+
+def ptr(a):
+    return None if a is None else ctypes.c_void_p(a.ctypes.data)
+
+
+def test_division_by_the_hosts_reciprocal(lib):
+    """All of 0 <= n < 2^31: ends and neighbours of multiples, for divisors that occur and for the largest."""
+    f = lib.fast_div_differs
+    f.restype = ctypes.c_int64
+    rng = np.random.default_rng(1)
+    divisors = {1, 2, 3, 2**31 - 1, 2**31 - 2} | {(1 << s) + d for s in range(2, 31) for d in (-1, 0, 1)}
+    divisors = sorted(divisors | set(range(1, 300)) | {int(x) for x in np.exp2(rng.uniform(0, 31, 2000))})
+    top = 2**31 - 1
+    for d in divisors:
+        q = np.unique(np.concatenate([[0, 1, top // d], rng.integers(0, top // d + 1, 40)]))
+        n = np.concatenate([q * d - 1, q * d, q * d + d - 1, [top, top - 1], rng.integers(0, top, 20)])
+        n = np.ascontiguousarray(n[(n >= 0) & (n <= top)], np.int32)
+        at = f(ptr(np.array([d], np.uint32)), 1, ptr(n), len(n))
+        assert at < 0, (d, n[at])
+
+
+# (kinds: 16-byte pieces, single elements, E4M3 codes - whose decode step stores its rows in the combine kernel)
+@pytest.mark.parametrize("kind,decode", [(0, False), (0, True), (1, False), (1, True), (2, False)])
+@pytest.mark.parametrize("Hkv,D,bs", [(1, 64, 16), (3, 128, 32), (5, 64, 64)])
+@pytest.mark.parametrize("slice_tokens", [1, 3, 8, None])       # tokens to a launch
+def test_cache_stores_slice_by_slice(lib, slice_tokens, decode, kind, Hkv, D, bs):
+    """Rows land where their slots say however the launches are cut; the rows of padding tokens (of empty sequences, in a
+    decode step) beyond those that there are, which a graph's fixed batch has, are not read."""
+    rng = np.random.default_rng(7 * Hkv + bs + kind)
+    tokens, rows, pool = 17, 13, 9
+    pad = 1 if kind == 1 else 8
+    ks, vs = Hkv * D + pad, Hkv * D + 2 * pad
+    k, v = (rng.integers(0, 100, (rows, s)).astype(np.float32) for s in (ks, vs))
+    k, v = ((x.view(np.uint32) >> 16).astype(np.uint16) for x in (k, v))    # bf16
+    dt = np.uint8 if kind == 2 else np.uint16
+    got = [np.full((pool + 2, Hkv, bs, D), 255, dt) for _ in range(2)]      # a block ahead of the cache and one behind it
+    want = [x.copy() for x in got]
+    slots = np.full(tokens, -1, np.int64)
+    slots[:rows] = rng.permutation(pool * bs)[:rows]
+    slots[2] = -1                                               # and one among them
+    tables, lens = np.full((tokens, 4), -1, np.int32), np.zeros(tokens, np.int32)
+    for t in range(tokens):
+        if slots[t] >= 0:
+            block = int(rng.integers(4))
+            tables[t, block], lens[t] = slots[t] // bs, block * bs + slots[t] % bs + 1
+    tables[4, (lens[4] - 1) // bs] = -1                         # no block: nothing is stored (decode)
+    for c, x in zip(want, (k, v)):
+        for t in range(rows):
+            if slots[t] >= 0 and not (decode and t == 4):
+                row = x[t, :Hkv * D].reshape(Hkv, D)
+                c[1 + slots[t] // bs, :, slots[t] % bs] = (row.astype(np.uint32) << 16).view(np.float32).astype(dt) if kind == 2 else row
+    per_token = Hkv * D // (1 if kind == 1 else 8)
+    most = 2**31 - 1 if slice_tokens is None else per_token * slice_tokens + per_token - 1
+    n = lib.cache_store(kind, ptr(k), ptr(v), rows, ctypes.c_int64(ks), ctypes.c_int64(vs), ptr(got[0][1:]), ptr(got[1][1:]),
+                        None if decode else ptr(slots), ptr(tables), ptr(lens), 4, tokens, Hkv, D, bs, most)
+    assert n == (1 if slice_tokens is None else -(-tokens // slice_tokens))
+    assert (got[0] == want[0]).all() and (got[1] == want[1]).all()
+
+
+def test_cache_slices_and_refusals(lib):
+    first, pieces = np.zeros(300, np.int64), np.zeros(300, np.int64)
+
+    def slices(tokens, Hkv, D, elems):
+        n = lib.cache_slices(ctypes.c_int64(Hkv * D), tokens, Hkv, D, elems, ptr(first), ptr(pieces), 300)
+        return n if n < 0 else [(int(a), int(b)) for a, b in zip(first[:n], pieces[:n])]
+    assert slices(4096, 8, 128, 8) == [(0, 4096 * 128)]
+    assert slices(2**24 - 1, 8, 128, 8) == [(0, 2**31 - 128)]   # 128 pieces to a token: the most that one launch takes
+    assert slices(2**24, 8, 128, 8) == [(0, 2**31 - 128), (2**24 - 1, 128)]
+    assert slices(5, 2**24 - 1, 128, 1) == [(t, 2**31 - 128) for t in range(5)]
+    assert slices(1, 2**24, 128, 1) == -2                       # one token is too much for a launch
+    most = (2**31 - 1) * 128 // 1024                            # tokens of 1024 pieces
+    assert len(slices(most, 8, 128, 1)) == 129 and slices(most + 1, 8, 128, 1) == -2
+
+
+@pytest.mark.parametrize("Hkv,D,bs", [(1, 64, 16), (3, 128, 32), (5, 64, 64), (2, 128, 16)])
+@pytest.mark.parametrize("seqs", [1, 4, 17, 32])
+def test_a_steps_store_of_its_new_rows(lib, seqs, Hkv, D, bs):
+    """store_new_rows: every sequence's row in its block; the rows of empty sequences, which need not exist, are not read."""
+    rng = np.random.default_rng(seqs + Hkv)
+    ks, vs, pool = Hkv * D + 8, Hkv * D, seqs + 3
+    lens = rng.integers(0, 4 * bs, seqs).astype(np.int32)
+    rows = max(seqs - 3, 1)
+    lens[rows:] = 0                                             # the last ones are a graph's padding
+    tables = np.full((seqs, 4), -1, np.int32)
+    tables[np.arange(seqs), np.maximum(lens - 1, 0) // bs] = rng.permutation(pool)[:seqs]
+    k, v = (rng.integers(0, 2**16, (rows, s)).astype(np.uint16) for s in (ks, vs))
+    got = [np.zeros((pool, Hkv, bs, D), np.uint16) for _ in range(2)]
+    want = [x.copy() for x in got]
+    for b in np.flatnonzero(lens > 0):
+        pos = lens[b] - 1
+        for c, x in zip(want, (k, v)):
+            c[tables[b, pos // bs], :, pos % bs] = x[b, :Hkv * D].reshape(Hkv, D)
+    assert lib.step_store(ptr(k), ptr(v), rows, ctypes.c_int64(ks), ctypes.c_int64(vs), ptr(got[0]), ptr(got[1]), ptr(tables), ptr(lens), 4,
+                          seqs, Hkv, D, bs) == 1
+    assert (got[0] == want[0]).all() and (got[1] == want[1]).all()
 
 
 def shape(lib, B, Hq, Hkv, max_q_len, whole_prompts=False, windowed=False, cus=256):
