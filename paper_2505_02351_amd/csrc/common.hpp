@@ -97,6 +97,14 @@ struct FastDiv {
     }
 };
 
+// n / d for n >= 0 and d >= 1 whose quotient is below 2^20, given 1 / d to within an ulp or two: the product is off by less than
+// half then, the whole number below it by one at most, which the remainder tells.
+__host__ __device__ __forceinline__ int div_by_inverse(int n, int d, float d_inv)
+{
+    const int x = (int)((float)n * d_inv), r = n - x * d;
+    return r < 0 ? x - 1 : r >= d ? x + 1 : x;
+}
+
 // Data-parallel-primitive lane exchange inside a row of 16 lanes (full VALU rate, no LDS).
 template <int CTRL> __device__ __forceinline__ float dpp(float x)
 {

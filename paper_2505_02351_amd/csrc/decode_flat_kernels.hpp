@@ -902,12 +902,7 @@ __global__ __launch_bounds__(GROUPS == 1 ? kReduceThreads : GROUPS * (D / 4)) vo
     const int Y = p.segs_per_seq;
     const int y = g * chunks + chunk;
     const int c = max(plan_total, 1);
-    // n / c for n >= 0 (the quotient is a unit's number, far below 2^20: one off at most before it is mended)
-    const float c_inv = __builtin_amdgcn_rcpf((float)c);
-    auto by_c = [&](int n) __attribute__((always_inline)) {
-        const int x = (int)((float)n * c_inv), r = n - x * c;
-        return r < 0 ? x - 1 : r >= c ? x + 1 : x;
-    };
+    const float c_inv = __builtin_amdgcn_rcpf((float)c);     // (quotients by c are units' numbers, far below 2^20)
     // the numbering the main kernel used
     int n_own, n_shared = 0, col_shared = 0, plan_shared = 0, v_shared = 0;
     if constexpr (SHARED) {
@@ -941,8 +936,8 @@ __global__ __launch_bounds__(GROUPS == 1 ? kReduceThreads : GROUPS * (D / 4)) vo
             // (the clamps only matter if the lengths changed under the kernels: they keep every read
             // inside the workspace; n == 0: nothing was streamed, nobody wrote the plan entry)
             const int F0 = n > 0 ? Y * P + y * n : 0;
-            const int u0 = min(max(by_c(F0), 0), p.num_units - 1);
-            np = n > 0 ? min(max(by_c(F0 + n - 1) - u0 + 1, 1), p.num_units - u0) : 0;
+            const int u0 = min(max(div_by_inverse(F0, c, c_inv), 0), p.num_units - 1);
+            np = n > 0 ? min(max(div_by_inverse(F0 + n - 1, c, c_inv) - u0 + 1, 1), p.num_units - u0) : 0;
             base = ((int64_t)u0 + (int64_t)vv * Y + y) * CS + col;          // slot stride between units: CS
         }
         for (int i0 = grp * kBatch; i0 < np; i0 += GROUPS * kBatch) {

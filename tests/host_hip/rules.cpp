@@ -1,6 +1,7 @@
 // The library's host rules and index arithmetic, callable from the tests (tests/test_host_rules.py).
 #include <setjmp.h>
 #include <signal.h>
+#include <stdlib.h>
 #include <sys/mman.h>
 
 #include <vector>
@@ -62,6 +63,18 @@ extern "C" int64_t fast_div_differs(const uint32_t* divisors, int num_divisors, 
         d.set(divisors[i]);
         for (int j = 0; j < n; ++j)
             if ((uint32_t)d.div(numerators[j]) != (uint32_t)numerators[j] / divisors[i]) return (int64_t)i * n + j;
+    }
+    return -1;
+}
+
+// The same by an inverse that is `ulps` units in the last place off.
+extern "C" int64_t div_by_inverse_differs(const int32_t* divisors, int num_divisors, const int32_t* numerators, int n, int ulps)
+{
+    for (int i = 0; i < num_divisors; ++i) {
+        float inv = 1.0f / (float)divisors[i];
+        for (int u = 0; u < abs(ulps); ++u) inv = nextafterf(inv, ulps > 0 ? INFINITY : 0.f);
+        for (int j = 0; j < n; ++j)
+            if (div_by_inverse(numerators[j], divisors[i], inv) != numerators[j] / divisors[i]) return (int64_t)i * n + j;
     }
     return -1;
 }

@@ -43,6 +43,21 @@ def test_division_by_the_hosts_reciprocal(lib):
         assert at < 0, (d, n[at])
 
 
+@pytest.mark.parametrize("ulps", [-2, -1, 0, 1, 2])         # v_rcp_f32 is good to one; the product rounds once more
+def test_division_by_a_rounded_inverse(lib, ulps):
+    """Quotients below 2^20 (those of the combine kernel are waves of a launch, a few thousand), numerators up to 2^30."""
+    f = lib.div_by_inverse_differs
+    f.restype = ctypes.c_int64
+    rng = np.random.default_rng(2)
+    for d in sorted(set(range(1, 200)) | {int(x) for x in np.exp2(rng.uniform(0, 30, 2000))}):
+        top = min(2**30 // d, 2**20 - 1)
+        q = np.unique(np.concatenate([[0, 1, top], rng.integers(0, top + 1, 40)]))
+        n = np.concatenate([q * d - 1, q * d, q * d + d - 1])
+        n = np.ascontiguousarray(n[n >= 0], np.int32)
+        at = f(ptr(np.array([d], np.int32)), 1, ptr(n), len(n), ulps)
+        assert at < 0, (d, n[at])
+
+
 # (kinds: 16-byte pieces, single elements, E4M3 codes - whose decode step stores its rows in the combine kernel)
 @pytest.mark.parametrize("kind,decode", [(0, False), (0, True), (1, False), (1, True), (2, False)])
 @pytest.mark.parametrize("Hkv,D,bs", [(1, 64, 16), (3, 128, 32), (5, 64, 64)])
