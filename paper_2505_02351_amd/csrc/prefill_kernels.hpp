@@ -66,27 +66,31 @@ namespace optgqa {
 constexpr float kPfSkipLog2 = OPTGQA_PF_SKIP_LOG2;
 // tiles between a look at whether the rest of the walk still matters, at the least (2, 4 and 8 measure the same)
 constexpr int kPfCheckTiles = 4;
-// ... and tiles that must be left for the look to pay (rest_judged costs about 2 us; 4 prompts of 205-351 over
-// 8-bit caches, 24 / 8 heads, at most 11 tiles: 27.3 us when looking from 4 tiles on, 24.9 from 12; 5 chunks
-// of up to 1 419 behind 630: 115 from 4, 117 from 12, 121 from 16)
+// ... and tiles that must be left for the look to pay (rest_judged costs about 2 us; looking from 4, 12 and 16 tiles
+// on: 5 chunks of up to 1 419 behind 630 110.0, 110.0 and 111.4 us, 5 prompts of 1 280 88.4, 87.9 and 89.9)
 constexpr int kPfJudgeTiles = 12;
 // tiles that a launch's longest possible walk must have for the kernel that looks to be taken (JUDGE).  (GPU time with it
-// and without, slopes: head_dim 64, 16 / 4 heads, 3 prompts of 1 024 27.2 and 25.4 us, 3 of 1 280 33.5 and 29.3, 12 of 1 280
-// 64.7 and 66.1, 3 of 2 560 69.5 and 81.2; head_dim 128, up to 1 093 over 8-bit caches, 32 / 4 heads, 50.5 and 46.7, 5 of
-// 1 024, 32 / 8, 68.3 and 71.1, 5 of 1 280 91.5 and 95.9, 5 chunks of up to 1 419 behind 630 112 and 121.)
+// and without, slopes: head_dim 64, 16 / 4 heads, 3 prompts of 1 024 26.2 and 24.2 us, 3 of 1 280 31.9 and 28.7, 3 of 1 536 38.5 and
+// 36.1, 12 of 1 280 64.8 and 65.3, 3 of 2 560 69.0 and 71.0; head_dim 128, 8 of 512, 32 / 8, 42.7 and 40.5, 364 to 1 093 over 8-bit
+// caches, 32 / 4, 40.2 and 39.4, 5 of 1 024, 32 / 8, 64.5 and 66.0, 5 of 1 152 77.7 and 79.9, 5 of 1 280 88.6 and 94.1, 5 chunks of
+// up to 1 419 behind 630 110 and 118.)
 template <int D> constexpr int kPfJudgeLongest = D == 128 ? 36 : 48;
 // tiles that a look which fails further on must have passed for the walk to leave them out (starting it anew costs about 3 us)
 constexpr int kPfJumpTiles = 8;
 // tiles that a walk must have for a wave's rows to be one head's; below, a token's heads are neighbouring rows, as they are
-// in memory (slopes, 8 prompts of 170-512, 32 / 8 heads, head_dim 128: 30.8 us by head, 29.4 by token; 24 / 8 heads over
-// 8-bit caches, 528: 28.4 and 28.3; 5 prompts of 657-1 972 with a window of 84, 16 / 4: 39.6 and 37.5; longer walks skip more
-// by head: 8 chunks of 512 behind 2 048: 117 and 122)
+// in memory (slopes, always by head and never: 8 prompts of 170-512, 16 / 4 heads, head_dim 64, 14.2 and 13.8 us; 32 / 8,
+// head_dim 128, 25.2 and 25.2, 8 chunks of 128 behind 300 19.3 and 19.2, of 256 behind 512 36.3 and 36.7; longer walks skip more by
+// head: 4 prompts of 1 024 55.7 and 56.2, 8 chunks of 512 behind 2 048 111.5 and 116.1.  Before rows went through LDS whole, short
+// walks by head lost 5 %.)
 constexpr int kPfByHeadTiles = 16;
 // tiles that a walk must have for two key groups to share it: below, the second group's waves end at once and the
-// first walks alone.  (Sharing costs a tile beyond the diagonal, a merge through LDS and two barriers.  Two groups
-// over one, GPU time of prompts and of chunks behind a cache, both types: head_dim 128 1.2-1.3 at 1 to 4 tiles, 0.99-1.14
-// at 9 and 10, 0.95-1.03 at 16, 0.9 at 24; head_dim 64 1.0-1.25, 0.82-1.08, 0.86-0.94, 0.8-0.9.  One prompt of 48 tokens,
-// 32 / 8 heads, head_dim 128: 10.4 us shared, 8.1 alone; a launch of 128-row workgroups of one group: 8.1.)
+// first walks alone.  (Sharing costs a tile beyond the diagonal, a merge through LDS and two barriers.  GPU time shared
+// over alone, 32 / 8 heads, one prompt or chunks of 40 behind a cache, both types:
+//   tiles             1           2           4           8           10          12          16          24
+//   head_dim 128  1.23-1.24   1.06-1.14   1.02-1.08   0.95-1.01   0.92-0.99   0.90-0.96   0.87-0.94   0.83-0.90
+//   head_dim 64   1.16        1.04-1.06   1.01-1.03   0.94-0.95   0.92-0.93   0.89-0.90   0.86-0.88   0.82-0.85
+// The lines date from a longer start, when shared and alone tied at 16 and 10 tiles; they do at 8 and 6 now, and walks in between
+// are up to 12 % slower than they could be.)
 template <int D> constexpr int kPfTwoGroupTiles = D == 128 ? 16 : 11;
 
 struct PrefillParams {
@@ -123,7 +127,7 @@ struct PrefillParams {
     void* v_cache_w;
 };
 
-// Workgroup shapes (template parameters WAVES and KS; 32 rows per wave, chosen in launch_prefill):
+// Workgroup shapes (template parameters WAVES and KS; 32 rows per wave, chosen in prefill_shape.hpp):
 //   8 waves            256 rows against one K/V tile, half the loader work and LDS stores per row;
 //   4 waves            128 rows, two workgroups to a CU: one's start and end under the other's walk;
 //   8 waves, KS = 2    128 rows, the walk's tiles dealt to two groups of four waves (each its own tile
@@ -131,7 +135,7 @@ struct PrefillParams {
 //                      there are too few workgroups to fill the chip (a workgroup with a short walk uses
 //                      one group only, kPfTwoGroupTiles).
 // With a sliding window always 4 waves: a workgroup's rows should span few keys, because every tile that
-// some row's window start or causal end cuts needs the masked path (launch_prefill has both sides' times).
+// some row's window start or causal end cuts needs the masked path (prefill_shape.hpp has both sides' times).
 constexpr int kPfKeys = 32;                              // keys per tile
 // LDS rows, elements: K rows padded by 8 (16-byte reads of 16 keys then cover all 64 banks), V rows
 // by 16 (so do the rows a transposing load touches) - head_dim 128: 272 / 288 bytes, 64: 144 / 160
@@ -205,7 +209,7 @@ template <> struct PfSoftmax<kBF16> {
 // even where it never runs, costs the loop around it its instruction order (no slopes, 5 prompts of 512, 16 / 4 heads,
 // head_dim 64, bf16: 15.3 us without it in the kernel, 16.4 with; 3 of 1 024: 24.3 and 27.1; 8 chunks of 512 behind 2 048,
 // 32 / 8 heads, head_dim 128: 217.8 and 220.2), and because a look costs what walks of up to kPfJudgeLongest tiles cannot
-// earn back (slopes, prompts of 512: 3 with 16 / 4 heads, head_dim 64, 13.6 and 15.6; 8 with 32 / 8, head_dim 128, 43.2 and 44.8).
+// earn back (slopes, prompts of 512: 3 with 16 / 4 heads, head_dim 64, 12.1 and 13.6; 8 with 32 / 8, head_dim 128, 40.5 and 42.7).
 template <int DT, bool KV8, bool WIN, bool CONTIG, bool JUDGE, int D, int WAVES, int KS, bool STEP>
 __device__ __forceinline__ void prefill_body(const PrefillParams& p)
 {
@@ -342,9 +346,9 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // pieces (kCPR per row and tensor; 2 * kCPR threads to a token, K row then V row).  The first kOwnBatch
     // tokens of every thread are loaded here, in front of the first tile fetch, and
     // stored once that tile has landed - one memory latency shared with the fetch instead of a
-    // load-then-store loop of its own in front of or behind the walk (each workgroup has the CU to
+    // load-then-store loop of its own in front of or behind the walk (a workgroup of 256 rows has the CU to
     // itself, so such a loop is not overlapped by anything: measured 2 us per workgroup round);
-    // whatever is left (more than 64 tokens per workgroup) goes out behind the output.
+    // whatever is left (more than kOwnBatch * own_step tokens per workgroup) goes out behind the output.
     constexpr int kOwnBatch = 4;
     typedef uint32_t own_u32x4 __attribute__((ext_vector_type(4)));
     const int own_tokens = ((CONTIG || STEP) && p.k_cache_w && gu == g * chunks) ? min(tokens_per_wg, n_b - tq0) : 0;

@@ -42,6 +42,8 @@ inline int64_t prefill_q_tiles(int waves, int heads_pow2_shift, int max_q_len)
 //                              256 rows               69.1  105.2  141.3   186.6               97.8                190.1   385.1
 //                              128 rows               65.9  100.7  134.2   177.5               81.6                184.2   395.6
 //   else                  -> 256 rows: half the loads and LDS stores per row.
+// The lines date from a longer start of a workgroup; with today's, windows of 2 048 and chunks that fill the CUs 1.75 times are
+// faster with 256 rows, and whole prompts with 128 up to six times (none of it tried over the ranges that a line serves).
 // What is counted are workgroups under the caller's bound: most of them may find no tokens, and then the launch is smaller
 // than it looks.  So prompts do not take 256 rows for a large bound alone, though prompts of 2 048 and more that are that
 // long gain by it (256 and 128 rows: 4 of 2 560 182.5 and 190.6, 2 of 2 560 108.9 and 110.4; but under bounds of that size

@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 
 def launch_shape(batch, Hq, Hkv, max_q_len, whole_prompt=False):
-    """The workgroup shape that a prefill launch takes on this card (launch_prefill's rule): "two" key groups of four
+    """The workgroup shape that a prefill launch takes on this card (prefill_shape.hpp's rule): "two" key groups of four
     waves, "4" waves, or "8" waves; and its query tiles."""
     import torch
     cus = torch.cuda.get_device_properties(0).multi_processor_count
