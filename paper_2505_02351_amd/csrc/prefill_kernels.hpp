@@ -17,8 +17,8 @@
 //                              element 4i + j), which after the softmax pack straight into ...
 //   O^T[dim][row] += V^T P^T   ... the B operands of the two output MFMAs of a 32-dim block, whose
 //                              contraction index runs over the tile's keys in exactly that
-//                              (permuted) order.  A = V^T: V lies in LDS in its natural [key][dim]
-//                              layout and is read with the LDS transpose load (ds_read_b64_tr_b16:
+//                              (permuted) order.  A = V^T: V lies in LDS as rows of dims (16-byte pieces
+//                              of a key) and is read with the LDS transpose load (ds_read_b64_tr_b16:
 //                              inside each group of 16 lanes, lane i receives element i % 4 of the
 //                              8-byte chunks addressed by lanes i/4, 4 + i/4, 8 + i/4, 12 + i/4),
 //                              so that a lane ends up with four consecutive keys of its dim from
@@ -137,15 +137,66 @@ struct PrefillParams {
 // With a sliding window always 4 waves: a workgroup's rows should span few keys, because every tile that
 // some row's window start or causal end cuts needs the masked path (prefill_shape.hpp has both sides' times).
 constexpr int kPfKeys = 32;                              // keys per tile
-// LDS rows, elements: K rows padded by 8 (16-byte reads of 16 keys then cover all 64 banks), V rows
-// by 16 (so do the rows a transposing load touches) - head_dim 128: 272 / 288 bytes, 64: 144 / 160
+// LDS rows of 8-bit caches' tiles and of a wave's strip, elements: K rows padded by 8 (16-byte reads of 16 keys then
+// cover all 64 banks), V rows by 16 (so do the rows a transposing load touches) - head_dim 128: 272 / 288 bytes, 64: 144 / 160
 template <int D> struct PfTile {
     static constexpr int kKRow = D + 8, kVRow = D + 16;
-    static constexpr int kLdsBytes = 2 * kPfKeys * (kKRow + kVRow) * 2;   // two buffers of one K and one V tile
+    static constexpr int kLdsBytes = 2 * kPfKeys * (kKRow + kVRow) * 2;   // two buffers of one K and one V tile (PfDirect's are smaller)
     static constexpr int kWaveBytes = 32 * kKRow * 2;                     // a wave's 32 query (output) rows, pitched as K rows
     // a workgroup of `waves` waves in `groups` key groups
     static constexpr int lds_bytes(int waves, int groups) { return groups * kLdsBytes + waves * kWaveBytes; }
 };
+
+// Tiles of 2-byte elements are written to LDS by the memory system itself (global_load_lds_dwordx4: 64 lanes' 16-byte
+// pieces to 1 KiB from the address in m0 on, lane by lane): no registers hold a tile on its way, no LDS stores, and with
+// wave-uniform addresses not one vector instruction.  (Through registers - loads, 16-byte LDS stores and their addresses -
+// a tile cost a wave 20 to 30 instructions: 8 prompts of 1 024, 32 / 8 heads, head_dim 128, 96.8 -> 86.0 us, 8 chunks of 512
+// behind 2 048 107.5 -> 103.3, without slopes 201 -> 195, with a window of 512 65.7 -> 61.8.)
+// Such a load cannot pad rows, but it may bring any piece to any lane.  A tile is groups of 4 rows (head_dim 64: 8), 1 KiB and
+// a pad of 16 (32) bytes each.  In a group pieces of 64 bytes - four lanes, 64 bytes of one row's, as the memory system likes
+// them - lie row behind row, then the next 64 bytes of all rows:
+//     offset = (column / 4) * (64 * rows) + row * 64 + (column % 4) * 16      (columns of 16 bytes; head_dim 64: column ^ 1 in rows 4-7)
+// What the score MFMAs read at once (one column of 16 rows) then lies in 16 different sixteenths of the 64 banks, and so do
+// the 32-byte pieces of four rows of a transposing load; and a lane's pieces are at constant distances.
+template <int D> struct PfDirect {
+    static constexpr int kRows = 512 / D, kGroups = 32 / kRows;           // rows of a group; groups of a tile
+    static constexpr int kGroup = 1024 + (D == 128 ? 16 : 32);            // bytes from group to group
+    static constexpr int kTile = kGroups * kGroup;                        // bytes of a tile (of 32 query rows, too)
+    // the row of its group and the column that lane l of a load brings
+    static __device__ __forceinline__ int load_row(int l) { return (l >> 2) & (kRows - 1); }
+    static __device__ __forceinline__ int load_col(int l)
+    {
+        return D == 128 ? (l >> 4) * 4 + (l & 3) : (l >> 5) * 4 + ((l & 3) ^ ((l >> 4) & 1));
+    }
+    // byte offset of dims 8 * h2 .. +7 of a row, and from there to the dims 16m further on
+    static __device__ __forceinline__ int row_at(int row, int h2)
+    {
+        return D == 128 ? (row >> 2) * kGroup + (row & 3) * 64 + h2 * 16
+                        : (row >> 3) * kGroup + (row & 7) * 64 + (h2 ^ ((row >> 2) & 1)) * 16;
+    }
+    static constexpr int dims_at(int m) { return (m >> 1) * 64 * kRows + (m & 1) * 32; }
+    // byte offset of what lane s16 of 16 addresses in a transposing load of keys 4 * h2 .. +3, dims 16 * dhalf .. +15, and
+    // from there to the keys 8 * k8 and the dims 32 * db further on
+    static __device__ __forceinline__ int keys_at(int s16, int dhalf, int h2)
+    {
+        return D == 128 ? h2 * kGroup + (s16 >> 2) * 64 + dhalf * 32 + (s16 & 3) * 8
+                        : (4 * h2 + (s16 >> 2)) * 64 + dhalf * 32 + (((s16 & 3) >> 1) ^ h2) * 16 + (s16 & 1) * 8;
+    }
+    static constexpr int further(int k8, int db) { return k8 * (8 / kRows) * kGroup + db * 64 * kRows; }
+};
+
+// One such load, to LDS address `lds` (wave-uniform) on; from a wave-uniform base and lane offsets, or from lane addresses.
+// In assembly because the compiler, which does not know which buffer a load writes, would have every later read of LDS wait
+// for it; wait_direct() comes before the barrier that publishes the tile.
+__device__ __forceinline__ void load_direct(uint32_t lds, const unsigned char* base, uint32_t lane_off)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds), "v"(lane_off), "s"(base) : "memory", "m0");
+}
+__device__ __forceinline__ void load_direct(uint32_t lds, const unsigned char* lane_addr)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds), "v"(lane_addr) : "memory", "m0");
+}
+__device__ __forceinline__ void wait_direct() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 template <int DT> __device__ __forceinline__ uint32_t pack2(float lo, float hi) { return narrow2<DT>(lo, hi); }
 
@@ -225,8 +276,12 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     constexpr int kCPR = D / 8;                         // 16-byte (8-element) column pieces per row
     constexpr int kKPT = kPfKeys * (D / 8) / (kPfWaves * 32);   // consecutive keys a loader thread moves per tile (half the threads per tensor)
     constexpr int ES = KV8 ? 1 : 2;                     // bytes per cache element
-    // two tile buffers, each a K tile [32][kPfKRow] followed by a V tile [32][kPfVRow]
-    constexpr int kKTile = kPfKeys * kPfKRow, kBuf = kKTile + kPfKeys * kPfVRow;   // (of each key group)
+    constexpr bool DIRECT = !KV8;                       // tiles go to LDS as they are (8-bit codes pass through registers, which widen them)
+    typedef PfDirect<D> Direct;
+    // two tile buffers, each a K tile followed by a V tile: PfDirect's, or [32][kPfKRow] and [32][kPfVRow]
+    constexpr int kKTile = DIRECT ? Direct::kTile / 2 : kPfKeys * kPfKRow;
+    constexpr int kBuf = kKTile + (DIRECT ? Direct::kTile / 2 : kPfKeys * kPfVRow);   // (of each key group)
+    static_assert(2 * 2 * kBuf <= PfTile<D>::kLdsBytes && Direct::kTile <= PfTile<D>::kWaveBytes, "both layouts fit");
     extern __shared__ __attribute__((aligned(16))) uint16_t tile_lds[];          // PfTile<D>::lds_bytes(WAVES, KS)
     __shared__ float vote[3][WAVES];                          // rest_judged
     __shared__ int nearest_bad;
@@ -375,44 +430,32 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         return (__attribute__((address_space(1))) own_u32x4*)(cache + (uint64_t)(uint32_t)blk * (uint32_t)(block_stride * 2)
                                             + (uint32_t)((tok & (bs - 1)) * (D * 2)));
     };
-    // ---- tile staging: threads 0..127 fetch K, 128..255 fetch V; either way a thread moves the
-    // same 16-byte column piece of kKPT consecutive keys (kCPR lanes cover one row) ----------------
-    const bool k_loader = wave < kPfWaves / 2;                   // wave-uniform (first half of the waves: K; second: V)
+    // ---- tiles: the first half of the waves fetches K, the second V -----------------------------------------
+    const bool k_loader = wave < kPfWaves / 2;                   // wave-uniform
     const int l_ahead = k_loader ? 1 : 0;                        // K tiles run one tile ahead of V tiles (below)
-    const int ld = k_loader ? tid : tid - kPfWaves * 32;
-    const int l_group = ld / kCPR, l_chunk = ld % kCPR;          // keys kKPT*group .. , dims 8*chunk ..
     const unsigned char* __restrict__ l_src = k_loader ? kc : vc;
     const int64_t l_row = CONTIG ? (k_loader ? p.k_in_stride : p.v_in_stride) * 2 : D * ES;   // bytes from key to key
-    // STEP: this lane's column piece of the first new token, and the inputs' bytes from token to token
-    const unsigned char* const l_in = (k_loader ? kin : vin) + 8 * l_chunk * 2;
+    // STEP: the first new token's row, and the inputs' bytes from token to token
+    const unsigned char* const l_in = k_loader ? kin : vin;
     const uint32_t l_in_row = STEP ? (uint32_t)((k_loader ? p.k_in_stride : p.v_in_stride) * 2) : 0u;
-    const int l_pitch = k_loader ? kPfKRow : kPfVRow;
-    const int l_dst = kKPT * l_group * l_pitch + 8 * l_chunk;
-    // One register stage: while tile t is computed, the loader's next tile sits in the other LDS
-    // buffer and the one after it is on its way to registers; the block id of the next tile to
-    // fetch is read one fetch earlier, so a fetch never waits for the table.  Fetches past the last
-    // tile re-read it (cache hits): no branches around loads, which keeps the compiler's load
-    // counting exact.
+    const uint32_t l_blk_bytes = (uint32_t)(block_stride * ES);                   // < 2^32: one block of all KV heads
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // native vectors: plain loads and stores
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-    typedef typename std::conditional<KV8, u32x2, u32x4>::type StageT;   // 8 elements of one key
-    StageT stage[kKPT];
     // Key groups: of every two consecutive tiles of the walk each group takes one.  The walk is made a
     // multiple of two long by starting it beyond the diagonal, where the causal mask hides every key.
     const int pad = KS == 1 ? 0 : (ntiles - kt0) & share;
     const int last_tile = ntiles - 1 + pad;                       // >= kt0
     const int nt = ntiles - kt0 + pad;                            // tiles this workgroup walks
+    const int steps = nt >> share;                                // ... in steps of a tile for each group
     // the tile of the walk's i-th step (i past the end: the last one again)
     auto tile_of = [&](int i) __attribute__((always_inline)) {
         const int ic = min((i << share) + kw, nt - (1 << share) + kw);
         return last_tile - ic;                                    // from the diagonal backwards
     };
-    auto load_blk = [&](int i) __attribute__((always_inline)) {
-        // the keys of a group share a block (groups are aligned, clamping keeps the block)
-        if (CONTIG) return 0;
-        const int key = min(tile_of(i) * kPfKeys + kKPT * l_group, kmax - 1);
-        return table[key >> bs_shift];
-    };
+    // A tile's place in LDS: the j-th tile of the walk sits in buffer j % 2.
+    const int group_base = kw * 2 * kBuf;
+    auto tile_base = [&](int j) __attribute__((always_inline)) { return group_base + (j & 1) * kBuf; };
+    auto tile_base_v = [&](int j) __attribute__((always_inline)) { return group_base + (j & 1) * kBuf + kKTile; };
 
     // Everything a workgroup starts with is asked for before anything is waited for: the block numbers of
     // the first tiles, the query rows, this workgroup's own new rows, then the first two tiles.  (What the source
@@ -420,58 +463,95 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // waited for there, and a load may sink to its use.  The few lines of asm below hold such places: one memory round trip
     // before the first tile instead of three, five where new rows are stored - 8 prompts of 2 560 383.9 -> 371.6 us, with the
     // divisions by FastDiv.)
-    const int blk_first = load_blk(0), blk_second = load_blk(1);
-    int blk_next = load_blk(2);
 
+    // ---- DIRECT: 1 KiB groups of a tile by loads to LDS; a loader wave's groups are consecutive keys of one block ----------
+    constexpr int kWaveGroups = Direct::kGroups / (kPfWaves / 2);
+    static_assert(kWaveGroups * Direct::kRows <= 16, "a wave's keys of a tile lie in one block");
+    const int d_first = kWaveGroups * Direct::kRows * (k_loader ? wave : wave - kPfWaves / 2);     // the first of them
+    const uint32_t d_off = (uint32_t)Direct::load_row(lane) * (uint32_t)l_row + 16u * (uint32_t)Direct::load_col(lane);
+    const bool far_rows = CONTIG && l_row >= (1ll << 29);        // (32-bit lane offsets reach seven rows)
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)tile_lds;
+    // A lane holds one of the 64 block numbers from d_block down, so that a tile costs a lane read instead of a load.
+    int d_block = 0, d_table = 0;
+    auto read_table = [&](int block) __attribute__((always_inline)) {
+        d_block = block;
+        d_table = table[max(block - lane, 0)];
+    };
+    if constexpr (DIRECT && !CONTIG) read_table(min(tile_of(0) * kPfKeys + d_first, kmax - 1) >> bs_shift);
+    // The tile of the walk's i-th step into that step's buffer (this wave's groups of K, or of V).  Every key of it is read, visible
+    // or not; rows past the sequence's last key, which only the first tile has, re-read that one.  `head`: one of the first two tiles.
+    auto direct_tile = [&](int i, auto head) __attribute__((always_inline)) {
+        const int key0 = tile_of(i) * kPfKeys, key = key0 + d_first;
+        const uint32_t lds = lds0 + 2 * (k_loader ? tile_base(i) : tile_base_v(i)) + (uint32_t)(d_first / Direct::kRows * Direct::kGroup);
+        const unsigned char* base = l_src;
+        if (CONTIG) {
+            base += (uint64_t)(uint32_t)key * (uint32_t)l_row;
+        } else {
+            const int block = min(key, kmax - 1) >> bs_shift;
+            if (__builtin_expect(d_block - block > 63, 0)) {
+                read_table(block);
+                asm volatile("" : "+v"(d_table));                // (waited for here, not on the way that reads no table)
+            }
+            base += (uint64_t)(uint32_t)__builtin_amdgcn_readlane(d_table, d_block - block) * l_blk_bytes + (uint32_t)((key & (bs - 1)) * (D * ES));
+        }
+        if (decltype(head)::value || __builtin_expect((CONTIG && far_rows) || (STEP && key0 + kPfKeys > pos0), 0)) {     // workgroup-uniform
+            // lane addresses.  STEP: a key at or above the first new position comes from the inputs, one below through the table
+#pragma unroll
+            for (int n = 0; n < kWaveGroups; ++n) {
+                const int k = min(key + n * Direct::kRows + Direct::load_row(lane), kmax - 1);
+                const unsigned char* a = CONTIG ? l_src + (uint64_t)(uint32_t)k * (uint32_t)l_row
+                                                : base + (int64_t)((k & (bs - 1)) - (key & (bs - 1))) * (D * ES);
+                if (STEP && k >= pos0) a = l_in + (uint64_t)(uint32_t)(k - pos0) * l_in_row;
+                load_direct(lds + n * Direct::kGroup, a + 16 * Direct::load_col(lane));
+            }
+        } else {
+#pragma unroll
+            for (int n = 0; n < kWaveGroups; ++n)
+                load_direct(lds + n * Direct::kGroup, base + (uint64_t)(n * Direct::kRows) * (uint32_t)l_row, d_off);
+        }
+    };
+
+    // ---- 8-bit caches: through registers, which widen the codes.  A thread moves the same 8-code column piece of kKPT
+    // consecutive keys (kCPR lanes cover one row).  One register stage: while tile t is computed, the loader's next tile sits in the other LDS
+    // buffer and the one after it is on its way to registers; the block id of the next tile to
+    // fetch is read one fetch earlier, so a fetch never waits for the table.  Fetches past the last
+    // tile re-read it (cache hits): no branches around loads, which keeps the compiler's load
+    // counting exact.
+    const int ld = k_loader ? tid : tid - kPfWaves * 32;
+    const int l_group = ld / kCPR, l_chunk = ld % kCPR;          // keys kKPT*group .. , dims 8*chunk ..
+    const int l_pitch = k_loader ? kPfKRow : kPfVRow;
+    const int l_dst = kKPT * l_group * l_pitch + 8 * l_chunk;
+    u32x2 stage[kKPT];                                           // 8 codes of a key each
+    auto load_blk = [&](int i) __attribute__((always_inline)) {
+        // the keys of a group share a block (groups are aligned, clamping keeps the block)
+        const int key = min(tile_of(i) * kPfKeys + kKPT * l_group, kmax - 1);
+        return table[key >> bs_shift];
+    };
+    int blk_first = 0, blk_second = 0, blk_next = 0;
+    if constexpr (!DIRECT) {
+        blk_first = load_blk(0), blk_second = load_blk(1);
+        blk_next = load_blk(2);
+    }
     // (address arithmetic kept short on purpose - this loop pays for every instruction: one 64-bit
     // multiply-add for the block, one shift-add for the first row, then per key a clamp and a shift-add;
     // rows past the sequence's last key re-read that key, which lies in the same block)
     const unsigned char* const l_lane = l_src + 8 * l_chunk * ES;                 // this lane's column piece
-    const uint32_t l_blk_bytes = (uint32_t)(block_stride * ES);                   // < 2^32: one block of all KV heads
-    // (head: one of the first two tiles, always chosen per key - behind a branch the compiler would have the fetch wait
-    // for everything asked for before it)
-    auto fetch_from = [&](StageT (&stage)[kKPT], int i, int blk, auto head) __attribute__((always_inline)) {
+    auto fetch_from = [&](u32x2 (&stage)[kKPT], int i, int blk) __attribute__((always_inline)) {
         const int key0 = min(tile_of(i) * kPfKeys + kKPT * l_group, kmax - 1);
         const int rmax = kmax - 1 - key0;                         // >= 0; < kKPT - 1 only at the sequence's end
-        const unsigned char* base;
-        if (CONTIG) base = l_lane + (uint64_t)(uint32_t)key0 * (uint32_t)l_row;
-        else base = l_lane + (uint64_t)(uint32_t)blk * l_blk_bytes + (uint32_t)((key0 & (bs - 1)) * (D * ES));
-        // STEP: a tile that ends below the first new position is all cache (the plain path: most
-        // tiles); otherwise the keys from that position on come from the inputs, chosen per key (the
-        // clamped key, so that rows past the last visible key re-read it from wherever it lives)
-        if (STEP && (decltype(head)::value || tile_of(i) * kPfKeys + kPfKeys > pos0)) {     // workgroup-uniform
+        const unsigned char* base = l_lane + (uint64_t)(uint32_t)blk * l_blk_bytes + (uint32_t)((key0 & (bs - 1)) * (D * ES));
 #pragma unroll
-            for (int j = 0; j < kKPT; ++j) {
-                const unsigned char* a = base + (uint32_t)(min(j, rmax) * (D * ES));
-                const int nk = key0 + min(j, rmax) - pos0;
-                if (nk >= 0) a = l_in + (uint64_t)(uint32_t)nk * l_in_row;
-                stage[j] = *reinterpret_cast<const StageT*>(a);
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < kKPT; ++j)
-                stage[j] = *reinterpret_cast<const StageT*>(base + (uint32_t)(min(j, rmax) * (CONTIG ? (int)l_row : D * ES)));
-        }
+        for (int j = 0; j < kKPT; ++j) stage[j] = *reinterpret_cast<const u32x2*>(base + (uint32_t)(min(j, rmax) * (D * ES)));
     };
-    auto fetch_tile = [&](StageT (&stage)[kKPT], int i) __attribute__((always_inline)) {
-        fetch_from(stage, i, blk_next, std::false_type{});
+    auto fetch_tile = [&](u32x2 (&stage)[kKPT], int i) __attribute__((always_inline)) {
+        fetch_from(stage, i, blk_next);
         blk_next = load_blk(i + 1);
     };
-    // A tile's place in LDS: the j-th tile of the walk sits in buffer j % 2.
-    const int group_base = kw * 2 * kBuf;
-    auto tile_base = [&](int j) __attribute__((always_inline)) { return group_base + (j & 1) * kBuf; };
-    auto tile_base_v = [&](int j) __attribute__((always_inline)) { return group_base + (j & 1) * kBuf + kKTile; };
-    auto store_tile = [&](const StageT (&stage)[kKPT], int buf) __attribute__((always_inline)) {
+    auto store_tile = [&](const u32x2 (&stage)[kKPT], int buf) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < kKPT; ++j) {
-            u32x4 w;
-            if constexpr (KV8) {
-                const uint4 x = widen8_e4m3<DT>(stage[j][0], stage[j][1]);
-                w = u32x4{x.x, x.y, x.z, x.w};
-            } else {
-                w = stage[j];
-            }
-            *reinterpret_cast<u32x4*>(&tile_lds[(k_loader ? tile_base(buf) : tile_base_v(buf)) + l_dst + j * l_pitch]) = w;
+            const uint4 x = widen8_e4m3<DT>(stage[j][0], stage[j][1]);
+            *reinterpret_cast<u32x4*>(&tile_lds[(k_loader ? tile_base(buf) : tile_base_v(buf)) + l_dst + j * l_pitch]) = u32x4{x.x, x.y, x.z, x.w};
         }
     };
 
@@ -510,14 +590,14 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     auto row_offset = [&](const Row& row) __attribute__((always_inline)) {   // bytes, from there
         return (uint64_t)(uint32_t)row.token * (uint32_t)(Hq * (D * 2)) + (uint32_t)(row.head * (D * 2));
     };
-    // The query rows come, and the output rows leave, whole rows at a time through an LDS strip of the wave's own:
-    // kCPR lanes to a row.  (From and to the operand layout directly, 64 lanes touch 32 rows of 16 or 32 bytes each:
+    // The query rows come, and the output rows leave, whole rows at a time through an LDS strip of the wave's own (DIRECT: the
+    // query rows like a tile, without passing through registers).  (From and to the operand layout directly, 64 lanes touch 32 rows of 16 or 32 bytes each:
     // a line per lane, and the memory pipeline's time for such lines is what a workgroup pays before and behind its walk.
     // 32 / 8 heads, head_dim 128: 8 chunks of 512 behind 2 048 121.1 -> 114.0 us, 8 prompts of 2 560 398.8 -> 383.9, 8 chunks
     // of 512 with a window of 512 74.6 -> 71.2; 5 prompts of 3-301, 16 / 4 heads, head_dim 64: 9.6 -> 9.3.)
-    uint16_t* const strip = tile_lds + KS * (2 * kBuf) + wg_wave * (kPfKeys * kPfKRow);
+    uint16_t* const strip = tile_lds + KS * (PfTile<D>::kLdsBytes / 2) + wg_wave * (kPfKeys * kPfKRow);
     const unsigned char* const qp = static_cast<const unsigned char*>(p.q) + rows_base;
-    u32x4 q_stage[kQ];
+    u32x4 q_stage[kQ];                                           // (not DIRECT)
     {
         const Row mine = row_at(n32);
         row_ok = mine.ok;
@@ -529,21 +609,36 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         // a row that does not exist never wants a tile: its sum is already beyond anything
         started = !row_ok;
         lsum = row_ok ? 0.f : INFINITY;
+        if constexpr (!DIRECT) {
 #pragma unroll
-        for (int m = 0; m < kQ; ++m)
-            q_stage[m] = *reinterpret_cast<const u32x4*>(qp + row_offset(row_at((64 / kCPR) * m + lane / kCPR)) + 16 * (lane % kCPR));
+            for (int m = 0; m < kQ; ++m)
+                q_stage[m] = *reinterpret_cast<const u32x4*>(qp + row_offset(row_at((64 / kCPR) * m + lane / kCPR)) + 16 * (lane % kCPR));
+        }
     }
     asm volatile("" ::: "memory");                               // (asked for here, before the tiles' block numbers are waited for)
-    StageT stage_first[kKPT];
-    fetch_from(stage_first, 0, blk_first, std::true_type{});
-    fetch_from(stage, 1, blk_second, std::true_type{});
-    {
+    u32x2 stage_first[kKPT];
+    if constexpr (DIRECT) {
+        const uint32_t lds = lds0 + KS * PfTile<D>::kLdsBytes + wg_wave * PfTile<D>::kWaveBytes;
+#pragma unroll
+        for (int n = 0; n < Direct::kGroups; ++n)
+            load_direct(lds + n * Direct::kGroup, qp + row_offset(row_at(n * Direct::kRows + Direct::load_row(lane))) + 16 * Direct::load_col(lane));
+        direct_tile(0, std::true_type{});
+        if (k_loader) direct_tile(1, std::true_type{});          // wave-uniform
+        wait_direct();
+        const unsigned char* const mine = reinterpret_cast<const unsigned char*>(strip) + Direct::row_at(n32, h2);
+#pragma unroll
+        for (int m = 0; m < kQ; ++m) qb[m] = *reinterpret_cast<const uint4*>(mine + Direct::dims_at(m));
+    } else {
+        fetch_from(stage_first, 0, blk_first);
+        fetch_from(stage, 1, blk_second);
 #pragma unroll
         for (int m = 0; m < kQ; ++m)
             *reinterpret_cast<u32x4*>(strip + ((64 / kCPR) * m + lane / kCPR) * kPfKRow + 8 * (lane % kCPR)) = q_stage[m];
         wave_lds_fence();
 #pragma unroll
         for (int m = 0; m < kQ; ++m) qb[m] = *reinterpret_cast<const uint4*>(strip + n32 * kPfKRow + 16 * m + 8 * h2);
+    }
+    {
         const uint32_t keep = row_ok ? 0xffffffffu : 0u;
 #pragma unroll
         for (int m = 0; m < kQ; ++m) qb[m] = make_uint4(qb[m].x & keep, qb[m].y & keep, qb[m].z & keep, qb[m].w & keep);
@@ -570,13 +665,21 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // ---- S^T = K Q^T : element 4i + j = score of key 32kt + 8i + 4h2 + j against row n32
     // (the accumulator starts from the tile-invariant part of the ALiBi term, already divided by the
     // score scale, so that one FMA per score finishes eq. (3))
-    auto scores = [&](int buf) __attribute__((always_inline)) {
+    const int k_at = DIRECT ? Direct::row_at(n32, h2) / 2 : n32 * kPfKRow + 8 * h2;
+    // `between`: what is issued behind the reads of the first four operands.  (A step's loads to LDS: in front of all reads
+    // they delay the MFMAs, behind the MFMAs the softmax.  Two key groups, whose waves issue four a step, one chunk of 512 behind 8 192,
+    // slopes: 134 us in front, 119 behind two reads, 116 behind four; behind the MFMAs everything is 2-5 % slower.)
+    auto scores = [&](int buf, auto between) __attribute__((always_inline)) {
         f32x16 st = key_bias;
+        auto read = [&](int m) __attribute__((always_inline)) {
+            return *reinterpret_cast<const uint4*>(&tile_lds[tile_base(buf) + k_at + (DIRECT ? Direct::dims_at(m) / 2 : 16 * m)]);
+        };
+        uint4 ka[4];
 #pragma unroll
-        for (int m = 0; m < kQ; ++m) {
-            const uint4 ka = *reinterpret_cast<const uint4*>(&tile_lds[tile_base(buf) + n32 * kPfKRow + 16 * m + 8 * h2]);
-            st = mfma32<DT>(ka, qb[m], st);
-        }
+        for (int m = 0; m < 4; ++m) ka[m] = read(m);
+        between();
+#pragma unroll
+        for (int m = 0; m < kQ; ++m) st = mfma32<DT>(m < 4 ? ka[m & 3] : read(m), qb[m], st);
         return st;
     };
     // kt: the tile's number along the context; buf: its number in the walk (LDS buffer buf % 2)
@@ -655,13 +758,15 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         typedef short i16x4 __attribute__((ext_vector_type(4)));
         typedef __attribute__((address_space(3))) i16x4* lds_i16x4_ptr;
         const int s16 = lane & 15, dhalf = (lane >> 4) & 1;
-        const uint16_t* vrow = &tile_lds[tile_base_v(buf) + (4 * h2 + (s16 >> 2)) * kPfVRow + 16 * dhalf + 4 * (s16 & 3)];
+        const uint16_t* vrow = &tile_lds[tile_base_v(buf) + (DIRECT ? Direct::keys_at(s16, dhalf, h2) / 2
+                                                                    : (4 * h2 + (s16 >> 2)) * kPfVRow + 16 * dhalf + 4 * (s16 & 3))];
+        auto further = [](int k8, int db) { return DIRECT ? Direct::further(k8, db) / 2 : 8 * k8 * kPfVRow + 32 * db; };
 #pragma unroll
         for (int db = 0; db < kDB; ++db)
 #pragma unroll
             for (int m = 0; m < 2; ++m) {
-                const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_ptr)(vrow + 16 * m * kPfVRow + 32 * db));
-                const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_ptr)(vrow + (16 * m + 8) * kPfVRow + 32 * db));
+                const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_ptr)(vrow + further(2 * m, db)));
+                const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_ptr)(vrow + further(2 * m + 1, db)));
                 const uint2 lo2 = __builtin_bit_cast(uint2, lo), hi2 = __builtin_bit_cast(uint2, hi);
                 const uint4 va = make_uint4(lo2.x, lo2.y, hi2.x, hi2.y);
                 acc[db] = mfma32<DT>(va, make_uint4(pk[m][0], pk[m][1], pk[m][2], pk[m][3]), acc[db]);
@@ -846,12 +951,14 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // Software pipeline: the score MFMAs of the walk's next tile are issued before the softmax of the
     // current one, so that the matrix pipe has work while the vector ALU does the exponentials
     // (measured: 3 % on the kernel).  For that the K tiles run one tile ahead of the V tiles: at the
-    // start of step j, K tiles j and j + 1 and V tile j are in LDS, K tile j + 2 and V tile j + 1 are
-    // on their way to registers.  Prologue:
-    store_tile(stage_first, 0);
-    if (k_loader) {                                              // wave-uniform
-        store_tile(stage, 1);
-        fetch_tile(stage, 2);
+    // start of step j, K tiles j and j + 1 and V tile j are in LDS, and K tile j + 2 and V tile j + 1 are
+    // on their way to registers (DIRECT: are asked for now).  Prologue:
+    if constexpr (!DIRECT) {
+        store_tile(stage_first, 0);
+        if (k_loader) {                                          // wave-uniform
+            store_tile(stage, 1);
+            fetch_tile(stage, 2);
+        }
     }
     if (own_tokens > 0) {                                        // the rows loaded at the top have landed with the tiles
         const global_byte_ptr cache = own_cache(threadIdx.x);
@@ -864,7 +971,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         }
     }
     __syncthreads();
-    f32x16 st_next = scores(0);
+    f32x16 st_next = scores(0, [] {});
     __syncthreads();                                             // buffer 0's K tile is overwritten during step 0
     // Tiles wholly inside every row's visible range need no mask: those that end at or below the
     // first row's position (causal side) and start at or above the last row's window start.
@@ -872,18 +979,25 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     const int n_window_cut = W > 0 ? (max(kmax - W, 0) + kPfKeys - 1) / kPfKeys : 0;
     // (plain loops rather than one with a branch in it, and no branch around the stores: the
     // compiler schedules a loop whose body is one straight line far better)
-    // While step j is computed, K tile j + 2 / V tile j + 1 (fetched one step earlier) go into the
-    // buffers that step j - 1 used and the next ones are fetched; the waves meet after every step.
+    // While step j is computed, K tile j + 2 / V tile j + 1 (through registers: fetched one step earlier) go into the
+    // buffers that step j - 1 used (and the next ones are fetched); the waves meet after every step.  (A third buffer for
+    // DIRECT tiles, two steps on their way: 8 chunks of 512 behind 2 048 103.3 -> 107.2 us, 8 prompts of 2 560 350 -> 363.)
     // The last step's look-ahead scores read a stale K buffer and are never used; stores past the
     // last tile put the clamped re-read of it into a buffer nobody reads again.
     // (two steps per trip with the two score registers swapping roles, so that no trip copies the
     // look-ahead scores into place)
     f32x16 st_other;
     auto one_tile = [&](int j, const f32x16& st_cur, f32x16& st_ahead, auto masked) __attribute__((always_inline)) {
-        st_ahead = scores(j + 1);
+        st_ahead = scores(j + 1, [&]() __attribute__((always_inline)) {
+            if (DIRECT && j + 1 + l_ahead < steps) direct_tile(j + 1 + l_ahead, std::false_type{});      // wave-uniform; none past the walk's end
+        });
         softmax_pv(last_tile - ((j << share) + kw), j, st_cur, masked);
-        store_tile(stage, j + 1 + l_ahead);
-        fetch_tile(stage, j + 2 + l_ahead);
+        if constexpr (DIRECT) {
+            wait_direct();
+        } else {
+            store_tile(stage, j + 1 + l_ahead);
+            fetch_tile(stage, j + 2 + l_ahead);
+        }
         __syncthreads();
     };
     // steps [from, to) of the walk
@@ -900,16 +1014,22 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     };
     // The walk goes on at step j, wherever it was (every wave has passed a barrier since it last read a tile).
     auto restart = [&](int j) __attribute__((always_inline)) {
-        blk_next = load_blk(j);
-        fetch_tile(stage, j);
-        store_tile(stage, j);
-        if (k_loader) {
-            fetch_tile(stage, j + 1);
-            store_tile(stage, j + 1);
+        if constexpr (DIRECT) {
+            direct_tile(j, std::false_type{});
+            if (k_loader && j + 1 < steps) direct_tile(j + 1, std::false_type{});
+            wait_direct();
+        } else {
+            blk_next = load_blk(j);
+            fetch_tile(stage, j);
+            store_tile(stage, j);
+            if (k_loader) {
+                fetch_tile(stage, j + 1);
+                store_tile(stage, j + 1);
+            }
+            fetch_tile(stage, j + 1 + l_ahead);
         }
-        fetch_tile(stage, j + 1 + l_ahead);
         __syncthreads();
-        st_next = scores(j);
+        st_next = scores(j, [] {});
         __syncthreads();
     };
     const int cut_end = max(kt0, min(n_window_cut, n_unmasked));   // tiles cut by some row's window start
@@ -917,7 +1037,6 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // from the diagonal backwards: the tiles the causal mask cuts come first, those that some
     // row's window start cuts (if there is a window) last
     // (in steps of a tile for each group: a step that any mask touches takes the masked path)
-    const int steps = nt >> share;
     const int from_plain = min((ntiles + pad - plain_end + share) >> share, steps);
     const int to_plain = WIN ? max(from_plain, ntiles - cut_end) : steps;
     run_tiles(0, from_plain, std::true_type{});
