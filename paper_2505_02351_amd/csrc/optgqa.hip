@@ -405,7 +405,8 @@ template <int DT, bool KV8, bool WIN, bool CONTIG, bool STEP, bool JUDGE, int D>
 int launch_prefill_d(const PrefillParams& p, dim3 grid, PrefillShape shape, hipStream_t st)
 {
     if constexpr (!WIN) {
-        if (shape == PrefillShape::k8Waves) return launch_prefill_w<DT, KV8, WIN, CONTIG, STEP, JUDGE, D, 8, 1>(p, grid, st);
+        if constexpr (KV8 || D == 128)                           // (prefill_shape_direct never takes it at head_dim 64)
+            if (shape == PrefillShape::k8Waves) return launch_prefill_w<DT, KV8, WIN, CONTIG, STEP, JUDGE, D, 8, 1>(p, grid, st);
         if (shape == PrefillShape::k8WavesTwoGroups)
             return launch_prefill_w<DT, KV8, WIN, CONTIG, STEP, JUDGE, D, 8, 2>(p, grid, st);
     }
@@ -449,7 +450,8 @@ int launch_prefill(PrefillParams p, int num_seqs, int max_q_len, int head_dim, i
     p.heads_pow2_shift = shift;
     p.units = num_seqs * p.num_kv_heads * (group / gh);
     const int64_t units8 = (p.units + 7) / 8 * 8;
-    const PrefillShape shape = prefill_shape(units8, shift, max_q_len, p.window > 0, contig, num_cus());
+    const PrefillShape shape = kv8 ? prefill_shape(units8, shift, max_q_len, p.window > 0, contig, num_cus())
+                                   : prefill_shape_direct(units8, shift, max_q_len, head_dim, p.slopes != nullptr, p.window > 0, contig, num_cus());
     p.q_tiles = (int)prefill_q_tiles(shape == PrefillShape::k8Waves ? 8 : 4, shift, max_q_len);
     p.group = group;
     p.chunks = group / gh;

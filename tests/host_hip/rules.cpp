@@ -144,3 +144,8 @@ extern "C" int prefill_shape_of(int64_t units8, int shift, int max_q_len, int wi
 {
     return (int)prefill_shape(units8, shift, max_q_len, windowed, whole_prompts, cus);
 }
+
+extern "C" int prefill_shape_direct_of(int64_t units8, int shift, int max_q_len, int head_dim, int slopes, int windowed, int whole_prompts, int cus)
+{
+    return (int)prefill_shape_direct(units8, shift, max_q_len, head_dim, slopes, windowed, whole_prompts, cus);
+}
