@@ -57,6 +57,16 @@ namespace optgqa {
 // way the four rows that a group of 16 lanes transposes, and the next group's four, fall in distinct banks
 template <int D> struct FlatRow { static constexpr int kV = D + 16; };
 
+// Tiles that an 8-bit cache's units must have under the caller's bound on the lengths, one unit to a SIMD, for them to be that many and to take
+// two tiles at a time (PAIRS), head_dim 128.  A tile is half a 2-byte cache's bytes, its chain of widening, scores, softmax, V through LDS and output
+// products as long; tile by tile the chain sets one wave's pace, and two waves to a SIMD, which share it, stream less evenly than
+// one (the older runs ahead).  Two tiles' chains side by side keep one wave busy, with as many bytes on their way as a 2-byte
+// cache's.  Short units gain more from twice as many starting at once.  (Steps, tile by tile with two waves to a SIMD, and in pairs
+// with one, us: 64 sequences of 1 023-8 191, 32 / 4 heads, 66.6 and 62.6, of 8 191 97.2 and 90.0, 4 of 32 767, 64 / 8 heads, 57.3 and
+// 52.5, 32 of 500-2 000, 16 / 16, 39.6 and 38.2; 64 of 63-511, 32 / 8 heads, 19.1 and 20.1, 8 of 255-2 047 15.4 and 16.0 - what such
+// lengths also lose under a bound far above them; head_dim 64, 64 of 1 023-8 191: 39.0 and 44.9.)
+constexpr int kPairUnitTiles = 32;
+
 // What a wave can park in LDS before it has to write it out: the results of up to kStagePieces
 // pieces, kStageCols query-head columns in all (one piece of a shared prefix, two at 8 heads per KV
 // head, five at 4).  Sized so that two workgroups still fit a CU's LDS.
@@ -217,18 +227,23 @@ template <int D> struct FlatTile {
     uint4 k[D / 32];    // K: token j16, dims 32i + 8hg .. +7
     uint4 v[D / 32];    // V: token (512 / D) * r + lane / (D / 8), dims 8 * (lane % (D / 8)) .. +7
 };
-template <int D> struct FlatTile8 {
+template <int D, bool PAIRS> struct FlatTile8 {
     uint4 k[D / 64];    // K: token j16, dims 64j + 16hg .. +15
     uint2 v[D / 32];    // V: as above, 8 one-byte codes
 };
+template <int D> struct FlatTile8<D, true> {
+    uint4 k[D / 64];
+    uint4 v[D / 64];    // V: token (1024 / D) * r + lane / (D / 16), dims 16 * (lane % (D / 16)) .. +15
+};
 
-template <int DT, bool FUSED, bool KV8 = false, bool SHARED = false, int D = 128>
-__global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8 : OPTGQA_FLAT_WAVES_PER_SIMD) void paged_decode_flat_kernel(const DecodeParams p)
+template <int DT, bool FUSED, bool KV8 = false, bool SHARED = false, int D = 128, bool PAIRS = false>
+__global__ __launch_bounds__(kDecodeWaves * 64, PAIRS ? 1 : KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8 : OPTGQA_FLAT_WAVES_PER_SIMD) void paged_decode_flat_kernel(const DecodeParams p)
 {
     static_assert(D == 128 || D == 64, "head_dim 128 or 64");
     static_assert(!(SHARED && KV8), "shared prefixes: 2-byte caches");
+    static_assert(!PAIRS || KV8, "two tiles at a time: 8-bit caches");
     constexpr bool NEW_TILE = FUSED && !KV8;            // the new token is a tile of its own, read from k_new / v_new
-    typedef typename std::conditional<KV8, FlatTile8<D>, FlatTile<D>>::type Tile;
+    typedef typename std::conditional<KV8, FlatTile8<D, PAIRS>, FlatTile<D>>::type Tile;
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     constexpr int ES = KV8 ? 1 : 2;                     // bytes per cache element
     constexpr int TILE = kMmaTile;
@@ -253,6 +268,8 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
     const int j16 = lane & 15;
     const int hg = lane >> 4;
     const int vcol = lane % LPR, vrow0 = lane / LPR;    // this lane's piece of a V tile: rows RPL * r + vrow0, dims 8 * vcol .. +7
+
+    const int vcol8 = lane % (LPR / 2), vrow8 = lane / (LPR / 2);   // ... of an 8-bit cache's: 16 codes, twice as many rows to a load
 
     const int B = p.num_seqs, Y = p.segs_per_seq;
     const int NV = SHARED ? 2 * B : B;                  // (virtual) sequences of the flat order
@@ -449,8 +466,10 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
 #pragma unroll
             for (int j = 0; j < D / 64; ++j) Tl.k[j] = stream_load16(s.k + (ko + 64u * j));
 #pragma unroll
-            for (int r = 0; r < NVL; ++r)
-                Tl.v[r] = stream_load8(s.v + (min((uint32_t)(RPL * r + vrow0), last) * (uint32_t)D + 8u * (uint32_t)vcol));
+            for (int r = 0; r < (PAIRS ? NVL / 2 : NVL); ++r) {
+                if constexpr (PAIRS) Tl.v[r] = stream_load16(s.v + (min((uint32_t)(2 * RPL * r + vrow8), last) * (uint32_t)D + 16u * (uint32_t)vcol8));
+                else Tl.v[r] = stream_load8(s.v + (min((uint32_t)(RPL * r + vrow0), last) * (uint32_t)D + 8u * (uint32_t)vcol));
+            }
         } else {
 #pragma unroll
             for (int i = 0; i < NQ; ++i) Tl.k[i] = stream_load16(s.k + (ko + 64u * i));
@@ -497,8 +516,9 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
         if (p.slopes) sd = p.slopes[hh0 + col_h];
     };
 
-    Tile buf[2];
+    Tile buf[PAIRS ? 4 : 2];      // (two pairs of tiles, see the piece loop)
     TileSrc d0, d1;               // what buf[0] / buf[1] hold (or are receiving)
+    TileSrc d2, d3;               // in pairs: buf[2] / buf[3]
     u32x4 qa[NQ];
     float slope2;                 // ALiBi slope (base 2) of column j16
     bool col_ok;                  // column j16 is a head
@@ -569,6 +589,10 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
         if (!chained) {
             d0 = tile_src(table, head_off, lo, L, n, has_new, reg_end, new_k, new_v, tau);
             load_tile(buf[0], d0);
+            if constexpr (PAIRS) {
+                d1 = tile_src(table, head_off, lo, L, n, has_new, reg_end, new_k, new_v, tau + min(1, j_last));
+                load_tile(buf[1], d1);
+            }
         }
         // ---- side effects of the piece, none of which anything in this launch reads: its partial
         // result; the new token's K / V rows into the cache if the piece ends a KV head's segment (Alg. 2,
@@ -617,6 +641,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
         const int64_t x_new_k = !has_next ? new_k : NEW_TILE ? nseg.b * p.k_new_stride + (int64_t)by_chunks.div(ny) * D : 0;
         const int64_t x_new_v = !has_next ? new_v : NEW_TILE ? nseg.b * p.v_new_stride + (int64_t)by_chunks.div(ny) * D : 0;
         const int x_ti = has_next ? 0 : tau + j_last;
+        const int x_ti2 = has_next ? min(1, n_tau_end - 1) : x_ti;           // (in pairs: and the tile after that)
 
         // ---- both contractions on 16-bit MFMAs, transposed so that nothing is transposed in registers:
         //   S^T[token][head] = K Q^T : A = the K tile as fetched (lane (token j16, slab hg)), B = the query
@@ -676,7 +701,8 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
 #pragma unroll
             for (int r = 0; r < NVL; ++r) {
                 uint4 vr;
-                if constexpr (KV8) vr = widen8_e4m3<DT>(Tl.v[r].x, Tl.v[r].y);
+                if constexpr (PAIRS) vr = uint4{};                   // (never called)
+                else if constexpr (KV8) vr = widen8_e4m3<DT>(Tl.v[r].x, Tl.v[r].y);
                 else vr = Tl.v[r];
                 *reinterpret_cast<uint4*>(v_rows + (16 * ODD + RPL * r + vrow0) * kFlatVRow + 8 * vcol) = vr;
             }
@@ -730,46 +756,131 @@ __global__ __launch_bounds__(kDecodeWaves * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8
         // loads, so the number in flight at each use is a compile-time constant).  The first half
         // prefetches into buf[1], the second into buf[0]; past the end of the piece the second half
         // fetches the next piece's first tile, which is therefore always found in buf[0].
-        const int trips = (ntw + 1) >> 1;
-        for (int it = 0; it < trips; ++it) {
-            const int j = 2 * it;
-            d1 = tile_src(table, head_off, lo, L, n, has_new, reg_end, new_k, new_v, tau + min(j + 1, j_last));
-            load_tile(buf[1], d1);
-            if (it == 0) {
-                // The piece's query rows and slopes become operands only now: where they are loaded, the wave would wait for
-                // them, and for the tile that is on its way, before it asked for the next one.  (A memory round trip less
-                // before the first tile and at each later piece; with it the divisions by the host's numbers, the scan
-                // without shuffles and the combine kernel's loads all ahead of its first branch: 16 sequences of 255-2 047
-                // 22.0 -> 20.5 us, 64 of 1 023-8 191 109.1 -> 107.3, over 8-bit caches 67.1 -> 65.6, in pairs 83.2 -> 80.6,
-                // with a window of 1 024 32.4 -> 31.0, 4 of 32 768 in partitions of 512 90.9 -> 89.5.)
-                const uint32_t keep = col_ok ? 0xffffffffu : 0u;
+        // The piece's query rows and slopes become operands only once its second step's tiles are asked for: where they are
+        // loaded, the wave would wait for them, and for the tile that is on its way, before that.  (A memory round trip less
+        // before the first tile and at each later piece; with it the divisions by the host's numbers, the scan
+        // without shuffles and the combine kernel's loads all ahead of its first branch: 16 sequences of 255-2 047
+        // 22.0 -> 20.5 us, 64 of 1 023-8 191 109.1 -> 107.3, over 8-bit caches 67.1 -> 65.6, in pairs 83.2 -> 80.6,
+        // with a window of 1 024 32.4 -> 31.0, 4 of 32 768 in partitions of 512 90.9 -> 89.5.)
+        auto settle_q = [&]() __attribute__((always_inline)) {
+            const uint32_t keep = col_ok ? 0xffffffffu : 0u;
+#pragma unroll
+            for (int i = 0; i < NQ; ++i) {
+                asm volatile("" : "+v"(qa[i]));
+                qa[i] &= keep;
+            }
+            if (fx & 1) {                                    // (one more dependent load that must not hold up the second tile's)
+                const int blk = scalar_load_i32(table + (Lm1 >> bs_shift));
+                fx_row = blk * block_stride + head_off + (int64_t)(Lm1 & (bs - 1)) * D;
+            }
+            asm volatile("" : "+v"(slope2));
+            slope2 = col_ok ? slope2 * kLog2e : 0.f;
+        };
+        // two tiles of an 8-bit cache (the second one only if `both`: else it is the first one again, and nothing of it is visible)
+        auto compute_pair = [&](const Tile& t0, const Tile& t1, const TileSrc& s0, const TileSrc& s1, bool both) __attribute__((always_inline)) {
+            f32x4 S[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+            if constexpr (PAIRS) {
 #pragma unroll
                 for (int i = 0; i < NQ; ++i) {
-                    asm volatile("" : "+v"(qa[i]));
-                    qa[i] &= keep;
-                }
-                if (fx & 1) {                                // (one more dependent load that must not hold up the second tile's)
-                    const int blk = scalar_load_i32(table + (Lm1 >> bs_shift));
-                    fx_row = blk * block_stride + head_off + (int64_t)(Lm1 & (bs - 1)) * D;
-                }
-                asm volatile("" : "+v"(slope2));
-                slope2 = col_ok ? slope2 * kLog2e : 0.f;
-            }
-            compute_tile(buf[0], d0, std::false_type{});
-            const bool more = j + 2 <= j_last;
-            d0 = tile_src(more ? table : x_table, more ? head_off : x_head_off, more ? lo : x_lo, more ? L : x_L,
-                          more ? n : x_n, more ? has_new : x_has_new, more ? reg_end : x_reg_end,
-                          more ? new_k : x_new_k, more ? new_v : x_new_v, more ? tau + j + 2 : x_ti);
-            load_tile(buf[0], d0);
-            if (j + 1 <= j_last) {
-                compute_tile(buf[1], d1, std::true_type{});
-            } else {
-                // odd number of tiles: the last even tile has no partner; give it rows of zeros
 #pragma unroll
-                for (int r = 0; r < NVL; ++r)
-                    *reinterpret_cast<uint4*>(v_rows + (16 + RPL * r + vrow0) * kFlatVRow + 8 * vcol) = make_uint4(0u, 0u, 0u, 0u);
-                const float none[4] = {0.f, 0.f, 0.f, 0.f};
-                weighted_sum(pend, none);
+                    for (int t = 0; t < 2; ++t) {
+                        const uint4 kk = (t == 0 ? t0 : t1).k[i >> 1];
+                        S[t] = mfma_qk<DT>((i & 1) ? widen8_e4m3<DT>(kk.z, kk.w) : widen8_e4m3<DT>(kk.x, kk.y), __builtin_bit_cast(uint4, qa[i]), S[t]);
+                    }
+                }
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int r = 0; r < NVL / 2; ++r) {
+                        const uint4 codes = (t == 0 ? t0 : t1).v[r];
+                        uint4* const row = reinterpret_cast<uint4*>(v_rows + (16 * t + 2 * RPL * r + vrow8) * kFlatVRow + 16 * vcol8);
+                        row[0] = widen8_e4m3<DT>(codes.x, codes.y);
+                        row[1] = widen8_e4m3<DT>(codes.z, codes.w);
+                    }
+            }
+            float x[2][4];
+            bool need = false;
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const TileSrc& src = t == 0 ? s0 : s1;
+                const unsigned span = t == 0 || both ? src.span : 0;
+                const int tok = src.tok0 + 4 * hg, r0 = src.rel0 + 4 * hg;
+#pragma unroll
+                for (int v4 = 0; v4 < 4; ++v4) {
+                    const bool visible = (unsigned)(r0 + v4) < span;
+                    x[t][v4] = visible ? fmaf(S[t][v4], scale2, slope2 * (float)(tok + v4 - rel_pos)) : -INFINITY;        // eq. (3), base 2
+                    need |= x[t][v4] > m_ref + FlatSoftmax<DT>::kThreshold;
+                }
+            }
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(need) != 0, 0)) {   // rare: the reference moves lazily
+                float mx = -INFINITY;
+#pragma unroll
+                for (int v4 = 0; v4 < 4; ++v4) mx = fmaxf(mx, fmaxf(x[0][v4], x[1][v4]));
+                mx = fmaxf(mx, __shfl_xor(mx, 16));              // a head's tokens live in 4 lanes (hg)
+                mx = fmaxf(mx, __shfl_xor(mx, 32));
+                const float m_new = fmaxf(m_ref, mx + FlatSoftmax<DT>::kHeadroom);
+                const float alpha = fast_exp2(m_ref - m_new);    // 1 when unchanged, 0 on first use
+                m_ref = m_new;
+                lsum *= alpha;
+#pragma unroll
+                for (int e = 0; e < NDB; ++e) acc[e] *= alpha;
+            }
+            float w[2][4];
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int v4 = 0; v4 < 4; ++v4) w[t][v4] = fast_exp2(x[t][v4] - m_ref);                    // eq. (4) numerators
+            weighted_sum(w[0], w[1]);
+        };
+
+        const int trips = (ntw + 1) >> 1;
+        if (PAIRS) {
+            // 8-bit caches: two tiles at a time, the next two on their way.  (A tile is half the bytes, its chain of widening, scores,
+            // softmax, LDS and output products as long: tile by tile the chain, not the stream, set the pace.)
+            const int pairs = (ntw + 1) >> 1;
+            for (int it = 0; it < pairs; it += 2) {
+                const int j = 2 * it;
+                d2 = tile_src(table, head_off, lo, L, n, false, reg_end, 0, 0, tau + min(j + 2, j_last));
+                load_tile(buf[PAIRS ? 2 : 0], d2);
+                d3 = tile_src(table, head_off, lo, L, n, false, reg_end, 0, 0, tau + min(j + 3, j_last));
+                load_tile(buf[PAIRS ? 3 : 1], d3);
+                if (it == 0) settle_q();
+                compute_pair(buf[0], buf[1], d0, d1, j + 1 <= j_last);
+                const bool more = j + 4 <= j_last;
+                d0 = tile_src(more ? table : x_table, more ? head_off : x_head_off, more ? lo : x_lo, more ? L : x_L, more ? n : x_n,
+                              false, more ? reg_end : x_reg_end, 0, 0, more ? tau + j + 4 : x_ti);
+                load_tile(buf[0], d0);
+                d1 = tile_src(more ? table : x_table, more ? head_off : x_head_off, more ? lo : x_lo, more ? L : x_L, more ? n : x_n,
+                              false, more ? reg_end : x_reg_end, 0, 0, more ? tau + min(j + 5, j_last) : x_ti2);
+                load_tile(buf[1], d1);
+                if (j + 2 <= j_last) compute_pair(buf[PAIRS ? 2 : 0], buf[PAIRS ? 3 : 1], d2, d3, j + 3 <= j_last);
+            }
+        } else {
+            // Two tiles per trip; every half issues exactly one tile of loads (no branches around
+            // loads, so the number in flight at each use is a compile-time constant).  The first half
+            // prefetches into buf[1], the second into buf[0]; past the end of the piece the second half
+            // fetches the next piece's first tile, which is therefore always found in buf[0].
+            for (int it = 0; it < trips; ++it) {
+                const int j = 2 * it;
+                d1 = tile_src(table, head_off, lo, L, n, has_new, reg_end, new_k, new_v, tau + min(j + 1, j_last));
+                load_tile(buf[1], d1);
+                if (it == 0) settle_q();
+                compute_tile(buf[0], d0, std::false_type{});
+                const bool more = j + 2 <= j_last;
+                d0 = tile_src(more ? table : x_table, more ? head_off : x_head_off, more ? lo : x_lo, more ? L : x_L,
+                              more ? n : x_n, more ? has_new : x_has_new, more ? reg_end : x_reg_end,
+                              more ? new_k : x_new_k, more ? new_v : x_new_v, more ? tau + j + 2 : x_ti);
+                load_tile(buf[0], d0);
+                if (j + 1 <= j_last) {
+                    compute_tile(buf[1], d1, std::true_type{});
+                } else {
+                    // odd number of tiles: the last even tile has no partner; give it rows of zeros
+#pragma unroll
+                    for (int r = 0; r < NVL; ++r)
+                        *reinterpret_cast<uint4*>(v_rows + (16 + RPL * r + vrow0) * kFlatVRow + 8 * vcol) = make_uint4(0u, 0u, 0u, 0u);
+                    const float none[4] = {0.f, 0.f, 0.f, 0.f};
+                    weighted_sum(pend, none);
+                }
             }
         }
 
