@@ -89,9 +89,10 @@ constexpr int kPfByHeadTiles = 16;
 //   tiles             1           2           4           8           10          12          16          24
 //   head_dim 128  1.23-1.24   1.06-1.14   1.02-1.08   0.95-1.01   0.92-0.99   0.90-0.96   0.87-0.94   0.83-0.90
 //   head_dim 64   1.16        1.04-1.06   1.01-1.03   0.94-0.95   0.92-0.93   0.89-0.90   0.86-0.88   0.82-0.85
-// The lines date from a longer start, when shared and alone tied at 16 and 10 tiles; they do at 8 and 6 now, and walks in between
-// are up to 12 % slower than they could be.)
-template <int D> constexpr int kPfTwoGroupTiles = D == 128 ? 16 : 11;
+// Measured before tiles went to LDS directly, but for the lines' own place.  With 16 (11) tiles and with 11 (8), GPU time of one prompt or of 4 chunks
+// of 40, us: head_dim 128, prompts of 384 12.8 and 12.5, of 448 14.1 and 13.6, chunks that end at 352 13.4 and 13.0, at 480 16.5 and 15.5; head_dim 64,
+// prompts of 256 8.6 and 8.1, of 320 9.7 and 9.0; with 8 (6) as with 11 (8), but 256 at head_dim 128 10.4 instead of 10.3.)
+template <int D> constexpr int kPfTwoGroupTiles = D == 128 ? 11 : 8;
 
 struct PrefillParams {
     void* out;                  // [T][Hq][D] dtype
