@@ -21,7 +21,7 @@ BUILD_DIR = os.path.join(ROOT, "_build")
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    "-Wno-unused-command-line-argument",
+    "-Wno-unused-command-line-argument", "-Werror=inline-asm",
 ]
 
 

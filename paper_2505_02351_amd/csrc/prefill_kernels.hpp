@@ -188,14 +188,16 @@ template <int D> struct PfDirect {
 
 // One such load, to LDS address `lds` (wave-uniform) on; from a wave-uniform base and lane offsets, or from lane addresses.
 // In assembly because the compiler, which does not know which buffer a load writes, would have every later read of LDS wait
-// for it; wait_direct() comes before the barrier that publishes the tile.
+// for it; wait_direct() comes before the barrier that publishes the tile.  (m0 is an operand, which the compiler sets: it is a
+// reserved register, and a statement that writes it by itself is not one that the compiler allows for.  The s_nop is the wait
+// state between that and the load.)
 __device__ __forceinline__ void load_direct(uint32_t lds, const unsigned char* base, uint32_t lane_off)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds), "v"(lane_off), "s"(base) : "memory", "m0");
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "{m0}"(lds), "v"(lane_off), "s"(base) : "memory");
 }
 __device__ __forceinline__ void load_direct(uint32_t lds, const unsigned char* lane_addr)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds), "v"(lane_addr) : "memory", "m0");
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "{m0}"(lds), "v"(lane_addr) : "memory");
 }
 __device__ __forceinline__ void wait_direct() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
