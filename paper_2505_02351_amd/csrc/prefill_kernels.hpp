@@ -55,6 +55,7 @@
 #include <type_traits>
 
 #include "decode_mma_kernels.hpp"
+#include "prefill_shape.hpp"
 
 namespace optgqa {
 
@@ -491,7 +492,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
             base += (uint64_t)(uint32_t)key * (uint32_t)l_row;
         } else {
             const int block = min(key, kmax - 1) >> bs_shift;
-            if (__builtin_expect(d_block - block > 63, 0)) {
+            if (__builtin_expect(!held_blocks_reach(d_block, block), 0)) {
                 read_table(block);
                 asm volatile("" : "+v"(d_table));                // (waited for here, not on the way that reads no table)
             }

@@ -1,8 +1,12 @@
-// Which workgroup shape a prefill launch takes: host code, nothing of HIP.
+// Which workgroup shape a prefill launch takes, and which block numbers a wave holds: nothing of HIP.
 #pragma once
 #include <stdint.h>
 
 namespace optgqa {
+
+// Lane l of a wave holds the number of its sequence's block `first` - l: whether one holds that of `block` (lane first - block).
+// A walk goes down the blocks, but where it is started anew after loads were asked for further on, it may go up.
+constexpr bool held_blocks_reach(int first, int block) { return (uint32_t)first - (uint32_t)block < 64u; }
 
 // Shapes of a prefill workgroup (see prefill_kernels.hpp): 128 rows, 256 rows, or 128 rows whose keys are
 // shared out between two groups of four waves.

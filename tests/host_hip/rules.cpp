@@ -149,3 +149,22 @@ extern "C" int prefill_shape_direct_of(int64_t units8, int shift, int max_q_len,
 {
     return (int)prefill_shape_direct(units8, shift, max_q_len, head_dim, slopes, windowed, whole_prompts, cus);
 }
+
+// The blocks that a wave would read, one after the other, through the numbers that its lanes hold (block n of the sequence: number
+// n + 1000; read anew where they do not reach).  Returns the first that it would find wrong, or -1.
+extern "C" int held_blocks_differ(const int32_t* blocks, int n, int* reads)
+{
+    int first = blocks[0], lanes[64];
+    auto read = [&](int block) {
+        first = block;
+        for (int l = 0; l < 64; ++l) lanes[l] = (block - l > 0 ? block - l : 0) + 1000;
+        ++*reads;
+    };
+    *reads = 0;
+    read(first);
+    for (int i = 0; i < n; ++i) {
+        if (!held_blocks_reach(first, blocks[i])) read(blocks[i]);
+        if (lanes[(first - blocks[i]) & 63] != blocks[i] + 1000) return i;
+    }
+    return -1;
+}

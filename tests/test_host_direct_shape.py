@@ -1,7 +1,9 @@
-"""CPU: the workgroup shape of a prefill launch whose tiles go to LDS directly, against the general rule's."""
+"""CPU: the workgroup shape of a prefill launch whose tiles go to LDS directly, against the general rule's; the block numbers that
+a wave of it holds."""
 import ctypes
 import random
 
+import numpy as np
 import pytest
 
 from test_host_rules import lib, shape  # noqa: F401  (lib: a fixture)
@@ -35,3 +37,21 @@ def test_two_groups_and_windows_are_the_general_rules(lib):
         got = direct(lib, *args, D=rng.choice([64, 128]), slopes=rng.random() < 0.5, windowed=windowed, cus=cus)
         any_ = shape(lib, *args, windowed=windowed, cus=cus)
         assert (got == "two") == (any_ == "two") and (not windowed or got == any_)
+
+
+@pytest.mark.parametrize("back", [0, 1, 2, 5, 100])             # blocks that a walk started anew may go back by
+def test_held_block_numbers(lib, back):
+    """Down the blocks by 1 to 4 at a time, now and then on by many, or back by a few: the right number each time."""
+    rng = random.Random(back)
+    for _ in range(300):
+        at = rng.randint(0, 3000)
+        walk, step = [at], rng.randint(1, 4)
+        while at > 0:
+            at -= rng.randint(5, 300) if rng.random() < 0.02 else step
+            if back and rng.random() < 0.05:
+                at = min(at + rng.randint(1, back), walk[0])
+            at = max(at, 0)
+            walk.append(at)
+        blocks, reads = np.array(walk, np.int32), ctypes.c_int()
+        assert lib.held_blocks_differ(ctypes.c_void_p(blocks.ctypes.data), len(blocks), ctypes.byref(reads)) == -1
+        assert back or reads.value <= 1 + walk[0] // 64
