@@ -57,15 +57,8 @@ namespace optgqa {
 // way the four rows that a group of 16 lanes transposes, and the next group's four, fall in distinct banks
 template <int D> struct FlatRow { static constexpr int kV = D + 16; };
 
-// Tiles that an 8-bit cache's units must have under the caller's bound on the lengths, one unit to a SIMD, for them to be that many and to take
-// two tiles at a time (PAIRS), head_dim 128.  A tile is half a 2-byte cache's bytes, its chain of widening, scores, softmax, V through LDS and output
-// products as long; tile by tile the chain sets one wave's pace, and two waves to a SIMD, which share it, stream less evenly than
-// one (the older runs ahead).  Two tiles' chains side by side keep one wave busy, with as many bytes on their way as a 2-byte
-// cache's.  Short units gain more from twice as many starting at once.  (Steps, tile by tile with two waves to a SIMD, and in pairs
-// with one, us: 64 sequences of 1 023-8 191, 32 / 4 heads, 66.6 and 62.6, of 8 191 97.2 and 90.0, 4 of 32 767, 64 / 8 heads, 57.3 and
-// 52.5, 32 of 500-2 000, 16 / 16, 39.6 and 38.2; 64 of 63-511, 32 / 8 heads, 19.1 and 20.1, 8 of 255-2 047 15.4 and 16.0 - what such
-// lengths also lose under a bound far above them; head_dim 64, 64 of 1 023-8 191: 39.0 and 44.9.)
-constexpr int kPairUnitTiles = 32;
+// Waves of a workgroup (CHOICE: see the kernel).
+template <bool CHOICE> struct FlatWaves { static constexpr int value = CHOICE ? 2 * kDecodeWaves : kDecodeWaves; };
 
 // What a wave can park in LDS before it has to write it out: the results of up to kStagePieces
 // pieces, kStageCols query-head columns in all (one piece of a shared prefix, two at 8 heads per KV
@@ -236,54 +229,19 @@ template <int D> struct FlatTile8<D, true> {
     uint4 v[D / 64];    // V: token (1024 / D) * r + lane / (D / 16), dims 16 * (lane % (D / 16)) .. +15
 };
 
-template <int DT, bool FUSED, bool KV8 = false, bool SHARED = false, int D = 128, bool PAIRS = false>
-__global__ __launch_bounds__(kDecodeWaves * 64, PAIRS ? 1 : KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8 : OPTGQA_FLAT_WAVES_PER_SIMD) void paged_decode_flat_kernel(const DecodeParams p)
+// What a wave finds its place by: lane i's chunk of the k = ceil(sequences / 64) (virtual) sequences from i * k on - its tiles, and with
+// up to 64 sequences their extents.
+struct FlatPlace {
+    int mine, incl;             // tiles of the chunk; of the chunks up to it
+    int len, shared, even;      // up to 64 sequences, lane i's: length; SHARED: tokens of the bundle's prefix, the prefix's tiles (its leader)
+};
+
+template <bool FUSED, bool KV8, bool SHARED> __device__ __forceinline__ FlatPlace flat_place(const DecodeParams& p, int lane)
 {
-    static_assert(D == 128 || D == 64, "head_dim 128 or 64");
-    static_assert(!(SHARED && KV8), "shared prefixes: 2-byte caches");
-    static_assert(!PAIRS || KV8, "two tiles at a time: 8-bit caches");
-    constexpr bool NEW_TILE = FUSED && !KV8;            // the new token is a tile of its own, read from k_new / v_new
-    typedef typename std::conditional<KV8, FlatTile8<D, PAIRS>, FlatTile<D>>::type Tile;
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    constexpr int ES = KV8 ? 1 : 2;                     // bytes per cache element
     constexpr int TILE = kMmaTile;
-    constexpr int kFlatVRow = FlatRow<D>::kV;
-    constexpr int NQ = D / 32;                          // score MFMAs per tile (32 dims each)
-    constexpr int NDB = D / 16;                         // 16-dim blocks of the output
-    constexpr int LPR = D / 8;                          // lanes that fetch one V row (8 elements each)
-    constexpr int RPL = 64 / LPR;                       // V rows per load
-    constexpr int NVL = TILE / RPL;                     // V loads per tile
-    static_assert(kMmaBufs == 2, "two register tile buffers: one in use, one in flight");
-
-    // per wave: the V rows of two consecutive tiles (32 tokens) in their natural [token][dim] layout
-    __shared__ __attribute__((aligned(16))) uint16_t v_lds[kDecodeWaves][2 * TILE][kFlatVRow];
-    // per wave: what finished pieces leave behind, parked until the unit ends (see "side effects" below)
-    constexpr int SROW = D + 4;                         // floats per parked column: D outputs, reference, weight sum; the
-                                                        // odd stride spreads the columns over the LDS banks
-    __shared__ __attribute__((aligned(16))) float st_lds[kDecodeWaves][kStageCols * SROW];
-    __shared__ int st_hdr[kDecodeWaves][kStagePieces][kStageHdrInts];
-
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int j16 = lane & 15;
-    const int hg = lane >> 4;
-    const int vcol = lane % LPR, vrow0 = lane / LPR;    // this lane's piece of a V tile: rows RPL * r + vrow0, dims 8 * vcol .. +7
-
-    const int vcol8 = lane % (LPR / 2), vrow8 = lane / (LPR / 2);   // ... of an 8-bit cache's: 16 codes, twice as many rows to a load
-
-    const int B = p.num_seqs, Y = p.segs_per_seq;
-    const int NV = SHARED ? 2 * B : B;                  // (virtual) sequences of the flat order
-    const int Hq = p.num_heads, Hkv = p.num_kv_heads, bs = p.block_size;
-    const int bs_shift = __builtin_ctz(bs);
-    const int GH = p.heads_per_wg;
-    const FastDiv by_chunks = p.by_chunks;
-    const int G = p.group, chunks = p.chunks;
-    const int CS = SHARED ? 16 : GH;                    // columns (query heads) per partial-result slot
-    const int u = blockIdx.x * kDecodeWaves + wave;
+    const int B = p.num_seqs, NV = SHARED ? 2 * B : B, W = p.window, bs = p.block_size;
     const int32_t* __restrict__ ctx = p.context_lens;
-    const int W = p.window;
-
-    // ---- where does this unit start?  level 1: lane i sums the tiles of sequences [i*k, (i+1)*k)
+    // ---- where does a unit start?  level 1: lane i sums the tiles of sequences [i*k, (i+1)*k)
     const int k = (NV + 63) >> 6;
     int mine = 0, my_len = 0;
     // Up to 64 sequences: lane i holds sequence i's length (and, SHARED, how many of its tokens are its
@@ -328,6 +286,60 @@ __global__ __launch_bounds__(kDecodeWaves * 64, PAIRS ? 1 : KV8 ? OPTGQA_FLAT_WG
             }
         }
     }
+    return FlatPlace{mine, wave_inclusive_scan(mine, lane), my_len, my_shared, my_even};
+}
+
+// Per wave, in LDS: the V rows of two consecutive tiles (32 tokens) in their natural [token][dim] layout, and what finished pieces
+// leave behind, parked until the unit ends (see "side effects" below).
+template <int D> struct FlatWave {
+    static constexpr int kStageRow = D + 4;             // floats per parked column: D outputs, reference, weight sum; the
+                                                        // odd stride spreads the columns over the LDS banks
+    __attribute__((aligned(16))) uint16_t v[2 * kMmaTile][FlatRow<D>::kV];
+    __attribute__((aligned(16))) float stage[kStageCols * kStageRow];
+    int hdr[kStagePieces][kStageHdrInts];
+};
+
+// Unit u of c tiles each (PAIRS: two tiles at a time, see decode_split.hpp).
+template <int DT, bool FUSED, bool KV8, bool SHARED, int D, bool PAIRS>
+__device__ __forceinline__ void flat_unit(const DecodeParams& p, FlatWave<D>& lds, const FlatPlace& place, int u, int c, int T)
+{
+    static_assert(D == 128 || D == 64, "head_dim 128 or 64");
+    static_assert(!(SHARED && KV8), "shared prefixes: 2-byte caches");
+    static_assert(!PAIRS || KV8, "two tiles at a time: 8-bit caches");
+    constexpr bool NEW_TILE = FUSED && !KV8;            // the new token is a tile of its own, read from k_new / v_new
+    typedef typename std::conditional<KV8, FlatTile8<D, PAIRS>, FlatTile<D>>::type Tile;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int ES = KV8 ? 1 : 2;                     // bytes per cache element
+    constexpr int TILE = kMmaTile;
+    constexpr int kFlatVRow = FlatRow<D>::kV;
+    constexpr int NQ = D / 32;                          // score MFMAs per tile (32 dims each)
+    constexpr int NDB = D / 16;                         // 16-dim blocks of the output
+    constexpr int LPR = D / 8;                          // lanes that fetch one V row (8 elements each)
+    constexpr int RPL = 64 / LPR;                       // V rows per load
+    constexpr int NVL = TILE / RPL;                     // V loads per tile
+    constexpr int SROW = FlatWave<D>::kStageRow;
+    static_assert(kMmaBufs == 2, "two register tile buffers: one in use, one in flight");
+
+    const int lane = threadIdx.x & 63;
+    const int j16 = lane & 15;
+    const int hg = lane >> 4;
+    const int vcol = lane % LPR, vrow0 = lane / LPR;    // this lane's piece of a V tile: rows RPL * r + vrow0, dims 8 * vcol .. +7
+
+    const int vcol8 = lane % (LPR / 2), vrow8 = lane / (LPR / 2);   // ... of an 8-bit cache's: 16 codes, twice as many rows to a load
+
+    const int B = p.num_seqs, Y = p.segs_per_seq;
+    const int NV = SHARED ? 2 * B : B;                  // (virtual) sequences of the flat order
+    const int Hq = p.num_heads, Hkv = p.num_kv_heads, bs = p.block_size;
+    const int bs_shift = __builtin_ctz(bs);
+    const int GH = p.heads_per_wg;
+    const FastDiv by_chunks = p.by_chunks;
+    const int G = p.group, chunks = p.chunks;
+    const int CS = SHARED ? 16 : GH;                    // columns (query heads) per partial-result slot
+    const int32_t* __restrict__ ctx = p.context_lens;
+    const int W = p.window;
+    const int k = (NV + 63) >> 6;
+    const bool in_lanes = B <= 64;
+    const int mine = place.mine, incl = place.incl, my_len = place.len, my_shared = place.shared, my_even = place.even;
     // the segments of (virtual) sequence v, a scalar
     auto seg_at = [&](int v) __attribute__((always_inline)) {
         if (!in_lanes) return flat_seg<FUSED, KV8, SHARED, true>(p, v);
@@ -354,10 +366,6 @@ __global__ __launch_bounds__(kDecodeWaves * 64, PAIRS ? 1 : KV8 ? OPTGQA_FLAT_WG
         }
         return s;
     };
-    const int incl = wave_inclusive_scan(mine, lane);
-    const int P_total = __builtin_amdgcn_readlane(incl, 63);
-    const int T = Y * P_total;
-    const int c = max(p.min_unit_tiles, p.by_units.div(T + p.num_units - 1));
     const int f0 = u * c;
     const int f1 = min(f0 + c, T);
     if (f0 >= f1) return;                                   // no workgroup-wide barrier below
@@ -516,9 +524,9 @@ __global__ __launch_bounds__(kDecodeWaves * 64, PAIRS ? 1 : KV8 ? OPTGQA_FLAT_WG
         if (p.slopes) sd = p.slopes[hh0 + col_h];
     };
 
-    Tile buf[PAIRS ? 4 : 2];      // (two pairs of tiles, see the piece loop)
-    TileSrc d0, d1;               // what buf[0] / buf[1] hold (or are receiving)
-    TileSrc d2, d3;               // in pairs: buf[2] / buf[3]
+    constexpr int kBufs = PAIRS ? 4 : 2;                // (two pairs of tiles, see the piece loop)
+    Tile buf[kBufs];
+    TileSrc src[kBufs];           // what they hold (or are receiving)
     u32x4 qa[NQ];
     float slope2;                 // ALiBi slope (base 2) of column j16
     bool col_ok;                  // column j16 is a head
@@ -540,14 +548,14 @@ __global__ __launch_bounds__(kDecodeWaves * 64, PAIRS ? 1 : KV8 ? OPTGQA_FLAT_WG
     };
     auto flush = [&](int count) __attribute__((always_inline)) {
         for (int k = 0; k < count; ++k) {
-            const int* h = &st_hdr[wave][k][0];
+            const int* h = &lds.hdr[k][0];
             const int64_t slot = (int64_t)(((uint64_t)(uint32_t)h[1] << 32) | (uint32_t)h[0]);
             const int ncols = h[2];
             side_effects(h[3], (int64_t)(((uint64_t)(uint32_t)h[5] << 32) | (uint32_t)h[4]),
                          (int64_t)(((uint64_t)(uint32_t)h[7] << 32) | (uint32_t)h[6]),
                          (int64_t)(((uint64_t)(uint32_t)h[9] << 32) | (uint32_t)h[8]), h[10], h[11]);
             if (j16 < ncols) {
-                const float* st = &st_lds[wave][0] + (h[12] + j16) * SROW;
+                const float* st = &lds.stage[0] + (h[12] + j16) * SROW;
                 const int64_t e0 = slot * CS + j16;
                 if (hg == 0) {
                     p.ws_m[e0] = st[D];
@@ -561,7 +569,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, PAIRS ? 1 : KV8 ? OPTGQA_FLAT_WG
         }
     };
     int staged = 0, staged_cols = 0;    // pieces parked in LDS, and the columns they take
-    bool chained = false;         // buf[0] / d0 were filled by the previous piece
+    bool chained = false;         // the first tile (in pairs: two) was asked for by the previous piece
     int f = f0;
     for (;;) {
         // ---- one piece: tiles [tau, tau_end) of segment (v, y) -------------------------------
@@ -587,11 +595,11 @@ __global__ __launch_bounds__(kDecodeWaves * 64, PAIRS ? 1 : KV8 ? OPTGQA_FLAT_WG
 
         load_q(qa, slope2, q_pos, col_ok, seg.b, seg.L, seg.shared != 0, y);
         if (!chained) {
-            d0 = tile_src(table, head_off, lo, L, n, has_new, reg_end, new_k, new_v, tau);
-            load_tile(buf[0], d0);
+            src[0] = tile_src(table, head_off, lo, L, n, has_new, reg_end, new_k, new_v, tau);
+            load_tile(buf[0], src[0]);
             if constexpr (PAIRS) {
-                d1 = tile_src(table, head_off, lo, L, n, has_new, reg_end, new_k, new_v, tau + min(1, j_last));
-                load_tile(buf[1], d1);
+                src[1] = tile_src(table, head_off, lo, L, n, has_new, reg_end, new_k, new_v, tau + min(1, j_last));
+                load_tile(buf[1], src[1]);
             }
         }
         // ---- side effects of the piece, none of which anything in this launch reads: its partial
@@ -657,7 +665,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, PAIRS ? 1 : KV8 ? OPTGQA_FLAT_WG
         f32x4 acc[NDB];                       // O^T: dims 16db + 4hg + v of head j16
 #pragma unroll
         for (int e = 0; e < NDB; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
-        uint16_t* const v_rows = &v_lds[wave][0][0];
+        uint16_t* const v_rows = &lds.v[0][0];
         typedef short i16x4 __attribute__((ext_vector_type(4)));
         typedef __attribute__((address_space(3))) i16x4* lds_i16x4_ptr;
         // position the ALiBi term is relative to: the segment's sequence, or (shared prefix) the column's
@@ -701,8 +709,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, PAIRS ? 1 : KV8 ? OPTGQA_FLAT_WG
 #pragma unroll
             for (int r = 0; r < NVL; ++r) {
                 uint4 vr;
-                if constexpr (PAIRS) vr = uint4{};                   // (never called)
-                else if constexpr (KV8) vr = widen8_e4m3<DT>(Tl.v[r].x, Tl.v[r].y);
+                if constexpr (KV8) vr = widen8_e4m3<DT>(Tl.v[r].x, Tl.v[r].y);
                 else vr = Tl.v[r];
                 *reinterpret_cast<uint4*>(v_rows + (16 * ODD + RPL * r + vrow0) * kFlatVRow + 8 * vcol) = vr;
             }
@@ -752,10 +759,6 @@ __global__ __launch_bounds__(kDecodeWaves * 64, PAIRS ? 1 : KV8 ? OPTGQA_FLAT_WG
             }
         };
 
-        // Two tiles per trip; every half issues exactly one tile of loads (no branches around
-        // loads, so the number in flight at each use is a compile-time constant).  The first half
-        // prefetches into buf[1], the second into buf[0]; past the end of the piece the second half
-        // fetches the next piece's first tile, which is therefore always found in buf[0].
         // The piece's query rows and slopes become operands only once its second step's tiles are asked for: where they are
         // loaded, the wave would wait for them, and for the tile that is on its way, before that.  (A memory round trip less
         // before the first tile and at each later piece; with it the divisions by the host's numbers, the scan
@@ -777,27 +780,25 @@ __global__ __launch_bounds__(kDecodeWaves * 64, PAIRS ? 1 : KV8 ? OPTGQA_FLAT_WG
             slope2 = col_ok ? slope2 * kLog2e : 0.f;
         };
         // two tiles of an 8-bit cache (the second one only if `both`: else it is the first one again, and nothing of it is visible)
-        auto compute_pair = [&](const Tile& t0, const Tile& t1, const TileSrc& s0, const TileSrc& s1, bool both) __attribute__((always_inline)) {
+        auto compute_pair = [&](const auto& t0, const auto& t1, const TileSrc& s0, const TileSrc& s1, bool both) __attribute__((always_inline)) {
             f32x4 S[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-            if constexpr (PAIRS) {
 #pragma unroll
-                for (int i = 0; i < NQ; ++i) {
+            for (int i = 0; i < NQ; ++i) {
 #pragma unroll
-                    for (int t = 0; t < 2; ++t) {
-                        const uint4 kk = (t == 0 ? t0 : t1).k[i >> 1];
-                        S[t] = mfma_qk<DT>((i & 1) ? widen8_e4m3<DT>(kk.z, kk.w) : widen8_e4m3<DT>(kk.x, kk.y), __builtin_bit_cast(uint4, qa[i]), S[t]);
-                    }
+                for (int t = 0; t < 2; ++t) {
+                    const uint4 kk = (t == 0 ? t0 : t1).k[i >> 1];
+                    S[t] = mfma_qk<DT>((i & 1) ? widen8_e4m3<DT>(kk.z, kk.w) : widen8_e4m3<DT>(kk.x, kk.y), __builtin_bit_cast(uint4, qa[i]), S[t]);
                 }
-#pragma unroll
-                for (int t = 0; t < 2; ++t)
-#pragma unroll
-                    for (int r = 0; r < NVL / 2; ++r) {
-                        const uint4 codes = (t == 0 ? t0 : t1).v[r];
-                        uint4* const row = reinterpret_cast<uint4*>(v_rows + (16 * t + 2 * RPL * r + vrow8) * kFlatVRow + 16 * vcol8);
-                        row[0] = widen8_e4m3<DT>(codes.x, codes.y);
-                        row[1] = widen8_e4m3<DT>(codes.z, codes.w);
-                    }
             }
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int r = 0; r < NVL / 2; ++r) {
+                    const uint4 codes = (t == 0 ? t0 : t1).v[r];
+                    uint4* const row = reinterpret_cast<uint4*>(v_rows + (16 * t + 2 * RPL * r + vrow8) * kFlatVRow + 16 * vcol8);
+                    row[0] = widen8_e4m3<DT>(codes.x, codes.y);
+                    row[1] = widen8_e4m3<DT>(codes.z, codes.w);
+                }
             float x[2][4];
             bool need = false;
 #pragma unroll
@@ -833,46 +834,45 @@ __global__ __launch_bounds__(kDecodeWaves * 64, PAIRS ? 1 : KV8 ? OPTGQA_FLAT_WG
             weighted_sum(w[0], w[1]);
         };
 
-        const int trips = (ntw + 1) >> 1;
-        if (PAIRS) {
+        if constexpr (PAIRS) {
             // 8-bit caches: two tiles at a time, the next two on their way.  (A tile is half the bytes, its chain of widening, scores,
-            // softmax, LDS and output products as long: tile by tile the chain, not the stream, set the pace.)
-            const int pairs = (ntw + 1) >> 1;
-            for (int it = 0; it < pairs; it += 2) {
-                const int j = 2 * it;
-                d2 = tile_src(table, head_off, lo, L, n, false, reg_end, 0, 0, tau + min(j + 2, j_last));
-                load_tile(buf[PAIRS ? 2 : 0], d2);
-                d3 = tile_src(table, head_off, lo, L, n, false, reg_end, 0, 0, tau + min(j + 3, j_last));
-                load_tile(buf[PAIRS ? 3 : 1], d3);
-                if (it == 0) settle_q();
-                compute_pair(buf[0], buf[1], d0, d1, j + 1 <= j_last);
+            // softmax, LDS and output products as long: tile by tile the chain, not the stream, set the pace.)  Past the end of the
+            // piece the second half fetches the next piece's first two tiles, always into buf[0] and buf[1].
+            for (int j = 0; j <= j_last; j += 4) {
+                src[2] = tile_src(table, head_off, lo, L, n, false, reg_end, 0, 0, tau + min(j + 2, j_last));
+                load_tile(buf[2], src[2]);
+                src[3] = tile_src(table, head_off, lo, L, n, false, reg_end, 0, 0, tau + min(j + 3, j_last));
+                load_tile(buf[3], src[3]);
+                if (j == 0) settle_q();
+                compute_pair(buf[0], buf[1], src[0], src[1], j + 1 <= j_last);
                 const bool more = j + 4 <= j_last;
-                d0 = tile_src(more ? table : x_table, more ? head_off : x_head_off, more ? lo : x_lo, more ? L : x_L, more ? n : x_n,
-                              false, more ? reg_end : x_reg_end, 0, 0, more ? tau + j + 4 : x_ti);
-                load_tile(buf[0], d0);
-                d1 = tile_src(more ? table : x_table, more ? head_off : x_head_off, more ? lo : x_lo, more ? L : x_L, more ? n : x_n,
-                              false, more ? reg_end : x_reg_end, 0, 0, more ? tau + min(j + 5, j_last) : x_ti2);
-                load_tile(buf[1], d1);
-                if (j + 2 <= j_last) compute_pair(buf[PAIRS ? 2 : 0], buf[PAIRS ? 3 : 1], d2, d3, j + 3 <= j_last);
+                src[0] = tile_src(more ? table : x_table, more ? head_off : x_head_off, more ? lo : x_lo, more ? L : x_L, more ? n : x_n,
+                                  false, more ? reg_end : x_reg_end, 0, 0, more ? tau + j + 4 : x_ti);
+                load_tile(buf[0], src[0]);
+                src[1] = tile_src(more ? table : x_table, more ? head_off : x_head_off, more ? lo : x_lo, more ? L : x_L, more ? n : x_n,
+                                  false, more ? reg_end : x_reg_end, 0, 0, more ? tau + min(j + 5, j_last) : x_ti2);
+                load_tile(buf[1], src[1]);
+                if (j + 2 <= j_last) compute_pair(buf[2], buf[3], src[2], src[3], j + 3 <= j_last);
             }
         } else {
             // Two tiles per trip; every half issues exactly one tile of loads (no branches around
             // loads, so the number in flight at each use is a compile-time constant).  The first half
             // prefetches into buf[1], the second into buf[0]; past the end of the piece the second half
             // fetches the next piece's first tile, which is therefore always found in buf[0].
+            const int trips = (ntw + 1) >> 1;
             for (int it = 0; it < trips; ++it) {
                 const int j = 2 * it;
-                d1 = tile_src(table, head_off, lo, L, n, has_new, reg_end, new_k, new_v, tau + min(j + 1, j_last));
-                load_tile(buf[1], d1);
+                src[1] = tile_src(table, head_off, lo, L, n, has_new, reg_end, new_k, new_v, tau + min(j + 1, j_last));
+                load_tile(buf[1], src[1]);
                 if (it == 0) settle_q();
-                compute_tile(buf[0], d0, std::false_type{});
+                compute_tile(buf[0], src[0], std::false_type{});
                 const bool more = j + 2 <= j_last;
-                d0 = tile_src(more ? table : x_table, more ? head_off : x_head_off, more ? lo : x_lo, more ? L : x_L,
-                              more ? n : x_n, more ? has_new : x_has_new, more ? reg_end : x_reg_end,
-                              more ? new_k : x_new_k, more ? new_v : x_new_v, more ? tau + j + 2 : x_ti);
-                load_tile(buf[0], d0);
+                src[0] = tile_src(more ? table : x_table, more ? head_off : x_head_off, more ? lo : x_lo, more ? L : x_L,
+                                  more ? n : x_n, more ? has_new : x_has_new, more ? reg_end : x_reg_end,
+                                  more ? new_k : x_new_k, more ? new_v : x_new_v, more ? tau + j + 2 : x_ti);
+                load_tile(buf[0], src[0]);
                 if (j + 1 <= j_last) {
-                    compute_tile(buf[1], d1, std::true_type{});
+                    compute_tile(buf[1], src[1], std::true_type{});
                 } else {
                     // odd number of tiles: the last even tile has no partner; give it rows of zeros
 #pragma unroll
@@ -894,7 +894,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, PAIRS ? 1 : KV8 ? OPTGQA_FLAT_WG
                 staged = staged_cols = 0;
             }
             if (j16 < ncols) {
-                float* st = &st_lds[wave][0] + (staged_cols + j16) * SROW;
+                float* st = &lds.stage[0] + (staged_cols + j16) * SROW;
 #pragma unroll
                 for (int db = 0; db < NDB; ++db)
                     *reinterpret_cast<float4*>(st + 16 * db + 4 * hg) = make_float4(acc[db][0], acc[db][1], acc[db][2], acc[db][3]);
@@ -904,7 +904,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, PAIRS ? 1 : KV8 ? OPTGQA_FLAT_WG
                 }
             }
             if (lane == 0) {
-                int* h = &st_hdr[wave][staged][0];
+                int* h = &lds.hdr[staged][0];
                 h[0] = (int)(uint32_t)slot, h[1] = (int)(slot >> 32), h[2] = ncols, h[3] = fx;
                 h[4] = (int)(uint32_t)fx_row, h[5] = (int)(fx_row >> 32);
                 h[6] = (int)(uint32_t)new_k, h[7] = (int)(new_k >> 32);
@@ -939,6 +939,32 @@ __global__ __launch_bounds__(kDecodeWaves * 64, PAIRS ? 1 : KV8 ? OPTGQA_FLAT_WG
         v = nv, y = ny, seg = nseg, tau = 0;
         chained = true;
     }
+}
+
+// CHOICE (8-bit caches, workgroups of twice as many waves, one to a CU): where the tiles reach p.pairs_from, half of the waves end at
+// once, and the others take half as many units, two tiles at a time.  (Two workgroups of four waves to a CU, of which half end:
+// the dispatcher does not leave one on every CU, 62.6 -> 64-66 us for 64 sequences of 1 023-8 191, 32 / 4 heads.)  Without that, neighbouring units
+// share a workgroup, unless there are too few to give every CU four.
+template <int DT, bool FUSED, bool KV8 = false, bool SHARED = false, int D = 128, bool CHOICE = false>
+__global__ __launch_bounds__(FlatWaves<CHOICE>::value * 64, KV8 ? OPTGQA_FLAT_WGS_PER_CU_KV8 : OPTGQA_FLAT_WAVES_PER_SIMD) void paged_decode_flat_kernel(const DecodeParams p)
+{
+    __shared__ FlatWave<D> lds[FlatWaves<CHOICE>::value];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const FlatPlace place = flat_place<FUSED, KV8, SHARED>(p, threadIdx.x & 63);
+    const int T = p.segs_per_seq * __builtin_amdgcn_readlane(place.incl, 63);
+    const int c = p.by_units.div(T + p.num_units - 1);
+    int u = blockIdx.x * kDecodeWaves + wave;
+    if constexpr (CHOICE) {
+        if (__builtin_expect(T >= p.pairs_from, 0)) {        // (behind the other way in the code: long units make up for the jump)
+            // tiles divided by half of the units, rounded up
+            const int c2 = 2 * c - (T - (c - 1) * p.num_units <= p.num_units / 2 ? 1 : 0);
+            if (wave < kDecodeWaves) flat_unit<DT, FUSED, KV8, SHARED, D, true>(p, lds[wave], place, u, c2, T);
+            return;
+        }
+        if (T >= p.num_units / 2) u = blockIdx.x * FlatWaves<CHOICE>::value + wave;
+        else if (wave >= kDecodeWaves) u += p.num_units / 2 - kDecodeWaves;
+    }
+    flat_unit<DT, FUSED, KV8, SHARED, D, false>(p, lds[wave], place, u, max(p.min_unit_tiles, c), T);
 }
 
 // Combine the partial results of the equal-work split: head h of sequence b collects slots

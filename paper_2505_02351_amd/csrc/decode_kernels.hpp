@@ -36,6 +36,7 @@ struct DecodeParams {
     int segs_per_seq;           // KV heads x head chunks
     int group, chunks;          // query heads per KV head; group / heads_per_wg
     FastDiv by_group, by_chunks, by_heads_per_wg, by_units;     // (units: num_units)
+    int pairs_from;             // 8-bit caches: tiles from which units are taken two tiles at a time (0: never)
     int32_t* plan;              // [num_seqs + 1]: tile prefix P_b per non-empty sequence, then tiles per unit
     float out_scale;            // multiplies the combined output (v_scale of an E4M3 cache, else 1)
     // E4M3 decode step: the new token is not among the streamed tiles; the combine kernel adds its term

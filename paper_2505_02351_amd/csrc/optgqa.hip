@@ -17,6 +17,7 @@
 #include "decode_mma_kernels.hpp"
 #include "decode_flat_kernels.hpp"
 #include "prefill_kernels.hpp"
+#include "decode_split.hpp"
 #include "prefill_shape.hpp"
 #include "probe_kernels.hpp"
 
@@ -172,7 +173,7 @@ struct SplitPlan {
 
 // Equal-work split: one workgroup per CU for 2-byte caches (one wave per SIMD streams best),
 // OPTGQA_FLAT_WGS_PER_CU_KV8 per CU for 8-bit caches (half the bytes per tile: the second wave
-// per SIMD hides the arithmetic; one where units are long, kPairUnitTiles); no wave with less than kFlatMinTiles tiles of 16 tokens when
+// per SIMD hides the arithmetic; half of them where units are long, decode_pairs_from); no wave with less than kFlatMinTiles tiles of 16 tokens when
 // the lengths are at their bound.  The workspace is sized for the larger of the two.
 int flat_workgroups(bool kv8) { return num_cus() * (kv8 ? OPTGQA_FLAT_WGS_PER_CU_KV8 : OPTGQA_FLAT_WGS_PER_CU); }
 int flat_max_workgroups() { return std::max(flat_workgroups(false), flat_workgroups(true)); }
@@ -325,12 +326,13 @@ int launch_decode_any(int dtype, int head_dim, A... args)
 // Equal-work kernel: `workgroups` was sized for the work; it is also capped by what
 // the device keeps resident at once, because a unit that has to wait for a free slot would start
 // when every other unit is nearly done.
-template <int DT, int D, bool FUSED, bool KV8 = false, bool SHARED = false, bool PAIRS = false>
+template <int DT, int D, bool FUSED, bool KV8 = false, bool SHARED = false, bool CHOICE = false>
 int launch_decode_flat_dt(DecodeParams p, int workgroups, hipStream_t st)
 {
+    constexpr int kWaves = FlatWaves<CHOICE>::value;
     static const int resident = [] {
         int per_cu = 0, dev = 0, cus = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, paged_decode_flat_kernel<DT, FUSED, KV8, SHARED, D, PAIRS>, kDecodeWaves * 64, 0) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, paged_decode_flat_kernel<DT, FUSED, KV8, SHARED, D, CHOICE>, kWaves * 64, 0) != hipSuccess ||
             hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
             return 0;
@@ -340,7 +342,7 @@ int launch_decode_flat_dt(DecodeParams p, int workgroups, hipStream_t st)
     if (workgroups > resident) workgroups = resident;
     const int group = p.num_heads / p.num_kv_heads;
     p.heads_per_wg = mfma_heads_per_workgroup(group);
-    p.num_units = std::min(workgroups * kDecodeWaves, p.num_units);      // (num_units came in as the plan's most)
+    p.num_units = std::min(workgroups * kWaves, p.num_units);      // (num_units came in as the plan's most)
     p.group = group;
     p.chunks = group / p.heads_per_wg;
     p.by_group.set(p.group);
@@ -350,7 +352,7 @@ int launch_decode_flat_dt(DecodeParams p, int workgroups, hipStream_t st)
     int rc;
     {
         KernelEvents ev(st);
-        rc = launch(paged_decode_flat_kernel<DT, FUSED, KV8, SHARED, D, PAIRS>, dim3(workgroups), dim3(kDecodeWaves * 64), 0, st, p);
+        rc = launch(paged_decode_flat_kernel<DT, FUSED, KV8, SHARED, D, CHOICE>, dim3(workgroups), dim3(kWaves * 64), 0, st, p);
     }
     if (rc != OPTGQA_OK) return rc;
     // More than four pieces to a segment on average: eight groups of threads to a head - unless that makes
@@ -367,13 +369,13 @@ int launch_decode_flat_dt(DecodeParams p, int workgroups, hipStream_t st)
 }
 
 template <int DT, int D>
-int launch_decode_flat_d(const DecodeParams& p, int workgroups, hipStream_t st, bool kv8, bool pairs)
+int launch_decode_flat_d(const DecodeParams& p, int workgroups, hipStream_t st, bool kv8)
 {
     if (p.shared_blocks && p.k_new) return launch_decode_flat_dt<DT, D, true, false, true>(p, workgroups, st);
     if (p.shared_blocks) return launch_decode_flat_dt<DT, D, false, false, true>(p, workgroups, st);
     if constexpr (D == 128) {
-        if (pairs && p.k_new) return launch_decode_flat_dt<DT, D, true, true, false, true>(p, std::min(workgroups, num_cus()), st);
-        if (pairs) return launch_decode_flat_dt<DT, D, false, true, false, true>(p, std::min(workgroups, num_cus()), st);
+        if (p.pairs_from && p.k_new) return launch_decode_flat_dt<DT, D, true, true, false, true>(p, workgroups / 2, st);
+        if (p.pairs_from) return launch_decode_flat_dt<DT, D, false, true, false, true>(p, workgroups / 2, st);
     }
     if (kv8 && p.k_new) return launch_decode_flat_dt<DT, D, true, true>(p, workgroups, st);
     if (kv8) return launch_decode_flat_dt<DT, D, false, true>(p, workgroups, st);
@@ -381,14 +383,13 @@ int launch_decode_flat_d(const DecodeParams& p, int workgroups, hipStream_t st, 
     return launch_decode_flat_dt<DT, D, false>(p, workgroups, st);
 }
 
-// pairs: an 8-bit cache's units are long (kPairUnitTiles)
-int launch_decode_flat(int dtype, int head_dim, const DecodeParams& p, int workgroups, hipStream_t st, bool kv8 = false, bool pairs = false)
+int launch_decode_flat(int dtype, int head_dim, const DecodeParams& p, int workgroups, hipStream_t st, bool kv8 = false)
 {
     if (head_dim == 128)
-        return dtype == OPTGQA_F16 ? launch_decode_flat_d<kF16, 128>(p, workgroups, st, kv8, pairs)
-                                   : launch_decode_flat_d<kBF16, 128>(p, workgroups, st, kv8, pairs);
-    return dtype == OPTGQA_F16 ? launch_decode_flat_d<kF16, 64>(p, workgroups, st, kv8, false)
-                               : launch_decode_flat_d<kBF16, 64>(p, workgroups, st, kv8, false);
+        return dtype == OPTGQA_F16 ? launch_decode_flat_d<kF16, 128>(p, workgroups, st, kv8)
+                                   : launch_decode_flat_d<kBF16, 128>(p, workgroups, st, kv8);
+    return dtype == OPTGQA_F16 ? launch_decode_flat_d<kF16, 64>(p, workgroups, st, kv8)
+                               : launch_decode_flat_d<kBF16, 64>(p, workgroups, st, kv8);
 }
 
 
@@ -673,6 +674,7 @@ int attention_impl(void* out, const void* q, const void* k_cache, const void* v_
     p.new_token_in_combine = 0;
     p.k_inv_scale = p.v_inv_scale = 1.f;
     p.min_unit_tiles = 1;
+    p.pairs_from = 0;
     p.shared_blocks = shared_blocks;
     p.bundle = shared_blocks ? kMmaMaxHeads / mfma_heads_per_workgroup(num_heads / num_kv_heads) : 1;
     p.k_scales = p.v_scales = nullptr;
@@ -722,9 +724,8 @@ int attention_impl(void* out, const void* q, const void* k_cache, const void* v_
         if (s.partition_size > 0) p.min_unit_tiles = s.partition_size / kMmaTile;        // fixed partitions
         p.segs_per_seq = s.segs_per_seq;
         const int cap = flat_workgroups(kv_scales != nullptr);
-        const int64_t tiles = (int64_t)num_seqs * s.segs_per_seq * ((max_context_len + kMmaTile - 1) / kMmaTile);        // at their bound
-        const bool pairs = kv_scales && head_dim == 128 && tiles >= (int64_t)kPairUnitTiles * kDecodeWaves * num_cus();
-        return launch_decode_flat(dtype, head_dim, p, s.workgroups < cap ? s.workgroups : cap, st, kv_scales != nullptr, pairs);
+        p.pairs_from = kv_scales && head_dim == 128 ? decode_pairs_from((int64_t)num_seqs * s.segs_per_seq, (int64_t)num_seqs * num_heads, max_context_len, num_cus()) : 0;
+        return launch_decode_flat(dtype, head_dim, p, s.workgroups < cap ? s.workgroups : cap, st, kv_scales != nullptr);
     }
     // unsplit: one workgroup per (sequence, KV head / head chunk) walks the whole context
     p.plan = nullptr;

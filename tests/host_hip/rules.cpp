@@ -8,6 +8,7 @@
 
 #include "cache_kernels.hpp"
 #include "decode_kernels.hpp"
+#include "decode_split.hpp"
 #include "prefill_shape.hpp"
 
 using namespace optgqa;
@@ -167,4 +168,9 @@ extern "C" int held_blocks_differ(const int32_t* blocks, int n, int* reads)
         if (lanes[(first - blocks[i]) & 63] != blocks[i] + 1000) return i;
     }
     return -1;
+}
+
+extern "C" int decode_pairs_from_of(int64_t segments, int64_t rows, int max_context_len, int cus)
+{
+    return decode_pairs_from(segments, rows, max_context_len, cus);
 }

@@ -168,3 +168,19 @@ def test_the_gpu_tests_know_the_rule(lib, monkeypatch):
         assert got == shape(lib, *args, cus=cus), (args, cus)
         seen.add(got)
     assert seen == {"two", "4", "8"}
+
+
+def test_the_gpu_tests_know_when_units_are_taken_in_pairs(lib):
+    from test_gpu_decode_pairs import pairs_from
+    rng = random.Random(2)
+    seen = [0, 0]
+    for _ in range(3000):
+        cus, Hkv = rng.choice([64, 256, 304]), rng.choice([1, 2, 3, 8])
+        B, Hq, bound = rng.randint(1, 400), Hkv * rng.choice([1, 2, 4, 7, 16, 17, 32]), int(2 ** rng.uniform(4, 17))
+        group = Hq // Hkv
+        segments = B * Hkv * (group // max(h for h in range(1, 17) if group % h == 0))
+        got = lib.decode_pairs_from_of(ctypes.c_int64(segments), ctypes.c_int64(B * Hq), bound, cus)
+        assert got == pairs_from(B, Hq, Hkv, bound, cus)
+        seen[got > 0] += 1
+    assert min(seen) > 300
+    assert lib.decode_pairs_from_of(ctypes.c_int64(2**26), ctypes.c_int64(2**30), 256, 256) == 2**31 - 1      # beyond any launch's tiles: never taken
