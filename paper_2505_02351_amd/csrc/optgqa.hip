@@ -456,8 +456,11 @@ int launch_prefill(PrefillParams p, int num_seqs, int max_q_len, int head_dim, i
     p.heads_pow2_shift = shift;
     p.units = num_seqs * p.num_kv_heads * (group / gh);
     const int64_t units8 = (p.units + 7) / 8 * 8;
-    const PrefillShape shape = kv8 ? prefill_shape(units8, shift, max_q_len, p.window > 0, contig, num_cus())
-                                   : prefill_shape_direct(units8, shift, max_q_len, head_dim, p.slopes != nullptr, p.window > 0, contig, num_cus());
+    const int64_t longest = contig ? max_q_len : (int64_t)p.max_blocks_per_seq * p.block_size;
+    const int64_t seen = p.window > 0 ? std::min<int64_t>(longest, (int64_t)p.window + max_q_len) : longest;      // (tokens, by some row or other)
+    const int64_t key_bytes = num_seqs * seen * (4ll * p.num_kv_heads * head_dim);
+    const PrefillShape shape = kv8 ? prefill_shape(units8, shift, max_q_len, p.window > 0, num_cus())
+                                   : prefill_shape_direct(units8, shift, max_q_len, head_dim, p.slopes != nullptr, p.window > 0, contig, num_cus(), key_bytes);
     p.q_tiles = (int)prefill_q_tiles(shape == PrefillShape::k8Waves ? 8 : 4, shift, max_q_len);
     p.group = group;
     p.chunks = group / gh;
@@ -473,7 +476,6 @@ int launch_prefill(PrefillParams p, int num_seqs, int max_q_len, int head_dim, i
     const dim3 grid((unsigned)blocks);
     KernelEvents ev(st);
     const bool f16 = dtype == OPTGQA_F16;
-    const int64_t longest = contig ? max_q_len : (int64_t)p.max_blocks_per_seq * p.block_size;
     const bool judge = p.slopes != nullptr && longest >= (head_dim == 128 ? kPfJudgeLongest<128> : kPfJudgeLongest<64>) * kPfKeys;
     if (step) {
         if (kv8 || contig || p.window > 0) return OPTGQA_ERR_UNSUPPORTED;

@@ -20,8 +20,8 @@ inline int64_t prefill_q_tiles(int waves, int heads_pow2_shift, int max_q_len)
 }
 
 // units8: (sequence, KV head, head chunk) triples rounded up to 8s; max_q_len: the caller's bound on the new tokens.
-// For tiles that pass through registers (8-bit caches), with which all its figures were measured; for those that do not it is
-// prefill_shape_direct's starting point.  In order (GPU time of passes in us; bf16, 32 / 8 heads, head_dim 128, slopes, where nothing else is said; see also
+// For tiles that pass through registers (8-bit caches: chunks only), with which all its figures were measured, e4m3 or before 2-byte tiles went to
+// LDS directly.  In order (GPU time of passes in us; bf16, 32 / 8 heads, head_dim 128, slopes, where nothing else is said; see also
 // prefill_kernels.hpp):
 //   a window              -> 128 rows, which span few keys.  8 chunks of 512, no slopes, with the cache write:
 //                              window              64     512   1 024   2 048   4 096
@@ -40,55 +40,61 @@ inline int64_t prefill_q_tiles(int waves, int heads_pow2_shift, int max_q_len)
 //                                               4 x 512  6 x 512 8 x 448 8 x 512  8 x 512
 //                              256 rows            92.7    99.3    98.7   111.7   218.1
 //                              128 rows            78.2    99.5   107.1   122.2   235.9
-//   whole prompts, not five times
-//                         -> 128 rows: the walks are short against what a workgroup costs before and behind its
-//                            walk, which two resident workgroups overlap.  8 prompts:
-//                              tokens, and workgroups  768  1 024  1 280   1 280, no slopes   1 280, head_dim 64   1 536   2 560
-//                              256 rows               69.1  105.2  141.3   186.6               97.8                190.1   385.1
-//                              128 rows               65.9  100.7  134.2   177.5               81.6                184.2   395.6
 //   else                  -> 256 rows: half the loads and LDS stores per row.
 // What is counted are workgroups under the caller's bound: most of them may find no tokens, and then the launch is smaller
 // than it looks.
-inline PrefillShape prefill_shape(int64_t units8, int heads_pow2_shift, int max_q_len, bool windowed, bool whole_prompts, int cus)
+inline PrefillShape prefill_shape(int64_t units8, int heads_pow2_shift, int max_q_len, bool windowed, int cus)
 {
     const int64_t blocks8 = units8 * prefill_q_tiles(8, heads_pow2_shift, max_q_len);
     const int64_t blocks4 = units8 * prefill_q_tiles(4, heads_pow2_shift, max_q_len);
     if (windowed) return PrefillShape::k4Waves;
     if (blocks4 <= cus) return PrefillShape::k8WavesTwoGroups;
-    if (blocks8 < 2 * cus || (whole_prompts && blocks8 <= 5 * cus)) return PrefillShape::k4Waves;
+    if (blocks8 < 2 * cus) return PrefillShape::k4Waves;
     return PrefillShape::k8Waves;
 }
 
+// Bytes of K and V rows that a launch reads, under the caller's bounds, that are more than the last-level cache keeps (256 MB).
+constexpr int64_t kPrefillFarKeys = 320000000;
+
 // The shape where tiles go to LDS directly (2-byte caches and inputs): a tile's loads cost 128 rows little more than 256, so two
-// workgroups of 128 rows, which hide each other's start, end and barriers, win over more of the range.  slopes: given.  (As above; 256 rows, and
-// 128; what the general rule gives goes for windows and two key groups.)
+// workgroups of 128 rows, which hide each other's start, end and barriers, win over more of the range.  slopes: given.  key_bytes: of K and V
+// rows.  (As above; 256 rows, and 128; what the general rule gives goes for windows and two key groups.)
 //   head_dim 64           -> 128 rows, always:
 //                                        8 x 2 560  16 x 2 560, no slopes  8 x 512 > 2 048  16 x 512 > 2 048  8 x 512 > 2 048, no slopes
 //                              256 rows     233.9        812.7                  69.5             134.5              132.0
 //                              128 rows     188.3        697.7                  67.1             123.5              127.1
-//   no slopes             -> 128 rows: nothing is skipped, and all steps of a workgroup are alike.  24 ragged chunks 231.8 and 213.4, 8 prompts
-//                            of 2 560 601 and 585, 16 of them 1 210 and 1 195, chunks of 512 behind 2 048: 6 182.9 and 159.8, 7 189.4 and
-//                            193.1, 8 209.9 and 208.7.
-//   256-row workgroups would not fill the CUs 1.75 times
-//                         -> 128 rows.  Chunks of 512 behind 2 048:
-//                              256-row workgroups      256     384     448     512    1 024
-//                              256 rows               90.6    94.4   100.6   105.8    213.7
-//                              128 rows               72.3    92.5   105.5   114.1    229.0
-//   whole prompts whose bound is at most 3 072 tokens, or that 256-row workgroups fill not five times
+//   256-row workgroups would not fill the CUs twice; with slopes and two of them or more to a unit, not 1.75 times
+//                         -> 128 rows.  Chunks behind 2 048, 1 000 and 1 000, heads 32 / 8, 32 / 8 and 16 / 16:
+//                              256-row workgroups   256   384   448   512  1 024      464 (29 x 125)      480 (30 x 2: one to a unit)
+//                              256 rows            90.6  94.4 100.6 105.8  213.7          90.1                   67.9
+//                              128 rows            72.3  92.5 105.5 114.1  229.0          90.3                   51.1
+//   no slopes             -> 128 rows: nothing is skipped, and all steps of a workgroup are alike (24 ragged chunks 231.8 and 213.4, 40 of 125 behind 1 000
+//                            163.2 and 149.1), but 256 where the keys are more than the last-level cache keeps - equal chunks' tiles of rows start together, one
+//                            sequence's far apart, and 128 read memory twice as often - or chunks are long (the bound stands for the length):
+//                              16 / 16 heads       100 x 131 > 1 000 (927 MB)  40 x 1 021 > 1 000 (662)  64 prompts of 1 523 (399)  16 x 1 021 > 1 000 (265)
+//                              256 rows                   340.1                     926.4                  1 271                     364.7
+//                              128 rows                   430.4                   1 058                    1 505                     352.1
+//                              32 / 8, chunks      16 x 509 > 300   5 x 1 604 > 2 097, fp16   40 x 1 500 > 300   8 x 2 560 > 300   8 x 4 096 > 300
+//                              256 rows                140.9             448.4                      1 712              761.0             1 711
+//                              128 rows                133.6             410.8                      1 752              796.3             1 809
+//   whole prompts, slopes, whose bound is at most 3 072 tokens, or that 256-row workgroups fill not five times
 //                         -> 128 rows; in a longer walk the loads that 256 rows save weigh more.  8 prompts:
 //                              tokens                 1 024   1 536   2 560   2 560, 16 prompts   4 096   2 560, fp16
 //                              256 rows                95.6   183.5   375.0        725.1           705.6      345.8
 //                              128 rows                88.6   165.7   355.5        723.2           732.3      321.3
 //   else                  -> 256 rows.
 inline PrefillShape prefill_shape_direct(int64_t units8, int heads_pow2_shift, int max_q_len, int head_dim, bool slopes, bool windowed,
-                                         bool whole_prompts, int cus)
+                                         bool whole_prompts, int cus, int64_t key_bytes)
 {
-    const PrefillShape any = prefill_shape(units8, heads_pow2_shift, max_q_len, windowed, whole_prompts, cus);
+    const PrefillShape any = prefill_shape(units8, heads_pow2_shift, max_q_len, windowed, cus);
     if (windowed || any == PrefillShape::k8WavesTwoGroups) return any;
-    const int64_t blocks8 = units8 * prefill_q_tiles(8, heads_pow2_shift, max_q_len);
-    if (head_dim == 64 || !slopes || 4 * blocks8 < 7 * cus) return PrefillShape::k4Waves;
-    if (whole_prompts && (blocks8 <= 5 * cus || max_q_len <= 3072)) return PrefillShape::k4Waves;
-    return PrefillShape::k8Waves;
+    const int64_t tiles4 = prefill_q_tiles(4, heads_pow2_shift, max_q_len), tiles8 = prefill_q_tiles(8, heads_pow2_shift, max_q_len);
+    const int64_t blocks8 = units8 * tiles8;
+    bool wide = head_dim == 128;
+    if (whole_prompts) wide = wide && blocks8 > 5 * cus && (slopes ? max_q_len > 3072 : key_bytes >= kPrefillFarKeys);
+    else if (slopes) wide = wide && 4 * blocks8 >= (tiles8 > 1 ? 7 : 8) * cus;
+    else wide = wide && blocks8 >= 2 * cus && ((tiles4 > tiles8 && key_bytes >= kPrefillFarKeys) || max_q_len > 2048);
+    return wide ? PrefillShape::k8Waves : PrefillShape::k4Waves;
 }
 
 }  // namespace optgqa

@@ -141,14 +141,14 @@ extern "C" int step_store(const uint16_t* k, const uint16_t* v, int rows, int64_
     }) ? 1 : -100;
 }
 
-extern "C" int prefill_shape_of(int64_t units8, int shift, int max_q_len, int windowed, int whole_prompts, int cus)
+extern "C" int prefill_shape_of(int64_t units8, int shift, int max_q_len, int windowed, int cus)
 {
-    return (int)prefill_shape(units8, shift, max_q_len, windowed, whole_prompts, cus);
+    return (int)prefill_shape(units8, shift, max_q_len, windowed, cus);
 }
 
-extern "C" int prefill_shape_direct_of(int64_t units8, int shift, int max_q_len, int head_dim, int slopes, int windowed, int whole_prompts, int cus)
+extern "C" int prefill_shape_direct_of(int64_t units8, int shift, int max_q_len, int head_dim, int slopes, int windowed, int whole_prompts, int cus, int64_t key_bytes)
 {
-    return (int)prefill_shape_direct(units8, shift, max_q_len, head_dim, slopes, windowed, whole_prompts, cus);
+    return (int)prefill_shape_direct(units8, shift, max_q_len, head_dim, slopes, windowed, whole_prompts, cus, key_bytes);
 }
 
 // The blocks that a wave would read, one after the other, through the numbers that its lanes hold (block n of the sequence: number

@@ -19,8 +19,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("ctx,alibi", [(0, True), (21, False), (530, True)])   # (16 tiles or more with slopes: a wave's rows are one head's)
 @pytest.mark.parametrize("dtype,D", [(W.BF16, 128), (W.F16, 64)])
 def test_rows_in_and_out(U, oracle, dtype, D, ctx, alibi, B, Hq, Hkv, q_len, shape):
-    assert launch_shape(B, Hq, Hkv, q_len)[0] == shape
     L = ctx + q_len
+    # (256 rows: with slopes, head_dim 128)
+    assert launch_shape(B, Hq, Hkv, q_len, D=D, slopes=alibi, longest=-(-L // 16) * 16)[0] == (shape if alibi and D == 128 or shape == "two" else "4")
     cfg = W.small_config(name="rows", kind="prefill", dtype=dtype, batch=B, num_heads=Hq, num_kv_heads=Hkv, head_dim=D,
                          block_size=16, num_blocks=B * -(-L // 16) + 3, ctx_lo=L, ctx_hi=L, q_len=q_len, seed=31 + B + q_len)
     case = W.make_case(cfg)
@@ -50,7 +51,7 @@ def test_whole_prompts_under_a_loose_bound(U, dtype, D, alibi, bound):
     import oracle as O
     import paper_2505_02351_amd as G
     B, Hq, Hkv, q_len = 2, 32, 8, 173
-    assert launch_shape(B, Hq, Hkv, bound, True)[0] == "4"
+    assert launch_shape(B, Hq, Hkv, bound, True, D=D, slopes=alibi, longest=bound)[0] == "4"
     cfg = W.small_config(name="long", kind="prefill", dtype=dtype, batch=B, num_heads=Hq, num_kv_heads=Hkv, head_dim=D,
                          block_size=16, num_blocks=B * 11 + 3, ctx_lo=q_len, ctx_hi=q_len, q_len=q_len, seed=bound)
     case = W.make_case(cfg)

@@ -9,32 +9,54 @@ from test_gpu_parity import U, fp8_caches, oracle_filled  # noqa: F401  (U: a fi
 pytestmark = pytest.mark.gpu
 
 
-def launch_shape(batch, Hq, Hkv, max_q_len, whole_prompt=False):
-    """The workgroup shape that a prefill launch takes on this card (prefill_shape.hpp's rule): "two" key groups of four
-    waves, "4" waves, or "8" waves; and its query tiles."""
-    import torch
-    cus = torch.cuda.get_device_properties(0).multi_processor_count
+def row_tiles(Hq, Hkv, max_q_len, rows):
+    """Workgroups of that many rows to a unit."""
     group = Hq // Hkv
     gh = max(h for h in range(1, 17) if group % h == 0)
-    pow2 = 1 << (gh - 1).bit_length()
-    units = -(-batch * Hkv * (group // gh) // 8) * 8
-    tiles4, tiles8 = -(-max_q_len // (128 // pow2)), -(-max_q_len // (256 // pow2))
-    if units * tiles4 <= cus:
-        return "two", tiles4
-    if units * tiles8 < 2 * cus or (whole_prompt and units * tiles8 <= 5 * cus):
+    return -(-max_q_len // (rows // (1 << (gh - 1).bit_length())))
+
+
+def units(batch, Hq, Hkv):
+    group = Hq // Hkv
+    return -(-batch * Hkv * (group // max(h for h in range(1, 17) if group % h == 0)) // 8) * 8
+
+
+def cus():
+    import torch
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+def launch_shape(batch, Hq, Hkv, max_q_len, whole_prompt=False, D=128, slopes=True, kv8=False, window=0, longest=0):
+    """The workgroup shape that a prefill launch takes on this card (prefill_shape.hpp's rules): "two" key groups of four
+    waves, "4" waves, or "8" waves; and its query tiles.  longest: tokens that a block table holds."""
+    tiles4, tiles8, u = row_tiles(Hq, Hkv, max_q_len, 128), row_tiles(Hq, Hkv, max_q_len, 256), units(batch, Hq, Hkv)
+    if window:
         return "4", tiles4
-    return "8", tiles8
+    if u * tiles4 <= cus():
+        return "two", tiles4
+    if kv8:
+        wide = u * tiles8 >= 2 * cus()
+    else:
+        far = 4 * batch * longest * Hkv * D >= 320000000
+        if whole_prompt:
+            wide = u * tiles8 > 5 * cus() and (max_q_len > 3072 if slopes else far)
+        elif slopes:
+            wide = 4 * u * tiles8 >= (7 if tiles8 > 1 else 8) * cus()
+        else:
+            wide = u * tiles8 >= 2 * cus() and (tiles4 > tiles8 and far or max_q_len > 2048)
+        wide = wide and D == 128
+    return ("8", tiles8) if wide else ("4", tiles4)
 
 
 LONGEST = 1600          # tokens that a launch's longest possible walk must have for its kernel to look at the rest of walks (48 tiles)
 
 
-def widen(case):
-    """Block tables as wide as a serving program's, for sequences of up to LONGEST tokens: what the launch goes by."""
+def widen(case, longest=LONGEST):
+    """Block tables as wide as a serving program's, for sequences of up to `longest` tokens: what the launch goes by."""
     bs = case.cfg.block_size
-    more = -(-LONGEST // bs) - case.block_tables.shape[1]
+    more = -(-longest // bs) - case.block_tables.shape[1]
     case.block_tables = np.pad(case.block_tables, ((0, 0), (0, max(more, 0))), constant_values=-1)
-    assert case.block_tables.shape[1] * bs >= 48 * 32
+    assert case.block_tables.shape[1] * bs >= longest
 
 
 def outlier_case(dtype, D, q_len, t0, slope, like, ctx=705, batch=2, seed=1, heads=(8, 2), block_size=16):
@@ -60,10 +82,10 @@ def outlier_case(dtype, D, q_len, t0, slope, like, ctx=705, batch=2, seed=1, hea
 
 @pytest.mark.parametrize("t0", [0, 15, 16, 333, 511])
 @pytest.mark.parametrize("dtype,D", [(W.BF16, 128), (W.F16, 64)])
-@pytest.mark.parametrize("batch,heads,q_len,shape", [(2, (8, 2), 24, "two"), (70, (8, 2), 70, "4"), (64, (8, 8), 70, "8")])
+@pytest.mark.parametrize("batch,heads,q_len,shape", [(2, (8, 2), 24, "two"), (70, (8, 2), 70, "4"), (64, (8, 8), 70, "8")])   # ("8": head_dim 128)
 @pytest.mark.parametrize("block_size", [16, 64])
 def test_a_far_key_that_matters_is_not_judged_away(U, oracle, block_size, batch, heads, q_len, shape, dtype, D, t0):
-    assert launch_shape(batch, *heads, q_len)[0] == shape
+    assert launch_shape(batch, *heads, q_len, D=D)[0] == (shape if D == 128 or shape == "two" else "4")
     case = outlier_case(dtype, D, q_len, t0, 0.25, "q", batch=batch, heads=heads, block_size=block_size)
     dev = U.DevCase(case)
     step = dev.prefill_step()
@@ -76,17 +98,19 @@ def test_a_far_key_that_matters_is_not_judged_away(U, oracle, block_size, batch,
 
 
 @pytest.mark.parametrize("t0", [0, 16, 511, 640])
-@pytest.mark.parametrize("batch,heads,shape", [(2, (8, 8), "two"), (6, (8, 2), "4"), (54, (8, 8), "8")])
+@pytest.mark.parametrize("batch,heads,shape,bound", [(2, (8, 8), "two", LONGEST), (6, (8, 2), "4", LONGEST), (54, (8, 8), "4", LONGEST),
+                                                     (54, (8, 8), "8", 3100)])      # ("8": head_dim 128)
 @pytest.mark.parametrize("dtype,D", [(W.BF16, 128), (W.F16, 64)])
-def test_a_far_key_of_a_whole_prompt(U, oracle, dtype, D, batch, heads, shape, t0):
+def test_a_far_key_of_a_whole_prompt(U, oracle, dtype, D, batch, heads, shape, bound, t0):
     import torch
     import oracle as O
     import paper_2505_02351_amd as G
-    assert launch_shape(batch, *heads, LONGEST, True)[0] == shape
+    assert launch_shape(batch, *heads, bound, True, D=D)[0] == (shape if D == 128 or shape == "two" else "4")
     case = outlier_case(dtype, D, 705, t0, 0.25, "q", batch=batch, heads=heads)
+    widen(case, bound)
     dev = U.DevCase(case)
     G.prompt_prefill(dev.out, dev.q, dev.k_new, dev.v_new, dev.k_cache, dev.v_cache, dev.block_tables, dev.cu_q_lens,
-                     dev.slopes, float(case.scale), LONGEST)
+                     dev.slopes, float(case.scale), bound)
     torch.cuda.synchronize()
     dev.check_canaries()
     rows = slice(None, case.cu_q_lens[2])       # sequences 0 and 1
@@ -101,7 +125,7 @@ def test_a_far_key_of_an_8_bit_cache(U, oracle, D, batch, heads, q_len, shape, t
     import torch
     import oracle as O
     import paper_2505_02351_amd as G
-    assert launch_shape(batch, *heads, q_len)[0] == shape
+    assert launch_shape(batch, *heads, q_len, D=D, kv8=True)[0] == shape
     case = outlier_case(W.BF16, D, q_len, t0, 1 / 16 if D == 128 else 1 / 32, "sign", batch=batch, heads=heads)
     kc8, vc8, dk, dv = fp8_caches(U, case, 0.0125, 0.02)
     qd = U.to_dev(case.q, W.BF16)
@@ -118,12 +142,12 @@ def test_a_far_key_of_an_8_bit_cache(U, oracle, D, batch, heads, q_len, shape, t
 
 @pytest.mark.parametrize("t0", [None, 5, 1000, 2000])
 @pytest.mark.parametrize("block_size", [16, 32])
-@pytest.mark.parametrize("batch,heads,shape", [(2, (8, 2), "two"), (64, (8, 8), "8")])
-def test_a_far_key_under_a_negative_slope(U, oracle, batch, heads, shape, block_size, t0):
+@pytest.mark.parametrize("batch,heads,D,shape", [(2, (8, 2), 64, "two"), (64, (8, 8), 64, "4"), (64, (8, 8), 128, "8")])
+def test_a_far_key_under_a_negative_slope(U, oracle, batch, heads, D, shape, block_size, t0):
     """Biases that grow with the distance, by 20 over the context; near keys whose scores lie 60 above the others' end the
     walk all the same - unless one far key's score makes up for what its bias leaves."""
-    ctx, q_len, D, slope = 2616, 24, 64, -2.0 ** -7
-    assert launch_shape(batch, *heads, q_len)[0] == shape
+    ctx, q_len, slope = 2616, 24, -2.0 ** -7
+    assert launch_shape(batch, *heads, q_len, D=D)[0] == shape
     cfg = W.small_config(name="negative", kind="prefill", dtype=W.BF16, batch=batch, num_heads=heads[0], num_kv_heads=heads[1],
                          head_dim=D, block_size=block_size, num_blocks=batch * -(-ctx // block_size), ctx_lo=ctx, ctx_hi=ctx,
                          q_len=q_len, seed=6)
@@ -152,14 +176,14 @@ def test_a_far_key_under_a_negative_slope(U, oracle, batch, heads, shape, block_
     U.check_scaled(step[rows], ref, W.BF16, f"negative slope, outlier at {t0}", max_exempt=1.0)
 
 
-# (two key groups; 8 waves)
-@pytest.mark.parametrize("B,Hq,Hkv,D", [(2, 8, 2, 128), (64, 8, 8, 64)])
-def test_half_a_rows_sum_does_not_judge_the_other_halfs_keys(U, oracle, B, Hq, Hkv, D):
+@pytest.mark.parametrize("B,Hq,Hkv,D,shape", [(2, 8, 2, 128, "two"), (64, 8, 8, 64, "4"), (64, 8, 8, 128, "8")])
+def test_half_a_rows_sum_does_not_judge_the_other_halfs_keys(U, oracle, B, Hq, Hkv, D, shape):
     """A row's sum is held by two lanes, of keys 8i .. 8i + 3 and 8i + 4 .. 8i + 7.  Two near keys of the first kind weigh
     2^23 times the others, so the far keys lie below 2^-24 of the whole sum, but not of the second lane's half of it:
     a tile of them is kept, and so must be the rest of the walk (their values are large: without them the output is
     off by 0.4 or more)."""
     ctx, q_len = 2616, 24
+    assert launch_shape(B, Hq, Hkv, q_len, D=D)[0] == shape
     cfg = W.small_config(name="halves", kind="prefill", dtype=W.BF16, batch=B, num_heads=Hq, num_kv_heads=Hkv, head_dim=D,
                          block_size=16, num_blocks=B * 164, ctx_lo=ctx, ctx_hi=ctx, q_len=q_len, seed=3)
     case = W.make_case(cfg, slopes=np.full(Hq, 2.0 ** -9, np.float32))
@@ -181,10 +205,11 @@ def test_half_a_rows_sum_does_not_judge_the_other_halfs_keys(U, oracle, B, Hq, H
     U.check_scaled(step[rows], ref, W.BF16, "halves", max_exempt=1.0)
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,D", [(2, 8, 2, 128), (64, 8, 8, 64)])
-def test_a_key_whose_norm_overflows_is_not_judged_away(U, oracle, B, Hq, Hkv, D):
+@pytest.mark.parametrize("B,Hq,Hkv,D,shape", [(2, 8, 2, 128, "two"), (64, 8, 8, 64, "4"), (64, 8, 8, 128, "8")])
+def test_a_key_whose_norm_overflows_is_not_judged_away(U, oracle, B, Hq, Hkv, D, shape):
     """Queries so small that their norms' squares vanish, one far key so large that its norm's square is infinite: the
     score between them is the row's largest by far."""
+    assert launch_shape(B, Hq, Hkv, 24, D=D)[0] == shape
     cfg = W.small_config(name="huge", kind="prefill", dtype=W.BF16, batch=B, num_heads=Hq, num_kv_heads=Hkv, head_dim=D,
                          block_size=16, num_blocks=B * 45, ctx_lo=705, ctx_hi=705, q_len=24, seed=4)
     case = W.make_case(cfg, slopes=np.full(Hq, 0.25, np.float32))
@@ -201,14 +226,16 @@ def test_a_key_whose_norm_overflows_is_not_judged_away(U, oracle, B, Hq, Hkv, D)
     U.check_scaled(step[rows], ref, W.BF16, "huge")
 
 
-# (sequences, heads, KV heads, head_dim): 1 and odd numbers of them, a lane's worth, one more (the plain order), in
-# every shape - the order by length is that of one group of four or of eight waves
-@pytest.mark.parametrize("B,Hq,Hkv,D,shape", [
-    (1, 8, 2, 128, "two"), (3, 6, 2, 64, "two"), (7, 40, 8, 128, "4"), (17, 16, 16, 128, "4"), (60, 16, 16, 64, "8"),
-    (64, 8, 2, 128, "4"), (65, 8, 2, 64, "4"), (64, 16, 4, 64, "8"), (65, 16, 4, 128, "8")])
-def test_ragged_launches_in_order_of_length(U, oracle, B, Hq, Hkv, D, shape):
+# (sequences, heads, KV heads, head_dim): 1 and odd numbers of them, a lane's worth, one more (the plain order) - the order by length is that of one
+# group of four or of eight waves, of these the latter over 8-bit caches only
+@pytest.mark.parametrize("B,Hq,Hkv,D,shape,shape8", [
+    (1, 8, 2, 128, "two", "two"), (3, 6, 2, 64, "two", "two"), (7, 40, 8, 128, "4", "4"), (17, 16, 16, 128, "4", "4"), (60, 16, 16, 64, "4", "8"),
+    (64, 8, 2, 128, "4", "4"), (65, 8, 2, 64, "4", "4"), (64, 16, 4, 64, "4", "8"), (65, 16, 4, 128, "4", "8"), (64, 16, 4, 128, "4", "8")])
+@pytest.mark.parametrize("kv8", [False, True])
+def test_ragged_launches_in_order_of_length(U, oracle, kv8, B, Hq, Hkv, D, shape, shape8):
     """No slopes; chunks of up to 90 new tokens (one of up to 180) behind 0 to 200 cached ones, one sequence without any."""
     import torch
+    import oracle as O
     import paper_2505_02351_amd as G
     lens = np.random.default_rng(77 + B).integers(1, 201, B).astype(np.int32)
     if B > 2:
@@ -216,19 +243,25 @@ def test_ragged_launches_in_order_of_length(U, oracle, B, Hq, Hkv, D, shape):
     cfg = W.small_config(name="ragged", kind="prefill", dtype=W.BF16, batch=B, num_heads=Hq, num_kv_heads=Hkv, head_dim=D,
                          block_size=16, num_blocks=B * 13 + 5, ctx_lo=1, ctx_hi=200, q_len=90, seed=77 + B)
     case = W.make_case(cfg, context_lens=lens)
-    kc, vc = oracle_filled(oracle, case)
     cu = case.cu_q_lens.copy()
     if B > 2:
         cu[2] = cu[1]                           # sequence 1 without new tokens, its rows sequence 2's: more of them
         assert np.diff(cu)[1] == 0 and 90 < np.diff(cu)[2] <= 180 <= lens[2]
-    got, tiles = launch_shape(B, Hq, Hkv, int(np.diff(cu).max()))
-    assert got == shape and (tiles > 1 or B == 1 or Hq == Hkv)
-    ref = oracle.paged_prefill(case.q, kc, vc, case.block_tables, case.context_lens, cu, None, case.scale, W.BF16)
+    most = int(np.diff(cu).max())
+    got, tiles = launch_shape(B, Hq, Hkv, most, D=D, slopes=False, kv8=kv8, longest=208)
+    assert got == (shape8 if kv8 else shape) and (tiles > 1 or B == 1 or Hq == Hkv)
     dev = U.DevCase(case)
-    dev.write_cache()
     dev.out.fill_(float("nan"))
-    G.paged_prefill(dev.out, dev.q, dev.k_cache, dev.v_cache, dev.block_tables, dev.context_lens,
-                    torch.from_numpy(cu).cuda(), None, float(case.scale), int(np.diff(cu).max()))
+    args = dev.block_tables, dev.context_lens, torch.from_numpy(cu).cuda(), None, float(case.scale)
+    if kv8:
+        kc, vc, dk, dv = fp8_caches(U, case, 0.0125, 0.02)
+        ref = O.paged_prefill_e4m3(case.q, kc, vc, case.block_tables, case.context_lens, cu, None, case.scale, 0.0125, 0.02, W.BF16)
+        G.paged_prefill_fp8(dev.out, dev.q, dk, dv, *args, 0.0125, 0.02, most)
+    else:
+        kc, vc = oracle_filled(oracle, case)
+        ref = oracle.paged_prefill(case.q, kc, vc, case.block_tables, case.context_lens, cu, None, case.scale, W.BF16)
+        dev.write_cache()
+        G.paged_prefill(dev.out, dev.q, dev.k_cache, dev.v_cache, *args, most)
     torch.cuda.synchronize()
     dev.check_canaries()
     U.check_scaled(U.to_host(dev.out), ref, W.BF16, f"ragged {B}")

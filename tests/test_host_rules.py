@@ -134,40 +134,51 @@ def test_a_steps_store_of_its_new_rows(lib, seqs, Hkv, D, bs):
     assert (got[0] == want[0]).all() and (got[1] == want[1]).all()
 
 
-def shape(lib, B, Hq, Hkv, max_q_len, whole_prompts=False, windowed=False, cus=256):
+def launch(B, Hq, Hkv):
+    """A launch's (units8, heads_pow2_shift)."""
     group = Hq // Hkv
     gh = max(h for h in range(1, 17) if group % h == 0)
-    units8 = -(-B * Hkv * (group // gh) // 8) * 8
-    return ["4", "8", "two"][lib.prefill_shape_of(ctypes.c_int64(units8), (gh - 1).bit_length(), max_q_len, windowed, whole_prompts, cus)]
+    return ctypes.c_int64(-(-B * Hkv * (group // gh) // 8) * 8), (gh - 1).bit_length()
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,max_q_len,whole,want", [
-    (1, 32, 8, 1024, False, "two"), (1, 32, 8, 1025, False, "4"),           # 256 and 264 workgroups of 128 rows
-    (8, 32, 8, 448, False, "4"), (8, 32, 8, 449, False, "8"),               # 448 and 512 of 256 rows
-    (8, 32, 8, 1280, True, "4"), (8, 32, 8, 1281, True, "8"),               # 1 280 and 1 344
-    # a bound of 2 048 and more may stand over prompts of any length: no line there
-    (4, 32, 8, 2047, True, "4"), (4, 32, 8, 2048, True, "4"), (4, 32, 8, 2560, True, "4"), (2, 32, 8, 4096, True, "4"),
-    (1, 32, 8, 8192, True, "4"), (4, 32, 4, 2560, True, "4"), (8, 32, 8, 2560, True, "8")])
-def test_prefill_shape(lib, B, Hq, Hkv, max_q_len, whole, want):
-    assert shape(lib, B, Hq, Hkv, max_q_len, whole) == want
+def shape(lib, B, Hq, Hkv, max_q_len, windowed=False, cus=256):
+    return ["4", "8", "two"][lib.prefill_shape_of(*launch(B, Hq, Hkv), max_q_len, windowed, cus)]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,max_q_len,want", [
+    (1, 32, 8, 1024, "two"), (1, 32, 8, 1025, "4"),                         # 256 and 264 workgroups of 128 rows
+    (8, 32, 8, 448, "4"), (8, 32, 8, 449, "8"), (8, 32, 8, 2560, "8")])     # 448 and 512 of 256 rows
+def test_prefill_shape(lib, B, Hq, Hkv, max_q_len, want):
+    assert shape(lib, B, Hq, Hkv, max_q_len) == want
     assert shape(lib, B, Hq, Hkv, max_q_len, windowed=True) == "4"
 
 
 def test_the_gpu_tests_know_the_rule(lib, monkeypatch):
-    """launch_shape, by which the GPU tests choose their launches, against the rule itself."""
+    """launch_shape, by which the GPU tests choose their launches, against the rules themselves."""
     import torch
     from test_gpu_prefill_walk import launch_shape
     rng = random.Random(1)
-    seen = set()
-    for _ in range(3000):
+    seen = {}
+    for _ in range(6000):
         cus = rng.choice([64, 256, 304])
         monkeypatch.setattr(torch.cuda, "get_device_properties", lambda _: types.SimpleNamespace(multi_processor_count=cus))
         Hkv = rng.choice([1, 2, 3, 8])
-        args = rng.randint(1, 70), Hkv * rng.choice([1, 2, 3, 4, 7, 16, 17, 32]), Hkv, int(2 ** rng.uniform(0, 13)), rng.random() < 0.5
-        got = launch_shape(*args)[0]
-        assert got == shape(lib, *args, cus=cus), (args, cus)
-        seen.add(got)
-    assert seen == {"two", "4", "8"}
+        args = rng.randint(1, 70), Hkv * rng.choice([1, 2, 3, 4, 7, 16, 17, 32]), Hkv, int(2 ** rng.uniform(0, 13))
+        kv8, D, slopes, longest = rng.random() < 0.3, rng.choice([64, 128]), rng.random() < 0.5, int(2 ** rng.uniform(5, 16))
+        whole = not kv8 and rng.random() < 0.4
+        window = 0 if kv8 or whole or rng.random() < 0.7 else int(2 ** rng.uniform(4, 13))
+        keys = args[0] * (min(longest, window + args[3]) if window else longest)
+        how = dict(D=D, slopes=slopes, kv8=kv8, window=window, longest=longest)
+        got = launch_shape(*args, whole, **how)[0]
+        if kv8:
+            assert got == shape(lib, *args, cus=cus), (args, cus)
+        else:
+            want = lib.prefill_shape_direct_of(*launch(*args[:3]), args[3], D, slopes, window > 0, whole, cus, ctypes.c_int64(4 * Hkv * D * keys))
+            assert got == ["4", "8", "two"][want], (args, whole, how, cus)
+        seen[got, kv8, whole, slopes] = seen.get((got, kv8, whole, slopes), 0) + 1
+    assert {s for s, *_ in seen} == {"two", "4", "8"}
+    assert {k[1:] for k in seen if k[0] == "8"} == {(True, False, True), (True, False, False), (False, False, True), (False, False, False),
+                                                    (False, True, True), (False, True, False)}
 
 
 def test_the_gpu_tests_know_when_units_are_taken_in_pairs(lib):
