@@ -1,5 +1,6 @@
 """GPU parity where a prefill tile goes to LDS without passing through registers: walks over more blocks than a lane read
-reaches without reading the table anew, and whole prompts under a bound for which they take 256-row workgroups."""
+reaches without reading the table anew, whole prompts under a bound for which they take 256-row workgroups, and rows of the inputs further
+apart than a lane's offset reaches."""
 import numpy as np
 import pytest
 
@@ -62,3 +63,32 @@ def test_whole_prompts_in_256_rows(U, dtype, q_len):
         rows = slice(cu[0], cu[-1])
         ref = O.prompt_attention(case.q[rows], case.k_new[rows], case.v_new[rows], cu - cu[0], case.slopes, case.scale, dtype)
         U.check_scaled(got[rows], ref, dtype, f"prompts {first}-{last}")
+
+
+# elements from token to token: the most that lane offsets of 32 bits reach over a load's rows, and the next
+@pytest.mark.parametrize("stride", [2**28 - 8, 2**28])
+@pytest.mark.parametrize("dtype,D,Hq,Hkv", [(W.BF16, 128, 4, 2), (W.F16, 64, 4, 1)])
+def test_rows_far_apart(U, dtype, D, Hq, Hkv, stride):
+    import torch
+    import oracle as O
+    import paper_2505_02351_amd as G
+    n = 97                                      # four tiles: those behind the first two have lane offsets, or lane addresses
+    cfg = W.small_config(name="apart", kind="prefill", dtype=dtype, batch=1, num_heads=Hq, num_kv_heads=Hkv, head_dim=D, block_size=16, num_blocks=8,
+                         ctx_lo=n, ctx_hi=n, q_len=n, seed=D)
+    case = W.make_case(cfg)
+    dev = U.DevCase(case)
+    row = Hkv * D
+    pool = torch.empty((n - 1) * stride + 2 * row, dtype=dev.q.dtype, device="cuda")             # 48 GiB, of which a few rows are touched
+    k, v = (pool[at:].as_strided((n, Hkv, D), (stride, D, 1)) for at in (0, row))
+    k.copy_(dev.k_new), v.copy_(dev.v_new)
+    dev.out.fill_(float("nan"))
+    G.prompt_prefill(dev.out, dev.q, k, v, dev.k_cache, dev.v_cache, dev.block_tables, dev.cu_q_lens, dev.slopes, float(case.scale), n)
+    torch.cuda.synchronize()
+    dev.check_canaries()
+    got = U.to_host(dev.out)
+    del pool, k, v
+    torch.cuda.empty_cache()
+    U.check_scaled(got, O.prompt_attention(case.q, case.k_new, case.v_new, case.cu_q_lens, case.slopes, case.scale, dtype), dtype, f"stride {stride}")
+    kc, vc = (x.copy() for x in (case.k_cache, case.v_cache))
+    O.reshape_and_cache(case.k_new, case.v_new, kc, vc, case.slot_mapping)
+    assert (U.to_host(dev.k_cache) == kc).all() and (U.to_host(dev.v_cache) == vc).all()
