@@ -395,16 +395,24 @@ int launch_decode_flat(int dtype, int head_dim, const DecodeParams& p, int workg
 
 // The tiled prefill kernel takes its LDS as dynamic shared memory (more than the 64 KiB a kernel
 // gets by default); the limit is raised once per instantiation.
+template <int DT, bool KV8, bool WIN, bool CONTIG, bool STEP, bool JUDGE, int D, int WAVES, int KS, bool DEEP>
+int launch_prefill_k(const PrefillParams& p, dim3 grid, hipStream_t st)
+{
+    void (*kernel)(PrefillParams);
+    if constexpr (STEP) kernel = paged_prefill_step_kernel<DT, JUDGE, D, WAVES, KS, DEEP>;
+    else kernel = paged_prefill_mma_kernel<DT, KV8, WIN, CONTIG, JUDGE, D, WAVES, KS, DEEP>;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, prefill_lds_bytes<D>(WAVES, KS, DEEP));
+    if (attr != hipSuccess) return OPTGQA_ERR_LAUNCH;
+    return launch(kernel, grid, dim3(WAVES * 64), prefill_lds_bytes<D>(WAVES, KS, DEEP), st, p);
+}
+
 template <int DT, bool KV8, bool WIN, bool CONTIG, bool STEP, bool JUDGE, int D, int WAVES, int KS>
 int launch_prefill_w(const PrefillParams& p, dim3 grid, hipStream_t st)
 {
-    void (*kernel)(PrefillParams);
-    if constexpr (STEP) kernel = paged_prefill_step_kernel<DT, JUDGE, D, WAVES, KS>;
-    else kernel = paged_prefill_mma_kernel<DT, KV8, WIN, CONTIG, JUDGE, D, WAVES, KS>;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, PfTile<D>::lds_bytes(WAVES, KS));
-    if (attr != hipSuccess) return OPTGQA_ERR_LAUNCH;
-    return launch(kernel, grid, dim3(WAVES * 64), PfTile<D>::lds_bytes(WAVES, KS), st, p);
+    if constexpr (!KV8 && !CONTIG)
+        if (p.deep) return launch_prefill_k<DT, KV8, WIN, CONTIG, STEP, JUDGE, D, WAVES, KS, true>(p, grid, st);
+    return launch_prefill_k<DT, KV8, WIN, CONTIG, STEP, JUDGE, D, WAVES, KS, false>(p, grid, st);
 }
 
 template <int DT, bool KV8, bool WIN, bool CONTIG, bool STEP, bool JUDGE, int D>
@@ -461,6 +469,7 @@ int launch_prefill(PrefillParams p, int num_seqs, int max_q_len, int head_dim, i
     const int64_t key_bytes = num_seqs * seen * (4ll * p.num_kv_heads * head_dim);
     const PrefillShape shape = kv8 ? prefill_shape(units8, shift, max_q_len, p.window > 0, num_cus())
                                    : prefill_shape_direct(units8, shift, max_q_len, head_dim, p.slopes != nullptr, p.window > 0, contig, num_cus(), key_bytes);
+    p.deep = !kv8 && !contig && prefill_deep(units8, shift, max_q_len, p.slopes != nullptr, p.window > 0, num_cus(), seen);
     p.q_tiles = (int)prefill_q_tiles(shape == PrefillShape::k8Waves ? 8 : 4, shift, max_q_len);
     p.group = group;
     p.chunks = group / gh;

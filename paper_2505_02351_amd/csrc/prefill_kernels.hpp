@@ -120,6 +120,7 @@ struct PrefillParams {
     FastDiv by_units_per_seq, by_chunks;
     FastDiv by_tiles, by_units;                     // with slopes: q_tiles and num_seqs, else ceil(units / 8) and units_per_seq
     int tiles_div, units_div;                       // those divisors
+    int deep;                   // tiles are asked for two steps ahead (the host's choice of a kernel)
     int window;                 // > 0: the query at position pos sees keys pos - window < j <= pos only
     // whole-prompt variant (CONTIG): K/V come from the step's contiguous inputs, not from the cache
     const void* k_in;           // [T][Hkv][D] with token strides (elements)
@@ -130,7 +131,7 @@ struct PrefillParams {
 };
 
 // Workgroup shapes (template parameters WAVES and KS; 32 rows per wave, chosen in prefill_shape.hpp):
-//   8 waves            256 rows against one K/V tile, half the loader work and LDS stores per row;
+//   8 waves            256 rows against one K/V tile, half the loads of it per row;
 //   4 waves            128 rows, two workgroups to a CU: one's start and end under the other's walk;
 //   8 waves, KS = 2    128 rows, the walk's tiles dealt to two groups of four waves (each its own tile
 //                      buffers), whose sums are merged through LDS at the end: half as long a walk where
@@ -185,6 +186,22 @@ template <int D> struct PfDirect {
                         : (4 * h2 + (s16 >> 2)) * 64 + dhalf * 32 + (((s16 & 3) >> 1) ^ h2) * 16 + (s16 & 1) * 8;
     }
     static constexpr int further(int k8, int db) { return k8 * (8 / kRows) * kGroup + db * 64 * kRows; }
+
+    // DEEP: a key group's LDS holds kDeepBuffers buffers of a K and a V tile each.  The waves' query rows lie behind K and V of the first
+    // tile and K of the second, where nothing is loaded before they have been read; the output rows, after the walk, from the
+    // beginning on (two groups: behind what they exchange).
+    static constexpr int kDeepBuffers = 4, kRowsAt = 3 * kTile;
+    static constexpr int group_bytes(int group_waves)
+    {
+        const int tiles = 2 * kDeepBuffers * kTile, rows = kRowsAt + group_waves * PfTile<D>::kWaveBytes;
+        return tiles > rows ? tiles : rows;
+    }
+    static constexpr int exchange_bytes(int waves, int groups) { return groups == 1 ? 0 : waves * 64 * (D / 64 * 4 * 16 + 8); }
+    static constexpr int deep_lds_bytes(int waves, int groups)
+    {
+        const int walk = groups * group_bytes(waves / groups), out = exchange_bytes(waves, groups) + waves * PfTile<D>::kWaveBytes;
+        return walk > out ? walk : out;
+    }
 };
 
 // One such load, to LDS address `lds` (wave-uniform) on; from a wave-uniform base and lane offsets, or from lane addresses.
@@ -200,7 +217,7 @@ __device__ __forceinline__ void load_direct(uint32_t lds, const unsigned char* l
 {
     asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "{m0}"(lds), "v"(lane_addr) : "memory");
 }
-__device__ __forceinline__ void wait_direct() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+template <int NEWER = 0> __device__ __forceinline__ void wait_direct() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NEWER) : "memory"); }
 
 template <int DT> __device__ __forceinline__ uint32_t pack2(float lo, float hi) { return narrow2<DT>(lo, hi); }
 
@@ -265,13 +282,16 @@ template <> struct PfSoftmax<kBF16> {
 // head_dim 64, bf16: 15.3 us without it in the kernel, 16.4 with; 3 of 1 024: 24.3 and 27.1; 8 chunks of 512 behind 2 048,
 // 32 / 8 heads, head_dim 128: 217.8 and 220.2), and because a look costs what walks of up to kPfJudgeLongest tiles cannot
 // earn back (slopes, prompts of 512: 3 with 16 / 4 heads, head_dim 64, 12.1 and 13.6; 8 with 32 / 8, head_dim 128, 40.5 and 42.7).
-template <int DT, bool KV8, bool WIN, bool CONTIG, bool JUDGE, int D, int WAVES, int KS, bool STEP>
+//
+// DEEP: tiles are asked for two steps ahead instead of one (prefill_shape.hpp says where).
+template <int DT, bool KV8, bool WIN, bool CONTIG, bool JUDGE, int D, int WAVES, int KS, bool DEEP, bool STEP>
 __device__ __forceinline__ void prefill_body(const PrefillParams& p)
 {
     static_assert(!(JUDGE && WIN), "a windowed walk is short: never judged");
     static_assert((WAVES == 4 && KS == 1) || (WAVES == 8 && !WIN && (KS == 1 || KS == 2)), "4 waves; without a window also 8, or 8 in two key groups");
     constexpr int kPfWaves = WAVES / KS, kPfRows = kPfWaves * 32;   // of one key group: its waves, and the workgroup's rows
     static_assert(!(CONTIG && (KV8 || WIN)), "the whole-prompt variant reads 2-byte inputs, full causal mask");
+    static_assert(!(DEEP && (KV8 || CONTIG)), "tiles that go to LDS directly, from a cache");
     static_assert(!(STEP && (KV8 || WIN || CONTIG)), "the one-call step runs over 2-byte caches, full causal mask");
     static_assert(D == 128 || D == 64, "head_dim 64 or 128");
     constexpr int kPfKRow = PfTile<D>::kKRow, kPfVRow = PfTile<D>::kVRow;
@@ -282,11 +302,15 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     constexpr int ES = KV8 ? 1 : 2;                     // bytes per cache element
     constexpr bool DIRECT = !KV8;                       // tiles go to LDS as they are (8-bit codes pass through registers, which widen them)
     typedef PfDirect<D> Direct;
-    // two tile buffers, each a K tile followed by a V tile: PfDirect's, or [32][kPfKRow] and [32][kPfVRow]
+    // tile buffers, each a K tile followed by a V tile: PfDirect's, or two of [32][kPfKRow] and [32][kPfVRow]
     constexpr int kKTile = DIRECT ? Direct::kTile / 2 : kPfKeys * kPfKRow;
-    constexpr int kBuf = kKTile + (DIRECT ? Direct::kTile / 2 : kPfKeys * kPfVRow);   // (of each key group)
-    static_assert(2 * 2 * kBuf <= PfTile<D>::kLdsBytes && Direct::kTile <= PfTile<D>::kWaveBytes, "both layouts fit");
-    extern __shared__ __attribute__((aligned(16))) uint16_t tile_lds[];          // PfTile<D>::lds_bytes(WAVES, KS)
+    constexpr int kBuf = kKTile + (DIRECT ? Direct::kTile / 2 : kPfKeys * kPfVRow);
+    constexpr int kBuffers = DEEP ? Direct::kDeepBuffers : 2, kLead = DEEP ? 2 : 1;      // kLead: steps that a tile is asked for ahead
+    static_assert(kLead < kBuffers && (kBuffers & (kBuffers - 1)) == 0, "K tiles j + 1 .. j + 1 + kLead, V tiles j .. j + kLead; a power of two");
+    constexpr int kGroupLds = DEEP ? Direct::group_bytes(kPfWaves) / 2 : kBuffers * kBuf;        // a key group's
+    static_assert(DEEP || 2 * 2 * kBuf <= PfTile<D>::kLdsBytes, "both layouts fit");
+    static_assert(Direct::kTile <= PfTile<D>::kWaveBytes, "a wave's query rows fit its strip");
+    extern __shared__ __attribute__((aligned(16))) uint16_t tile_lds[];          // prefill_lds_bytes<D>(WAVES, KS, DEEP)
     __shared__ float vote[3][WAVES];                          // rest_judged
     __shared__ int nearest_bad;
     __shared__ uint32_t least_norm2;
@@ -456,10 +480,10 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         const int ic = min((i << share) + kw, nt - (1 << share) + kw);
         return last_tile - ic;                                    // from the diagonal backwards
     };
-    // A tile's place in LDS: the j-th tile of the walk sits in buffer j % 2.
-    const int group_base = kw * 2 * kBuf;
-    auto tile_base = [&](int j) __attribute__((always_inline)) { return group_base + (j & 1) * kBuf; };
-    auto tile_base_v = [&](int j) __attribute__((always_inline)) { return group_base + (j & 1) * kBuf + kKTile; };
+    // A tile's place in LDS: the j-th tile of the walk sits in buffer j % kBuffers.
+    const int group_base = kw * kGroupLds;
+    auto tile_base = [&](int j) __attribute__((always_inline)) { return group_base + (j & (kBuffers - 1)) * kBuf; };
+    auto tile_base_v = [&](int j) __attribute__((always_inline)) { return group_base + (j & (kBuffers - 1)) * kBuf + kKTile; };
 
     // Everything a workgroup starts with is asked for before anything is waited for: the block numbers of
     // the first tiles, the query rows, this workgroup's own new rows, then the first two tiles.  (What the source
@@ -475,6 +499,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     const uint32_t d_off = (uint32_t)Direct::load_row(lane) * (uint32_t)l_row + 16u * (uint32_t)Direct::load_col(lane);
     const bool far_rows = CONTIG && l_row >= (1ll << 29);        // (32-bit lane offsets reach seven rows)
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)tile_lds;
+    const uint32_t d_lds = lds0 + 2 * (k_loader ? 0 : kKTile) + (uint32_t)(d_first / Direct::kRows * Direct::kGroup);
     // A lane holds one of the 64 block numbers from d_block down, so that a tile costs a lane read instead of a load.
     int d_block = 0, d_table = 0;
     auto read_table = [&](int block) __attribute__((always_inline)) {
@@ -485,20 +510,21 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // The tile of the walk's i-th step into that step's buffer (this wave's groups of K, or of V).  Every key of it is read, visible
     // or not; rows past the sequence's last key, which only the first tile has, re-read that one.  `head`: one of the first two tiles.
     auto direct_tile = [&](int i, auto head) __attribute__((always_inline)) {
-        const int key0 = tile_of(i) * kPfKeys, key = key0 + d_first;
-        const uint32_t lds = lds0 + 2 * (k_loader ? tile_base(i) : tile_base_v(i)) + (uint32_t)(d_first / Direct::kRows * Direct::kGroup);
+        constexpr bool HEAD = decltype(head)::value;             // (later tiles: i < steps, and all of their keys exist)
+        const int key0 = (HEAD ? tile_of(i) : last_tile - (i << share) - kw) * kPfKeys, key = key0 + d_first;
+        const uint32_t lds = d_lds + 2 * tile_base(i);
         const unsigned char* base = l_src;
         if (CONTIG) {
             base += (uint64_t)(uint32_t)key * (uint32_t)l_row;
         } else {
-            const int block = min(key, kmax - 1) >> bs_shift;
+            const int block = (HEAD ? min(key, kmax - 1) : key) >> bs_shift;
             if (__builtin_expect(!held_blocks_reach(d_block, block), 0)) {
                 read_table(block);
                 asm volatile("" : "+v"(d_table));                // (waited for here, not on the way that reads no table)
             }
             base += (uint64_t)(uint32_t)__builtin_amdgcn_readlane(d_table, d_block - block) * l_blk_bytes + (uint32_t)((key & (bs - 1)) * (D * ES));
         }
-        if (decltype(head)::value || __builtin_expect((CONTIG && far_rows) || (STEP && key0 + kPfKeys > pos0), 0)) {     // workgroup-uniform
+        if (HEAD || __builtin_expect((CONTIG && far_rows) || (STEP && key0 + kPfKeys > pos0), 0)) {     // workgroup-uniform
             // lane addresses.  STEP: a key at or above the first new position comes from the inputs, one below through the table
 #pragma unroll
             for (int n = 0; n < kWaveGroups; ++n) {
@@ -599,7 +625,9 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // a line per lane, and the memory pipeline's time for such lines is what a workgroup pays before and behind its walk.
     // 32 / 8 heads, head_dim 128: 8 chunks of 512 behind 2 048 121.1 -> 114.0 us, 8 prompts of 2 560 398.8 -> 383.9, 8 chunks
     // of 512 with a window of 512 74.6 -> 71.2; 5 prompts of 3-301, 16 / 4 heads, head_dim 64: 9.6 -> 9.3.)
-    uint16_t* const strip = tile_lds + KS * (PfTile<D>::kLdsBytes / 2) + wg_wave * (kPfKeys * kPfKRow);
+    const int q_strip = DEEP ? 2 * group_base + Direct::kRowsAt + wave * PfTile<D>::kWaveBytes
+                             : KS * PfTile<D>::kLdsBytes + wg_wave * PfTile<D>::kWaveBytes;               // bytes
+    uint16_t* const strip = tile_lds + (DEEP ? Direct::exchange_bytes(WAVES, KS) + wg_wave * PfTile<D>::kWaveBytes : q_strip) / 2;     // of the output rows
     const unsigned char* const qp = static_cast<const unsigned char*>(p.q) + rows_base;
     u32x4 q_stage[kQ];                                           // (not DIRECT)
     {
@@ -622,14 +650,14 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     asm volatile("" ::: "memory");                               // (asked for here, before the tiles' block numbers are waited for)
     u32x2 stage_first[kKPT];
     if constexpr (DIRECT) {
-        const uint32_t lds = lds0 + KS * PfTile<D>::kLdsBytes + wg_wave * PfTile<D>::kWaveBytes;
+        const uint32_t lds = lds0 + q_strip;
 #pragma unroll
         for (int n = 0; n < Direct::kGroups; ++n)
             load_direct(lds + n * Direct::kGroup, qp + row_offset(row_at(n * Direct::kRows + Direct::load_row(lane))) + 16 * Direct::load_col(lane));
         direct_tile(0, std::true_type{});
         if (k_loader) direct_tile(1, std::true_type{});          // wave-uniform
         wait_direct();
-        const unsigned char* const mine = reinterpret_cast<const unsigned char*>(strip) + Direct::row_at(n32, h2);
+        const unsigned char* const mine = reinterpret_cast<const unsigned char*>(tile_lds) + q_strip + Direct::row_at(n32, h2);
 #pragma unroll
         for (int m = 0; m < kQ; ++m) qb[m] = *reinterpret_cast<const uint4*>(mine + Direct::dims_at(m));
     } else {
@@ -686,7 +714,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         for (int m = 0; m < kQ; ++m) st = mfma32<DT>(m < 4 ? ka[m & 3] : read(m), qb[m], st);
         return st;
     };
-    // kt: the tile's number along the context; buf: its number in the walk (LDS buffer buf % 2)
+    // kt: the tile's number along the context; buf: its number in the walk (LDS buffer buf % kBuffers)
     auto softmax_pv = [&](int kt, int buf, f32x16 st, auto masked) __attribute__((always_inline)) {
         constexpr bool MASKED = decltype(masked)::value;
         // ---- bias, causal mask, lazily referenced exponentials (eq. (3), (4)) --------------------
@@ -787,7 +815,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // first visible keys are all one lane's, the other's half stays zero as long as its weights round to zero -
     // fp16, a steep slope, with two key groups 36 keys or more to the next of them - and a row without a sum wants
     // every tile.  What this leaves out is below 2^-54 of the row's sum a key.)
-    // (A skipped tile still costs its fetch, LDS stores, score MFMAs and barrier, 0.45 us; the keys read here
+    // (A skipped tile still costs its fetch, score MFMAs and barrier, 0.45 us when tiles passed through registers; the keys read here
     // cost 0.1.  8 chunks of 512 behind 2 048, 32 / 8 heads: step 156 -> 120 us together with the rows by
     // head above; 8 prompts of 2 560: 452 -> 403.)
     // By Cauchy-Schwarz |q.k| <= |q||k|, so key j is out of the question for a row if
@@ -956,7 +984,8 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // current one, so that the matrix pipe has work while the vector ALU does the exponentials
     // (measured: 3 % on the kernel).  For that the K tiles run one tile ahead of the V tiles: at the
     // start of step j, K tiles j and j + 1 and V tile j are in LDS, and K tile j + 2 and V tile j + 1 are
-    // on their way to registers (DIRECT: are asked for now).  Prologue:
+    // on their way to registers (DIRECT: are asked for now; DEEP: are on their way to LDS, and the ones
+    // after them are asked for now).  Prologue:
     if constexpr (!DIRECT) {
         store_tile(stage_first, 0);
         if (k_loader) {                                          // wave-uniform
@@ -975,29 +1004,39 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         }
     }
     __syncthreads();
+    // the tiles that are on their way at the start of step j
+    auto direct_lead = [&](int j) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 1; i < kLead; ++i)
+            if (j + i + l_ahead < steps) direct_tile(j + i + l_ahead, std::false_type{});
+    };
+    direct_lead(0);
     f32x16 st_next = scores(0, [] {});
-    __syncthreads();                                             // buffer 0's K tile is overwritten during step 0
+    __syncthreads();                                             // buffer 0's K tile may be overwritten during step 0
     // Tiles wholly inside every row's visible range need no mask: those that end at or below the
     // first row's position (causal side) and start at or above the last row's window start.
     const int n_unmasked = min(ntiles, max(0, (pos_min + 1) / kPfKeys));
     const int n_window_cut = W > 0 ? (max(kmax - W, 0) + kPfKeys - 1) / kPfKeys : 0;
     // (plain loops rather than one with a branch in it, and no branch around the stores: the
     // compiler schedules a loop whose body is one straight line far better)
-    // While step j is computed, K tile j + 2 / V tile j + 1 (through registers: fetched one step earlier) go into the
-    // buffers that step j - 1 used (and the next ones are fetched); the waves meet after every step.  (A third buffer for
-    // DIRECT tiles, two steps on their way: 8 chunks of 512 behind 2 048 103.3 -> 107.2 us, 8 prompts of 2 560 350 -> 363.)
-    // The last step's look-ahead scores read a stale K buffer and are never used; stores past the
-    // last tile put the clamped re-read of it into a buffer nobody reads again.
+    // While step j is computed, K tile j + 2 / V tile j + 1 (through registers: fetched one step earlier; DEEP: asked
+    // for one step earlier, and the next ones are asked for) go into buffers that step j - 1 and those before it used;
+    // the waves meet after every step.  (Two steps ahead is for walks that prefill_deep names, and never for whole
+    // prompts: with a third buffer, 8 chunks of 512 behind 2 048 103.3 -> 107.2 us, 8 prompts of 2 560 350 -> 363.)
+    // The last step's look-ahead scores read a stale K buffer and are never used; through registers, stores past
+    // the last tile put the clamped re-read of it into a buffer nobody reads again, and DIRECT asks for none.
     // (two steps per trip with the two score registers swapping roles, so that no trip copies the
     // look-ahead scores into place)
     f32x16 st_other;
     auto one_tile = [&](int j, const f32x16& st_cur, f32x16& st_ahead, auto masked) __attribute__((always_inline)) {
+        const bool more = j + kLead + l_ahead < steps;           // wave-uniform; nothing is asked for past the walk's end
         st_ahead = scores(j + 1, [&]() __attribute__((always_inline)) {
-            if (DIRECT && j + 1 + l_ahead < steps) direct_tile(j + 1 + l_ahead, std::false_type{});      // wave-uniform; none past the walk's end
+            if (DIRECT && more) direct_tile(j + kLead + l_ahead, std::false_type{});
         });
         softmax_pv(last_tile - ((j << share) + kw), j, st_cur, masked);
         if constexpr (DIRECT) {
-            wait_direct();
+            if (kLead == 1 || !more) wait_direct();
+            else wait_direct<(kLead - 1) * kWaveGroups>();       // K tile j + 2 or V tile j + 1 is there, what was asked for later need not be
         } else {
             store_tile(stage, j + 1 + l_ahead);
             fetch_tile(stage, j + 2 + l_ahead);
@@ -1007,6 +1046,14 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // steps [from, to) of the walk
     auto run_tiles = [&](int from, int to, auto masked) __attribute__((always_inline)) {
         int j = from;
+        // (as many steps to a trip as there are buffers, whose places are then the same in every trip)
+        if constexpr (DEEP && !decltype(masked)::value && (!JUDGE || D == 64))
+            for (; j + 3 < to; j += 4) {
+                one_tile(j, st_next, st_other, masked);
+                one_tile(j + 1, st_other, st_next, masked);
+                one_tile(j + 2, st_next, st_other, masked);
+                one_tile(j + 3, st_other, st_next, masked);
+            }
         for (; j + 1 < to; j += 2) {
             one_tile(j, st_next, st_other, masked);
             one_tile(j + 1, st_other, st_next, masked);
@@ -1019,6 +1066,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     // The walk goes on at step j, wherever it was (every wave has passed a barrier since it last read a tile).
     auto restart = [&](int j) __attribute__((always_inline)) {
         if constexpr (DIRECT) {
+            if constexpr (DEEP) wait_direct();                   // (tiles that are left out)
             direct_tile(j, std::false_type{});
             if (k_loader && j + 1 < steps) direct_tile(j + 1, std::false_type{});
             wait_direct();
@@ -1033,6 +1081,7 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
             fetch_tile(stage, j + 1 + l_ahead);
         }
         __syncthreads();
+        direct_lead(j);
         st_next = scores(j, [] {});
         __syncthreads();
     };
@@ -1062,6 +1111,10 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
         j = to;
     }
     if constexpr (WIN) run_tiles(to_plain, steps, std::true_type{});
+    if constexpr (DEEP && JUDGE) {                               // tiles on their way that nobody reads any more: not into the output rows
+        wait_direct();
+        __syncthreads();
+    }
 
     // ---- two key groups: merge (max / rescale / add), each wave of a pair finishing half of the dims ----
     // The waves of a row block hold the same rows in the same lanes; each leaves its reference, its sum
@@ -1071,7 +1124,8 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     const int db0 = kw * kDBW;
     if constexpr (KS == 2) if (share) {
         constexpr int kPieces = kDBW * 4;                        // 16-byte pieces per lane and wave, and a pair of floats
-        static_assert(WAVES * 64 * (kPieces * 16 + 8) <= KS * PfTile<D>::kLdsBytes, "the exchange fits the tile buffers");
+        static_assert(DEEP ? WAVES * 64 * (kPieces * 16 + 8) == Direct::exchange_bytes(WAVES, KS)
+                           : WAVES * 64 * (kPieces * 16 + 8) <= KS * PfTile<D>::kLdsBytes, "the exchange has its place");
         float4* const xch = reinterpret_cast<float4*>(tile_lds);
         float2* const xch_ml = reinterpret_cast<float2*>(xch + WAVES * 64 * kPieces);
         const int pair_mine = kw * kPfWaves + row_block, pair_theirs = (1 - kw) * kPfWaves + row_block;
@@ -1156,17 +1210,23 @@ __device__ __forceinline__ void prefill_body(const PrefillParams& p)
     }
 }
 
-template <int DT, bool KV8, bool WIN, bool CONTIG, bool JUDGE, int D, int WAVES, int KS>
+// bytes of dynamic LDS
+template <int D> constexpr int prefill_lds_bytes(int waves, int groups, bool deep)
+{
+    return deep ? PfDirect<D>::deep_lds_bytes(waves, groups) : PfTile<D>::lds_bytes(waves, groups);
+}
+
+template <int DT, bool KV8, bool WIN, bool CONTIG, bool JUDGE, int D, int WAVES, int KS, bool DEEP>
 __global__ __launch_bounds__(WAVES * 64, OPTGQA_PF_WAVES_PER_SIMD) void paged_prefill_mma_kernel(const PrefillParams p)
 {
-    prefill_body<DT, KV8, WIN, CONTIG, JUDGE, D, WAVES, KS, false>(p);
+    prefill_body<DT, KV8, WIN, CONTIG, JUDGE, D, WAVES, KS, DEEP, false>(p);
 }
 
 // cache write + prefill over the cached context in one launch (see STEP above)
-template <int DT, bool JUDGE, int D, int WAVES, int KS>
+template <int DT, bool JUDGE, int D, int WAVES, int KS, bool DEEP>
 __global__ __launch_bounds__(WAVES * 64, OPTGQA_PF_WAVES_PER_SIMD) void paged_prefill_step_kernel(const PrefillParams p)
 {
-    prefill_body<DT, false, false, false, JUDGE, D, WAVES, KS, true>(p);
+    prefill_body<DT, false, false, false, JUDGE, D, WAVES, KS, DEEP, true>(p);
 }
 
 }  // namespace optgqa

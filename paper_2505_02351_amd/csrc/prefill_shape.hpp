@@ -97,4 +97,25 @@ inline PrefillShape prefill_shape_direct(int64_t units8, int heads_pow2_shift, i
     return wide ? PrefillShape::k8Waves : PrefillShape::k4Waves;
 }
 
+// Whether tiles that go to LDS directly, from a cache, are asked for two steps ahead instead of one.  seen: tokens that a row may see, under the width of the
+// block tables (and a window).  One step is a memory latency or less where few rows are computed faster than their next keys arrive, and with slopes,
+// where most heads' walks end early, for the long walks that are left.  Elsewhere the buffers and instructions of the second step cost 2 to 4 %.
+// Time of through registers, as it was once, over that with one step, and over that with two: geometric mean and least of random shapes (bf16 and
+// fp16, 1-100 sequences, caches in turn that are no longer in the last-level cache):
+//   one tile of 128 rows to a unit, at most one workgroup to a CU
+//                            200-500 seen       500-1 000       1 000-2 000      2 000-4 096      beyond
+//     slopes, head_dim 128  1.13 .99 | 1.12 1.02   1.09 .87 | 1.10 1.03   1.05 .81 | 1.13 1.04   1.04 .86 | 1.16 1.03    .93 .73 | 1.16 1.05
+//     none, head_dim 128    1.12 .98 | 1.11 1.00   1.06 .87 | 1.09 1.03   1.01 .81 | 1.08 1.03    .92 .77 | 1.07  .99    .90 .74 | 1.09 1.00
+//     none, head_dim 64     1.10 .97 | 1.07 1.00   1.04 .91 | 1.03 1.00   1.01 .85 | 1.04  .99    .97 .81 | 1.04  .97    .93 .77 | 1.03  .96
+//     window, head_dim 128  1.07 .98 | 1.04  .99   1.07 .90 | 1.07 1.04   1.05 .90 | 1.11 1.08   1.06 .87 | 1.13 1.09
+//   two tiles             1.10 1.04 | 1.07 1.00  1.08 1.02 | 1.06 1.00   1.08 .98 | 1.08  .98   1.08 .96 | 1.09  .98    .99 .82 | 1.12  .98
+//   more workgroups, one or two tiles: 257-512 of them 1.00 .86 | 1.11 .94, beyond 1.29 .85 | 1.38 .78
+//   three tiles and more, slopes, beyond 4 096: .93 .82 | 1.16 .95 (8 chunks of 512 behind 2 048 109 us and 109)
+inline bool prefill_deep(int64_t units8, int heads_pow2_shift, int max_q_len, bool slopes, bool windowed, int cus, int64_t seen)
+{
+    const int64_t tiles4 = prefill_q_tiles(4, heads_pow2_shift, max_q_len);
+    if (tiles4 > 2) return slopes && !windowed && tiles4 <= 16 && seen >= 4096;
+    return units8 * tiles4 > cus || seen >= (tiles4 == 1 ? 512 : 1000);
+}
+
 }  // namespace optgqa

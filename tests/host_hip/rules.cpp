@@ -151,6 +151,11 @@ extern "C" int prefill_shape_direct_of(int64_t units8, int shift, int max_q_len,
     return (int)prefill_shape_direct(units8, shift, max_q_len, head_dim, slopes, windowed, whole_prompts, cus, key_bytes);
 }
 
+extern "C" int prefill_deep_of(int64_t units8, int shift, int max_q_len, int slopes, int windowed, int cus, int64_t seen)
+{
+    return prefill_deep(units8, shift, max_q_len, slopes, windowed, cus, seen);
+}
+
 // The blocks that a wave would read, one after the other, through the numbers that its lanes hold (block n of the sequence: number
 // n + 1000; read anew where they do not reach).  Returns the first that it would find wrong, or -1.
 extern "C" int held_blocks_differ(const int32_t* blocks, int n, int* reads)

@@ -48,6 +48,15 @@ def launch_shape(batch, Hq, Hkv, max_q_len, whole_prompt=False, D=128, slopes=Tr
     return ("8", tiles8) if wide else ("4", tiles4)
 
 
+def launch_deep(batch, Hq, Hkv, max_q_len, slopes=True, window=0, longest=0):
+    """Whether a launch over 2-byte caches asks for its tiles two steps ahead."""
+    tiles4 = row_tiles(Hq, Hkv, max_q_len, 128)
+    seen = min(longest, window + max_q_len) if window else longest
+    if tiles4 > 2:
+        return slopes and not window and tiles4 <= 16 and seen >= 4096
+    return units(batch, Hq, Hkv) * tiles4 > cus() or seen >= (512 if tiles4 == 1 else 1000)
+
+
 LONGEST = 1600          # tokens that a launch's longest possible walk must have for its kernel to look at the rest of walks (48 tiles)
 
 

@@ -154,11 +154,11 @@ def test_prefill_shape(lib, B, Hq, Hkv, max_q_len, want):
 
 
 def test_the_gpu_tests_know_the_rule(lib, monkeypatch):
-    """launch_shape, by which the GPU tests choose their launches, against the rules themselves."""
+    """launch_shape and launch_deep, by which the GPU tests choose their launches, against the rules themselves."""
     import torch
-    from test_gpu_prefill_walk import launch_shape
+    from test_gpu_prefill_walk import launch_deep, launch_shape
     rng = random.Random(1)
-    seen = {}
+    seen, deep = {}, {}
     for _ in range(6000):
         cus = rng.choice([64, 256, 304])
         monkeypatch.setattr(torch.cuda, "get_device_properties", lambda _: types.SimpleNamespace(multi_processor_count=cus))
@@ -175,8 +175,12 @@ def test_the_gpu_tests_know_the_rule(lib, monkeypatch):
         else:
             want = lib.prefill_shape_direct_of(*launch(*args[:3]), args[3], D, slopes, window > 0, whole, cus, ctypes.c_int64(4 * Hkv * D * keys))
             assert got == ["4", "8", "two"][want], (args, whole, how, cus)
+            if not whole:
+                two_ahead = bool(lib.prefill_deep_of(*launch(*args[:3]), args[3], slopes, window > 0, cus, ctypes.c_int64(keys // args[0])))
+                assert launch_deep(*args, **{k: v for k, v in how.items() if k not in ("kv8", "D")}) == two_ahead
+                deep[got, two_ahead] = deep.get((got, two_ahead), 0) + 1
         seen[got, kv8, whole, slopes] = seen.get((got, kv8, whole, slopes), 0) + 1
-    assert {s for s, *_ in seen} == {"two", "4", "8"}
+    assert {s for s, *_ in seen} == {"two", "4", "8"} and len(deep) == 6
     assert {k[1:] for k in seen if k[0] == "8"} == {(True, False, True), (True, False, False), (False, False, True), (False, False, False),
                                                     (False, True, True), (False, True, False)}
 
