@@ -12,6 +12,7 @@
 //              sequence b has n_b = ceil(L_b / 16) tiles per segment and Y segments
 //   flat order F(b, y, tau) = Y * P_b + y * n_b + tau,  P_b = sum_{b' < b} n_b',  T = Y * P_B
 //   unit u     (one wave) owns flat tiles [u*c, min((u+1)*c, T)),  c = ceil(T / U)
+//              (8-bit caches: U by the tiles that there are, decode_split.hpp)
 //
 // A unit's range is a short list of pieces, each inside one segment; per piece the wave runs a
 // register-prefetched matrix-core loop (K/V tiles fetched one tile ahead straight into VGPRs, as

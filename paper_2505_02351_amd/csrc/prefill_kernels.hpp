@@ -24,11 +24,11 @@
 //                              so that a lane ends up with four consecutive keys of its dim from
 //                              one instruction.
 // (32x32x16 rather than 16x16x32 MFMAs: same flops per cycle, half as many matrix and LDS
-// instructions per tile, and a row's scores live in 2 lanes instead of 4.  Measured on this chip, a
-// SIMD does not overlap 16x16x32 MFMAs of one wave with vector instructions of another at all, and
-// 32x32x16 ones only partly, and a wave issues at most one instruction every ~4.4 cycles: the
-// loop's cost is close to MFMA cycles plus 4.4 cycles per other instruction, so instruction
-// count per tile is what this kernel is tuned for.)
+// instructions per tile, and a row's scores live in 2 lanes instead of 4.  Measured on one CU, a
+// SIMD overlaps such MFMAs of one wave with vector instructions of another - 16 of them and 64 FMAs take 521
+// cycles together - but a wave issues at most one instruction every ~4.4 cycles and the loop is a chain of scores,
+// softmax, products and a barrier, of 2 090 to 2 335 cycles a tile for 1 536 of MFMAs: the instructions of a tile are
+// what this kernel is tuned for.)
 // Scores, sums and the output accumulate in fp32.  For the second contraction the softmax
 // weights must become 2-byte values:
 //   fp16: one rounding (11 significant bits); the lazily moved reference of the exponentials (see
@@ -86,13 +86,13 @@ constexpr int kPfJumpTiles = 8;
 constexpr int kPfByHeadTiles = 16;
 // tiles that a walk must have for two key groups to share it: below, the second group's waves end at once and the
 // first walks alone.  (Sharing costs a tile beyond the diagonal, a merge through LDS and two barriers.  GPU time shared
-// over alone, 32 / 8 heads, one prompt or chunks of 40 behind a cache, both types:
-//   tiles             1           2           4           8           10          12          16          24
-//   head_dim 128  1.23-1.24   1.06-1.14   1.02-1.08   0.95-1.01   0.92-0.99   0.90-0.96   0.87-0.94   0.83-0.90
-//   head_dim 64   1.16        1.04-1.06   1.01-1.03   0.94-0.95   0.92-0.93   0.89-0.90   0.86-0.88   0.82-0.85
-// Measured before tiles went to LDS directly, but for the lines' own place.  With 16 (11) tiles and with 11 (8), GPU time of one prompt or of 4 chunks
-// of 40, us: head_dim 128, prompts of 384 12.8 and 12.5, of 448 14.1 and 13.6, chunks that end at 352 13.4 and 13.0, at 480 16.5 and 15.5; head_dim 64,
-// prompts of 256 8.6 and 8.1, of 320 9.7 and 9.0; with 8 (6) as with 11 (8), but 256 at head_dim 128 10.4 instead of 10.3.)
+// over alone, 32 / 8 heads, one prompt with slopes or 4 chunks of 40 behind a cache without, bf16 and fp16, 8 sets of inputs in turn:
+//   tiles                       1           2           4           6           8           10          11          12          16          24
+//   head_dim 128, prompt    1.26        1.15-1.17   1.09-1.12   1.04-1.07   1.00-1.03   0.97-1.03   0.98-1.02   0.95-0.99   0.92-0.95   0.90-0.93
+//   head_dim 128, chunks                1.03-1.05   1.01-1.02   0.96-0.99   0.94-0.95   0.92-0.94   0.96-0.97   0.91        0.89        0.85-0.86
+//   head_dim 64, prompt     1.18        1.08-1.09   1.02-1.04   0.98-0.99   0.94-0.95   0.91-0.92   0.93        0.89-0.90   0.85-0.87   0.83-0.84
+//   head_dim 64, chunks                 1.02        0.96-1.00   0.93-0.95   0.91-0.92   0.88-0.89   0.92-0.94   0.86-0.88   0.83-0.84   0.80
+// The lines lie where prompts tie, or a little beyond: a prompt's first rows have the shorter walks.)
 template <int D> constexpr int kPfTwoGroupTiles = D == 128 ? 11 : 8;
 
 struct PrefillParams {
@@ -153,8 +153,9 @@ template <int D> struct PfTile {
 // Tiles of 2-byte elements are written to LDS by the memory system itself (global_load_lds_dwordx4: 64 lanes' 16-byte
 // pieces to 1 KiB from the address in m0 on, lane by lane): no registers hold a tile on its way, no LDS stores, and with
 // wave-uniform addresses not one vector instruction.  (Through registers - loads, 16-byte LDS stores and their addresses -
-// a tile cost a wave 20 to 30 instructions: 8 prompts of 1 024, 32 / 8 heads, head_dim 128, 96.8 -> 86.0 us, 8 chunks of 512
-// behind 2 048 107.5 -> 103.3, without slopes 201 -> 195, with a window of 512 65.7 -> 61.8.)
+// a tile cost a wave 20 to 30 instructions.  32 / 8 heads, head_dim 128, the same caches again and again: 8 prompts of 1 024 96.8 -> 86.0 us,
+// 8 chunks of 512 behind 2 048 107.5 -> 103.3, without slopes 201 -> 195, with a window of 512 65.7 -> 61.8; whole steps over caches in turn, with 128 rows
+// in more launches: those chunks 113.1 -> 110.0, with the window 71.3 -> 68.7, 8 prompts of 2 560 366.7 -> 352.0.  Few rows behind long contexts lost: prefill_deep.)
 // Such a load cannot pad rows, but it may bring any piece to any lane.  A tile is groups of 4 rows (head_dim 64: 8), 1 KiB and
 // a pad of 16 (32) bytes each.  In a group pieces of 64 bytes - four lanes, 64 bytes of one row's, as the memory system likes
 // them - lie row behind row, then the next 64 bytes of all rows:
