@@ -27,7 +27,7 @@
 // instructions per tile, and a row's scores live in 2 lanes instead of 4.  Measured on one CU, a
 // SIMD overlaps such MFMAs of one wave with vector instructions of another - 16 of them and 64 FMAs take 521
 // cycles together - but a wave issues at most one instruction every ~4.4 cycles and the loop is a chain of scores,
-// softmax, products and a barrier, of 2 090 to 2 335 cycles a tile for 1 536 of MFMAs: the instructions of a tile are
+// softmax, products and a barrier, 2 090 to 2 335 cycles a tile for a pair of waves whose MFMAs take 1 536 (bf16): the instructions of a tile are
 // what this kernel is tuned for.)
 // Scores, sums and the output accumulate in fp32.  For the second contraction the softmax
 // weights must become 2-byte values:
@@ -92,7 +92,7 @@ constexpr int kPfByHeadTiles = 16;
 //   head_dim 128, chunks                1.03-1.05   1.01-1.02   0.96-0.99   0.94-0.95   0.92-0.94   0.96-0.97   0.91        0.89        0.85-0.86
 //   head_dim 64, prompt     1.18        1.08-1.09   1.02-1.04   0.98-0.99   0.94-0.95   0.91-0.92   0.93        0.89-0.90   0.85-0.87   0.83-0.84
 //   head_dim 64, chunks                 1.02        0.96-1.00   0.93-0.95   0.91-0.92   0.88-0.89   0.92-0.94   0.86-0.88   0.83-0.84   0.80
-// The lines lie where prompts tie, or a little beyond: a prompt's first rows have the shorter walks.)
+// The lines lie where prompts tie, or a little beyond.)
 template <int D> constexpr int kPfTwoGroupTiles = D == 128 ? 11 : 8;
 
 struct PrefillParams {

@@ -78,8 +78,8 @@ constexpr int64_t kPrefillFarKeys = 320000000;
 //                              256 rows                140.9             448.4                      1 712              761.0             1 711
 //                              128 rows                133.6             410.8                      1 752              796.3             1 809
 //   whole prompts, slopes, whose bound is at most 3 072 tokens, or that 256-row workgroups fill not five times
-//                         -> 128 rows; in a longer walk the loads that 256 rows save weigh more.  (They tie at 2 816; prompts are often shorter than
-//                            their bound, and then 128 rows win.)  8 prompts, the first two columns with the same inputs again and again, the others with three sets in turn:
+//                         -> 128 rows; in a longer walk the loads that 256 rows save weigh more.  (They tie at 2 816; prompts may be shorter than
+//                            their bound, and then 128 rows win: 4 of 768 under 2 048, tiles through registers, 40.6 and 37.2.)  8 prompts, the first two columns with the same inputs again and again, the others with three sets in turn:
 //                              tokens                 1 024   1 536   2 560   2 816   3 072   3 328   3 584   4 096   16 x 3 072   16 x 3 584
 //                              256 rows                95.6   183.5   342.2   392.1   441.2   492.0   546.9   662.2      902.6      1 085.7
 //                              128 rows                88.6   165.7   340.5   394.0   449.2   509.4   562.0   689.4      917.6      1 115.4
